@@ -53,8 +53,10 @@
  * thresholds not NaN and not negative; x and weights finite.
  *
  * Determinism: results do not depend on the run, on the batch a token is in
- * (for batches of one size class) or on the stream; every reduction has a
- * fixed order and no floating-point atomics are used.
+ * (for batches of one size class: 1 token, 2 to 64, and above 64 the batches
+ * whose passes of up to 2048 rows split d_ff into as many chunks) or on the
+ * stream; every reduction has a fixed order and no floating-point atomics
+ * are used.
  *
  * Concurrency: calls on different streams use different workspaces and may
  * overlap.  Calls on one stream are ordered by the stream.
@@ -105,7 +107,9 @@ int sats_mlp_forward(const sats_bf16 *x, const int32_t *token_ids,
  * calls at d <= 4096 and d_ff <= 16384 (any number of layers up to 64, bf16)
  * and small batches; a call whose workspace does not fit returns
  * SATS_ERR_WORKSPACE before any device work.  Every call on a device shares
- * that device's array and leaves its last contents there: each call first
+ * that device's array and leaves its last contents there (more than 64 tokens
+ * run in passes of 64 here, where sats_mlp_forward takes larger ones: the
+ * outputs then agree within rounding): each call first
  * clears the array's arrival counters with a small kernel (no memset), and
  * calls that overlap on one device (other streams or threads) race and must
  * not be issued.  sats_device_status also reports a bounded wait that gave up

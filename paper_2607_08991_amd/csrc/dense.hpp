@@ -898,13 +898,22 @@ __global__ __launch_bounds__(kDenseThreads) void cal_err_kernel(CalErrArgs a) {
 #undef SATS_DENSE_STEP8
 #undef SATS_DENSE_STEP
 
+// Row blocks (the layout of h and p in prefill.hpp): 16 rows by 32 k, chunk q
+// (16 bytes) of row r at q ^ pf_swz(r) of the row's 64 bytes.  A 16-byte LDS
+// read serves lanes 0-3, 12-15, 20-27 (and so on) at once: with rows on the
+// lanes of each 16 and k on the groups of 16, these must differ in the chunk
+// of their bank pair, which the order 0, 2, 3, 1 over rows 0-3, 4-7, ... gives
+// (measured: no bank conflicts; 0, 1, 2, 3 has one per two reads).
+__device__ __forceinline__ int pf_swz(int r) { return ((r >> 1) & 2) ^ (((r >> 3) & 1) * 3); }
+
 struct GlueArgs {
-  const int *ctl;
+  const int *ctl;         // null: `rows` rows, each its own token (perm unused)
+  int rows;
   const int *perm;
   const float *part;      // [KSPLIT][n_dense][d]
   int ksplit, d;
   uint16_t *out;          // last layer: [n][d] of the pass, rows through perm; else null
-  uint16_t *hnext;        // otherwise: next layer input of the dense group, [n_dense][d]
+  uint16_t *hnext;        // otherwise: next layer input of the dense group, [n_dense][d] (ctl null: row blocks)
   uint16_t *layer_in;     // optional: inspection copy of the next layer input, rows through perm
   // LoRA (zpart null: none): y += s z B_down for sparse-path rows, z the sum
   // over the nzb column tiles of zpart [nzb][kDenseMaxTokens][rank], in tile order
@@ -919,9 +928,9 @@ struct GlueArgs {
 // 4 t .. 4 t + 3 and issues its loads of every partial at once
 constexpr int kGlueThreads = 1024;
 __global__ __launch_bounds__(kGlueThreads) void dense_glue_kernel(GlueArgs a) {
-  if (!a.ctl[1]) return;
+  if (a.ctl && !a.ctl[1]) return;
   const int m = blockIdx.x;
-  const int nd = a.ctl[0];
+  const int nd = a.ctl ? a.ctl[0] : a.rows;
   if (m >= nd) return;
   __shared__ float ssw[kGlueThreads / 64];
   const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6;
@@ -987,7 +996,7 @@ __global__ __launch_bounds__(kGlueThreads) void dense_glue_kernel(GlueArgs a) {
       y += t;
     }
   }
-  const int row = a.perm[m];
+  const int row = a.ctl ? a.perm[m] : m;
   if (a.out) {
     if (on) {
       uint16_t *o = a.out + (size_t)row * a.d + c;
@@ -1013,7 +1022,10 @@ __global__ __launch_bounds__(kGlueThreads) void dense_glue_kernel(GlueArgs a) {
 #pragma unroll
     for (int i = 0; i < 4; ++i) h[i] = f32_to_bf16(y[i] / scale);
     const uint2 hv = make_uint2((uint32_t)h[0] | ((uint32_t)h[1] << 16), (uint32_t)h[2] | ((uint32_t)h[3] << 16));
-    *reinterpret_cast<uint2 *>(a.hnext + (size_t)m * a.d + c) = hv;
+    const size_t o = a.ctl ? (size_t)m * a.d + c
+                           : ((size_t)(m >> 4) * ((a.d + 31) / 32) + (c >> 5)) * 512 + (m & 15) * 32 +
+                                 (((c >> 3) & 3) ^ pf_swz(m & 15)) * 8 + (c & 7);
+    *reinterpret_cast<uint2 *>(a.hnext + o) = hv;
     if (a.layer_in) *reinterpret_cast<uint2 *>(a.layer_in + (size_t)row * a.d + c) = hv;
   }
 }

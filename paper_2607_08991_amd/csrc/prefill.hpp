@@ -1,0 +1,469 @@
+// Batches of more than 64 tokens (prompts, evaluation windows): both products
+// of a layer as tiled matrix-core products over every row of the pass.
+//
+// pf_pack_kernel    the call input in row blocks, and the route of each row.
+// pf_gateup_kernel  p = SiLU(h W_gate) (h W_up), each row under its own route
+//                   and keep rule (Eq. 1, 2, 4-5, 13): BM rows by NT columns
+//                   of both projections per workgroup.
+// pf_down_kernel    partial y over one chunk of d_ff: BM rows by BN columns.
+// The partials are added in chunk order by dense_glue_kernel.
+//
+// At 64 rows a pass is bound by the weight stream (235 MB of W_gate and W_up
+// per pass at the Llama-3.1-8B shape); more rows per pass reuse every weight
+// byte until the matrix cores are the bound.  A workgroup of 8 wavefronts
+// walks k in steps of 32 through rings of LDS stages that are loaded by
+// buffer loads writing LDS.  The MFMA operands of step s + 1 are read from
+// LDS under the products of step s, so a step starts with its products right
+// after the barrier.  A stage is refilled one barrier after the products
+// that used its last operands.
+//
+// Bound: the matrix cores, after the weight stream.  1000 rows of a
+// Llama-3.1-8B layer (352 Gflop): 16 passes of 64 rows took 1303 us; these
+// kernels take 320 us (1.10 Pflop/s; a large library product reaches 1.18):
+// gate/up 233 us, down 90 us.  Without its loads the gate/up loop takes 169 us.
+//
+// Layouts.  The left operands (h, p) are kept in row blocks: 16 rows by 32 k,
+// 1 KB, the blocks of 16 rows in k order; chunk q (16 bytes) of row r sits at
+// q ^ pf_swz(r) of the row's 64 bytes, so that a load of a block is 1 KB in a
+// row and the 16-byte LDS reads of a wavefront (16 rows at one k) fall in
+// distinct banks.  W_gate_T and W_up_T rows are staged 64 k (a 128-byte line)
+// at a time, chunk q of row r at q ^ (r & 7): half lines double the requests
+// on the L2, which then bounds the product (gate/up 280 us with h and the
+// weights in 64-byte pieces).  W_down rows are staged 32 at a time, BN columns each;
+// the pair of chunks of columns 16 c .. 16 c + 15 of row r sits at pair
+// c ^ pf_kswz(r), so that the transposing LDS reads (ds_read_b64_tr_b16: 4
+// rows x 16 columns per 16 lanes) fall in distinct banks.
+#pragma once
+
+#include "dense.hpp"
+
+namespace sats {
+
+constexpr int kPfThreads = 512;  // 8 wavefronts
+constexpr int kPfKC = 32;        // k per step
+
+// transposed operand of a k-row tile (pitch bytes per row): columns 16 ct ..
+// 16 ct + 15, this lane's column l16, rows 8 g .. 8 g + 7.  Of each group of
+// 16 lanes, lane i reads 4 columns 4 (i % 4) .. of row i / 4 and receives
+// column i of the 4 rows.
+typedef short s16x4 __attribute__((ext_vector_type(4)));
+typedef short s16x8 __attribute__((ext_vector_type(8)));
+typedef __attribute__((address_space(3))) s16x4 lds_s16x4;
+__device__ __forceinline__ int pf_kswz(int r) { return (r & 3) | (((r >> 3) & 1) << 2); }
+__device__ __forceinline__ bf16x8 pf_krow_operand(uint8_t *tile, int pitch, int ct, int g, int l16) {
+  s16x4 v[2];
+#pragma unroll
+  for (int h = 0; h < 2; ++h) {
+    const int r = 8 * g + 4 * h + (l16 >> 2);
+    v[h] = __builtin_amdgcn_ds_read_tr16_b64_v4i16(
+        (lds_s16x4 *)(tile + r * pitch + (ct ^ pf_kswz(r)) * 32 + (l16 & 3) * 8));
+  }
+  const s16x8 b = {v[0][0], v[0][1], v[0][2], v[0][3], v[1][0], v[1][1], v[1][2], v[1][3]};
+  return __builtin_bit_cast(bf16x8, b);
+}
+// operand of a row block: row r of the block's 16, k = 8 g .. 8 g + 7
+__device__ __forceinline__ bf16x8 pf_block_operand(const uint8_t *blk, int r, int g) {
+  return __builtin_bit_cast(bf16x8, *reinterpret_cast<const u32x4 *>(blk + r * 64 + (g ^ pf_swz(r)) * 16));
+}
+
+struct PfArgs {
+  const uint16_t *A;      // row blocks of h (gate/up) or p (down)
+  const uint16_t *Wg, *Wu;  // gate/up: [N][K] each
+  const uint16_t *Wd;     // down: [K][N]
+  uint16_t *P;            // gate/up: row blocks of p
+  float *part;            // down: partials [ks][n][N]
+  const float *thr;       // layer threshold, or null (base path for every row)
+  const uint8_t *gbase;   // base-path flag of each row (gate/up; allocated to whole tiles of 256)
+  uint8_t *keep_out;      // optional [n][N] keep flags
+  int n, K, N;            // rows; reduction length; output columns
+  int mtiles, units;      // row tiles; column tiles (times k chunks, down)
+  int ks, kchunk;         // down: k chunks and their length (a multiple of 32)
+  float *cal_g;           // calibration: g in float32, [n][N] ...
+  uint16_t *cal_ph, *cal_pl;  // ... and p as two bf16 terms (hi = rne(p), lo = rne(p - hi))
+};
+
+// The rows of x in row blocks (rows past n and k past d zero), the base-path
+// flags, and the inspection copies of both.  A wavefront per block.
+struct PfPackArgs {
+  const uint16_t *x;      // [n][d]
+  uint16_t *A;            // row blocks
+  uint8_t *gbase;         // [n]
+  const int32_t *ids;
+  const uint8_t *lut;
+  int route_mode;
+  int n, d;
+  uint8_t *route_out;     // optional [n]
+  uint16_t *layer_in;     // optional [n][d]
+};
+__global__ __launch_bounds__(kThreads) void pf_pack_kernel(PfPackArgs a) {
+  const int lane = threadIdx.x & 63;
+  const int nb = (a.d + kPfKC - 1) / kPfKC;
+  const int b = blockIdx.x * (kThreads / 64) + (threadIdx.x >> 6);  // block: row tile b / nb, k block b % nb
+  if (b >= (a.n + 15) / 16 * nb) return;
+  const int r = lane >> 2, m = b / nb * 16 + r, k = b % nb * kPfKC + 8 * ((lane & 3) ^ pf_swz(r));
+  u32x4 v = {0u, 0u, 0u, 0u};
+  if (m < a.n && k < a.d) {
+    v = *reinterpret_cast<const u32x4 *>(a.x + (size_t)m * a.d + k);
+    if (a.layer_in) *reinterpret_cast<u32x4 *>(a.layer_in + (size_t)m * a.d + k) = v;
+  }
+  *reinterpret_cast<u32x4 *>(a.A + (size_t)b * 512 + 8 * lane) = v;
+  if (b % nb == 0 && (lane & 3) == 0 && m < a.n && a.gbase) {
+    const uint8_t base = (uint8_t)token_is_base(a.route_mode, a.ids, a.lut, m);
+    a.gbase[m] = base;
+    if (a.route_out) a.route_out[m] = base;
+  }
+}
+
+// Workgroup b (on XCD b mod 8) takes row tile j % mtiles of unit 8 (j /
+// mtiles) + b % 8, j = b / 8: the row tiles of a unit run side by side on one
+// XCD, whose L2 then reads the unit's weights from memory once.
+__device__ __forceinline__ bool pf_tile(const PfArgs &a, int &mt, int &unit) {
+  const int j = blockIdx.x >> 3;
+  mt = j % a.mtiles;
+  unit = (j / a.mtiles) * 8 + (blockIdx.x & 7);
+  return unit < a.units;
+}
+
+// Waits until at most VM of this wavefront's loads are outstanding, then
+// meets the other wavefronts (its LDS reads may still be under way: the
+// buffer refilled next holds operands already used).
+template <int VM> __device__ __forceinline__ void pf_barrier() {
+  static_assert(VM >= 0 && VM < 64, "vmcnt range");
+  __builtin_amdgcn_s_waitcnt((VM & 15) | (7 << 4) | (15 << 8) | ((VM >> 4) << 14));
+  __builtin_amdgcn_s_barrier();
+}
+
+// 16 bytes per lane from base + voff + soff of the buffer into LDS at dst +
+// 16 * lane; a lane whose voff is kDenseOffNone reads zeros (soff is the
+// same for the wavefront, so a step costs no address arithmetic per lane)
+__device__ __forceinline__ void pf_dma(__amdgpu_buffer_rsrc_t r, uint8_t *dst, uint32_t voff, uint32_t soff) {
+  __builtin_amdgcn_raw_ptr_buffer_load_lds(r, (lds_void *)dst, 16, (int)voff, (int)soff, 0, 0);
+}
+
+// The ring buffers are an array per stage: the compiler then knows which
+// stage a pending load writes and adds no wait of its own before the LDS
+// reads of another (it tells at most 8 apart).
+
+// ---------------------------------------------------------------- gate/up
+
+// BM = 256: wavefront w takes rows 64 (w / 2) .. + 63 and all NT columns of
+// W_gate (w even) or W_up (w odd).  BM = 128: rows 64 (w / 4) .. + 63 and
+// half of the columns.  The rings hold 4 stages of h (32 k) and WR of the
+// weights (64 k, used by steps 2 j and 2 j + 1).
+template <int BM, int NT, bool CAL>
+__global__ __launch_bounds__(kPfThreads, 2) void pf_gateup_kernel(PfArgs a) {
+  constexpr int WPG = 8 / (BM / 64);           // wavefronts per 64-row group
+  constexpr int CW = NT / (WPG / 2);           // columns per wavefront
+  constexpr int MT = 4, CT = CW / 16;          // its 16 x 16 tiles
+  constexpr int IA = BM / 128;                 // 1 KB loads per wavefront: a stage of h ...
+  constexpr int IW = 2 * NT / 64;              // ... and of the weights (8 rows each)
+  constexpr int SA = BM * 64, SW = IW * 8192;  // stage bytes
+  constexpr int WR = 4 * SA + 4 * SW <= 160 * 1024 ? 4 : 3;
+  static_assert(4 * SA + WR * SW <= 160 * 1024 && CT * 16 == CW && NT % 32 == 0, "rings and tile shapes");
+  __shared__ __attribute__((aligned(1024))) uint8_t a0[SA], a1[SA], a2[SA], a3[SA], w0[SW], w1[SW], w2[SW],
+      w3[WR > 3 ? SW : 16];
+  auto abuf = [&](int i) -> uint8_t * { return (i &= 3) == 0 ? a0 : i == 1 ? a1 : i == 2 ? a2 : a3; };
+  auto wbuf = [&](int i) -> uint8_t * { return (i %= WR) == 0 ? w0 : i == 1 ? w1 : i == 2 ? w2 : w3; };
+  int mt0, unit;
+  if (!pf_tile(a, mt0, unit)) return;
+  const int lane = threadIdx.x & 63, w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int g = lane >> 4, l16 = lane & 15;
+  const int m0 = mt0 * BM, n0 = unit * NT;
+  const int K = a.K, N = a.N, S = (K + kPfKC - 1) / kPfKC;
+  const int grp = w / WPG, mat = (w % WPG) / (WPG / 2), half = w % (WPG / 2);
+  // base-path flags of the rows this lane finishes (see the epilogue), four to a word
+  const int lm0 = 64 * grp + (mat ? 0 : 32);
+  uint32_t base4[MT / 2];
+#pragma unroll
+  for (int i = 0; i < MT / 2; ++i)
+    base4[i] = CAL ? 0u : *reinterpret_cast<const uint32_t *>(a.gbase + m0 + lm0 + 16 * i + 4 * g);
+  const int rows16 = (a.n + 15) / 16;
+  const __amdgpu_buffer_rsrc_t rsa = dense_rsrc(a.A, (uint32_t)((size_t)rows16 * S * 1024));
+  const uint32_t wbytes = (uint32_t)((size_t)N * K * 2);
+  // h: load i = w + 8 q of a stage is row block m0 / 16 + i at the stage's k (past the last row: zeros)
+  uint32_t aoff[IA];
+#pragma unroll
+  for (int q = 0; q < IA; ++q) {
+    const int rb = m0 / 16 + w + 8 * q;
+    aoff[q] = rb < rows16 ? (uint32_t)rb * (uint32_t)S * 1024u + 16u * lane : kDenseOffNone;
+  }
+  // weights: load i = w + 8 q of a stage is rows 8 i .. 8 i + 7 of [W_gate | W_up], 128 bytes each
+  const int lr = lane >> 3, lq = (lane & 7) ^ lr;
+  uint32_t woff[IW];
+#pragma unroll
+  for (int q = 0; q < IW; ++q) {
+    const int row = 8 * (w + 8 * q) + lr, c = n0 + (row < NT ? row : row - NT);
+    woff[q] = row < 2 * NT && c < N ? (uint32_t)(((size_t)c * K + 8 * lq) * 2) : kDenseOffNone;
+  }
+  auto issue_a = [&](uint8_t *buf, int s) {
+#pragma unroll
+    for (int q = 0; q < IA; ++q)
+      pf_dma(rsa, buf + (w + 8 * q) * 1024, s < S ? aoff[q] : kDenseOffNone, (uint32_t)s * 1024u);
+  };
+  auto issue_w = [&](uint8_t *buf, int j) {
+    const bool v = 64 * j + 8 * lq < K;
+#pragma unroll
+    for (int q = 0; q < IW; ++q) {
+      const int i = w + 8 * q;
+      pf_dma(dense_rsrc(i < NT / 8 ? a.Wg : a.Wu, wbytes), buf + i * 1024,
+             v ? woff[q] : kDenseOffNone, (uint32_t)j * 128u);
+    }
+  };
+  bf16x8 oa0[MT], oa1[MT], ob[CT];  // operands: h of even and of odd steps, weights
+  auto load_a = [&](const uint8_t *buf, int t) { return pf_block_operand(buf + (4 * grp + t) * 1024, l16, g); };
+  auto load_b = [&](const uint8_t *buf, int t, int h) {  // k half h of the stage
+    const int r = mat * NT + half * CW + 16 * t + l16;
+    return __builtin_bit_cast(bf16x8,
+                              *reinterpret_cast<const u32x4 *>(buf + r * 128 + ((4 * h + g) ^ (r & 7)) * 16));
+  };
+  f32x4v acc[MT][CT];
+#pragma unroll
+  for (int i = 0; i < MT; ++i)
+#pragma unroll
+    for (int j = 0; j < CT; ++j) acc[i][j] = f32x4v{0.f, 0.f, 0.f, 0.f};
+  // the order of the loop's loads, from 2 WR - 2 steps before the first
+#pragma unroll
+  for (int s = 2 - 2 * WR; s < 0; ++s) {
+    if (s + 3 >= 0) issue_a(abuf(s + 3), s + 3);
+    if (s % 2 == 0) issue_w(wbuf(s / 2 + WR - 1), s / 2 + WR - 1);
+  }
+  pf_barrier<2 * IA + IW>();
+#pragma unroll
+  for (int t = 0; t < MT; ++t) oa0[t] = load_a(a0, t);
+#pragma unroll
+  for (int t = 0; t < CT; ++t) ob[t] = load_b(w0, t, 0);
+  // step s: the stages of step s + 1 have landed, and every wavefront is done
+  // with the products of step s - 1; the stages it used last are refilled,
+  // and the operands of step s + 1 are read under the products (a weight
+  // operand once its last product is issued, into the same registers)
+  auto step = [&](int s, int p, bf16x8(&xa)[MT], bf16x8(&ya)[MT]) {  // s = p modulo the round
+    pf_barrier<IA + IW>();
+    issue_a(abuf(p + 3), s + 3);
+    if (p % 2 == 0) issue_w(wbuf(p / 2 + WR - 1), s / 2 + WR - 1);
+    const uint8_t *an = abuf(p + 1), *wn = wbuf((p + 1) / 2);
+#pragma unroll
+    for (int t = 0; t < MT; ++t) ya[t] = load_a(an, t);
+#pragma unroll
+    for (int j = 0; j < CT; ++j) {
+#pragma unroll
+      for (int i = 0; i < MT; ++i) acc[i][j] = mfma16(xa[i], ob[j], acc[i][j]);
+      ob[j] = load_b(wn, j, (p + 1) & 1);
+    }
+#pragma unroll
+    for (int i = 0; i < MT * CT; ++i) {  // a product, and an LDS read beside the first ones and the last of a column
+      __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);
+      if (i < MT || i % MT == MT - 1) __builtin_amdgcn_sched_group_barrier(0x100, 1, 0);
+    }
+  };
+  constexpr int U = WR == 3 ? 12 : 8;  // steps of a round: whole turns of both rings
+  for (int s0 = 0; s0 < S; s0 += U) {
+    step(s0, 0, oa0, oa1);
+    step(s0 + 1, 1, oa1, oa0);
+    step(s0 + 2, 2, oa0, oa1);
+    step(s0 + 3, 3, oa1, oa0);
+    step(s0 + 4, 4, oa0, oa1);
+    step(s0 + 5, 5, oa1, oa0);
+    step(s0 + 6, 6, oa0, oa1);
+    step(s0 + 7, 7, oa1, oa0);
+    if constexpr (U > 8) {
+      step(s0 + 8, 8, oa0, oa1);
+      step(s0 + 9, 9, oa1, oa0);
+      step(s0 + 10, 10, oa0, oa1);
+      step(s0 + 11, 11, oa1, oa0);
+    }
+  }
+  __builtin_amdgcn_s_waitcnt(0);  // the zero-filling loads past the range land too
+  __syncthreads();
+  // epilogue: the wavefronts of W_gate and W_up of the same rows and columns
+  // (a pair) trade half of their tiles through LDS, lane to lane: the W_up
+  // one finishes row tiles 0 and 1, the W_gate one 2 and 3
+  const int pair = grp * (WPG / 2) + half;  // 4 pairs
+  static_assert(MT / 2 * CT * 1024 <= SA && MT * CT * 1024 <= SW, "the exchange fits the stage buffers");
+  uint8_t *xw = pair == 0 ? w0 : pair == 1 ? w1 : pair == 2 ? w2 : a0;   // SiLU inputs for the W_up wavefront
+  uint8_t *xu = pair == 3 ? a1 : xw + MT / 2 * CT * 1024;               // h W_up for the W_gate wavefront
+  f32x4v *xo = reinterpret_cast<f32x4v *>(mat ? xu : xw) + lane;
+  uint8_t *xi = mat ? xw : xu;
+  f32x4v own[MT / 2][CT];  // (moved, not selected by index: the accumulators stay in registers)
+  if (mat) {
+#pragma unroll
+    for (int i = 0; i < MT / 2; ++i)
+#pragma unroll
+      for (int j = 0; j < CT; ++j) xo[(i * CT + j) * 64] = acc[i + MT / 2][j], own[i][j] = acc[i][j];
+  } else {
+#pragma unroll
+    for (int i = 0; i < MT / 2; ++i)
+#pragma unroll
+      for (int j = 0; j < CT; ++j) xo[(i * CT + j) * 64] = acc[i][j], own[i][j] = acc[i + MT / 2][j];
+  }
+  __syncthreads();
+  const float thr = !CAL && a.thr ? *a.thr : 0.0f;
+  const int c0 = n0 + half * CW;
+  uint64_t kept = 0;  // bit 4 (i CT + j) + r
+#pragma unroll
+  for (int i = 0; i < MT / 2; ++i)
+#pragma unroll
+    for (int j = 0; j < CT; ++j) {
+      const int t = i * CT + j;
+      const f32x4v o = reinterpret_cast<const f32x4v *>(xi)[t * 64 + lane];
+      const f32x4v av = mat ? o : own[i][j], uv = mat ? own[i][j] : o;
+      uint16_t pb[4];
+#pragma unroll
+      for (int r = 0; r < 4; ++r) {
+        const float gv = silu(av[r]), pv = gv * uv[r];
+        if constexpr (CAL) {
+          const int m = m0 + lm0 + 16 * i + 4 * g + r, c = c0 + 16 * j + l16;
+          if (m < a.n && c < N) {
+            const uint16_t hi = f32_to_bf16(pv);
+            const size_t e = (size_t)m * N + c;
+            a.cal_g[e] = gv;
+            a.cal_ph[e] = hi;
+            a.cal_pl[e] = f32_to_bf16(pv - bf16_to_f32(hi));
+          }
+        } else {
+          const bool keep = ((base4[i] >> (8 * r)) & 0xffu) || fabsf(gv) >= thr;
+          kept |= (uint64_t)keep << ((4 * t + r) & 63);
+          pb[r] = f32_to_bf16(keep ? pv : 0.0f);
+        }
+      }
+      // the tile as 16 rows of 16 columns, over the part of the exchange already read
+      if constexpr (!CAL)
+#pragma unroll
+        for (int r = 0; r < 4; ++r) *reinterpret_cast<uint16_t *>(xi + t * 512 + (4 * g + r) * 32 + l16 * 2) = pb[r];
+    }
+  if constexpr (CAL) return;
+  // 16 bytes (a row's 8 columns) per lane and store: lane (row r, chunk q) of tile t
+  const int nbp = (N + kPfKC - 1) / kPfKC;  // k blocks of a row block of p
+#pragma unroll
+  for (int e = 0; e < MT / 2 * CT / 2; ++e) {
+    const int t = 2 * e + (lane & 1), r = (lane >> 2), q = (lane >> 1) & 1;
+    const u32x4 v = *reinterpret_cast<const u32x4 *>(xi + t * 512 + r * 32 + q * 16);
+    const int m = m0 + lm0 + 16 * (t / CT) + r, c = c0 + 16 * (t % CT) + 8 * q;
+    if (m < a.n && c < N)
+      *reinterpret_cast<u32x4 *>(a.P + ((size_t)(m >> 4) * nbp + (c >> 5)) * 512 + r * 32 +
+                                 (((c >> 3) & 3) ^ pf_swz(r)) * 8) = v;
+  }
+  if (a.keep_out)
+    for (int b = 0; b < MT / 2 * CT * 4; ++b) {
+      const int t = b >> 2, m = m0 + lm0 + 16 * (t / CT) + 4 * g + (b & 3), c = c0 + 16 * (t % CT) + l16;
+      if (m < a.n && c < N) a.keep_out[(size_t)m * N + c] = (uint8_t)((kept >> b) & 1);
+    }
+}
+
+// ---------------------------------------------------------------- down
+
+// Wavefront w takes rows (BM / WM) (w / WN) .. and columns (BN / WN) (w % WN)
+// .. of the tile; unit u is column tile u / ks and k chunk u % ks.
+template <int BM, int BN>
+__global__ __launch_bounds__(kPfThreads, 2) void pf_down_kernel(PfArgs a) {
+  constexpr int WM = BM == 256 && BN == 128 ? 4 : 2, WN = 8 / WM;
+  constexpr int MT = BM / WM / 16, CT = BN / WN / 16;
+  constexpr int IA = BM / 128, IW = BN / 128;  // 1 KB loads per wavefront and stage: p, W_down
+  constexpr int SA = BM * 64, SB = SA + BN * 64;
+  constexpr int R = SB <= 16 * 1024 ? 8 : SB <= 24 * 1024 ? 6 : 4;
+  constexpr int PB = BN * 2, RPL = 1024 / PB;  // W_down tile: bytes per row, rows per load
+  __shared__ __attribute__((aligned(1024))) uint8_t rg0[SB], rg1[SB], rg2[SB], rg3[SB], rg4[R > 4 ? SB : 16],
+      rg5[R > 4 ? SB : 16], rg6[R > 6 ? SB : 16], rg7[R > 6 ? SB : 16];
+  auto rb = [&](int i) -> uint8_t * {  // stage buffer i mod R
+    i %= R;
+    return i == 0 ? rg0 : i == 1 ? rg1 : i == 2 ? rg2 : i == 3 ? rg3 : i == 4 ? rg4 : i == 5 ? rg5 : i == 6 ? rg6 : rg7;
+  };
+  int mt0, unit;
+  if (!pf_tile(a, mt0, unit)) return;
+  const int lane = threadIdx.x & 63, w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int g = lane >> 4, l16 = lane & 15;
+  const int kc = unit % a.ks, m0 = mt0 * BM, n0 = (unit / a.ks) * BN;
+  const int K = a.K, N = a.N;
+  const int kb = kc * a.kchunk, ke = min(K, kb + a.kchunk);
+  const int S = ke > kb ? (ke - kb + kPfKC - 1) / kPfKC : 0;
+  const int wm = w / WN, wn = w % WN;
+  const int rows16 = (a.n + 15) / 16, nbp = (K + kPfKC - 1) / kPfKC;
+  const __amdgpu_buffer_rsrc_t rsp = dense_rsrc(a.A, (uint32_t)((size_t)rows16 * nbp * 1024));
+  const __amdgpu_buffer_rsrc_t rsw = dense_rsrc(a.Wd, (uint32_t)((size_t)K * N * 2));
+  // p: chunk q of each row holds k = 8 q .. of the block; chunks at or past ke are read as zeros
+  const int aq = 8 * ((lane & 3) ^ pf_swz(lane >> 2));
+  uint32_t aoff[IA], woff[IW];
+  const int wr = lane / (PB / 16);  // W_down: row of the lane's piece within the load
+#pragma unroll
+  for (int q = 0; q < IA; ++q) {
+    const int b = m0 / 16 + w + 8 * q;
+    aoff[q] = b < rows16 ? ((uint32_t)b * (uint32_t)nbp + (uint32_t)(kb / kPfKC)) * 1024u + 16u * lane : kDenseOffNone;
+  }
+#pragma unroll
+  for (int q = 0; q < IW; ++q) {
+    const int r = (w + 8 * q) * RPL + wr, p = lane % (PB / 16), c = n0 + 8 * (((p >> 1) ^ pf_kswz(r)) * 2 + (p & 1));
+    woff[q] = c < N ? (uint32_t)(((size_t)(kb + r) * N + c) * 2) : kDenseOffNone;
+  }
+  auto issue = [&](uint8_t *buf, int s) {
+    const int left = ke - kb - s * kPfKC;  // k of the chunk from this step on
+#pragma unroll
+    for (int q = 0; q < IA; ++q)
+      pf_dma(rsp, buf + (w + 8 * q) * 1024, aq < left ? aoff[q] : kDenseOffNone, (uint32_t)s * 1024u);
+#pragma unroll
+    for (int q = 0; q < IW; ++q)
+      pf_dma(rsw, buf + SA + (w + 8 * q) * 1024, wr + (w + 8 * q) * RPL < left ? woff[q] : kDenseOffNone,
+             (uint32_t)s * (uint32_t)(kPfKC * 2 * N));
+  };
+  bf16x8 oa[MT], ob0[CT], ob1[CT];  // operands: p, W_down of even and of odd steps
+  auto load_a = [&](const uint8_t *buf, int t) { return pf_block_operand(buf + (wm * MT + t) * 1024, l16, g); };
+  auto load_b = [&](uint8_t *buf, int t) { return pf_krow_operand(buf + SA, PB, wn * CT + t, g, l16); };
+  f32x4v acc[MT][CT];
+#pragma unroll
+  for (int i = 0; i < MT; ++i)
+#pragma unroll
+    for (int j = 0; j < CT; ++j) acc[i][j] = f32x4v{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+  for (int s = 0; s < R - 1; ++s) issue(rb(s), s);
+  pf_barrier<(R - 2) * (IA + IW)>();
+#pragma unroll
+  for (int t = 0; t < MT; ++t) oa[t] = load_a(rg0, t);
+#pragma unroll
+  for (int t = 0; t < CT; ++t) ob0[t] = load_b(rg0, t);
+  // step s, as in the gate/up kernel (a p operand is read once its last
+  // product is issued, into the same registers)
+  auto step = [&](int s, int p, bf16x8(&xb)[CT], bf16x8(&yb)[CT]) {
+    pf_barrier<(R - 3) * (IA + IW)>();
+    issue(rb(p + R - 1), s + R - 1);
+    uint8_t *nxt = rb(p + 1);
+#pragma unroll
+    for (int t = 0; t < CT; ++t) yb[t] = load_b(nxt, t);
+#pragma unroll
+    for (int i = 0; i < MT; ++i) {
+#pragma unroll
+      for (int j = 0; j < CT; ++j) acc[i][j] = mfma16(oa[i], xb[j], acc[i][j]);
+      oa[i] = load_a(nxt, i);
+    }
+#pragma unroll
+    for (int i = 0; i < MT * CT; ++i) {
+      __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);
+      if (i < 2 * CT || i % CT == CT - 1) __builtin_amdgcn_sched_group_barrier(0x100, 1, 0);
+    }
+  };
+  for (int s0 = 0; s0 < S; s0 += R) {
+    step(s0, 0, ob0, ob1);
+    step(s0 + 1, 1, ob1, ob0);
+    step(s0 + 2, 2, ob0, ob1);
+    step(s0 + 3, 3, ob1, ob0);
+    if constexpr (R > 4) {
+      step(s0 + 4, 4, ob0, ob1);
+      step(s0 + 5, 5, ob1, ob0);
+    }
+    if constexpr (R > 6) {
+      step(s0 + 6, 6, ob0, ob1);
+      step(s0 + 7, 7, ob1, ob0);
+    }
+  }
+  __builtin_amdgcn_s_waitcnt(0);
+#pragma unroll
+  for (int i = 0; i < MT; ++i)
+#pragma unroll
+    for (int r = 0; r < 4; ++r) {
+      const int m = m0 + (wm * MT + i) * 16 + 4 * g + r;
+      if (m >= a.n) continue;
+      float *o = a.part + ((size_t)kc * a.n + m) * N + n0 + wn * CT * 16 + l16;
+#pragma unroll
+      for (int j = 0; j < CT; ++j)
+        if (n0 + (wn * CT + j) * 16 + l16 < N) o[16 * j] = acc[i][j][r];
+    }
+}
+
+}  // namespace sats

@@ -19,6 +19,7 @@
 #include "kernels.hpp"
 #include "decode.hpp"
 #include "dense.hpp"
+#include "prefill.hpp"
 #include "calib.hpp"
 #include "route.hpp"
 
@@ -277,6 +278,114 @@ bool batch_mfma(int esz, bool vec_ok, int np, bool lora, int64_t d, int64_t d_ff
 }
 bool batch_whole() { return g_opt.batch_path != SATS_BATCH_SPLIT; }
 
+// ------------------------------------------------- batches of more than 64 tokens
+
+constexpr int kPfMaxPass = 2048;  // rows of a pass, at most
+
+// Tiles of one pass of np rows (see prefill.hpp).
+struct PfPlan {
+  int bm, nt;            // gate/up: rows and columns (of each projection) per workgroup
+  int dbm, dbn;          // down: rows and columns per workgroup
+  int ks, kchunk;        // down: d_ff chunks and their length
+};
+
+// Rows of every pass but the last: equal shares, whole 256-row tiles.
+int pf_pass(int64_t n) {
+  const int64_t passes = (n + kPfMaxPass - 1) / kPfMaxPass;
+  return (int)(((n + passes - 1) / passes + 255) / 256 * 256);
+}
+
+// A step of 32 k costs a workgroup of bm x bn products (mt x ct MFMA tiles
+// per wavefront) the larger of its products (16 cycles each on 4 matrix
+// cores) and its LDS reads (128 bytes per cycle), and the barrier.
+double pf_step_cycles(int bm, int bn, int mt, int ct) {
+  return std::max(bm * bn / 64.0, 64.0 * (mt + ct)) + 60.0;
+}
+
+// The tiles with the least modelled time: rounds of workgroups over the
+// compute units times the cycles of one; for the down-projection also the
+// partials' write and read (about 2000 bytes per cycle).
+PfPlan pf_plan(int64_t np, int64_t d, int64_t d_ff) {
+  const int64_t cus = std::max(1, device_cus());
+  auto cdiv = [](int64_t a, int64_t b) { return (a + b - 1) / b; };
+  PfPlan p{};
+  double best = 1e300;
+  for (const auto &[bm, nt] : {std::pair<int, int>{256, 128}, {256, 96}, {256, 64}, {128, 64}}) {
+    const double c = (double)cdiv(cdiv(np, bm) * cdiv(d_ff, nt), cus) *
+                     (double)(cdiv(d, sats::kPfKC) + 16) * pf_step_cycles(bm, 2 * nt, 4, bm == 256 ? nt / 16 : nt / 32);
+    if (c < best) best = c, p.bm = bm, p.nt = nt;
+  }
+  best = 1e300;
+  for (const auto &[bm, bn] : {std::pair<int, int>{256, 256}, {256, 128}, {128, 256}, {128, 128}})
+    for (int ks = 1; ks <= sats::kDenseMaxKsplit; ++ks) {
+      const int64_t kch = cdiv(cdiv(d_ff, ks), sats::kPfKC) * sats::kPfKC;
+      if (cdiv(d_ff, kch) != ks) continue;
+      const int mt = bm == 256 && bn == 256 ? 8 : 4, ct = bm == 128 && bn == 128 ? 2 : 4;
+      const double c = (double)cdiv(cdiv(np, bm) * cdiv(d, bn) * ks, cus) * (double)(kch / sats::kPfKC + 16) *
+                           pf_step_cycles(bm, bn, mt, ct) + (double)ks * np * d * 8.0 / 2000.0;
+      if (c < best) best = c, p.dbm = bm, p.dbn = bn, p.ks = ks, p.kchunk = (int)kch;
+    }
+  return p;
+}
+
+struct PfBuffers {
+  uint16_t *h, *p;  // row blocks of the layer input and of p
+  float *part;      // [ks][np][d]
+  uint8_t *gbase;   // [np], whole tiles of 256
+  uint8_t *keep;    // [np][d_ff] keep flags (inspection)
+};
+// elements of n rows of length k in row blocks
+int64_t pf_block_elems(int64_t n, int64_t k) { return (n + 15) / 16 * ((k + 31) / 32) * 512; }
+size_t pf_layout(char *base, int64_t np, int ks, int64_t d, int64_t d_ff, PfBuffers *b) {
+  Carve c{base};
+  PfBuffers t{};
+  t.h = c.take<uint16_t>(pf_block_elems(np, d));
+  t.p = c.take<uint16_t>(pf_block_elems(np, d_ff));
+  t.gbase = c.take<uint8_t>((np + 255) / 256 * 256);
+  t.part = c.take<float>((int64_t)ks * np * d);
+  t.keep = c.take<uint8_t>(np * d_ff);
+  if (b) *b = t;
+  return c.off;
+}
+// Workspace of a call of n tokens (every pass), and of any call of up to n.
+size_t pf_bytes(int64_t n, int64_t d, int64_t d_ff) {
+  const int pass = pf_pass(n);
+  size_t b = 0;
+  for (int64_t base = 0; base < n; base += pass) {
+    const int64_t np = std::min<int64_t>(pass, n - base);
+    b = std::max(b, pf_layout(nullptr, np, pf_plan(np, d, d_ff).ks, d, d_ff, nullptr));
+    if (base + 2 * pass < n) base += (n - base - 2 * pass) / pass * pass;  // the passes between are alike
+  }
+  return b;
+}
+size_t pf_bytes_upto(int64_t n, int64_t d, int64_t d_ff) {
+  size_t b = 0;
+  for (int64_t m = 128; m < std::min<int64_t>(n, kPfMaxPass) + 128; m += 128)
+    b = std::max(b, pf_layout(nullptr, m, pf_plan(m, d, d_ff).ks, d, d_ff, nullptr));
+  return b;
+}
+
+// bf16 batches of more than 64 tokens with every row on the matrix cores:
+// the tiled products.  (At 64 tokens and below the 64-row kernels stream the
+// weights at the memory's rate and skip W_down rows that no token keeps.)
+bool pf_ok(int esz, bool vec_ok, int64_t n, int64_t d, int64_t d_ff) {
+  return n > kMaxPass && batch_mfma(esz, vec_ok, kMaxPass, false, d, d_ff) && batch_whole();
+}
+
+typedef void (*PfKernel)(sats::PfArgs);
+PfKernel pf_gateup_fn(const PfPlan &p) {
+  using namespace sats;
+  if (p.bm == 128) return pf_gateup_kernel<128, 64, false>;
+  return p.nt == 128 ? pf_gateup_kernel<256, 128, false> : p.nt == 96 ? pf_gateup_kernel<256, 96, false>
+                                                                      : pf_gateup_kernel<256, 64, false>;
+}
+PfKernel pf_down_fn(const PfPlan &p) {
+  using namespace sats;
+  if (p.dbm == 256) return p.dbn == 256 ? pf_down_kernel<256, 256> : pf_down_kernel<256, 128>;
+  return p.dbn == 256 ? pf_down_kernel<128, 256> : pf_down_kernel<128, 128>;
+}
+unsigned pf_grid(int mtiles, int units) { return (unsigned)((units + 7) / 8 * 8 * mtiles); }
+
 struct Workspace {
   char *mem = nullptr;
   size_t bytes = 0;
@@ -420,6 +529,92 @@ struct Call {
   bool noalloc;
 };
 
+// One pass of np > 64 rows from token `base` on (see pf_ok).
+int run_prefill(const Call &c, char *mem, int64_t base, int np) {
+  using namespace sats;
+  const int64_t d = c.d, d_ff = c.d_ff;
+  const size_t wl = (size_t)d * (size_t)d_ff;
+  const PfPlan p = pf_plan(np, d, d_ff);
+  PfBuffers b{};
+  pf_layout(mem, np, p.ks, d, d_ff, &b);
+  const bool lists = c.active_count || c.active_idx;
+  {
+    PfPackArgs pa{};
+    pa.x = static_cast<const uint16_t *>(c.x) + base * d;
+    pa.A = b.h;
+    pa.gbase = b.gbase;
+    pa.ids = c.ids ? c.ids + base : nullptr;
+    pa.lut = c.lut;
+    pa.route_mode = c.route_mode;
+    pa.n = np;
+    pa.d = (int)d;
+    pa.route_out = c.route_out ? c.route_out + base : nullptr;
+    pa.layer_in = c.layer_in ? static_cast<uint16_t *>(c.layer_in) + base * d : nullptr;
+    const int blocks = (np + 15) / 16 * (int)((d + kPfKC - 1) / kPfKC);
+    hipLaunchKernelGGL(pf_pack_kernel, dim3((blocks + 3) / 4), dim3(kThreads), 0, c.stream, pa);
+    HIP_TRY(hipGetLastError());
+  }
+  PfArgs a{};
+  a.n = np;
+  for (int64_t l = 0; l < c.L; ++l) {
+    PfArgs u = a;
+    u.A = b.h;
+    u.gbase = b.gbase;
+    u.Wg = static_cast<const uint16_t *>(c.Wg) + l * wl;
+    u.Wu = static_cast<const uint16_t *>(c.Wu) + l * wl;
+    u.P = b.p;
+    u.thr = c.thr ? c.thr + l : nullptr;
+    u.keep_out = lists ? b.keep : nullptr;
+    u.K = (int)d;
+    u.N = (int)d_ff;
+    u.mtiles = (np + p.bm - 1) / p.bm;
+    u.units = (int)((d_ff + p.nt - 1) / p.nt);
+    {
+      TimedLaunch tl(SATS_K_DENSE, c.stream);
+      hipExtLaunchKernelGGL(pf_gateup_fn(p), dim3(pf_grid(u.mtiles, u.units)), dim3(kPfThreads), 0, c.stream, tl.start,
+                            tl.stop, 0, u);
+    }
+    HIP_TRY(hipGetLastError());
+    PfArgs w = a;
+    w.A = b.p;
+    w.Wd = static_cast<const uint16_t *>(c.Wd) + l * wl;
+    w.part = b.part;
+    w.K = (int)d_ff;
+    w.N = (int)d;
+    w.ks = p.ks;
+    w.kchunk = p.kchunk;
+    w.mtiles = (np + p.dbm - 1) / p.dbm;
+    w.units = (int)((d + p.dbn - 1) / p.dbn) * p.ks;
+    {
+      TimedLaunch tl(SATS_K_DENSE_DOWN, c.stream);
+      hipExtLaunchKernelGGL(pf_down_fn(p), dim3(pf_grid(w.mtiles, w.units)), dim3(kPfThreads), 0, c.stream, tl.start,
+                            tl.stop, 0, w);
+    }
+    HIP_TRY(hipGetLastError());
+    GlueArgs ga{};
+    ga.rows = np;
+    ga.part = b.part;
+    ga.ksplit = p.ks;
+    ga.d = (int)d;
+    ga.out = l == c.L - 1 ? static_cast<uint16_t *>(c.out) + base * d : nullptr;
+    ga.hnext = b.h;
+    ga.layer_in = c.layer_in && l + 1 < c.L ? static_cast<uint16_t *>(c.layer_in) + ((l + 1) * c.n + base) * d : nullptr;
+    hipLaunchKernelGGL(dense_glue_kernel, dim3(np), dim3(kGlueThreads), 0, c.stream, ga);
+    HIP_TRY(hipGetLastError());
+    if (lists) {
+      CompactArgs ca{};
+      ca.keep = b.keep;
+      ca.idx = c.active_idx ? c.active_idx + (l * c.n + base) * d_ff : nullptr;
+      ca.count = c.active_count ? c.active_count + l * c.n + base : nullptr;
+      ca.n = np;
+      ca.d_ff = (int)d_ff;
+      TimedLaunch tl(SATS_K_INSPECT, c.stream);
+      hipExtLaunchKernelGGL(compact_kernel, dim3(np), dim3(kThreads), 0, c.stream, tl.start, tl.stop, 0, ca);
+      HIP_TRY(hipGetLastError());
+    }
+  }
+  return SATS_OK;
+}
 
 template <typename T, int VEC, int NT>
 int run_pass(const Call &c, const Plan &p, const Buffers &b, unsigned *counters, int64_t base, int np) {
@@ -842,6 +1037,15 @@ int run(const Call &c) {
     if (!lora_batched(c, esz, vec_ok)) return run_lora<T>(c, vec_ok);
   }
   const int64_t lrank = c.Ag ? c.rank : 0;
+  if (!c.Ag && !c.noalloc && pf_ok(esz, vec_ok, c.n, c.d, c.d_ff)) {
+    Workspace *ws = nullptr;
+    int rc = ensure_workspace(c.stream, pf_bytes(c.n, c.d, c.d_ff), kCtl, &ws);
+    if (rc) return rc;
+    const int pass = pf_pass(c.n);
+    for (int64_t base = 0; base < c.n; base += pass)
+      if ((rc = run_prefill(c, ws->mem, base, (int)std::min<int64_t>(pass, c.n - base)))) return rc;
+    return SATS_OK;
+  }
   // single-token path: one token, vector layout, h fits the LDS copy
   bool decode = c.n == 1 && vec_ok && g_opt.single_token != SATS_SINGLE_OFF;
   DecodePlan dp;
@@ -1611,6 +1815,8 @@ int sats_reserve(int64_t max_tokens, int64_t d, int64_t d_ff, int64_t n_layers, 
                                        elem_bytes == 2 ? sats::kLoraMaxRank : 0));
         nc = std::max(nc, counter_count(p, pass, dp));
       }
+  if (pf_ok(elem_bytes, d % (16 / elem_bytes) == 0 && d_ff % (16 / elem_bytes) == 0, max_tokens, d, d_ff))
+    bytes = std::max(bytes, pf_bytes_upto(max_tokens, d, d_ff));
   Workspace *ws = nullptr;
   return ensure_workspace(stream, bytes, nc, &ws);
 }
