@@ -35,6 +35,8 @@
 // rows x 16 columns per 16 lanes) fall in distinct banks.
 #pragma once
 
+#include <type_traits>
+
 #include "dense.hpp"
 
 namespace sats {
@@ -71,6 +73,7 @@ struct PfArgs {
   const uint16_t *Wg, *Wu;  // gate/up: [N][K] each
   const uint16_t *Wd;     // down: [K][N]
   uint16_t *P;            // gate/up: row blocks of p
+  size_t pterm;           // split p: elements from one term's row blocks to the next's (P, A)
   float *part;            // down: partials [ks][n][N]
   const float *thr;       // layer threshold, or null (base path for every row)
   const uint8_t *gbase;   // base-path flag of each row (gate/up; allocated to whole tiles of 256)
@@ -140,6 +143,21 @@ __device__ __forceinline__ void pf_dma(__amdgpu_buffer_rsrc_t r, uint8_t *dst, u
   __builtin_amdgcn_raw_ptr_buffer_load_lds(r, (lds_void *)dst, 16, (int)voff, (int)soff, 0, 0);
 }
 
+// Sums of split shapes are folded: the accumulators of four steps (128 k) are
+// added to a second set and restart at zero.  A float32 sum
+// over 4096 k in one accumulator is about four times further from 64 bits
+// than the compacted kernels' (64 lanes of 64 terms each), which those shapes
+// take otherwise; folded, it is as near.
+template <int MT, int CT> __device__ __forceinline__ void pf_fold(f32x4v (&sum)[MT][CT], f32x4v (&acc)[MT][CT]) {
+#pragma unroll
+  for (int i = 0; i < MT; ++i)
+#pragma unroll
+    for (int j = 0; j < CT; ++j) {
+      sum[i][j] += acc[i][j];
+      acc[i][j] = f32x4v{0.f, 0.f, 0.f, 0.f};
+    }
+}
+
 // The ring buffers are an array per stage: the compiler then knows which
 // stage a pending load writes and adds no wait of its own before the LDS
 // reads of another (it tells at most 8 apart).
@@ -150,8 +168,13 @@ __device__ __forceinline__ void pf_dma(__amdgpu_buffer_rsrc_t r, uint8_t *dst, u
 // W_gate (w even) or W_up (w odd).  BM = 128: rows 64 (w / 4) .. + 63 and
 // half of the columns.  The rings hold 4 stages of h (32 k) and WR of the
 // weights (64 k, used by steps 2 j and 2 j + 1).
-template <int BM, int NT, bool CAL>
+// MODE: how p leaves the kernel.
+enum { PF_P16 = 0,   // rounded to bf16
+       PF_SPLIT = 1,  // three bf16 terms whose sum is p: rne(p), rne of the remainder, and the rest
+       PF_CAL = 2 };  // calibration: g in float32, and p as two terms, without the keep rule
+template <int BM, int NT, int MODE>
 __global__ __launch_bounds__(kPfThreads, 2) void pf_gateup_kernel(PfArgs a) {
+  constexpr bool CAL = MODE == PF_CAL;
   constexpr int WPG = 8 / (BM / 64);           // wavefronts per 64-row group
   constexpr int CW = NT / (WPG / 2);           // columns per wavefront
   constexpr int MT = 4, CT = CW / 16;          // its 16 x 16 tiles
@@ -221,6 +244,9 @@ __global__ __launch_bounds__(kPfThreads, 2) void pf_gateup_kernel(PfArgs a) {
   for (int i = 0; i < MT; ++i)
 #pragma unroll
     for (int j = 0; j < CT; ++j) acc[i][j] = f32x4v{0.f, 0.f, 0.f, 0.f};
+  constexpr bool FOLD = MODE == PF_SPLIT;
+  static_assert(!FOLD || CT <= 4, "registers of the second set");
+  f32x4v sum[FOLD ? MT : 1][FOLD ? CT : 1] = {};
   // the order of the loop's loads, from 2 WR - 2 steps before the first
 #pragma unroll
   for (int s = 2 - 2 * WR; s < 0; ++s) {
@@ -261,10 +287,12 @@ __global__ __launch_bounds__(kPfThreads, 2) void pf_gateup_kernel(PfArgs a) {
     step(s0 + 1, 1, oa1, oa0);
     step(s0 + 2, 2, oa0, oa1);
     step(s0 + 3, 3, oa1, oa0);
+    if constexpr (FOLD) pf_fold(sum, acc);
     step(s0 + 4, 4, oa0, oa1);
     step(s0 + 5, 5, oa1, oa0);
     step(s0 + 6, 6, oa0, oa1);
     step(s0 + 7, 7, oa1, oa0);
+    if constexpr (FOLD) pf_fold(sum, acc);
     if constexpr (U > 8) {
       step(s0 + 8, 8, oa0, oa1);
       step(s0 + 9, 9, oa1, oa0);
@@ -273,6 +301,11 @@ __global__ __launch_bounds__(kPfThreads, 2) void pf_gateup_kernel(PfArgs a) {
     }
   }
   __builtin_amdgcn_s_waitcnt(0);  // the zero-filling loads past the range land too
+  if constexpr (FOLD)
+#pragma unroll
+    for (int i = 0; i < MT; ++i)
+#pragma unroll
+      for (int j = 0; j < CT; ++j) acc[i][j] = sum[i][j];
   __syncthreads();
   // epilogue: the wavefronts of W_gate and W_up of the same rows and columns
   // (a pair) trade half of their tiles through LDS, lane to lane: the W_up
@@ -306,7 +339,7 @@ __global__ __launch_bounds__(kPfThreads, 2) void pf_gateup_kernel(PfArgs a) {
       const int t = i * CT + j;
       const f32x4v o = reinterpret_cast<const f32x4v *>(xi)[t * 64 + lane];
       const f32x4v av = mat ? o : own[i][j], uv = mat ? own[i][j] : o;
-      uint16_t pb[4];
+      float pk[4];
 #pragma unroll
       for (int r = 0; r < 4; ++r) {
         const float gv = silu(av[r]), pv = gv * uv[r];
@@ -322,13 +355,18 @@ __global__ __launch_bounds__(kPfThreads, 2) void pf_gateup_kernel(PfArgs a) {
         } else {
           const bool keep = ((base4[i] >> (8 * r)) & 0xffu) || fabsf(gv) >= thr;
           kept |= (uint64_t)keep << ((4 * t + r) & 63);
-          pb[r] = f32_to_bf16(keep ? pv : 0.0f);
+          pk[r] = keep ? pv : 0.0f;
         }
       }
       // the tile as 16 rows of 16 columns, over the part of the exchange already read
       if constexpr (!CAL)
 #pragma unroll
-        for (int r = 0; r < 4; ++r) *reinterpret_cast<uint16_t *>(xi + t * 512 + (4 * g + r) * 32 + l16 * 2) = pb[r];
+        for (int r = 0; r < 4; ++r) {
+          if constexpr (MODE == PF_SPLIT)
+            *reinterpret_cast<float *>(xi + t * 1024 + (4 * g + r) * 64 + l16 * 4) = pk[r];
+          else
+            *reinterpret_cast<uint16_t *>(xi + t * 512 + (4 * g + r) * 32 + l16 * 2) = f32_to_bf16(pk[r]);
+        }
     }
   if constexpr (CAL) return;
   // 16 bytes (a row's 8 columns) per lane and store: lane (row r, chunk q) of tile t
@@ -336,11 +374,26 @@ __global__ __launch_bounds__(kPfThreads, 2) void pf_gateup_kernel(PfArgs a) {
 #pragma unroll
   for (int e = 0; e < MT / 2 * CT / 2; ++e) {
     const int t = 2 * e + (lane & 1), r = (lane >> 2), q = (lane >> 1) & 1;
-    const u32x4 v = *reinterpret_cast<const u32x4 *>(xi + t * 512 + r * 32 + q * 16);
     const int m = m0 + lm0 + 16 * (t / CT) + r, c = c0 + 16 * (t % CT) + 8 * q;
-    if (m < a.n && c < N)
-      *reinterpret_cast<u32x4 *>(a.P + ((size_t)(m >> 4) * nbp + (c >> 5)) * 512 + r * 32 +
-                                 (((c >> 3) & 3) ^ pf_swz(r)) * 8) = v;
+    uint16_t *o = a.P + ((size_t)(m >> 4) * nbp + (c >> 5)) * 512 + r * 32 + (((c >> 3) & 3) ^ pf_swz(r)) * 8;
+    if constexpr (MODE == PF_SPLIT) {
+      float v[8];
+      *reinterpret_cast<f32x4v *>(v) = *reinterpret_cast<const f32x4v *>(xi + t * 1024 + r * 64 + q * 32);
+      *reinterpret_cast<f32x4v *>(v + 4) = *reinterpret_cast<const f32x4v *>(xi + t * 1024 + r * 64 + q * 32 + 16);
+#pragma unroll
+      for (int h = 0; h < 3; ++h) {
+        uint16_t b[8];
+#pragma unroll
+        for (int k = 0; k < 8; ++k) {
+          b[k] = f32_to_bf16(v[k]);
+          v[k] -= bf16_to_f32(b[k]);
+        }
+        if (m < a.n && c < N) *reinterpret_cast<u32x4 *>(o + h * a.pterm) = *reinterpret_cast<const u32x4 *>(b);
+      }
+    } else {
+      const u32x4 v = *reinterpret_cast<const u32x4 *>(xi + t * 512 + r * 32 + q * 16);
+      if (m < a.n && c < N) *reinterpret_cast<u32x4 *>(o) = v;
+    }
   }
   if (a.keep_out)
     for (int b = 0; b < MT / 2 * CT * 4; ++b) {
@@ -353,20 +406,31 @@ __global__ __launch_bounds__(kPfThreads, 2) void pf_gateup_kernel(PfArgs a) {
 
 // Wavefront w takes rows (BM / WM) (w / WN) .. and columns (BN / WN) (w % WN)
 // .. of the tile; unit u is column tile u / ks and k chunk u % ks.
-template <int BM, int BN>
+// SPLIT: p comes as three bf16 terms, each multiplied with the same W_down
+// operands (a stage holds the terms' blocks; tiles of 128 rows, for the LDS
+// they take).  With two terms (16 bits of p) the sums were 4e-6 from those of
+// float32 p, and roundings of the next layer's input that fell the other way
+// moved a two-layer result by up to half its own rounding error; with three
+// the two agree.
+template <int BM, int BN, bool SPLIT>
 __global__ __launch_bounds__(kPfThreads, 2) void pf_down_kernel(PfArgs a) {
   constexpr int WM = BM == 256 && BN == 128 ? 4 : 2, WN = 8 / WM;
   constexpr int MT = BM / WM / 16, CT = BN / WN / 16;
-  constexpr int IA = BM / 128, IW = BN / 128;  // 1 KB loads per wavefront and stage: p, W_down
-  constexpr int SA = BM * 64, SB = SA + BN * 64;
-  constexpr int R = SB <= 16 * 1024 ? 8 : SB <= 24 * 1024 ? 6 : 4;
+  constexpr int NP = SPLIT ? 3 : 1;            // terms of p
+  constexpr int IA = BM / 128, IW = BN / 128;  // 1 KB loads per wavefront and stage: a term of p, W_down
+  constexpr int SA = BM * 64, SB = SA + BN * 64, SL = SPLIT ? 2 * SA : 16;  // stage bytes; further terms of p apart
+  static_assert(!SPLIT || BM == 128, "LDS of a stage");
+  constexpr int R = SPLIT ? 4 : SB <= 16 * 1024 ? 8 : SB <= 24 * 1024 ? 6 : 4;
   constexpr int PB = BN * 2, RPL = 1024 / PB;  // W_down tile: bytes per row, rows per load
-  __shared__ __attribute__((aligned(1024))) uint8_t rg0[SB], rg1[SB], rg2[SB], rg3[SB], rg4[R > 4 ? SB : 16],
-      rg5[R > 4 ? SB : 16], rg6[R > 6 ? SB : 16], rg7[R > 6 ? SB : 16];
+  __shared__ __attribute__((aligned(1024))) uint8_t rg0[SB], rg1[SB], rg2[SB], rg3[SB],
+      rg4[R > 4 ? SB : 16], rg5[R > 4 ? SB : 16], rg6[R > 6 ? SB : 16], rg7[R > 6 ? SB : 16], l0[SL], l1[SL], l2[SL],
+      l3[SL];
   auto rb = [&](int i) -> uint8_t * {  // stage buffer i mod R
     i %= R;
     return i == 0 ? rg0 : i == 1 ? rg1 : i == 2 ? rg2 : i == 3 ? rg3 : i == 4 ? rg4 : i == 5 ? rg5 : i == 6 ? rg6 : rg7;
   };
+  auto lb = [&](int i) -> uint8_t * { return (i %= R) == 0 ? l0 : i == 1 ? l1 : i == 2 ? l2 : l3; };
+  (void)lb;
   int mt0, unit;
   if (!pf_tile(a, mt0, unit)) return;
   const int lane = threadIdx.x & 63, w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
@@ -377,7 +441,7 @@ __global__ __launch_bounds__(kPfThreads, 2) void pf_down_kernel(PfArgs a) {
   const int S = ke > kb ? (ke - kb + kPfKC - 1) / kPfKC : 0;
   const int wm = w / WN, wn = w % WN;
   const int rows16 = (a.n + 15) / 16, nbp = (K + kPfKC - 1) / kPfKC;
-  const __amdgpu_buffer_rsrc_t rsp = dense_rsrc(a.A, (uint32_t)((size_t)rows16 * nbp * 1024));
+  const uint32_t pbytes = (uint32_t)((size_t)rows16 * nbp * 1024);
   const __amdgpu_buffer_rsrc_t rsw = dense_rsrc(a.Wd, (uint32_t)((size_t)K * N * 2));
   // p: chunk q of each row holds k = 8 q .. of the block; chunks at or past ke are read as zeros
   const int aq = 8 * ((lane & 3) ^ pf_swz(lane >> 2));
@@ -393,11 +457,13 @@ __global__ __launch_bounds__(kPfThreads, 2) void pf_down_kernel(PfArgs a) {
     const int r = (w + 8 * q) * RPL + wr, p = lane % (PB / 16), c = n0 + 8 * (((p >> 1) ^ pf_kswz(r)) * 2 + (p & 1));
     woff[q] = c < N ? (uint32_t)(((size_t)(kb + r) * N + c) * 2) : kDenseOffNone;
   }
-  auto issue = [&](uint8_t *buf, int s) {
+  auto issue = [&](uint8_t *buf, uint8_t *lo, int s) {
     const int left = ke - kb - s * kPfKC;  // k of the chunk from this step on
 #pragma unroll
-    for (int q = 0; q < IA; ++q)
-      pf_dma(rsp, buf + (w + 8 * q) * 1024, aq < left ? aoff[q] : kDenseOffNone, (uint32_t)s * 1024u);
+    for (int q = 0; q < NP * IA; ++q)
+      pf_dma(dense_rsrc(a.A + (q / IA) * a.pterm, pbytes),
+             (q < IA ? buf : lo + (q / IA - 1) * SA) + (w + 8 * (q % IA)) * 1024,
+             aq < left ? aoff[q % IA] : kDenseOffNone, (uint32_t)s * 1024u);
 #pragma unroll
     for (int q = 0; q < IW; ++q)
       pf_dma(rsw, buf + SA + (w + 8 * q) * 1024, wr + (w + 8 * q) * RPL < left ? woff[q] : kDenseOffNone,
@@ -411,21 +477,23 @@ __global__ __launch_bounds__(kPfThreads, 2) void pf_down_kernel(PfArgs a) {
   for (int i = 0; i < MT; ++i)
 #pragma unroll
     for (int j = 0; j < CT; ++j) acc[i][j] = f32x4v{0.f, 0.f, 0.f, 0.f};
+  f32x4v sum[SPLIT ? MT : 1][SPLIT ? CT : 1] = {};
 #pragma unroll
-  for (int s = 0; s < R - 1; ++s) issue(rb(s), s);
-  pf_barrier<(R - 2) * (IA + IW)>();
+  for (int s = 0; s < R - 1; ++s) issue(rb(s), lb(s), s);
+  constexpr int IS = NP * IA + IW;  // loads of a stage
+  pf_barrier<(R - 2) * IS>();
 #pragma unroll
   for (int t = 0; t < MT; ++t) oa[t] = load_a(rg0, t);
 #pragma unroll
   for (int t = 0; t < CT; ++t) ob0[t] = load_b(rg0, t);
-  // step s, as in the gate/up kernel (a p operand is read once its last
-  // product is issued, into the same registers)
-  auto step = [&](int s, int p, bf16x8(&xb)[CT], bf16x8(&yb)[CT]) {
-    pf_barrier<(R - 3) * (IA + IW)>();
-    issue(rb(p + R - 1), s + R - 1);
-    uint8_t *nxt = rb(p + 1);
-#pragma unroll
-    for (int t = 0; t < CT; ++t) yb[t] = load_b(nxt, t);
+  // (opaque: against a constant offset the compiler sees that the loads of
+  // the second term write elsewhere, finds none it knows to write here, and
+  // waits for all)
+  int third = SA;
+  asm volatile("" : "+s"(third));
+  // products of the p operands held with xb, each p operand replaced by the
+  // one at `nxt` once its last product is issued
+  auto prod = [&](const uint8_t *nxt, bf16x8(&xb)[CT], auto reads) {
 #pragma unroll
     for (int i = 0; i < MT; ++i) {
 #pragma unroll
@@ -435,8 +503,21 @@ __global__ __launch_bounds__(kPfThreads, 2) void pf_down_kernel(PfArgs a) {
 #pragma unroll
     for (int i = 0; i < MT * CT; ++i) {
       __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);
-      if (i < 2 * CT || i % CT == CT - 1) __builtin_amdgcn_sched_group_barrier(0x100, 1, 0);
+      if (i < reads.value || i % CT == CT - 1) __builtin_amdgcn_sched_group_barrier(0x100, 1, 0);
     }
+  };
+  // step s, as in the gate/up kernel (with split p the first two terms' products
+  // come before the barrier: they need nothing of stage s + 1)
+  auto step = [&](int s, int p, bf16x8(&xb)[CT], bf16x8(&yb)[CT]) {
+    if constexpr (SPLIT) {
+      prod(lb(p), xb, std::integral_constant<int, 0>{});
+      prod(lb(p) + third, xb, std::integral_constant<int, 0>{});
+    }
+    pf_barrier<(R - 3) * IS>();
+    issue(rb(p + R - 1), lb(p + R - 1), s + R - 1);
+#pragma unroll
+    for (int t = 0; t < CT; ++t) yb[t] = load_b(rb(p + 1), t);
+    prod(rb(p + 1), xb, std::integral_constant<int, 2 * CT>{});
   };
   for (int s0 = 0; s0 < S; s0 += R) {
     step(s0, 0, ob0, ob1);
@@ -451,8 +532,14 @@ __global__ __launch_bounds__(kPfThreads, 2) void pf_down_kernel(PfArgs a) {
       step(s0 + 6, 6, ob0, ob1);
       step(s0 + 7, 7, ob1, ob0);
     }
+    if constexpr (SPLIT) pf_fold(sum, acc);
   }
   __builtin_amdgcn_s_waitcnt(0);
+  if constexpr (SPLIT)
+#pragma unroll
+    for (int i = 0; i < MT; ++i)
+#pragma unroll
+      for (int j = 0; j < CT; ++j) acc[i][j] = sum[i][j];
 #pragma unroll
   for (int i = 0; i < MT; ++i)
 #pragma unroll

@@ -278,7 +278,7 @@ bool batch_mfma(int esz, bool vec_ok, int np, bool lora, int64_t d, int64_t d_ff
 }
 bool batch_whole() { return g_opt.batch_path != SATS_BATCH_SPLIT; }
 
-// ------------------------------------------------- batches of more than 64 tokens
+// ------------------------------------------------- tiled products (prefill.hpp)
 
 constexpr int kPfMaxPass = 2048;  // rows of a pass, at most
 
@@ -302,6 +302,10 @@ double pf_step_cycles(int bm, int bn, int mt, int ct) {
   return std::max(bm * bn / 64.0, 64.0 * (mt + ct)) + 60.0;
 }
 
+// Whether p is kept as three bf16 terms: shapes outside the 64-row kernels' tiles,
+// whose other batch kernels keep p in float32.
+bool pf_split(int64_t d, int64_t d_ff) { return d % sats::kDenseDownNT != 0 || d_ff % sats::kDenseKC != 0; }
+
 // The tiles with the least modelled time: rounds of workgroups over the
 // compute units times the cycles of one; for the down-projection also the
 // partials' write and read (about 2000 bytes per cycle).
@@ -309,8 +313,10 @@ PfPlan pf_plan(int64_t np, int64_t d, int64_t d_ff) {
   const int64_t cus = std::max(1, device_cus());
   auto cdiv = [](int64_t a, int64_t b) { return (a + b - 1) / b; };
   PfPlan p{};
+  const bool split = pf_split(d, d_ff);
   double best = 1e300;
   for (const auto &[bm, nt] : {std::pair<int, int>{256, 128}, {256, 96}, {256, 64}, {128, 64}}) {
+    if (split && nt != 64) continue;
     const double c = (double)cdiv(cdiv(np, bm) * cdiv(d_ff, nt), cus) *
                      (double)(cdiv(d, sats::kPfKC) + 16) * pf_step_cycles(bm, 2 * nt, 4, bm == 256 ? nt / 16 : nt / 32);
     if (c < best) best = c, p.bm = bm, p.nt = nt;
@@ -320,19 +326,20 @@ PfPlan pf_plan(int64_t np, int64_t d, int64_t d_ff) {
     for (int ks = 1; ks <= sats::kDenseMaxKsplit; ++ks) {
       const int64_t kch = cdiv(cdiv(d_ff, ks), sats::kPfKC) * sats::kPfKC;
       if (cdiv(d_ff, kch) != ks) continue;
+      if (split && bm != 128) continue;
       const int mt = bm == 256 && bn == 256 ? 8 : 4, ct = bm == 128 && bn == 128 ? 2 : 4;
       const double c = (double)cdiv(cdiv(np, bm) * cdiv(d, bn) * ks, cus) * (double)(kch / sats::kPfKC + 16) *
-                           pf_step_cycles(bm, bn, mt, ct) + (double)ks * np * d * 8.0 / 2000.0;
+                           (split ? 3.0 : 1.0) * pf_step_cycles(bm, bn, mt, ct) + (double)ks * np * d * 8.0 / 2000.0;
       if (c < best) best = c, p.dbm = bm, p.dbn = bn, p.ks = ks, p.kchunk = (int)kch;
     }
   return p;
 }
 
 struct PfBuffers {
-  uint16_t *h, *p;  // row blocks of the layer input and of p
-  float *part;      // [ks][np][d]
-  uint8_t *gbase;   // [np], whole tiles of 256
-  uint8_t *keep;    // [np][d_ff] keep flags (inspection)
+  uint16_t *h, *p;       // row blocks of the layer input and of p (split: of its three terms)
+  float *part;           // [ks][np][d]
+  uint8_t *gbase;        // [np], whole tiles of 256
+  uint8_t *keep;         // [np][d_ff] keep flags (inspection)
 };
 // elements of n rows of length k in row blocks
 int64_t pf_block_elems(int64_t n, int64_t k) { return (n + 15) / 16 * ((k + 31) / 32) * 512; }
@@ -340,7 +347,7 @@ size_t pf_layout(char *base, int64_t np, int ks, int64_t d, int64_t d_ff, PfBuff
   Carve c{base};
   PfBuffers t{};
   t.h = c.take<uint16_t>(pf_block_elems(np, d));
-  t.p = c.take<uint16_t>(pf_block_elems(np, d_ff));
+  t.p = c.take<uint16_t>((pf_split(d, d_ff) ? 3 : 1) * pf_block_elems(np, d_ff));
   t.gbase = c.take<uint8_t>((np + 255) / 256 * 256);
   t.part = c.take<float>((int64_t)ks * np * d);
   t.keep = c.take<uint8_t>(np * d_ff);
@@ -349,40 +356,50 @@ size_t pf_layout(char *base, int64_t np, int ks, int64_t d, int64_t d_ff, PfBuff
 }
 // Workspace of a call of n tokens (every pass), and of any call of up to n.
 size_t pf_bytes(int64_t n, int64_t d, int64_t d_ff) {
-  const int pass = pf_pass(n);
+  const int64_t pass = pf_pass(n), last = n - (n - 1) / pass * pass;
   size_t b = 0;
-  for (int64_t base = 0; base < n; base += pass) {
-    const int64_t np = std::min<int64_t>(pass, n - base);
+  for (const int64_t np : {std::min(pass, n), last})
     b = std::max(b, pf_layout(nullptr, np, pf_plan(np, d, d_ff).ks, d, d_ff, nullptr));
-    if (base + 2 * pass < n) base += (n - base - 2 * pass) / pass * pass;  // the passes between are alike
-  }
   return b;
 }
 size_t pf_bytes_upto(int64_t n, int64_t d, int64_t d_ff) {
   size_t b = 0;
-  for (int64_t m = 128; m < std::min<int64_t>(n, kPfMaxPass) + 128; m += 128)
+  for (int64_t m = 1; m <= std::min<int64_t>(n, kPfMaxPass); ++m)
     b = std::max(b, pf_layout(nullptr, m, pf_plan(m, d, d_ff).ks, d, d_ff, nullptr));
   return b;
 }
 
-// bf16 batches of more than 64 tokens with every row on the matrix cores:
-// the tiled products.  (At 64 tokens and below the 64-row kernels stream the
-// weights at the memory's rate and skip W_down rows that no token keeps.)
-bool pf_ok(int esz, bool vec_ok, int64_t n, int64_t d, int64_t d_ff) {
-  return n > kMaxPass && batch_mfma(esz, vec_ok, kMaxPass, false, d, d_ff) && batch_whole();
+// Whether a batch runs on the tiled products: bf16, rows of 16-byte pieces
+// (`aligned`: every array on 16 bytes), matrices and p below 2 GB, every row
+// on the matrix cores, and
+//  - more than 64 tokens.  At 64 and below the 64-row kernels stream the
+//    weights at the memory's rate and skip W_down rows that no token keeps
+//    (64 tokens of a Llama-3.1-8B layer 75 us; here about 110); above, each
+//    further pass streams them again (1000 tokens 1303 us; here 331), or
+//  - 2 or more tokens of a shape that is not on the 64-row kernels' tiles and
+//    would take the compacted kernels (7 tokens through two layers of 1024 x
+//    2730: 186 us there).
+bool pf_ok(int esz, bool aligned, int64_t n, int64_t d, int64_t d_ff) {
+  return esz == 2 && aligned && d % 8 == 0 && d <= 4096 && d_ff <= (1 << 19) - 32 &&
+         (uint64_t)d * d_ff * 2 < (1ull << 31) && (n > kMaxPass || (n >= sats::kMfmaMinTokens && pf_split(d, d_ff))) &&
+         (g_opt.batch_path == SATS_BATCH_AUTO || g_opt.batch_path == SATS_BATCH_MFMA);
 }
 
 typedef void (*PfKernel)(sats::PfArgs);
-PfKernel pf_gateup_fn(const PfPlan &p) {
+template <int MODE> PfKernel pf_gateup_fn(const PfPlan &p) {
   using namespace sats;
-  if (p.bm == 128) return pf_gateup_kernel<128, 64, false>;
-  return p.nt == 128 ? pf_gateup_kernel<256, 128, false> : p.nt == 96 ? pf_gateup_kernel<256, 96, false>
-                                                                      : pf_gateup_kernel<256, 64, false>;
+  if (p.bm == 128) return pf_gateup_kernel<128, 64, MODE>;
+  if constexpr (MODE != PF_SPLIT) {
+    if (p.nt == 128) return pf_gateup_kernel<256, 128, MODE>;
+    if (p.nt == 96) return pf_gateup_kernel<256, 96, MODE>;
+  }
+  return pf_gateup_kernel<256, 64, MODE>;
 }
-PfKernel pf_down_fn(const PfPlan &p) {
+template <bool SPLIT> PfKernel pf_down_fn(const PfPlan &p) {
   using namespace sats;
-  if (p.dbm == 256) return p.dbn == 256 ? pf_down_kernel<256, 256> : pf_down_kernel<256, 128>;
-  return p.dbn == 256 ? pf_down_kernel<128, 256> : pf_down_kernel<128, 128>;
+  if constexpr (!SPLIT)
+    if (p.dbm == 256) return p.dbn == 256 ? pf_down_kernel<256, 256, false> : pf_down_kernel<256, 128, false>;
+  return p.dbn == 256 ? pf_down_kernel<128, 256, SPLIT> : pf_down_kernel<128, 128, SPLIT>;
 }
 unsigned pf_grid(int mtiles, int units) { return (unsigned)((units + 7) / 8 * 8 * mtiles); }
 
@@ -529,7 +546,7 @@ struct Call {
   bool noalloc;
 };
 
-// One pass of np > 64 rows from token `base` on (see pf_ok).
+// One pass of np rows from token `base` on through the tiled products (see pf_ok).
 int run_prefill(const Call &c, char *mem, int64_t base, int np) {
   using namespace sats;
   const int64_t d = c.d, d_ff = c.d_ff;
@@ -537,7 +554,7 @@ int run_prefill(const Call &c, char *mem, int64_t base, int np) {
   const PfPlan p = pf_plan(np, d, d_ff);
   PfBuffers b{};
   pf_layout(mem, np, p.ks, d, d_ff, &b);
-  const bool lists = c.active_count || c.active_idx;
+  const bool lists = c.active_count || c.active_idx, split = pf_split(d, d_ff);
   {
     PfPackArgs pa{};
     pa.x = static_cast<const uint16_t *>(c.x) + base * d;
@@ -563,6 +580,7 @@ int run_prefill(const Call &c, char *mem, int64_t base, int np) {
     u.Wg = static_cast<const uint16_t *>(c.Wg) + l * wl;
     u.Wu = static_cast<const uint16_t *>(c.Wu) + l * wl;
     u.P = b.p;
+    u.pterm = (size_t)pf_block_elems(np, d_ff);
     u.thr = c.thr ? c.thr + l : nullptr;
     u.keep_out = lists ? b.keep : nullptr;
     u.K = (int)d;
@@ -571,12 +589,13 @@ int run_prefill(const Call &c, char *mem, int64_t base, int np) {
     u.units = (int)((d_ff + p.nt - 1) / p.nt);
     {
       TimedLaunch tl(SATS_K_DENSE, c.stream);
-      hipExtLaunchKernelGGL(pf_gateup_fn(p), dim3(pf_grid(u.mtiles, u.units)), dim3(kPfThreads), 0, c.stream, tl.start,
+      hipExtLaunchKernelGGL(split ? pf_gateup_fn<PF_SPLIT>(p) : pf_gateup_fn<PF_P16>(p), dim3(pf_grid(u.mtiles, u.units)), dim3(kPfThreads), 0, c.stream, tl.start,
                             tl.stop, 0, u);
     }
     HIP_TRY(hipGetLastError());
     PfArgs w = a;
     w.A = b.p;
+    w.pterm = u.pterm;
     w.Wd = static_cast<const uint16_t *>(c.Wd) + l * wl;
     w.part = b.part;
     w.K = (int)d_ff;
@@ -587,7 +606,7 @@ int run_prefill(const Call &c, char *mem, int64_t base, int np) {
     w.units = (int)((d + p.dbn - 1) / p.dbn) * p.ks;
     {
       TimedLaunch tl(SATS_K_DENSE_DOWN, c.stream);
-      hipExtLaunchKernelGGL(pf_down_fn(p), dim3(pf_grid(w.mtiles, w.units)), dim3(kPfThreads), 0, c.stream, tl.start,
+      hipExtLaunchKernelGGL(split ? pf_down_fn<true>(p) : pf_down_fn<false>(p), dim3(pf_grid(w.mtiles, w.units)), dim3(kPfThreads), 0, c.stream, tl.start,
                             tl.stop, 0, w);
     }
     HIP_TRY(hipGetLastError());
@@ -1026,9 +1045,11 @@ int run(const Call &c) {
       return fail(SATS_ERR_ARG, "out overlaps x without being equal to it");
   }
   const int vec = 16 / esz;
-  const bool vec_ok = c.d % vec == 0 && c.d_ff % vec == 0 && aligned16(c.x) && aligned16(c.out) &&
-                      aligned16(c.Wg) && aligned16(c.Wu) && aligned16(c.Wd) &&
-                      (!c.layer_in || aligned16(c.layer_in));
+  // rows of 16-byte pieces at aligned addresses; the compacted and the LoRA
+  // kernels also need columns in whole pieces
+  const bool vec_d = c.d % vec == 0 && aligned16(c.x) && aligned16(c.out) && aligned16(c.Wg) && aligned16(c.Wu) &&
+                     aligned16(c.Wd) && (!c.layer_in || aligned16(c.layer_in));
+  const bool vec_ok = vec_d && c.d_ff % vec == 0;
   const int pass = (int)std::min<int64_t>(c.n, kMaxPass);
   const Plan p = make_plan(c.d, c.d_ff, esz, vec_ok, pass);
   if (c.Ag) {
@@ -1037,17 +1058,30 @@ int run(const Call &c) {
     if (!lora_batched(c, esz, vec_ok)) return run_lora<T>(c, vec_ok);
   }
   const int64_t lrank = c.Ag ? c.rank : 0;
-  if (!c.Ag && !c.noalloc && pf_ok(esz, vec_ok, c.n, c.d, c.d_ff)) {
-    Workspace *ws = nullptr;
-    int rc = ensure_workspace(c.stream, pf_bytes(c.n, c.d, c.d_ff), kCtl, &ws);
-    if (rc) return rc;
-    const int pass = pf_pass(c.n);
-    for (int64_t base = 0; base < c.n; base += pass)
-      if ((rc = run_prefill(c, ws->mem, base, (int)std::min<int64_t>(pass, c.n - base)))) return rc;
-    return SATS_OK;
+  if (!c.Ag && pf_ok(esz, vec_d, c.n, c.d, c.d_ff)) {
+    const size_t need = pf_bytes(c.n, c.d, c.d_ff);
+    char *mem = nullptr;
+    int rc = 0;
+    // the allocation-free call takes this path when its workspace fits
+    if (c.noalloc) {
+      if (need <= kScratchBytes - kScratchCounterBytes) {
+        if ((rc = scratch_addr(&mem))) return rc;
+        mem += kScratchCounterBytes;
+      }
+    } else {
+      Workspace *ws = nullptr;
+      if ((rc = ensure_workspace(c.stream, need, kCtl, &ws))) return rc;
+      mem = ws->mem;
+    }
+    if (mem) {
+      const int rows = pf_pass(c.n);
+      for (int64_t base = 0; base < c.n; base += rows)
+        if ((rc = run_prefill(c, mem, base, (int)std::min<int64_t>(rows, c.n - base)))) return rc;
+      return SATS_OK;
+    }
   }
   // single-token path: one token, vector layout, h fits the LDS copy
-  bool decode = c.n == 1 && vec_ok && g_opt.single_token != SATS_SINGLE_OFF;
+  bool decode = c.n == 1 && vec_d && g_opt.single_token != SATS_SINGLE_OFF;
   DecodePlan dp;
   if (decode) decode = make_decode_plan(c.d, c.d_ff, esz, &dp);
   const size_t bytes = layout(nullptr, p, pass, c.d, c.d_ff, esz, c.L, dp, nullptr, lrank);
@@ -1815,7 +1849,7 @@ int sats_reserve(int64_t max_tokens, int64_t d, int64_t d_ff, int64_t n_layers, 
                                        elem_bytes == 2 ? sats::kLoraMaxRank : 0));
         nc = std::max(nc, counter_count(p, pass, dp));
       }
-  if (pf_ok(elem_bytes, d % (16 / elem_bytes) == 0 && d_ff % (16 / elem_bytes) == 0, max_tokens, d, d_ff))
+  if (pf_ok(elem_bytes, true, max_tokens, d, d_ff))
     bytes = std::max(bytes, pf_bytes_upto(max_tokens, d, d_ff));
   Workspace *ws = nullptr;
   return ensure_workspace(stream, bytes, nc, &ws);
@@ -1903,12 +1937,16 @@ int sats_query_path(int64_t n_tokens, int64_t d, int64_t d_ff, int elem_bytes, i
   *path = 0;
   if (n_tokens == 0) return SATS_OK;
   const int vec = 16 / elem_bytes;
-  const bool vec_ok = aligned16 && d % vec == 0 && d_ff % vec == 0;
+  const bool vec_d = aligned16 && d % vec == 0, vec_ok = vec_d && d_ff % vec == 0;
   const int cus = n_cus > 0 ? n_cus : device_cus();
   DecodePlan dp;
-  if (n_tokens == 1 && vec_ok && g_opt.single_token != SATS_SINGLE_OFF &&
+  if (n_tokens == 1 && vec_d && g_opt.single_token != SATS_SINGLE_OFF &&
       make_decode_plan(d, d_ff, elem_bytes, &dp, 0, cus)) {
     *path = SATS_PATH_SINGLE_TOKEN;
+    return SATS_OK;
+  }
+  if (pf_ok(elem_bytes, vec_d, n_tokens, d, d_ff)) {
+    *path = SATS_PATH_BATCH_MFMA;
     return SATS_OK;
   }
   const int np = (int)std::min<int64_t>(n_tokens, kMaxPass);

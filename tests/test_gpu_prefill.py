@@ -1,6 +1,7 @@
-"""Batches of more than 64 tokens (the tiled matrix-core products) against the
-oracle: rows and columns at the edges of their tiles and of the 16-row blocks,
-stacks, both routes, and passes of unequal length.  Tolerances are those of
+"""The tiled matrix-core products (batches of more than 64 tokens, and batches
+of shapes that are on no whole tile) against the oracle: rows and columns at
+the edges of their tiles and of the 16-row blocks, widths in 16-byte pieces
+only, stacks, both routes, and passes of unequal length.  Tolerances are those of
 tests/harness.py: p and the output are rounded to bf16 (2^-9 each) and the
 sums are float32, well inside the 2e-2 bound on the largest element."""
 import numpy as np
@@ -21,6 +22,16 @@ CASES = [
     (105, 2, 256, 1024, 256),
     (106, 3, 640, 1536, 257),    # k of 20 steps
     (107, 1, 2048, 6144, 700),
+    # widths of 16-byte rows only: p in two terms
+    (120, 2, 24, 41, 2),         # less than one step of k, less than one tile
+    (121, 2, 264, 333, 7),
+    (122, 1, 1000, 2730, 66),    # k ends in the first half of a weight stage
+    (123, 3, 200, 77, 130),
+    (124, 1, 384, 1000, 16),     # only d_ff off the tiles
+    (125, 2, 520, 1600, 300),    # only d off the tiles
+    (126, 1, 2056, 5999, 520),
+    # one token, d_ff in no whole 16-byte pieces: the single-token kernels
+    (127, 2, 256, 1001, 1),
 ]
 
 
@@ -29,7 +40,7 @@ def test_prefill_matches_oracle_and_inspection_changes_nothing(seed, L, d, dff, 
     print(f"prefill case seed={seed} L={L} d={d} d_ff={dff} n={n}", flush=True)
     c = synth.small_case(seed, L, d, dff, "bf16", n, vocab=40, n_dense_ids=12, w_std=1.0 / np.sqrt(d))
     ts = case_thresholds(c, "bf16", seed=seed)
-    tokens = sorted({0, 15, 16, 63, 64, n // 2, min(n - 1, 127), min(n - 1, 128), min(n - 1, 255), n - 1})
+    tokens = sorted({t for t in (0, 15, 16, 63, 64, n // 2, 127, 128, 255, n - 1) if t < n})
     for lut in (None, c["route_lut"]):
         res = run_gpu(c, ts, lut, "bf16")
         worst = check_against_oracle(c, ts, lut, "bf16", res, tokens=tokens)
@@ -58,3 +69,23 @@ def test_prefill_in_two_passes_gives_each_half_alone():
         parts.append(from_dev(o))
     torch.cuda.synchronize()
     np.testing.assert_array_equal(from_dev(out), np.concatenate(parts))
+
+
+@pytest.mark.parametrize("d,dff,n", [(264, 333, 7), (128, 256, 100)])
+def test_allocation_free_call_takes_the_same_kernels(d, dff, n):
+    """A batch whose workspace fits the fixed scratch gives sats_mlp_forward's bits."""
+    import torch
+    import paper_2607_08991_amd as sats
+    c = synth.small_case(131, 2, d, dff, "bf16", n, vocab=40, n_dense_ids=12, w_std=1.0 / np.sqrt(d))
+    ts = case_thresholds(c, "bf16", seed=131)
+    assert sats.sats_query_path(n, d, dff, 2) == sats.SATS_PATH_BATCH_MFMA
+    x, w = to_dev(c["x"], "bf16"), list(weights_dev(c, "bf16"))
+    ids, lut = to_dev(np.asarray(c["token_ids"], np.int32), "bf16"), to_dev(c["route_lut"], "bf16")
+    thr = torch.tensor(np.asarray(ts, np.float32)).cuda()
+    outs = []
+    for call in (sats.sats_mlp_forward, sats.sats_mlp_forward_noalloc):
+        o = torch.empty_like(x)
+        call(x, ids, *w, thr, lut, o, n, d, dff, 2)
+        outs.append(from_dev(o))
+    torch.cuda.synchronize()
+    np.testing.assert_array_equal(*outs)
