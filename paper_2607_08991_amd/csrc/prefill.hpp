@@ -144,10 +144,10 @@ __device__ __forceinline__ void pf_dma(__amdgpu_buffer_rsrc_t r, uint8_t *dst, u
 }
 
 // Sums of split shapes are folded: the accumulators of four steps (128 k) are
-// added to a second set and restart at zero.  A float32 sum
-// over 4096 k in one accumulator is about four times further from 64 bits
-// than the compacted kernels' (64 lanes of 64 terms each), which those shapes
-// take otherwise; folded, it is as near.
+// added to a second set and restart at zero.  A float32 sum over 4096 k in one
+// accumulator is about four times further from 64 bits than the compacted
+// kernels' (64 lanes of 64 terms each), which those shapes take otherwise;
+// folded, it is as near.
 template <int MT, int CT> __device__ __forceinline__ void pf_fold(f32x4v (&sum)[MT][CT], f32x4v (&acc)[MT][CT]) {
 #pragma unroll
   for (int i = 0; i < MT; ++i)
@@ -156,6 +156,20 @@ template <int MT, int CT> __device__ __forceinline__ void pf_fold(f32x4v (&sum)[
       sum[i][j] += acc[i][j];
       acc[i][j] = f32x4v{0.f, 0.f, 0.f, 0.f};
     }
+}
+
+// Eight columns of p as three bf16 terms, 16 bytes of each term's row blocks.
+__device__ __forceinline__ void pf_store_terms(uint16_t *o, size_t pterm, float (&v)[8]) {
+#pragma unroll
+  for (int h = 0; h < 3; ++h) {
+    uint16_t b[8];
+#pragma unroll
+    for (int k = 0; k < 8; ++k) {
+      b[k] = f32_to_bf16(v[k]);
+      v[k] -= bf16_to_f32(b[k]);
+    }
+    *reinterpret_cast<u32x4 *>(o + h * pterm) = *reinterpret_cast<const u32x4 *>(b);
+  }
 }
 
 // The ring buffers are an array per stage: the compiler then knows which
@@ -380,16 +394,7 @@ __global__ __launch_bounds__(kPfThreads, 2) void pf_gateup_kernel(PfArgs a) {
       float v[8];
       *reinterpret_cast<f32x4v *>(v) = *reinterpret_cast<const f32x4v *>(xi + t * 1024 + r * 64 + q * 32);
       *reinterpret_cast<f32x4v *>(v + 4) = *reinterpret_cast<const f32x4v *>(xi + t * 1024 + r * 64 + q * 32 + 16);
-#pragma unroll
-      for (int h = 0; h < 3; ++h) {
-        uint16_t b[8];
-#pragma unroll
-        for (int k = 0; k < 8; ++k) {
-          b[k] = f32_to_bf16(v[k]);
-          v[k] -= bf16_to_f32(b[k]);
-        }
-        if (m < a.n && c < N) *reinterpret_cast<u32x4 *>(o + h * a.pterm) = *reinterpret_cast<const u32x4 *>(b);
-      }
+      if (m < a.n && c < N) pf_store_terms(o, a.pterm, v);
     } else {
       const u32x4 v = *reinterpret_cast<const u32x4 *>(xi + t * 512 + r * 32 + q * 16);
       if (m < a.n && c < N) *reinterpret_cast<u32x4 *>(o) = v;
@@ -550,6 +555,208 @@ __global__ __launch_bounds__(kPfThreads, 2) void pf_down_kernel(PfArgs a) {
 #pragma unroll
       for (int j = 0; j < CT; ++j)
         if (n0 + (wn * CT + j) * 16 + l16 < N) o[16 * j] = acc[i][j][r];
+    }
+}
+
+// ---------------------------------------------------------------- up to 64 rows
+
+// The same products for at most 16 MT <= 64 rows of a split shape, where the
+// weights' stream and the latency of a short loop are the bound: stages of 64
+// k (whole 128-byte lines), every wavefront 16 columns of all rows, and
+// enough workgroups to spread short matrices over the chip (the tiles of 128
+// rows above put 7 tokens of a 1024 x 2730 layer on 43 workgroups: gate/up
+// 14.8 and down 8.1 us; here 7.8 and 4.0).  Grid: column tiles (times k chunks).  Three or more loads per
+// wavefront and stage; slots of the stage that nothing needs are read as zeros
+// without a memory access.
+
+// Columns [nt b, nt b + nt) of both projections: wavefronts 0-3 W_gate, 4-7 W_up.
+template <int MT>
+__global__ __launch_bounds__(kPfThreads, 2) void sm_gateup_kernel(PfArgs a, int nt) {
+  constexpr int SW = 16 * 1024, SB = SW + 8 * 1024, R = 6;  // W_gate and W_up 8 KB each, h
+  __shared__ __attribute__((aligned(1024))) uint8_t rg0[SB], rg1[SB], rg2[SB], rg3[SB], rg4[SB], rg5[SB];
+  auto rb = [&](int i) -> uint8_t * {
+    return (i %= R) == 0 ? rg0 : i == 1 ? rg1 : i == 2 ? rg2 : i == 3 ? rg3 : i == 4 ? rg4 : rg5;
+  };
+  const int lane = threadIdx.x & 63, w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int g = lane >> 4, l16 = lane & 15, mat = w >> 2, ct = w & 3;
+  const int K = a.K, N = a.N, n0 = blockIdx.x * nt;
+  const int nb = (K + kPfKC - 1) / kPfKC, S = (nb + 1) / 2;
+  uint32_t base4[MT];
+#pragma unroll
+  for (int i = 0; i < MT; ++i) base4[i] = *reinterpret_cast<const uint32_t *>(a.gbase + 16 * i + 4 * g);
+  const int rows16 = (a.n + 15) / 16;
+  const __amdgpu_buffer_rsrc_t rsa = dense_rsrc(a.A, (uint32_t)(rows16 * nb * 1024));
+  const uint32_t wbytes = (uint32_t)((size_t)N * K * 2);
+  const __amdgpu_buffer_rsrc_t rsg = dense_rsrc(a.Wg, wbytes), rsu = dense_rsrc(a.Wu, wbytes);
+  // wavefront w: rows 8 w .. 8 w + 7 of each projection, and block w & 1 of row tile w / 2 of h
+  const int lr = lane >> 3, lq = (lane & 7) ^ lr, row = 8 * w + lr;
+  const uint32_t woff = row < nt && n0 + row < N ? (uint32_t)(((size_t)(n0 + row) * K + 8 * lq) * 2) : kDenseOffNone;
+  const uint32_t aoff = w / 2 < MT && w / 2 < rows16 ? (uint32_t)((w / 2 * nb + (w & 1)) * 1024 + 16 * lane) : kDenseOffNone;
+  auto issue = [&](uint8_t *buf, int s) {
+    const bool v = 64 * s + 8 * lq < K;
+    pf_dma(rsg, buf + w * 1024, v ? woff : kDenseOffNone, (uint32_t)s * 128u);
+    pf_dma(rsu, buf + 8192 + w * 1024, v ? woff : kDenseOffNone, (uint32_t)s * 128u);
+    pf_dma(rsa, buf + SW + w * 1024, 2 * s + (w & 1) < nb ? aoff : kDenseOffNone, (uint32_t)s * 2048u);
+  };
+  bf16x8 oa0[2][MT], oa1[2][MT], ob0[2], ob1[2];  // operands of even and odd stages
+  auto load = [&](const uint8_t *buf, bf16x8(&xa)[2][MT], bf16x8(&xb)[2]) {
+#pragma unroll
+    for (int h = 0; h < 2; ++h) {
+      const int r = 16 * ct + l16;
+      xb[h] = __builtin_bit_cast(bf16x8, *reinterpret_cast<const u32x4 *>(buf + mat * 8192 + r * 128 +
+                                                                         ((4 * h + g) ^ (r & 7)) * 16));
+#pragma unroll
+      for (int i = 0; i < MT; ++i) xa[h][i] = pf_block_operand(buf + SW + (2 * i + h) * 1024, l16, g);
+    }
+  };
+  f32x4v acc[MT][1] = {}, sum[MT][1] = {};
+#pragma unroll
+  for (int s = 0; s < R - 1; ++s) issue(rb(s), s);
+  pf_barrier<(R - 2) * 3>();
+  load(rg0, oa0, ob0);
+  // stage s: stage s + 1 has landed, every wavefront holds the operands of stage s
+  auto step = [&](int s, int p, bf16x8(&xa)[2][MT], bf16x8(&xb)[2], bf16x8(&ya)[2][MT], bf16x8(&yb)[2]) {
+    pf_barrier<(R - 3) * 3>();
+    issue(rb(p + R - 1), s + R - 1);
+    load(rb(p + 1), ya, yb);
+#pragma unroll
+    for (int h = 0; h < 2; ++h)
+#pragma unroll
+      for (int i = 0; i < MT; ++i) acc[i][0] = mfma16(xa[h][i], xb[h], acc[i][0]);
+  };
+  for (int s0 = 0; s0 < S; s0 += R) {
+    step(s0, 0, oa0, ob0, oa1, ob1);
+    step(s0 + 1, 1, oa1, ob1, oa0, ob0);
+    pf_fold(sum, acc);
+    step(s0 + 2, 2, oa0, ob0, oa1, ob1);
+    step(s0 + 3, 3, oa1, ob1, oa0, ob0);
+    pf_fold(sum, acc);
+    step(s0 + 4, 4, oa0, ob0, oa1, ob1);
+    step(s0 + 5, 5, oa1, ob1, oa0, ob0);
+    pf_fold(sum, acc);
+  }
+  __builtin_amdgcn_s_waitcnt(0);
+  __syncthreads();
+  // epilogue: SiLU lane to lane to the wavefront of W_up, p through LDS to 16-byte stores of its terms
+  uint8_t *xt = rg0 + ct * MT * 1024;
+  if (mat == 0) {
+#pragma unroll
+    for (int i = 0; i < MT; ++i) {
+      f32x4v v;
+#pragma unroll
+      for (int r = 0; r < 4; ++r) v[r] = silu(sum[i][0][r]);
+      reinterpret_cast<f32x4v *>(xt)[i * 64 + lane] = v;
+    }
+  }
+  __syncthreads();
+  if (mat == 0 || 16 * ct >= nt) return;
+  const float thr = a.thr ? *a.thr : 0.0f;
+  const int nbp = (N + kPfKC - 1) / kPfKC, c0 = n0 + 16 * ct;
+#pragma unroll
+  for (int i = 0; i < MT; ++i) {
+    const f32x4v gv = reinterpret_cast<const f32x4v *>(xt)[i * 64 + lane];
+#pragma unroll
+    for (int r = 0; r < 4; ++r) {
+      const int m = 16 * i + 4 * g + r, c = c0 + l16;
+      const bool keep = ((base4[i] >> (8 * r)) & 0xffu) || fabsf(gv[r]) >= thr;
+      *reinterpret_cast<float *>(xt + i * 1024 + (4 * g + r) * 64 + l16 * 4) = keep ? gv[r] * sum[i][0][r] : 0.0f;
+      if (a.keep_out && m < a.n && c < N) a.keep_out[(size_t)m * N + c] = (uint8_t)keep;
+    }
+  }
+  // lane: row, half of the tile's columns (8), and one of two row tiles
+#pragma unroll
+  for (int i0 = 0; i0 < MT; i0 += 2) {
+    const int i = i0 + (lane & 1), r = lane >> 2, q = (lane >> 1) & 1, m = 16 * i + r, c = c0 + 8 * q;
+    if (i >= MT || m >= a.n || c >= N) continue;
+    float v[8];
+    *reinterpret_cast<f32x4v *>(v) = *reinterpret_cast<const f32x4v *>(xt + i * 1024 + r * 64 + q * 32);
+    *reinterpret_cast<f32x4v *>(v + 4) = *reinterpret_cast<const f32x4v *>(xt + i * 1024 + r * 64 + q * 32 + 16);
+    pf_store_terms(a.P + ((size_t)i * nbp + (c >> 5)) * 512 + r * 32 + (((c >> 3) & 3) ^ pf_swz(r)) * 8, a.pterm, v);
+  }
+}
+
+// 128 columns of one k chunk: wavefront w columns 16 w .. 16 w + 15.
+template <int MT>
+__global__ __launch_bounds__(kPfThreads, 2) void sm_down_kernel(PfArgs a) {
+  constexpr int IP = (6 * MT + 7) / 8;                       // loads of p per wavefront and stage (6 MT KB)
+  constexpr int SW = 16 * 1024, SB = SW + IP * 8 * 1024, R = SB <= 24 * 1024 ? 6 : 4, IS = 2 + IP;
+  __shared__ __attribute__((aligned(1024))) uint8_t rg0[SB], rg1[SB], rg2[SB], rg3[SB], rg4[R > 4 ? SB : 16],
+      rg5[R > 4 ? SB : 16];
+  auto rb = [&](int i) -> uint8_t * {
+    return (i %= R) == 0 ? rg0 : i == 1 ? rg1 : i == 2 ? rg2 : i == 3 ? rg3 : i == 4 ? rg4 : rg5;
+  };
+  const int lane = threadIdx.x & 63, w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int g = lane >> 4, l16 = lane & 15;
+  const int K = a.K, N = a.N, kc = blockIdx.x % a.ks, n0 = blockIdx.x / a.ks * 128;
+  const int kb = kc * a.kchunk, ke = min(K, kb + a.kchunk);
+  const int S = ke > kb ? (ke - kb + 63) / 64 : 0;
+  const int rows16 = (a.n + 15) / 16, nbp = (K + kPfKC - 1) / kPfKC;
+  const __amdgpu_buffer_rsrc_t rsw = dense_rsrc(a.Wd, (uint32_t)((size_t)K * N * 2));
+  const uint32_t pbytes = (uint32_t)(rows16 * nbp * 1024);
+  // W_down: load q of wavefront w is rows 4 (w + 8 q) .. + 3 of the stage, 256 bytes each
+  const int wr = 4 * w + (lane >> 4);
+  uint32_t woff[2], aoff[IP];
+#pragma unroll
+  for (int q = 0; q < 2; ++q) {
+    const int r = wr + 32 * q, c = n0 + 8 * (((l16 >> 1) ^ pf_kswz(r)) * 2 + (l16 & 1));
+    woff[q] = c < N ? (uint32_t)(((size_t)(kb + r) * N + c) * 2) : kDenseOffNone;
+  }
+  // p: load i = w + 8 q is term i / (2 MT), row tile (i / 2) % MT, k block i & 1 of the stage
+  const int aq = 8 * ((lane & 3) ^ pf_swz(lane >> 2)) + kPfKC * (w & 1);
+#pragma unroll
+  for (int q = 0; q < IP; ++q) {
+    const int i = w + 8 * q, t = i / 2 % MT;
+    aoff[q] = i < 6 * MT && t < rows16 ? (uint32_t)((t * nbp + kb / kPfKC + (i & 1)) * 1024 + 16 * lane) : kDenseOffNone;
+  }
+  auto issue = [&](uint8_t *buf, int s) {
+    const int left = ke - kb - 64 * s;
+#pragma unroll
+    for (int q = 0; q < 2; ++q)
+      pf_dma(rsw, buf + (w + 8 * q) * 1024, wr + 32 * q < left ? woff[q] : kDenseOffNone, (uint32_t)s * (uint32_t)(128 * N));
+#pragma unroll
+    for (int q = 0; q < IP; ++q)
+      pf_dma(dense_rsrc(a.A + min((w + 8 * q) / (2 * MT), 2) * a.pterm, pbytes), buf + SW + (w + 8 * q) * 1024,
+             aq < left ? aoff[q] : kDenseOffNone, (uint32_t)s * 2048u);
+  };
+  f32x4v acc[MT][1] = {}, sum[MT][1] = {};
+#pragma unroll
+  for (int s = 0; s < R - 1; ++s) issue(rb(s), s);
+  // (operands read where they are used: a chunk has few stages)
+  auto step = [&](int s, int p) {
+    pf_barrier<(R - 2) * IS>();
+    issue(rb(p + R - 1), s + R - 1);
+    uint8_t *buf = rb(p);
+#pragma unroll
+    for (int h = 0; h < 2; ++h) {
+      const bf16x8 b = pf_krow_operand(buf + h * 8192, 256, w, g, l16);
+#pragma unroll
+      for (int t = 0; t < 3; ++t)
+#pragma unroll
+        for (int i = 0; i < MT; ++i)
+          acc[i][0] = mfma16(pf_block_operand(buf + SW + ((t * MT + i) * 2 + h) * 1024, l16, g), b, acc[i][0]);
+    }
+  };
+  for (int s0 = 0; s0 < S; s0 += R) {
+    step(s0, 0);
+    step(s0 + 1, 1);
+    pf_fold(sum, acc);
+    step(s0 + 2, 2);
+    step(s0 + 3, 3);
+    pf_fold(sum, acc);
+    if constexpr (R > 4) {
+      step(s0 + 4, 4);
+      step(s0 + 5, 5);
+      pf_fold(sum, acc);
+    }
+  }
+  __builtin_amdgcn_s_waitcnt(0);
+  const int c = n0 + 16 * w + l16;
+#pragma unroll
+  for (int i = 0; i < MT; ++i)
+#pragma unroll
+    for (int r = 0; r < 4; ++r) {
+      const int m = 16 * i + 4 * g + r;
+      if (m < a.n && c < N) a.part[((size_t)kc * a.n + m) * N + c] = sum[i][0][r];
     }
 }
 

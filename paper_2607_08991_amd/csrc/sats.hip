@@ -287,6 +287,7 @@ struct PfPlan {
   int bm, nt;            // gate/up: rows and columns (of each projection) per workgroup
   int dbm, dbn;          // down: rows and columns per workgroup
   int ks, kchunk;        // down: d_ff chunks and their length
+  bool small;            // the kernels of up to 64 rows (nt a multiple of 16)
 };
 
 // Rows of every pass but the last: equal shares, whole 256-row tiles.
@@ -314,6 +315,15 @@ PfPlan pf_plan(int64_t np, int64_t d, int64_t d_ff) {
   auto cdiv = [](int64_t a, int64_t b) { return (a + b - 1) / b; };
   PfPlan p{};
   const bool split = pf_split(d, d_ff);
+  if (split && np <= kMaxPass) {
+    // gate/up columns and down chunks (whole 64-row stages) for a workgroup per compute unit
+    p.small = true;
+    p.nt = (int)std::clamp<int64_t>(cdiv(cdiv(d_ff, cus), 16) * 16, 16, 64);
+    const int64_t ks = std::clamp<int64_t>(cus / cdiv(d, 128), 1, std::min<int64_t>(sats::kDenseMaxKsplit, cdiv(d_ff, 64)));
+    p.kchunk = (int)(cdiv(cdiv(d_ff, ks), 64) * 64);
+    p.ks = (int)cdiv(d_ff, p.kchunk);
+    return p;
+  }
   double best = 1e300;
   for (const auto &[bm, nt] : {std::pair<int, int>{256, 128}, {256, 96}, {256, 64}, {128, 64}}) {
     if (split && nt != 64) continue;
@@ -378,7 +388,7 @@ size_t pf_bytes_upto(int64_t n, int64_t d, int64_t d_ff) {
 //    further pass streams them again (1000 tokens 1303 us; here 331), or
 //  - 2 or more tokens of a shape that is not on the 64-row kernels' tiles and
 //    would take the compacted kernels (7 tokens through two layers of 1024 x
-//    2730: 186 us there).
+//    2730: 186 us there, 35 here).
 bool pf_ok(int esz, bool aligned, int64_t n, int64_t d, int64_t d_ff) {
   return esz == 2 && aligned && d % 8 == 0 && d <= 4096 && d_ff <= (1 << 19) - 32 &&
          (uint64_t)d * d_ff * 2 < (1ull << 31) && (n > kMaxPass || (n >= sats::kMfmaMinTokens && pf_split(d, d_ff))) &&
@@ -400,6 +410,17 @@ template <bool SPLIT> PfKernel pf_down_fn(const PfPlan &p) {
   if constexpr (!SPLIT)
     if (p.dbm == 256) return p.dbn == 256 ? pf_down_kernel<256, 256, false> : pf_down_kernel<256, 128, false>;
   return p.dbn == 256 ? pf_down_kernel<128, 256, SPLIT> : pf_down_kernel<128, 128, SPLIT>;
+}
+typedef void (*SmGateup)(sats::PfArgs, int);
+SmGateup sm_gateup_fn(int np) {
+  using namespace sats;
+  const int mt = (np + 15) / 16;
+  return mt <= 1 ? sm_gateup_kernel<1> : mt == 2 ? sm_gateup_kernel<2> : mt == 3 ? sm_gateup_kernel<3> : sm_gateup_kernel<4>;
+}
+PfKernel sm_down_fn(int np) {
+  using namespace sats;
+  const int mt = (np + 15) / 16;
+  return mt <= 1 ? sm_down_kernel<1> : mt == 2 ? sm_down_kernel<2> : mt == 3 ? sm_down_kernel<3> : sm_down_kernel<4>;
 }
 unsigned pf_grid(int mtiles, int units) { return (unsigned)((units + 7) / 8 * 8 * mtiles); }
 
@@ -585,9 +606,13 @@ int run_prefill(const Call &c, char *mem, int64_t base, int np) {
     u.keep_out = lists ? b.keep : nullptr;
     u.K = (int)d;
     u.N = (int)d_ff;
-    u.mtiles = (np + p.bm - 1) / p.bm;
     u.units = (int)((d_ff + p.nt - 1) / p.nt);
-    {
+    if (p.small) {
+      TimedLaunch tl(SATS_K_DENSE, c.stream);
+      hipExtLaunchKernelGGL(sm_gateup_fn(np), dim3((unsigned)u.units), dim3(kPfThreads), 0, c.stream, tl.start, tl.stop,
+                            0, u, p.nt);
+    } else {
+      u.mtiles = (np + p.bm - 1) / p.bm;
       TimedLaunch tl(SATS_K_DENSE, c.stream);
       hipExtLaunchKernelGGL(split ? pf_gateup_fn<PF_SPLIT>(p) : pf_gateup_fn<PF_P16>(p), dim3(pf_grid(u.mtiles, u.units)), dim3(kPfThreads), 0, c.stream, tl.start,
                             tl.stop, 0, u);
@@ -602,9 +627,13 @@ int run_prefill(const Call &c, char *mem, int64_t base, int np) {
     w.N = (int)d;
     w.ks = p.ks;
     w.kchunk = p.kchunk;
-    w.mtiles = (np + p.dbm - 1) / p.dbm;
-    w.units = (int)((d + p.dbn - 1) / p.dbn) * p.ks;
-    {
+    if (p.small) {
+      TimedLaunch tl(SATS_K_DENSE_DOWN, c.stream);
+      hipExtLaunchKernelGGL(sm_down_fn(np), dim3((unsigned)((d + 127) / 128 * p.ks)), dim3(kPfThreads), 0, c.stream,
+                            tl.start, tl.stop, 0, w);
+    } else {
+      w.mtiles = (np + p.dbm - 1) / p.dbm;
+      w.units = (int)((d + p.dbn - 1) / p.dbn) * p.ks;
       TimedLaunch tl(SATS_K_DENSE_DOWN, c.stream);
       hipExtLaunchKernelGGL(split ? pf_down_fn<true>(p) : pf_down_fn<false>(p), dim3(pf_grid(w.mtiles, w.units)), dim3(kPfThreads), 0, c.stream, tl.start,
                             tl.stop, 0, w);
