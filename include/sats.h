@@ -342,7 +342,9 @@ int sats_set_options(const sats_options *opt);
  * under the calling thread's options, answered on the host without device
  * work: *path receives SATS_PATH_SINGLE_TOKEN, SATS_PATH_BATCH_MFMA,
  * SATS_PATH_BATCH_SPLIT or SATS_PATH_BATCH_COMPACT (for the first pass of
- * up to 64 tokens; 0 for n_tokens == 0).  elem_bytes: 2 (bf16) or 4
+ * up to 64 tokens; 0 for n_tokens == 0).  SATS_PATH_BATCH_COMPACT also names
+ * the float32 batch kernels (float32 matrix-core products where rows are
+ * 16-byte pieces and d <= 4096, else the compacted kernels).  elem_bytes: 2 (bf16) or 4
  * (float32); aligned16: whether x, out and the weights are 16-byte aligned;
  * n_cus: compute units of the device (0: the current device's).  Errors:
  * SATS_ERR_NULL, SATS_ERR_SHAPE and SATS_ERR_ARG as for the forward calls.

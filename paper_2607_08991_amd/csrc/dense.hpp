@@ -898,7 +898,7 @@ __global__ __launch_bounds__(kDenseThreads) void cal_err_kernel(CalErrArgs a) {
 #undef SATS_DENSE_STEP8
 #undef SATS_DENSE_STEP
 
-// Row blocks (the layout of h and p in prefill.hpp): 16 rows by 32 k, chunk q
+// Row blocks (the layout of h and p in prefill.hpp): 16 rows by 64 bytes, chunk q
 // (16 bytes) of row r at q ^ pf_swz(r) of the row's 64 bytes.  A 16-byte LDS
 // read serves lanes 0-3, 12-15, 20-27 (and so on) at once: with rows on the
 // lanes of each 16 and k on the groups of 16, these must differ in the chunk
@@ -912,9 +912,9 @@ struct GlueArgs {
   const int *perm;
   const float *part;      // [KSPLIT][n_dense][d]
   int ksplit, d;
-  uint16_t *out;          // last layer: [n][d] of the pass, rows through perm; else null
-  uint16_t *hnext;        // otherwise: next layer input of the dense group, [n_dense][d] (ctl null: row blocks)
-  uint16_t *layer_in;     // optional: inspection copy of the next layer input, rows through perm
+  void *out;              // last layer: [n][d] of the pass (T), rows through perm; else null
+  void *hnext;        // otherwise: next layer input of the dense group, [n_dense][d] (ctl null: row blocks)
+  void *layer_in;         // optional: inspection copy of the next layer input, rows through perm
   // LoRA (zpart null: none): y += s z B_down for sparse-path rows, z the sum
   // over the nzb column tiles of zpart [nzb][kDenseMaxTokens][rank], in tile order
   const float *zpart;
@@ -927,7 +927,7 @@ struct GlueArgs {
 // one workgroup per dense token (blockIdx.x); thread t owns columns
 // 4 t .. 4 t + 3 and issues its loads of every partial at once
 constexpr int kGlueThreads = 1024;
-__global__ __launch_bounds__(kGlueThreads) void dense_glue_kernel(GlueArgs a) {
+template <typename T> __global__ __launch_bounds__(kGlueThreads) void dense_glue_kernel(GlueArgs a) {
   if (a.ctl && !a.ctl[1]) return;
   const int m = blockIdx.x;
   const int nd = a.ctl ? a.ctl[0] : a.rows;
@@ -938,7 +938,7 @@ __global__ __launch_bounds__(kGlueThreads) void dense_glue_kernel(GlueArgs a) {
   const bool on = c < a.d;
   // LoRA, sparse-path row: B_down[k][c .. c + 3] of the first 16 ranks, loaded
   // with the partials (it does not depend on z)
-  const bool lora = a.zpart && !a.gbase[m];
+  const bool lora = sizeof(T) == 2 && a.zpart && !a.gbase[m];
   constexpr int kBdPre = 16;
   uint2 bpre[kBdPre];
 #pragma unroll
@@ -999,11 +999,9 @@ __global__ __launch_bounds__(kGlueThreads) void dense_glue_kernel(GlueArgs a) {
   const int row = a.ctl ? a.perm[m] : m;
   if (a.out) {
     if (on) {
-      uint16_t *o = a.out + (size_t)row * a.d + c;
-      o[0] = f32_to_bf16(y[0]);
-      o[1] = f32_to_bf16(y[1]);
-      o[2] = f32_to_bf16(y[2]);
-      o[3] = f32_to_bf16(y[3]);
+      T *o = static_cast<T *>(a.out) + (size_t)row * a.d + c;
+#pragma unroll
+      for (int i = 0; i < 4; ++i) o[i] = Elem<T>::round(y[i]);
     }
     return;
   }
@@ -1018,15 +1016,17 @@ __global__ __launch_bounds__(kGlueThreads) void dense_glue_kernel(GlueArgs a) {
   for (int i = 0; i < kGlueThreads / 64; ++i) tot += ssw[i];
   const float scale = sqrtf(tot / (float)a.d + kGlueEps);
   if (on) {
-    uint16_t h[4];
+    struct alignas(4 * sizeof(T)) Quad {
+      T v[4];
+    } h;
 #pragma unroll
-    for (int i = 0; i < 4; ++i) h[i] = f32_to_bf16(y[i] / scale);
-    const uint2 hv = make_uint2((uint32_t)h[0] | ((uint32_t)h[1] << 16), (uint32_t)h[2] | ((uint32_t)h[3] << 16));
+    for (int i = 0; i < 4; ++i) h.v[i] = Elem<T>::round(y[i] / scale);
+    constexpr int KB = 64 / sizeof(T), CE = 16 / sizeof(T);  // elements of a block's row and of a chunk
     const size_t o = a.ctl ? (size_t)m * a.d + c
-                           : ((size_t)(m >> 4) * ((a.d + 31) / 32) + (c >> 5)) * 512 + (m & 15) * 32 +
-                                 (((c >> 3) & 3) ^ pf_swz(m & 15)) * 8 + (c & 7);
-    *reinterpret_cast<uint2 *>(a.hnext + o) = hv;
-    if (a.layer_in) *reinterpret_cast<uint2 *>(a.layer_in + (size_t)row * a.d + c) = hv;
+                           : ((size_t)(m >> 4) * ((a.d + KB - 1) / KB) + c / KB) * (16 * KB) + (m & 15) * KB +
+                                 ((c / CE & 3) ^ pf_swz(m & 15)) * CE + c % CE;
+    *reinterpret_cast<Quad *>(static_cast<T *>(a.hnext) + o) = h;
+    if (a.layer_in) *reinterpret_cast<Quad *>(static_cast<T *>(a.layer_in) + (size_t)row * a.d + c) = h;
   }
 }
 

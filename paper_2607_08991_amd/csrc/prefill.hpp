@@ -69,9 +69,9 @@ __device__ __forceinline__ bf16x8 pf_block_operand(const uint8_t *blk, int r, in
 }
 
 struct PfArgs {
-  const uint16_t *A;      // row blocks of h (gate/up) or p (down)
-  const uint16_t *Wg, *Wu;  // gate/up: [N][K] each
-  const uint16_t *Wd;     // down: [K][N]
+  const uint16_t *A;      // row blocks of h (gate/up) or p (down); float32 data for the float32 kernels
+  const uint16_t *Wg, *Wu;  // gate/up: [N][K] each (the same)
+  const uint16_t *Wd;     // down: [K][N] (the same)
   uint16_t *P;            // gate/up: row blocks of p
   size_t pterm;           // split p: elements from one term's row blocks to the next's (P, A)
   float *part;            // down: partials [ks][n][N]
@@ -88,28 +88,28 @@ struct PfArgs {
 // The rows of x in row blocks (rows past n and k past d zero), the base-path
 // flags, and the inspection copies of both.  A wavefront per block.
 struct PfPackArgs {
-  const uint16_t *x;      // [n][d]
-  uint16_t *A;            // row blocks
+  const uint8_t *x;       // [n] rows of `bytes` bytes (a multiple of 16)
+  uint8_t *A;             // row blocks
   uint8_t *gbase;         // [n]
   const int32_t *ids;
   const uint8_t *lut;
   int route_mode;
-  int n, d;
+  int n, bytes;
   uint8_t *route_out;     // optional [n]
-  uint16_t *layer_in;     // optional [n][d]
+  uint8_t *layer_in;      // optional copy of x
 };
 __global__ __launch_bounds__(kThreads) void pf_pack_kernel(PfPackArgs a) {
   const int lane = threadIdx.x & 63;
-  const int nb = (a.d + kPfKC - 1) / kPfKC;
+  const int nb = (a.bytes + 63) / 64;
   const int b = blockIdx.x * (kThreads / 64) + (threadIdx.x >> 6);  // block: row tile b / nb, k block b % nb
   if (b >= (a.n + 15) / 16 * nb) return;
-  const int r = lane >> 2, m = b / nb * 16 + r, k = b % nb * kPfKC + 8 * ((lane & 3) ^ pf_swz(r));
+  const int r = lane >> 2, m = b / nb * 16 + r, k = b % nb * 64 + 16 * ((lane & 3) ^ pf_swz(r));
   u32x4 v = {0u, 0u, 0u, 0u};
-  if (m < a.n && k < a.d) {
-    v = *reinterpret_cast<const u32x4 *>(a.x + (size_t)m * a.d + k);
-    if (a.layer_in) *reinterpret_cast<u32x4 *>(a.layer_in + (size_t)m * a.d + k) = v;
+  if (m < a.n && k < a.bytes) {
+    v = *reinterpret_cast<const u32x4 *>(a.x + (size_t)m * a.bytes + k);
+    if (a.layer_in) *reinterpret_cast<u32x4 *>(a.layer_in + (size_t)m * a.bytes + k) = v;
   }
-  *reinterpret_cast<u32x4 *>(a.A + (size_t)b * 512 + 8 * lane) = v;
+  *reinterpret_cast<u32x4 *>(a.A + (size_t)b * 1024 + 16 * lane) = v;
   if (b % nb == 0 && (lane & 3) == 0 && m < a.n && a.gbase) {
     const uint8_t base = (uint8_t)token_is_base(a.route_mode, a.ids, a.lut, m);
     a.gbase[m] = base;
@@ -560,17 +560,60 @@ __global__ __launch_bounds__(kPfThreads, 2) void pf_down_kernel(PfArgs a) {
 
 // ---------------------------------------------------------------- up to 64 rows
 
-// The same products for at most 16 MT <= 64 rows of a split shape, where the
-// weights' stream and the latency of a short loop are the bound: stages of 64
-// k (whole 128-byte lines), every wavefront 16 columns of all rows, and
-// enough workgroups to spread short matrices over the chip (the tiles of 128
-// rows above put 7 tokens of a 1024 x 2730 layer on 43 workgroups: gate/up
-// 14.8 and down 8.1 us; here 7.8 and 4.0).  Grid: column tiles (times k chunks).  Three or more loads per
-// wavefront and stage; slots of the stage that nothing needs are read as zeros
-// without a memory access.
+// The same products for at most 16 MT <= 64 rows, for split shapes and for
+// float32, where the weights' stream and the latency of a short loop are the
+// bound: stages of 128 bytes of each weight row (64 k, float32: 32), every
+// wavefront 16 columns of all rows, and enough workgroups to spread short
+// matrices over the chip (the tiles of 128 rows above put 7 tokens of a 1024 x
+// 2730 layer on 43 workgroups: gate/up 14.8 and down 8.1 us; here 7.8 and
+// 4.0).  Grid: column tiles (times k chunks).  Slots of a stage that nothing
+// needs are read as zeros without a memory access.
+//
+// float32 products are v_mfma_f32_16x16x4_f32, four to a 64-byte block of 16
+// k: a lane holds k = 4 g .. 4 g + 3 of its row or column (one 16-byte LDS
+// read), and product i takes element i of both operands, so each k meets
+// itself.  The compacted kernels they replace form every product on the
+// vector units, 4 tokens a tile, and read the weights once a tile (16 tokens
+// of a Qwen3-8B layer: 563 us, here 117: 604 MB at 5.2 TB/s).
+
+// Every stage sums into accumulators of its own, which the next stage adds to
+// the total under its products, with a compensation term (Kahan's sum): only
+// the sums within a stage carry rounding.  Plain folds of 64 k left float32
+// results 1.4 times as far from 64 bits as the compacted kernels'; these are
+// as near or nearer (1.9e-7 to 2.1e-7 of a layer's output, there 2.0e-7 to
+// 3.4e-7).
+template <int MT> __device__ __forceinline__ void sm_fold(f32x4v (&sum)[MT], f32x4v (&comp)[MT], const f32x4v (&acc)[MT]) {
+#pragma unroll
+  for (int i = 0; i < MT; ++i) {
+    const f32x4v y = acc[i] - comp[i], t = sum[i] + y;
+    comp[i] = (t - sum[i]) - y;
+    sum[i] = t;
+  }
+}
+
+// acc[i] = (first) or += the block product of row tile i (operand x[i]) and b
+template <typename T, int MT>
+__device__ __forceinline__ void sm_mfma(const u32x4 (&x)[MT], const u32x4 &b, f32x4v (&acc)[MT], bool first) {
+  const f32x4v zero = {0.f, 0.f, 0.f, 0.f};
+  if constexpr (sizeof(T) == 2) {
+#pragma unroll
+    for (int i = 0; i < MT; ++i)
+      acc[i] = mfma16(__builtin_bit_cast(bf16x8, x[i]), __builtin_bit_cast(bf16x8, b), first ? zero : acc[i]);
+  } else {
+#pragma unroll
+    for (int e = 0; e < 4; ++e)
+#pragma unroll
+      for (int i = 0; i < MT; ++i)
+        acc[i] = __builtin_amdgcn_mfma_f32_16x16x4f32(__uint_as_float(x[i][e]), __uint_as_float(b[e]),
+                                                      first && e == 0 ? zero : acc[i], 0, 0, 0);
+  }
+}
+__device__ __forceinline__ u32x4 sm_block_operand(const uint8_t *blk, int r, int g) {
+  return *reinterpret_cast<const u32x4 *>(blk + r * 64 + (g ^ pf_swz(r)) * 16);
+}
 
 // Columns [nt b, nt b + nt) of both projections: wavefronts 0-3 W_gate, 4-7 W_up.
-template <int MT>
+template <typename T, int MT>
 __global__ __launch_bounds__(kPfThreads, 2) void sm_gateup_kernel(PfArgs a, int nt) {
   constexpr int SW = 16 * 1024, SB = SW + 8 * 1024, R = 6;  // W_gate and W_up 8 KB each, h
   __shared__ __attribute__((aligned(1024))) uint8_t rg0[SB], rg1[SB], rg2[SB], rg3[SB], rg4[SB], rg5[SB];
@@ -580,61 +623,60 @@ __global__ __launch_bounds__(kPfThreads, 2) void sm_gateup_kernel(PfArgs a, int 
   const int lane = threadIdx.x & 63, w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int g = lane >> 4, l16 = lane & 15, mat = w >> 2, ct = w & 3;
   const int K = a.K, N = a.N, n0 = blockIdx.x * nt;
-  const int nb = (K + kPfKC - 1) / kPfKC, S = (nb + 1) / 2;
+  constexpr int E = sizeof(T), KB = 64 / E;  // bytes of an element, k of a block
+  const int nb = (K + KB - 1) / KB, S = (nb + 1) / 2;
   uint32_t base4[MT];
 #pragma unroll
   for (int i = 0; i < MT; ++i) base4[i] = *reinterpret_cast<const uint32_t *>(a.gbase + 16 * i + 4 * g);
   const int rows16 = (a.n + 15) / 16;
   const __amdgpu_buffer_rsrc_t rsa = dense_rsrc(a.A, (uint32_t)(rows16 * nb * 1024));
-  const uint32_t wbytes = (uint32_t)((size_t)N * K * 2);
+  const uint32_t wbytes = (uint32_t)((size_t)N * K * E);
   const __amdgpu_buffer_rsrc_t rsg = dense_rsrc(a.Wg, wbytes), rsu = dense_rsrc(a.Wu, wbytes);
   // wavefront w: rows 8 w .. 8 w + 7 of each projection, and block w & 1 of row tile w / 2 of h
   const int lr = lane >> 3, lq = (lane & 7) ^ lr, row = 8 * w + lr;
-  const uint32_t woff = row < nt && n0 + row < N ? (uint32_t)(((size_t)(n0 + row) * K + 8 * lq) * 2) : kDenseOffNone;
+  const uint32_t woff = row < nt && n0 + row < N ? (uint32_t)((size_t)(n0 + row) * K * E + 16 * lq) : kDenseOffNone;
   const uint32_t aoff = w / 2 < MT && w / 2 < rows16 ? (uint32_t)((w / 2 * nb + (w & 1)) * 1024 + 16 * lane) : kDenseOffNone;
   auto issue = [&](uint8_t *buf, int s) {
-    const bool v = 64 * s + 8 * lq < K;
+    const bool v = 128 * s + 16 * lq < K * E;
     pf_dma(rsg, buf + w * 1024, v ? woff : kDenseOffNone, (uint32_t)s * 128u);
     pf_dma(rsu, buf + 8192 + w * 1024, v ? woff : kDenseOffNone, (uint32_t)s * 128u);
     pf_dma(rsa, buf + SW + w * 1024, 2 * s + (w & 1) < nb ? aoff : kDenseOffNone, (uint32_t)s * 2048u);
   };
-  bf16x8 oa0[2][MT], oa1[2][MT], ob0[2], ob1[2];  // operands of even and odd stages
-  auto load = [&](const uint8_t *buf, bf16x8(&xa)[2][MT], bf16x8(&xb)[2]) {
+  u32x4 oa0[2][MT], oa1[2][MT], ob0[2], ob1[2];  // operands of even and odd stages
+  auto load = [&](const uint8_t *buf, u32x4(&xa)[2][MT], u32x4(&xb)[2]) {
 #pragma unroll
     for (int h = 0; h < 2; ++h) {
       const int r = 16 * ct + l16;
-      xb[h] = __builtin_bit_cast(bf16x8, *reinterpret_cast<const u32x4 *>(buf + mat * 8192 + r * 128 +
-                                                                         ((4 * h + g) ^ (r & 7)) * 16));
+      xb[h] = *reinterpret_cast<const u32x4 *>(buf + mat * 8192 + r * 128 + ((4 * h + g) ^ (r & 7)) * 16);
 #pragma unroll
-      for (int i = 0; i < MT; ++i) xa[h][i] = pf_block_operand(buf + SW + (2 * i + h) * 1024, l16, g);
+      for (int i = 0; i < MT; ++i) xa[h][i] = sm_block_operand(buf + SW + (2 * i + h) * 1024, l16, g);
     }
   };
-  f32x4v acc[MT][1] = {}, sum[MT][1] = {};
+  f32x4v acc0[MT] = {}, acc1[MT] = {}, sum[MT] = {}, comp[MT] = {};  // stage sums (even, odd); total
 #pragma unroll
   for (int s = 0; s < R - 1; ++s) issue(rb(s), s);
   pf_barrier<(R - 2) * 3>();
   load(rg0, oa0, ob0);
   // stage s: stage s + 1 has landed, every wavefront holds the operands of stage s
-  auto step = [&](int s, int p, bf16x8(&xa)[2][MT], bf16x8(&xb)[2], bf16x8(&ya)[2][MT], bf16x8(&yb)[2]) {
+  auto step = [&](int s, int p, u32x4(&xa)[2][MT], u32x4(&xb)[2], u32x4(&ya)[2][MT], u32x4(&yb)[2],
+                  f32x4v(&cur)[MT], const f32x4v(&prv)[MT]) {
     pf_barrier<(R - 3) * 3>();
     issue(rb(p + R - 1), s + R - 1);
     load(rb(p + 1), ya, yb);
 #pragma unroll
-    for (int h = 0; h < 2; ++h)
-#pragma unroll
-      for (int i = 0; i < MT; ++i) acc[i][0] = mfma16(xa[h][i], xb[h], acc[i][0]);
+    for (int h = 0; h < 2; ++h) sm_mfma<T, MT>(xa[h], xb[h], cur, h == 0);
+    sm_fold(sum, comp, prv);
+    __builtin_amdgcn_sched_barrier(0);  // (the next step's reads stay there: registers)
   };
   for (int s0 = 0; s0 < S; s0 += R) {
-    step(s0, 0, oa0, ob0, oa1, ob1);
-    step(s0 + 1, 1, oa1, ob1, oa0, ob0);
-    pf_fold(sum, acc);
-    step(s0 + 2, 2, oa0, ob0, oa1, ob1);
-    step(s0 + 3, 3, oa1, ob1, oa0, ob0);
-    pf_fold(sum, acc);
-    step(s0 + 4, 4, oa0, ob0, oa1, ob1);
-    step(s0 + 5, 5, oa1, ob1, oa0, ob0);
-    pf_fold(sum, acc);
+    step(s0, 0, oa0, ob0, oa1, ob1, acc0, acc1);
+    step(s0 + 1, 1, oa1, ob1, oa0, ob0, acc1, acc0);
+    step(s0 + 2, 2, oa0, ob0, oa1, ob1, acc0, acc1);
+    step(s0 + 3, 3, oa1, ob1, oa0, ob0, acc1, acc0);
+    step(s0 + 4, 4, oa0, ob0, oa1, ob1, acc0, acc1);
+    step(s0 + 5, 5, oa1, ob1, oa0, ob0, acc1, acc0);
   }
+  sm_fold(sum, comp, acc1);  // (rounds end on an odd stage)
   __builtin_amdgcn_s_waitcnt(0);
   __syncthreads();
   // epilogue: SiLU lane to lane to the wavefront of W_up, p through LDS to 16-byte stores of its terms
@@ -644,14 +686,14 @@ __global__ __launch_bounds__(kPfThreads, 2) void sm_gateup_kernel(PfArgs a, int 
     for (int i = 0; i < MT; ++i) {
       f32x4v v;
 #pragma unroll
-      for (int r = 0; r < 4; ++r) v[r] = silu(sum[i][0][r]);
+      for (int r = 0; r < 4; ++r) v[r] = silu(sum[i][r]);
       reinterpret_cast<f32x4v *>(xt)[i * 64 + lane] = v;
     }
   }
   __syncthreads();
   if (mat == 0 || 16 * ct >= nt) return;
   const float thr = a.thr ? *a.thr : 0.0f;
-  const int nbp = (N + kPfKC - 1) / kPfKC, c0 = n0 + 16 * ct;
+  const int c0 = n0 + 16 * ct;
 #pragma unroll
   for (int i = 0; i < MT; ++i) {
     const f32x4v gv = reinterpret_cast<const f32x4v *>(xt)[i * 64 + lane];
@@ -659,27 +701,42 @@ __global__ __launch_bounds__(kPfThreads, 2) void sm_gateup_kernel(PfArgs a, int 
     for (int r = 0; r < 4; ++r) {
       const int m = 16 * i + 4 * g + r, c = c0 + l16;
       const bool keep = ((base4[i] >> (8 * r)) & 0xffu) || fabsf(gv[r]) >= thr;
-      *reinterpret_cast<float *>(xt + i * 1024 + (4 * g + r) * 64 + l16 * 4) = keep ? gv[r] * sum[i][0][r] : 0.0f;
+      *reinterpret_cast<float *>(xt + i * 1024 + (4 * g + r) * 64 + l16 * 4) = keep ? gv[r] * sum[i][r] : 0.0f;
       if (a.keep_out && m < a.n && c < N) a.keep_out[(size_t)m * N + c] = (uint8_t)keep;
     }
   }
-  // lane: row, half of the tile's columns (8), and one of two row tiles
+  if constexpr (E == 4) {  // a tile is a row block: lane's row and 4 columns
+    const int r = lane >> 2, q = lane & 3, nbp = (N + 15) / 16;
 #pragma unroll
-  for (int i0 = 0; i0 < MT; i0 += 2) {
-    const int i = i0 + (lane & 1), r = lane >> 2, q = (lane >> 1) & 1, m = 16 * i + r, c = c0 + 8 * q;
-    if (i >= MT || m >= a.n || c >= N) continue;
-    float v[8];
-    *reinterpret_cast<f32x4v *>(v) = *reinterpret_cast<const f32x4v *>(xt + i * 1024 + r * 64 + q * 32);
-    *reinterpret_cast<f32x4v *>(v + 4) = *reinterpret_cast<const f32x4v *>(xt + i * 1024 + r * 64 + q * 32 + 16);
-    pf_store_terms(a.P + ((size_t)i * nbp + (c >> 5)) * 512 + r * 32 + (((c >> 3) & 3) ^ pf_swz(r)) * 8, a.pterm, v);
+    for (int i = 0; i < MT; ++i)
+      if (16 * i + r < a.n && c0 + 4 * q < N)
+        *reinterpret_cast<u32x4 *>(reinterpret_cast<uint8_t *>(a.P) + ((size_t)i * nbp + (c0 >> 4)) * 1024 + r * 64 +
+                                   (q ^ pf_swz(r)) * 16) =
+            *reinterpret_cast<const u32x4 *>(xt + i * 1024 + r * 64 + q * 16);
+  } else {
+    // lane: row, half of the tile's columns (8), and one of two row tiles
+    const int nbp = (N + kPfKC - 1) / kPfKC;
+#pragma unroll
+    for (int i0 = 0; i0 < MT; i0 += 2) {
+      const int i = i0 + (lane & 1), r = lane >> 2, q = (lane >> 1) & 1, m = 16 * i + r, c = c0 + 8 * q;
+      if (i >= MT || m >= a.n || c >= N) continue;
+      float v[8];
+      *reinterpret_cast<f32x4v *>(v) = *reinterpret_cast<const f32x4v *>(xt + i * 1024 + r * 64 + q * 32);
+      *reinterpret_cast<f32x4v *>(v + 4) = *reinterpret_cast<const f32x4v *>(xt + i * 1024 + r * 64 + q * 32 + 16);
+      pf_store_terms(a.P + ((size_t)i * nbp + (c >> 5)) * 512 + r * 32 + (((c >> 3) & 3) ^ pf_swz(r)) * 8, a.pterm, v);
+    }
   }
 }
 
-// 128 columns of one k chunk: wavefront w columns 16 w .. 16 w + 15.
-template <int MT>
+// 128 columns of one k chunk: wavefront w columns 16 w .. 16 w + 15.  A stage
+// holds 16 KB of W_down (64 rows, float32: 32) and the blocks of p of its k:
+// three terms of two blocks per row tile (float32: one).
+template <typename T, int MT>
 __global__ __launch_bounds__(kPfThreads, 2) void sm_down_kernel(PfArgs a) {
-  constexpr int IP = (6 * MT + 7) / 8;                       // loads of p per wavefront and stage (6 MT KB)
+  constexpr int E = sizeof(T), KB = 64 / E, KS = 2 * KB, NP = E == 2 ? 3 : 1;  // k of a block and a stage; terms of p
+  constexpr int IP = (2 * NP * MT + 7) / 8;                  // loads of p per wavefront and stage (2 NP MT KB)
   constexpr int SW = 16 * 1024, SB = SW + IP * 8 * 1024, R = SB <= 24 * 1024 ? 6 : 4, IS = 2 + IP;
+  constexpr int RPL = 1024 / (128 * E);                      // rows of W_down per load
   __shared__ __attribute__((aligned(1024))) uint8_t rg0[SB], rg1[SB], rg2[SB], rg3[SB], rg4[R > 4 ? SB : 16],
       rg5[R > 4 ? SB : 16];
   auto rb = [&](int i) -> uint8_t * {
@@ -689,66 +746,80 @@ __global__ __launch_bounds__(kPfThreads, 2) void sm_down_kernel(PfArgs a) {
   const int g = lane >> 4, l16 = lane & 15;
   const int K = a.K, N = a.N, kc = blockIdx.x % a.ks, n0 = blockIdx.x / a.ks * 128;
   const int kb = kc * a.kchunk, ke = min(K, kb + a.kchunk);
-  const int S = ke > kb ? (ke - kb + 63) / 64 : 0;
-  const int rows16 = (a.n + 15) / 16, nbp = (K + kPfKC - 1) / kPfKC;
-  const __amdgpu_buffer_rsrc_t rsw = dense_rsrc(a.Wd, (uint32_t)((size_t)K * N * 2));
+  const int S = ke > kb ? (ke - kb + KS - 1) / KS : 0;
+  const int rows16 = (a.n + 15) / 16, nbp = (K + KB - 1) / KB;
+  const __amdgpu_buffer_rsrc_t rsw = dense_rsrc(a.Wd, (uint32_t)((size_t)K * N * E));
   const uint32_t pbytes = (uint32_t)(rows16 * nbp * 1024);
-  // W_down: load q of wavefront w is rows 4 (w + 8 q) .. + 3 of the stage, 256 bytes each
-  const int wr = 4 * w + (lane >> 4);
+  // W_down: load q of wavefront w is rows RPL (w + 8 q) .. of the stage, 128 columns each.
+  // bf16: the pair of chunks of 16 columns swizzled by pf_kswz; float32: the 64 bytes of
+  // 16 columns by the row's group of four, so that the four rows a wavefront's 4-byte
+  // LDS read takes (k = i, 4 + i, ..) fall in distinct banks
+  const int wr = RPL * w + lane / (64 / RPL), wp = lane % (64 / RPL);
   uint32_t woff[2], aoff[IP];
 #pragma unroll
   for (int q = 0; q < 2; ++q) {
-    const int r = wr + 32 * q, c = n0 + 8 * (((l16 >> 1) ^ pf_kswz(r)) * 2 + (l16 & 1));
-    woff[q] = c < N ? (uint32_t)(((size_t)(kb + r) * N + c) * 2) : kDenseOffNone;
+    const int r = wr + 8 * RPL * q;
+    const int c = n0 + (E == 2 ? 8 * (((wp >> 1) ^ pf_kswz(r)) * 2 + (wp & 1)) : 16 * ((wp >> 2) ^ ((r >> 2) & 3)) + 4 * (wp & 3));
+    woff[q] = c < N ? (uint32_t)(((size_t)(kb + r) * N + c) * E) : kDenseOffNone;
   }
-  // p: load i = w + 8 q is term i / (2 MT), row tile (i / 2) % MT, k block i & 1 of the stage
-  const int aq = 8 * ((lane & 3) ^ pf_swz(lane >> 2)) + kPfKC * (w & 1);
+  // p: load i = w + 8 q is term i / (2 MT), row tile (i / 2) % MT, block i & 1 of the stage
+  const int aq = 16 / E * ((lane & 3) ^ pf_swz(lane >> 2)) + KB * (w & 1);
 #pragma unroll
   for (int q = 0; q < IP; ++q) {
     const int i = w + 8 * q, t = i / 2 % MT;
-    aoff[q] = i < 6 * MT && t < rows16 ? (uint32_t)((t * nbp + kb / kPfKC + (i & 1)) * 1024 + 16 * lane) : kDenseOffNone;
+    aoff[q] = i < 2 * NP * MT && t < rows16 ? (uint32_t)((t * nbp + kb / KB + (i & 1)) * 1024 + 16 * lane) : kDenseOffNone;
   }
   auto issue = [&](uint8_t *buf, int s) {
-    const int left = ke - kb - 64 * s;
+    const int left = ke - kb - KS * s;
 #pragma unroll
     for (int q = 0; q < 2; ++q)
-      pf_dma(rsw, buf + (w + 8 * q) * 1024, wr + 32 * q < left ? woff[q] : kDenseOffNone, (uint32_t)s * (uint32_t)(128 * N));
+      pf_dma(rsw, buf + (w + 8 * q) * 1024, wr + 8 * RPL * q < left ? woff[q] : kDenseOffNone,
+             (uint32_t)s * (uint32_t)(KS * E * N));
 #pragma unroll
     for (int q = 0; q < IP; ++q)
-      pf_dma(dense_rsrc(a.A + min((w + 8 * q) / (2 * MT), 2) * a.pterm, pbytes), buf + SW + (w + 8 * q) * 1024,
+      pf_dma(dense_rsrc(a.A + min((w + 8 * q) / (2 * MT), NP - 1) * a.pterm, pbytes), buf + SW + (w + 8 * q) * 1024,
              aq < left ? aoff[q] : kDenseOffNone, (uint32_t)s * 2048u);
   };
-  f32x4v acc[MT][1] = {}, sum[MT][1] = {};
+  f32x4v acc0[MT] = {}, acc1[MT] = {}, sum[MT] = {}, comp[MT] = {};  // stage sums (even, odd); total
 #pragma unroll
   for (int s = 0; s < R - 1; ++s) issue(rb(s), s);
   // (operands read where they are used: a chunk has few stages)
-  auto step = [&](int s, int p) {
+  auto step = [&](int s, int p, f32x4v(&cur)[MT], const f32x4v(&prv)[MT]) {
     pf_barrier<(R - 2) * IS>();
     issue(rb(p + R - 1), s + R - 1);
     uint8_t *buf = rb(p);
 #pragma unroll
     for (int h = 0; h < 2; ++h) {
-      const bf16x8 b = pf_krow_operand(buf + h * 8192, 256, w, g, l16);
+      u32x4 b;
+      if constexpr (E == 2) {
+        b = __builtin_bit_cast(u32x4, pf_krow_operand(buf + h * 8192, 256, w, g, l16));
+      } else {
 #pragma unroll
-      for (int t = 0; t < 3; ++t)
+        for (int i = 0; i < 4; ++i)
+          b[i] = *reinterpret_cast<const uint32_t *>(buf + (16 * h + 4 * g + i) * 512 + (w ^ g) * 64 + l16 * 4);
+      }
 #pragma unroll
-        for (int i = 0; i < MT; ++i)
-          acc[i][0] = mfma16(pf_block_operand(buf + SW + ((t * MT + i) * 2 + h) * 1024, l16, g), b, acc[i][0]);
+      for (int t = 0; t < NP; ++t) {
+        u32x4 x[MT];
+#pragma unroll
+        for (int i = 0; i < MT; ++i) x[i] = sm_block_operand(buf + SW + ((t * MT + i) * 2 + h) * 1024, l16, g);
+        sm_mfma<T, MT>(x, b, cur, h == 0 && t == 0);
+      }
     }
+    sm_fold(sum, comp, prv);
+    __builtin_amdgcn_sched_barrier(0);
   };
   for (int s0 = 0; s0 < S; s0 += R) {
-    step(s0, 0);
-    step(s0 + 1, 1);
-    pf_fold(sum, acc);
-    step(s0 + 2, 2);
-    step(s0 + 3, 3);
-    pf_fold(sum, acc);
+    step(s0, 0, acc0, acc1);
+    step(s0 + 1, 1, acc1, acc0);
+    step(s0 + 2, 2, acc0, acc1);
+    step(s0 + 3, 3, acc1, acc0);
     if constexpr (R > 4) {
-      step(s0 + 4, 4);
-      step(s0 + 5, 5);
-      pf_fold(sum, acc);
+      step(s0 + 4, 4, acc0, acc1);
+      step(s0 + 5, 5, acc1, acc0);
     }
   }
+  sm_fold(sum, comp, acc1);  // (rounds end on an odd stage)
   __builtin_amdgcn_s_waitcnt(0);
   const int c = n0 + 16 * w + l16;
 #pragma unroll
@@ -756,7 +827,7 @@ __global__ __launch_bounds__(kPfThreads, 2) void sm_down_kernel(PfArgs a) {
 #pragma unroll
     for (int r = 0; r < 4; ++r) {
       const int m = 16 * i + 4 * g + r;
-      if (m < a.n && c < N) a.part[((size_t)kc * a.n + m) * N + c] = sum[i][0][r];
+      if (m < a.n && c < N) a.part[((size_t)kc * a.n + m) * N + c] = sum[i][r];
     }
 }
 

@@ -291,7 +291,8 @@ struct PfPlan {
 };
 
 // Rows of every pass but the last: equal shares, whole 256-row tiles.
-int pf_pass(int64_t n) {
+int pf_pass(int64_t n, int esz) {
+  if (esz == 4) return kMaxPass;  // float32: 64 rows already meet the matrix cores' rate
   const int64_t passes = (n + kPfMaxPass - 1) / kPfMaxPass;
   return (int)(((n + passes - 1) / passes + 255) / 256 * 256);
 }
@@ -310,17 +311,18 @@ bool pf_split(int64_t d, int64_t d_ff) { return d % sats::kDenseDownNT != 0 || d
 // The tiles with the least modelled time: rounds of workgroups over the
 // compute units times the cycles of one; for the down-projection also the
 // partials' write and read (about 2000 bytes per cycle).
-PfPlan pf_plan(int64_t np, int64_t d, int64_t d_ff) {
+PfPlan pf_plan(int64_t np, int64_t d, int64_t d_ff, int esz) {
   const int64_t cus = std::max(1, device_cus());
   auto cdiv = [](int64_t a, int64_t b) { return (a + b - 1) / b; };
   PfPlan p{};
   const bool split = pf_split(d, d_ff);
-  if (split && np <= kMaxPass) {
-    // gate/up columns and down chunks (whole 64-row stages) for a workgroup per compute unit
+  if (esz == 4 || (split && np <= kMaxPass)) {
+    // gate/up columns and down chunks (whole stages) for a workgroup per compute unit
+    const int64_t stage = esz == 4 ? 32 : 64;
     p.small = true;
     p.nt = (int)std::clamp<int64_t>(cdiv(cdiv(d_ff, cus), 16) * 16, 16, 64);
-    const int64_t ks = std::clamp<int64_t>(cus / cdiv(d, 128), 1, std::min<int64_t>(sats::kDenseMaxKsplit, cdiv(d_ff, 64)));
-    p.kchunk = (int)(cdiv(cdiv(d_ff, ks), 64) * 64);
+    const int64_t ks = std::clamp<int64_t>(cus / cdiv(d, 128), 1, std::min<int64_t>(sats::kDenseMaxKsplit, cdiv(d_ff, stage)));
+    p.kchunk = (int)(cdiv(cdiv(d_ff, ks), stage) * stage);
     p.ks = (int)cdiv(d_ff, p.kchunk);
     return p;
   }
@@ -346,18 +348,18 @@ PfPlan pf_plan(int64_t np, int64_t d, int64_t d_ff) {
 }
 
 struct PfBuffers {
-  uint16_t *h, *p;       // row blocks of the layer input and of p (split: of its three terms)
+  uint8_t *h, *p;        // row blocks of the layer input and of p (split: of its three terms)
   float *part;           // [ks][np][d]
   uint8_t *gbase;        // [np], whole tiles of 256
   uint8_t *keep;         // [np][d_ff] keep flags (inspection)
 };
-// elements of n rows of length k in row blocks
-int64_t pf_block_elems(int64_t n, int64_t k) { return (n + 15) / 16 * ((k + 31) / 32) * 512; }
-size_t pf_layout(char *base, int64_t np, int ks, int64_t d, int64_t d_ff, PfBuffers *b) {
+// bytes of n rows of length k in row blocks
+int64_t pf_block_bytes(int64_t n, int64_t k, int esz) { return (n + 15) / 16 * ((k * esz + 63) / 64) * 1024; }
+size_t pf_layout(char *base, int64_t np, int ks, int64_t d, int64_t d_ff, int esz, PfBuffers *b) {
   Carve c{base};
   PfBuffers t{};
-  t.h = c.take<uint16_t>(pf_block_elems(np, d));
-  t.p = c.take<uint16_t>((pf_split(d, d_ff) ? 3 : 1) * pf_block_elems(np, d_ff));
+  t.h = c.take<uint8_t>(pf_block_bytes(np, d, esz));
+  t.p = c.take<uint8_t>((esz == 2 && pf_split(d, d_ff) ? 3 : 1) * pf_block_bytes(np, d_ff, esz));
   t.gbase = c.take<uint8_t>((np + 255) / 256 * 256);
   t.part = c.take<float>((int64_t)ks * np * d);
   t.keep = c.take<uint8_t>(np * d_ff);
@@ -365,23 +367,23 @@ size_t pf_layout(char *base, int64_t np, int ks, int64_t d, int64_t d_ff, PfBuff
   return c.off;
 }
 // Workspace of a call of n tokens (every pass), and of any call of up to n.
-size_t pf_bytes(int64_t n, int64_t d, int64_t d_ff) {
-  const int64_t pass = pf_pass(n), last = n - (n - 1) / pass * pass;
+size_t pf_bytes(int64_t n, int64_t d, int64_t d_ff, int esz) {
+  const int64_t pass = pf_pass(n, esz), last = n - (n - 1) / pass * pass;
   size_t b = 0;
   for (const int64_t np : {std::min(pass, n), last})
-    b = std::max(b, pf_layout(nullptr, np, pf_plan(np, d, d_ff).ks, d, d_ff, nullptr));
+    b = std::max(b, pf_layout(nullptr, np, pf_plan(np, d, d_ff, esz).ks, d, d_ff, esz, nullptr));
   return b;
 }
-size_t pf_bytes_upto(int64_t n, int64_t d, int64_t d_ff) {
+size_t pf_bytes_upto(int64_t n, int64_t d, int64_t d_ff, int esz) {
   size_t b = 0;
-  for (int64_t m = 1; m <= std::min<int64_t>(n, kPfMaxPass); ++m)
-    b = std::max(b, pf_layout(nullptr, m, pf_plan(m, d, d_ff).ks, d, d_ff, nullptr));
+  for (int64_t m = 1; m <= std::min<int64_t>(n, esz == 4 ? kMaxPass : kPfMaxPass); ++m)
+    b = std::max(b, pf_layout(nullptr, m, pf_plan(m, d, d_ff, esz).ks, d, d_ff, esz, nullptr));
   return b;
 }
 
-// Whether a batch runs on the tiled products: bf16, rows of 16-byte pieces
-// (`aligned`: every array on 16 bytes), matrices and p below 2 GB, every row
-// on the matrix cores, and
+// Whether a batch runs on the tiled products: rows of 16-byte pieces
+// (`aligned`: every array on 16 bytes), matrices and p below 2 GB, and
+// for bf16, with every row on the matrix cores,
 //  - more than 64 tokens.  At 64 and below the 64-row kernels stream the
 //    weights at the memory's rate and skip W_down rows that no token keeps
 //    (64 tokens of a Llama-3.1-8B layer 75 us; here about 110); above, each
@@ -389,9 +391,14 @@ size_t pf_bytes_upto(int64_t n, int64_t d, int64_t d_ff) {
 //  - 2 or more tokens of a shape that is not on the 64-row kernels' tiles and
 //    would take the compacted kernels (7 tokens through two layers of 1024 x
 //    2730: 186 us there, 35 here).
+// and float32 batches of 2 or more tokens (16 tokens of a Qwen3-8B layer 563 us on the
+// compacted kernels, 117 here; 2 tokens of 3712 x 14016, half the columns kept: 163 and 118).
 bool pf_ok(int esz, bool aligned, int64_t n, int64_t d, int64_t d_ff) {
-  return esz == 2 && aligned && d % 8 == 0 && d <= 4096 && d_ff <= (1 << 19) - 32 &&
-         (uint64_t)d * d_ff * 2 < (1ull << 31) && (n > kMaxPass || (n >= sats::kMfmaMinTokens && pf_split(d, d_ff))) &&
+  if (!aligned || d * esz % 16 != 0 || d > 4096 || d_ff > (1 << 19) - 32 || (uint64_t)d * d_ff * esz >= (1ull << 31) ||
+      n < sats::kMfmaMinTokens)
+    return false;
+  if (esz == 4) return true;
+  return (n > kMaxPass || pf_split(d, d_ff)) &&
          (g_opt.batch_path == SATS_BATCH_AUTO || g_opt.batch_path == SATS_BATCH_MFMA);
 }
 
@@ -412,15 +419,17 @@ template <bool SPLIT> PfKernel pf_down_fn(const PfPlan &p) {
   return p.dbn == 256 ? pf_down_kernel<128, 256, SPLIT> : pf_down_kernel<128, 128, SPLIT>;
 }
 typedef void (*SmGateup)(sats::PfArgs, int);
-SmGateup sm_gateup_fn(int np) {
+template <typename T> SmGateup sm_gateup_fn(int np) {
   using namespace sats;
   const int mt = (np + 15) / 16;
-  return mt <= 1 ? sm_gateup_kernel<1> : mt == 2 ? sm_gateup_kernel<2> : mt == 3 ? sm_gateup_kernel<3> : sm_gateup_kernel<4>;
+  return mt <= 1 ? sm_gateup_kernel<T, 1> : mt == 2 ? sm_gateup_kernel<T, 2>
+                                        : mt == 3   ? sm_gateup_kernel<T, 3> : sm_gateup_kernel<T, 4>;
 }
-PfKernel sm_down_fn(int np) {
+template <typename T> PfKernel sm_down_fn(int np) {
   using namespace sats;
   const int mt = (np + 15) / 16;
-  return mt <= 1 ? sm_down_kernel<1> : mt == 2 ? sm_down_kernel<2> : mt == 3 ? sm_down_kernel<3> : sm_down_kernel<4>;
+  return mt <= 1 ? sm_down_kernel<T, 1> : mt == 2 ? sm_down_kernel<T, 2>
+                                      : mt == 3   ? sm_down_kernel<T, 3> : sm_down_kernel<T, 4>;
 }
 unsigned pf_grid(int mtiles, int units) { return (unsigned)((units + 7) / 8 * 8 * mtiles); }
 
@@ -568,27 +577,28 @@ struct Call {
 };
 
 // One pass of np rows from token `base` on through the tiled products (see pf_ok).
-int run_prefill(const Call &c, char *mem, int64_t base, int np) {
+template <typename T> int run_prefill(const Call &c, char *mem, int64_t base, int np) {
   using namespace sats;
+  constexpr int esz = sizeof(T);
   const int64_t d = c.d, d_ff = c.d_ff;
   const size_t wl = (size_t)d * (size_t)d_ff;
-  const PfPlan p = pf_plan(np, d, d_ff);
+  const PfPlan p = pf_plan(np, d, d_ff, esz);
   PfBuffers b{};
-  pf_layout(mem, np, p.ks, d, d_ff, &b);
+  pf_layout(mem, np, p.ks, d, d_ff, esz, &b);
   const bool lists = c.active_count || c.active_idx, split = pf_split(d, d_ff);
   {
     PfPackArgs pa{};
-    pa.x = static_cast<const uint16_t *>(c.x) + base * d;
+    pa.x = static_cast<const uint8_t *>(c.x) + (size_t)base * d * esz;
     pa.A = b.h;
     pa.gbase = b.gbase;
     pa.ids = c.ids ? c.ids + base : nullptr;
     pa.lut = c.lut;
     pa.route_mode = c.route_mode;
     pa.n = np;
-    pa.d = (int)d;
+    pa.bytes = (int)d * esz;
     pa.route_out = c.route_out ? c.route_out + base : nullptr;
-    pa.layer_in = c.layer_in ? static_cast<uint16_t *>(c.layer_in) + base * d : nullptr;
-    const int blocks = (np + 15) / 16 * (int)((d + kPfKC - 1) / kPfKC);
+    pa.layer_in = c.layer_in ? static_cast<uint8_t *>(c.layer_in) + (size_t)base * d * esz : nullptr;
+    const int blocks = (np + 15) / 16 * (int)((d * esz + 63) / 64);
     hipLaunchKernelGGL(pf_pack_kernel, dim3((blocks + 3) / 4), dim3(kThreads), 0, c.stream, pa);
     HIP_TRY(hipGetLastError());
   }
@@ -596,12 +606,12 @@ int run_prefill(const Call &c, char *mem, int64_t base, int np) {
   a.n = np;
   for (int64_t l = 0; l < c.L; ++l) {
     PfArgs u = a;
-    u.A = b.h;
+    u.A = reinterpret_cast<const uint16_t *>(b.h);
     u.gbase = b.gbase;
-    u.Wg = static_cast<const uint16_t *>(c.Wg) + l * wl;
-    u.Wu = static_cast<const uint16_t *>(c.Wu) + l * wl;
-    u.P = b.p;
-    u.pterm = (size_t)pf_block_elems(np, d_ff);
+    u.Wg = reinterpret_cast<const uint16_t *>(static_cast<const T *>(c.Wg) + l * wl);
+    u.Wu = reinterpret_cast<const uint16_t *>(static_cast<const T *>(c.Wu) + l * wl);
+    u.P = reinterpret_cast<uint16_t *>(b.p);
+    u.pterm = (size_t)pf_block_bytes(np, d_ff, 2) / 2;
     u.thr = c.thr ? c.thr + l : nullptr;
     u.keep_out = lists ? b.keep : nullptr;
     u.K = (int)d;
@@ -609,7 +619,7 @@ int run_prefill(const Call &c, char *mem, int64_t base, int np) {
     u.units = (int)((d_ff + p.nt - 1) / p.nt);
     if (p.small) {
       TimedLaunch tl(SATS_K_DENSE, c.stream);
-      hipExtLaunchKernelGGL(sm_gateup_fn(np), dim3((unsigned)u.units), dim3(kPfThreads), 0, c.stream, tl.start, tl.stop,
+      hipExtLaunchKernelGGL(sm_gateup_fn<T>(np), dim3((unsigned)u.units), dim3(kPfThreads), 0, c.stream, tl.start, tl.stop,
                             0, u, p.nt);
     } else {
       u.mtiles = (np + p.bm - 1) / p.bm;
@@ -619,9 +629,9 @@ int run_prefill(const Call &c, char *mem, int64_t base, int np) {
     }
     HIP_TRY(hipGetLastError());
     PfArgs w = a;
-    w.A = b.p;
+    w.A = reinterpret_cast<const uint16_t *>(b.p);
     w.pterm = u.pterm;
-    w.Wd = static_cast<const uint16_t *>(c.Wd) + l * wl;
+    w.Wd = reinterpret_cast<const uint16_t *>(static_cast<const T *>(c.Wd) + l * wl);
     w.part = b.part;
     w.K = (int)d_ff;
     w.N = (int)d;
@@ -629,7 +639,7 @@ int run_prefill(const Call &c, char *mem, int64_t base, int np) {
     w.kchunk = p.kchunk;
     if (p.small) {
       TimedLaunch tl(SATS_K_DENSE_DOWN, c.stream);
-      hipExtLaunchKernelGGL(sm_down_fn(np), dim3((unsigned)((d + 127) / 128 * p.ks)), dim3(kPfThreads), 0, c.stream,
+      hipExtLaunchKernelGGL(sm_down_fn<T>(np), dim3((unsigned)((d + 127) / 128 * p.ks)), dim3(kPfThreads), 0, c.stream,
                             tl.start, tl.stop, 0, w);
     } else {
       w.mtiles = (np + p.dbm - 1) / p.dbm;
@@ -644,10 +654,10 @@ int run_prefill(const Call &c, char *mem, int64_t base, int np) {
     ga.part = b.part;
     ga.ksplit = p.ks;
     ga.d = (int)d;
-    ga.out = l == c.L - 1 ? static_cast<uint16_t *>(c.out) + base * d : nullptr;
+    ga.out = l == c.L - 1 ? static_cast<T *>(c.out) + base * d : nullptr;
     ga.hnext = b.h;
-    ga.layer_in = c.layer_in && l + 1 < c.L ? static_cast<uint16_t *>(c.layer_in) + ((l + 1) * c.n + base) * d : nullptr;
-    hipLaunchKernelGGL(dense_glue_kernel, dim3(np), dim3(kGlueThreads), 0, c.stream, ga);
+    ga.layer_in = c.layer_in && l + 1 < c.L ? static_cast<T *>(c.layer_in) + ((l + 1) * c.n + base) * d : nullptr;
+    hipLaunchKernelGGL(dense_glue_kernel<T>, dim3(np), dim3(kGlueThreads), 0, c.stream, ga);
     HIP_TRY(hipGetLastError());
     if (lists) {
       CompactArgs ca{};
@@ -792,7 +802,7 @@ int run_pass(const Call &c, const Plan &p, const Buffers &b, unsigned *counters,
         ga.nzb = (int)((d_ff + nt_gu - 1) / nt_gu);
         ga.lscale = c.lscale;
       }
-      hipLaunchKernelGGL(dense_glue_kernel, dim3(np), dim3(kGlueThreads), 0, c.stream, ga);
+      hipLaunchKernelGGL(dense_glue_kernel<uint16_t>, dim3(np), dim3(kGlueThreads), 0, c.stream, ga);
       HIP_TRY(hipGetLastError());
     }
     auto compact = [&]() -> int {
@@ -1088,7 +1098,7 @@ int run(const Call &c) {
   }
   const int64_t lrank = c.Ag ? c.rank : 0;
   if (!c.Ag && pf_ok(esz, vec_d, c.n, c.d, c.d_ff)) {
-    const size_t need = pf_bytes(c.n, c.d, c.d_ff);
+    const size_t need = pf_bytes(c.n, c.d, c.d_ff, esz);
     char *mem = nullptr;
     int rc = 0;
     // the allocation-free call takes this path when its workspace fits
@@ -1103,9 +1113,9 @@ int run(const Call &c) {
       mem = ws->mem;
     }
     if (mem) {
-      const int rows = pf_pass(c.n);
+      const int rows = pf_pass(c.n, esz);
       for (int64_t base = 0; base < c.n; base += rows)
-        if ((rc = run_prefill(c, mem, base, (int)std::min<int64_t>(rows, c.n - base)))) return rc;
+        if ((rc = run_prefill<T>(c, mem, base, (int)std::min<int64_t>(rows, c.n - base)))) return rc;
       return SATS_OK;
     }
   }
@@ -1879,7 +1889,7 @@ int sats_reserve(int64_t max_tokens, int64_t d, int64_t d_ff, int64_t n_layers, 
         nc = std::max(nc, counter_count(p, pass, dp));
       }
   if (pf_ok(elem_bytes, true, max_tokens, d, d_ff))
-    bytes = std::max(bytes, pf_bytes_upto(max_tokens, d, d_ff));
+    bytes = std::max(bytes, pf_bytes_upto(max_tokens, d, d_ff, elem_bytes));
   Workspace *ws = nullptr;
   return ensure_workspace(stream, bytes, nc, &ws);
 }
@@ -1975,7 +1985,7 @@ int sats_query_path(int64_t n_tokens, int64_t d, int64_t d_ff, int elem_bytes, i
     return SATS_OK;
   }
   if (pf_ok(elem_bytes, vec_d, n_tokens, d, d_ff)) {
-    *path = SATS_PATH_BATCH_MFMA;
+    *path = elem_bytes == 4 ? SATS_PATH_BATCH_COMPACT : SATS_PATH_BATCH_MFMA;
     return SATS_OK;
   }
   const int np = (int)std::min<int64_t>(n_tokens, kMaxPass);

@@ -1,9 +1,10 @@
-"""The tiled matrix-core products (batches of more than 64 tokens, and batches
-of shapes that are on no whole tile) against the oracle: rows and columns at
+"""The tiled matrix-core products (batches of more than 64 tokens, batches of
+shapes that are on no whole tile, and float32 batches) against the oracle: rows and columns at
 the edges of their tiles and of the 16-row blocks, widths in 16-byte pieces
 only, stacks, both routes, and passes of unequal length.  Tolerances are those of
 tests/harness.py: p and the output are rounded to bf16 (2^-9 each) and the
-sums are float32, well inside the 2e-2 bound on the largest element."""
+sums are float32, well inside the 2e-2 bound on the largest element; float32
+batches keep float32 throughout (1e-5)."""
 import numpy as np
 import pytest
 
@@ -35,16 +36,29 @@ CASES = [
 ]
 
 
-@pytest.mark.parametrize("seed,L,d,dff,n", CASES)
-def test_prefill_matches_oracle_and_inspection_changes_nothing(seed, L, d, dff, n):
-    print(f"prefill case seed={seed} L={L} d={d} d_ff={dff} n={n}", flush=True)
-    c = synth.small_case(seed, L, d, dff, "bf16", n, vocab=40, n_dense_ids=12, w_std=1.0 / np.sqrt(d))
-    ts = case_thresholds(c, "bf16", seed=seed)
+# float32 batches (passes of up to 64 rows)
+F32 = [
+    (140, 2, 20, 37, 2),         # less than one stage of k, less than one tile
+    (141, 2, 260, 333, 7),
+    (142, 1, 1028, 2730, 16),
+    (143, 3, 128, 512, 17),
+    (144, 1, 512, 1536, 48),
+    (145, 2, 384, 1001, 64),
+    (146, 2, 132, 200, 67),      # a second pass of 3 rows
+    (147, 1, 4096, 1024, 33),
+]
+
+
+@pytest.mark.parametrize("dtype,seed,L,d,dff,n", [("bf16", *c) for c in CASES] + [("f32", *c) for c in F32])
+def test_prefill_matches_oracle_and_inspection_changes_nothing(dtype, seed, L, d, dff, n):
+    print(f"prefill case seed={seed} L={L} d={d} d_ff={dff} n={n} {dtype}", flush=True)
+    c = synth.small_case(seed, L, d, dff, dtype, n, vocab=40, n_dense_ids=12, w_std=1.0 / np.sqrt(d))
+    ts = case_thresholds(c, dtype, seed=seed)
     tokens = sorted({t for t in (0, 15, 16, 63, 64, n // 2, 127, 128, 255, n - 1) if t < n})
     for lut in (None, c["route_lut"]):
-        res = run_gpu(c, ts, lut, "bf16")
-        worst = check_against_oracle(c, ts, lut, "bf16", res, tokens=tokens)
-        fwd = run_gpu(c, ts, lut, "bf16", inspect=False, out_is_x=lut is None)
+        res = run_gpu(c, ts, lut, dtype)
+        worst = check_against_oracle(c, ts, lut, dtype, res, tokens=tokens)
+        fwd = run_gpu(c, ts, lut, dtype, inspect=False, out_is_x=lut is None)
         np.testing.assert_array_equal(fwd["out"], res["out"])
         print(f"  lut={'yes' if lut is not None else 'no'} worst rel err {worst:.3g}", flush=True)
 
