@@ -127,14 +127,6 @@ struct DenseArgs {
   int K, N, kchunk;       // reduction length, output columns, k per split (down)
   int nt;                 // gate/up: output columns per workgroup (a multiple of 8, at most 64)
   int hcap;               // rows of H allocated (the first stages read them all, before the group's size is known)
-  float *cal_g;           // calibration (gate/up): g = SiLU(a) in float32, [rows][N] (P unused) ...
-  uint16_t *cal_ph, *cal_pl;  // ... and p = g u as two bf16 terms, hi = rne(p), lo = rne(p - hi)
-  // calibration in one launch (the CAL instance): workgroup b takes column tile
-  // (b / 8 / cal_passes) * 8 + b % 8 and pass (b / 8) % cal_passes (rows
-  // 64 pass ..; ctl, H, hcap and the cal outputs above are those of pass 0):
-  // the passes of a tile run at once on one XCD (workgroup b on XCD b mod 8)
-  // and read its weights through that XCD's L2; tiles past cal_tiles return
-  int cal_passes, cal_tiles;
   // LoRA adapters of the sparse path (gate/up with LORA): lv [2][kDenseMaxTokens][rank]
   // = s (h A_gate), s (h A_up) per group row; B_gate [rank][N], B_up_T [N][rank] and
   // A_down [N][rank] of the layer; zpart [tiles][kDenseMaxTokens][rank]: per column
@@ -305,7 +297,7 @@ __device__ __forceinline__ f32x4v mfma16(const bf16x8 &a, const bf16x8 &b, const
 // shapes).  Wavefronts 0-3 accumulate h W_gate, 4-7 h W_up, 16 columns each.
 // Groups of one row tile use the eight-stage ring of 18 KB stages, larger ones
 // six stages of 24 KB.
-template <int MT, bool LORA = false, bool CAL = false>
+template <int MT, bool LORA = false>
 __global__ __launch_bounds__(kDenseThreads) void dense_gateup_kernel(DenseArgs a) {
   constexpr int NB = MT == 1 ? 8 : 6, SB = MT == 1 ? 18 * 1024 : kDenseStageBytes;  // ring stages and their bytes
   __shared__ __attribute__((aligned(1024))) uint8_t ring[NB * SB];
@@ -314,19 +306,7 @@ __global__ __launch_bounds__(kDenseThreads) void dense_gateup_kernel(DenseArgs a
   uint8_t *const rg6 = ring + (NB > 6 ? 6 : 0) * SB, *const rg7 = ring + (NB > 7 ? 7 : 0) * SB;
   (void)rg6;
   (void)rg7;
-  int tile = blockIdx.x;
-  if (CAL) {  // calibration passes in one launch (see DenseArgs)
-    const int j = blockIdx.x >> 3, pass = j % a.cal_passes;
-    tile = (j / a.cal_passes) * 8 + (blockIdx.x & 7);
-    if (tile >= a.cal_tiles) return;
-    const size_t rows = (size_t)pass * kDenseMaxTokens;
-    a.ctl += 2 * pass;
-    a.H += rows * a.K;
-    a.hcap -= (int)rows;
-    a.cal_g += rows * a.N;
-    a.cal_ph += rows * a.N;
-    a.cal_pl += rows * a.N;
-  }
+  const int tile = blockIdx.x;
   // the group's control words are read while the first two stages load
   // (every allocated row of H: rows past the group feed only results that
   // are not stored); a workgroup of an empty group then waits for its loads
@@ -474,26 +454,6 @@ __global__ __launch_bounds__(kDenseThreads) void dense_gateup_kernel(DenseArgs a
       for (int r = 0; r < 4; ++r) xs[(16 * mt + 4 * g + r) * kDenseXP + c] = silu(acc[mt][r]);
   }
   __syncthreads();
-  if (a.cal_g) {  // calibration: g and p = g u (float32, no keep rule), p split into bf16 hi + lo
-    if (mat == 1) {
-#pragma unroll
-      for (int mt = 0; mt < MT; ++mt)
-#pragma unroll
-        for (int r = 0; r < 4; ++r) {
-          const int m = 16 * mt + 4 * g + r;
-          if (m < nd && c < ncol) {
-            const float gv = xs[m * kDenseXP + c];
-            const float pv = gv * acc[mt][r];
-            const uint16_t hi = f32_to_bf16(pv);
-            const size_t o = (size_t)m * N + n0 + c;
-            a.cal_g[o] = gv;
-            a.cal_ph[o] = hi;
-            a.cal_pl[o] = f32_to_bf16(pv - bf16_to_f32(hi));
-          }
-        }
-    }
-    return;
-  }
   if (mat == 1) {
     const float thr = a.thr ? *a.thr : 0.0f;
     bool any = false;  // some row of the group keeps column c

@@ -1193,7 +1193,7 @@ struct CalBuffers {
   double *errsum = nullptr;
   double *rsum = nullptr;          // [ceil(n / 64)][16] workgroup sums of the Eq. 6 terms
   float *ny2 = nullptr;            // [n] ||y||^2 of each row (from the first product)
-  int *ctl = nullptr;              // [passes][2] rows of each gate/up pass, MFMA on
+  uint8_t *hp = nullptr;           // the rows of a gate/up pass in row blocks
 };
 
 // The calibration buffers are kept per device from call to call (grown when
@@ -1234,7 +1234,7 @@ int cal_release_all() {
     const CalBuffers &b = kv.second.b;
     for (void *q : {(void *)b.G, (void *)b.ph, (void *)b.pl, (void *)b.cnt, (void *)b.WdT, (void *)b.part,
                     (void *)b.hpart, (void *)b.hist, (void *)b.prefix, (void *)b.rank, (void *)b.tk, (void *)b.thr15,
-                    (void *)b.ge15, (void *)b.errsum, (void *)b.ctl, (void *)b.rsum, (void *)b.ny2})
+                    (void *)b.ge15, (void *)b.errsum, (void *)b.hp, (void *)b.rsum, (void *)b.ny2})
       if (q) HIP_TRY(hipFree(q));
   }
   g_cal.clear();
@@ -1262,38 +1262,39 @@ int cal_check_shape(int64_t n, int64_t d, int64_t d_ff) {
   return SATS_OK;
 }
 
-// g and p of n calibration rows (MFMA, 64 rows per pass) into G, ph, pl.
+// g and p of n calibration rows into G, ph, pl: the tiled gate/up product, up
+// to kPfMaxPass rows at a time.
 int cal_gate_up(const uint16_t *h, const uint16_t *Wg, const uint16_t *Wu, int64_t n, int64_t d, int64_t d_ff,
                 CalBuffers &cb, hipStream_t s) {
   using namespace sats;
-  const int64_t passes = (n + kDenseMaxTokens - 1) / kDenseMaxTokens;
-  std::vector<int> ctl(2 * passes);
-  for (int64_t i = 0; i < passes; ++i) {
-    ctl[2 * i] = (int)std::min<int64_t>(kDenseMaxTokens, n - i * kDenseMaxTokens);
-    ctl[2 * i + 1] = 1;
+  const int pass = pf_pass(n, 2);
+  for (int64_t base = 0; base < n; base += pass) {
+    const int np = (int)std::min<int64_t>(pass, n - base);
+    const PfPlan p = pf_plan(np, d, d_ff, 2);
+    PfPackArgs pa{};
+    pa.x = reinterpret_cast<const uint8_t *>(h + base * d);
+    pa.A = cb.hp;
+    pa.n = np;
+    pa.bytes = (int)d * 2;
+    hipLaunchKernelGGL(pf_pack_kernel, dim3((unsigned)(((np + 15) / 16 * (d / kPfKC) + 3) / 4)), dim3(kThreads), 0, s, pa);
+    HIP_TRY(hipGetLastError());
+    PfArgs a{};
+    a.A = reinterpret_cast<const uint16_t *>(cb.hp);
+    a.Wg = Wg;
+    a.Wu = Wu;
+    a.n = np;
+    a.K = (int)d;
+    a.N = (int)d_ff;
+    a.mtiles = (np + p.bm - 1) / p.bm;
+    a.units = (int)((d_ff + p.nt - 1) / p.nt);
+    a.cal_g = cb.G + base * d_ff;
+    a.cal_ph = cb.ph + base * d_ff;
+    a.cal_pl = cb.pl + base * d_ff;
+    TimedLaunch tl(SATS_K_CAL_GATEUP, s);
+    hipExtLaunchKernelGGL(pf_gateup_fn<PF_CAL>(p), dim3(pf_grid(a.mtiles, a.units)), dim3(kPfThreads), 0, s, tl.start,
+                          tl.stop, 0, a);
+    HIP_TRY(hipGetLastError());
   }
-  HIP_TRY(hipMemcpyAsync(cb.ctl, ctl.data(), ctl.size() * sizeof(int), hipMemcpyHostToDevice, s));
-  // every pass in one launch, the passes of a column tile side by side on
-  // one XCD so that its weights come from HBM about once (see DenseArgs)
-  DenseArgs da{};
-  da.ctl = cb.ctl;
-  da.H = h;
-  da.Wg = Wg;
-  da.Wt = Wu;
-  da.K = (int)d;
-  da.N = (int)d_ff;
-  da.nt = dense_tile_cols(d_ff);
-  da.hcap = (int)n;  // calibration rows from pass 0's first on
-  da.cal_g = cb.G;
-  da.cal_ph = cb.ph;
-  da.cal_pl = cb.pl;
-  da.cal_passes = (int)passes;
-  da.cal_tiles = (int)((d_ff + da.nt - 1) / da.nt);
-  const int64_t grid = (int64_t)((da.cal_tiles + 7) / 8) * 8 * passes;
-  TimedLaunch tl(SATS_K_CAL_GATEUP, s);
-  hipExtLaunchKernelGGL(dense_gateup_kernel<4, false, true>, dim3((unsigned)grid), dim3(kDenseThreads), 0, s, tl.start,
-                        tl.stop, 0, da);
-  HIP_TRY(hipGetLastError());
   return SATS_OK;
 }
 
@@ -1424,7 +1425,7 @@ int cal_buffers(CalBuffers &cb, int64_t n, int64_t d, int64_t d_ff) {
       (rc = cal_alloc(&b.rank, &k[9], sats::kCalMaxLevels)) || (rc = cal_alloc(&b.tk, &k[10], sats::kCalMaxLevels)) ||
       (rc = cal_alloc(&b.thr15, &k[11], sats::kCalCand)) || (rc = cal_alloc(&b.ge15, &k[12], sats::kCalCand)) ||
       (rc = cal_alloc(&b.errsum, &k[13], sats::kCalCand)) ||
-      (rc = cal_alloc(&b.ctl, &k[14], 2 * ((n + sats::kDenseMaxTokens - 1) / sats::kDenseMaxTokens))) ||
+      (rc = cal_alloc(&b.hp, &k[14], (size_t)pf_block_bytes(std::min<int64_t>(n, kPfMaxPass), d, 2))) ||
       (rc = cal_alloc(&b.rsum, &k[15], (size_t)((n + 63) / 64) * 16)) || (rc = cal_alloc(&b.ny2, &k[16], (size_t)n)))
     return rc;
   cb = b;
@@ -2087,7 +2088,7 @@ const char *sats_kernel_name(int kind) {
     case SATS_K_DEC_REDUCE: return "dec_reduce_kernel";
     case SATS_K_DEC_REDUCE_LORA: return "dec_reduce_lora_kernel";
     case SATS_K_CAL_ERR: return "cal_err_kernel";
-    case SATS_K_CAL_GATEUP: return "dense_gateup_kernel (calibration)";
+    case SATS_K_CAL_GATEUP: return "pf_gateup_kernel (calibration)";
     default: return "";
   }
 }
