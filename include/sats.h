@@ -183,7 +183,7 @@ int sats_mlp_forward_inspect_f32(const float *x, const int32_t *token_ids,
  * kept rows.  rank is 8, 16, 32 or 64; the adapter arrays must be 16-byte
  * aligned.  Batches of two or more bf16 tokens whose shapes fit the matrix-core
  * path (d a multiple of 128 and at most 4096, d_ff a multiple of 64) run in
- * passes of up to 64 tokens with every row on the matrix cores: each row
+ * passes of up to 64 tokens (above 128 tokens 2048) with every row on the matrix cores: each row
  * applies its own route and keep rule, the gate and up adapter terms are
  * added in float32 before SiLU and the keep rule, z = p A_down is summed per
  * 64-column tile and scale z B_down is added with the output.  Otherwise the

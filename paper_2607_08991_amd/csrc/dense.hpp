@@ -876,11 +876,11 @@ struct GlueArgs {
   void *hnext;        // otherwise: next layer input of the dense group, [n_dense][d] (ctl null: row blocks)
   void *layer_in;         // optional: inspection copy of the next layer input, rows through perm
   // LoRA (zpart null: none): y += s z B_down for sparse-path rows, z the sum
-  // over the nzb column tiles of zpart [nzb][kDenseMaxTokens][rank], in tile order
+  // over the nzb partials of zpart [nzb][zrows][rank], in order
   const float *zpart;
   const uint16_t *Bd;     // [rank][d] of the layer
   const uint8_t *gbase;
-  int rank, nzb;
+  int rank, nzb, zrows;
   float lscale;
 };
 
@@ -920,8 +920,8 @@ template <typename T> __global__ __launch_bounds__(kGlueThreads) void dense_glue
     const int R = a.rank, i = tid % R, q = tid / R;
     // thread (q, i) adds tiles q, q + Q, ...; then the Q group sums in order
     if (q < Q)
-      zf[tid] = (q < a.nzb) ? sum_coherent(a.zpart + ((size_t)q * kDenseMaxTokens + m) * R + i,
-                                           (size_t)Q * kDenseMaxTokens * R, (a.nzb - q + Q - 1) / Q)
+      zf[tid] = (q < a.nzb) ? sum_coherent(a.zpart + ((size_t)q * a.zrows + m) * R + i, (size_t)Q * a.zrows * R,
+                                           (a.nzb - q + Q - 1) / Q)
                             : 0.0f;
     __syncthreads();
     if (tid < R) {
@@ -1004,14 +1004,25 @@ template <typename T> __global__ __launch_bounds__(kGlueThreads) void dense_glue
 constexpr int kLoraVChunks = 16;
 constexpr int kLoraVMaxChunk = 4096 / kLoraVChunks;  // k rows per chunk (d <= 4096)
 constexpr int kLoraVMaxRank = 64;    // ranks 8, 16, 32, 64
+//
+// The tiled products (ctl null) take every row of a pass at once: H comes and
+// s (h A) leaves in row blocks, as the operand of 4 R further k steps of the
+// gate/up product, [hi | lo] of s (h A_gate), then of s (h A_up) (hi the bf16
+// value, lo its rounded remainder); and a third layer of workgroups writes
+// B_gate transposed, the other operand of those steps.
 struct LoraVArgs {
-  const int *ctl;          // [0] rows of the group, [1] MFMA path on
+  const int *ctl;          // [0] rows of the group, [1] MFMA path on; null: `rows` rows, row blocks
+  int rows;
   const uint8_t *gbase;
   const uint16_t *H;       // [rows][K] bf16 layer input of the group
   const uint16_t *Ag, *Au; // [K][R] of the layer
-  float *vpart;            // [2][4][kLoraVChunks][16][R]
+  float *vpart;            // [2][row tiles][kLoraVChunks][16][R]
   float *lv;               // [2][kDenseMaxTokens][R]
-  unsigned *cnt;           // [8] arrival counts (zero between launches)
+  uint16_t *ext;           // ctl null: row blocks of [rows][4 R]
+  const uint16_t *Bg;      // ctl null: B_gate [R][N] of the layer ...
+  uint16_t *BgT;           // ... and its transpose [N][R]
+  int N;
+  unsigned *cnt;           // [2][row tiles] arrival counts (zero between launches)
   int K, R;
   float s;
 };
@@ -1019,9 +1030,20 @@ __global__ __launch_bounds__(256) void lora_v_kernel(LoraVArgs a) {
   __shared__ uint16_t hs[16 * kLoraVMaxChunk];
   __shared__ uint16_t as[kLoraVMaxChunk * kLoraVMaxRank];
   __shared__ int flag;
-  if (!a.ctl[1]) return;
-  const int nd = min(a.ctl[0], kDenseMaxTokens);
+  if (a.ctl && !a.ctl[1]) return;
+  const int nd = a.ctl ? min(a.ctl[0], kDenseMaxTokens) : a.rows;
   const int ch = blockIdx.x, mt = blockIdx.y, ad = blockIdx.z, tid = threadIdx.x;
+  if (ad == 2) {  // B_gate^T: a thread per column and 8 ranks
+    const int per = a.R / 8, tot = a.N * per, step = gridDim.x * gridDim.y * 256;
+    for (int e = (blockIdx.y * gridDim.x + ch) * 256 + tid; e < tot; e += step) {
+      const int c = e % a.N, q = e / a.N;
+      uint16_t b[8];
+#pragma unroll
+      for (int i = 0; i < 8; ++i) b[i] = a.Bg[(size_t)(8 * q + i) * a.N + c];
+      *reinterpret_cast<u32x4 *>(a.BgT + (size_t)c * a.R + 8 * q) = *reinterpret_cast<const u32x4 *>(b);
+    }
+    return;
+  }
   if (16 * mt >= nd) return;  // the whole (row tile, adapter) returns: no arrivals
   const int R = a.R, kch = a.K / kLoraVChunks, k0 = ch * kch;
   const uint16_t *A = ad ? a.Au : a.Ag;
@@ -1029,7 +1051,12 @@ __global__ __launch_bounds__(256) void lora_v_kernel(LoraVArgs a) {
   for (int e = tid; e < 16 * kch / 8; e += 256) {
     const int r = e / (kch / 8), q = e % (kch / 8), m = 16 * mt + r;
     u32x4 v = {0u, 0u, 0u, 0u};
-    if (m < nd) v = *reinterpret_cast<const u32x4 *>(a.H + (size_t)m * a.K + k0 + 8 * q);
+    if (m < nd) {
+      const int kq = k0 / 8 + q;  // chunk of the row
+      const size_t o = a.ctl ? (size_t)m * a.K + 8 * kq
+                             : ((size_t)mt * (a.K / 32) + (kq >> 2)) * 512 + r * 32 + ((kq & 3) ^ pf_swz(r)) * 8;
+      v = *reinterpret_cast<const u32x4 *>(a.H + o);
+    }
     *reinterpret_cast<u32x4 *>(hs + r * kch + 8 * q) = v;
   }
   {  // A's chunk: at most kLoraVMaxChunk * kLoraVMaxRank / 8 / 256 = 8 16-byte loads per thread, all issued first
@@ -1087,11 +1114,12 @@ __global__ __launch_bounds__(256) void lora_v_kernel(LoraVArgs a) {
     for (int s2 = 1; s2 < NS; ++s2)
 #pragma unroll
       for (int j = 0; j < 4; ++j) acc[j] += red[(s2 * 16 + r) * R + 4 * q + j];
-  float *vp = a.vpart + ((size_t)(ad * 4 + mt) * kLoraVChunks) * 16 * R;  // [chunk][16][R]
+  const int slot = ad * gridDim.y + mt;
+  float *vp = a.vpart + ((size_t)slot * kLoraVChunks) * 16 * R;  // [chunk][16][R]
   if (act)
 #pragma unroll
     for (int j = 0; j < 4; ++j) store_coherent(vp + ((size_t)ch * 16 + r) * R + 4 * q + j, acc[j]);
-  if (!arrive_last(a.cnt + ad * 4 + mt, gridDim.x, &flag)) return;
+  if (!arrive_last(a.cnt + slot, gridDim.x, &flag)) return;
   const int m = 16 * mt + r;
   if (act && m < nd) {
     float v[4][kLoraVChunks];
@@ -1100,12 +1128,28 @@ __global__ __launch_bounds__(256) void lora_v_kernel(LoraVArgs a) {
 #pragma unroll
       for (int c2 = 0; c2 < kLoraVChunks; ++c2) v[j][c2] = load_coherent(vp + ((size_t)c2 * 16 + r) * R + 4 * q + j);
     const bool base = a.gbase[m];
+    float t[4];
 #pragma unroll
     for (int j = 0; j < 4; ++j) {
-      float t = 0.0f;
+      t[j] = 0.0f;
 #pragma unroll
-      for (int c2 = 0; c2 < kLoraVChunks; ++c2) t += v[j][c2];  // chunk order
-      a.lv[((size_t)ad * kDenseMaxTokens + m) * R + 4 * q + j] = base ? 0.0f : a.s * t;
+      for (int c2 = 0; c2 < kLoraVChunks; ++c2) t[j] += v[j][c2];  // chunk order
+      t[j] = base ? 0.0f : a.s * t[j];
+      if (a.ctl) a.lv[((size_t)ad * kDenseMaxTokens + m) * R + 4 * q + j] = t[j];
+    }
+    if (!a.ctl) {
+#pragma unroll
+      for (int h = 0; h < 2; ++h) {
+        uint16_t b[4];
+#pragma unroll
+        for (int j = 0; j < 4; ++j) {
+          b[j] = f32_to_bf16(t[j]);
+          t[j] -= bf16_to_f32(b[j]);
+        }
+        const int ke = (2 * ad + h) * R + 4 * q;  // k of the four among the 4 R
+        *reinterpret_cast<uint2 *>(a.ext + ((size_t)mt * ((4 * R + 31) / 32) + (ke >> 5)) * 512 + r * 32 +
+                                   (((ke >> 3) & 3) ^ pf_swz(r)) * 8 + (ke & 7)) = *reinterpret_cast<const uint2 *>(b);
+      }
     }
   }
 }

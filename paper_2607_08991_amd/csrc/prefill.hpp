@@ -83,6 +83,9 @@ struct PfArgs {
   int ks, kchunk;         // down: k chunks and their length (a multiple of 32)
   float *cal_g;           // calibration: g in float32, [n][N] ...
   uint16_t *cal_ph, *cal_pl;  // ... and p as two bf16 terms (hi = rne(p), lo = rne(p - hi))
+  const uint16_t *ext;    // PF_LORA: row blocks of the further k of h; B_gate^T and B_up_T [N][rank]
+  const uint16_t *BgT, *BuT;
+  int rank;
 };
 
 // The rows of x in row blocks (rows past n and k past d zero), the base-path
@@ -185,7 +188,11 @@ __device__ __forceinline__ void pf_store_terms(uint16_t *o, size_t pterm, float 
 // MODE: how p leaves the kernel.
 enum { PF_P16 = 0,   // rounded to bf16
        PF_SPLIT = 1,  // three bf16 terms whose sum is p: rne(p), rne of the remainder, and the rest
-       PF_CAL = 2 };  // calibration: g in float32, and p as two terms, without the keep rule
+       PF_CAL = 2,    // calibration: g in float32, and p as two terms, without the keep rule
+       PF_LORA = 3 }; // as PF_P16, with 4 R further k for the adapters (K a multiple of 64): rows of
+                      // h continue with [hi | lo] of s (h A_gate) and of s (h A_up), W_gate rows with
+                      // B_gate twice and zeros, W_up rows with zeros and B_up twice, so that the adapter
+                      // terms are in the sums before SiLU and the keep rule
 template <int BM, int NT, int MODE>
 __global__ __launch_bounds__(kPfThreads, 2) void pf_gateup_kernel(PfArgs a) {
   constexpr bool CAL = MODE == PF_CAL;
@@ -206,8 +213,11 @@ __global__ __launch_bounds__(kPfThreads, 2) void pf_gateup_kernel(PfArgs a) {
   const int lane = threadIdx.x & 63, w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int g = lane >> 4, l16 = lane & 15;
   const int m0 = mt0 * BM, n0 = unit * NT;
-  const int K = a.K, N = a.N, S = (K + kPfKC - 1) / kPfKC;
+  constexpr bool LORA = MODE == PF_LORA;
+  const int K = a.K, N = a.N, S0 = (K + kPfKC - 1) / kPfKC;
+  const int R4 = LORA ? 4 * a.rank : 0, SE = (R4 + kPfKC - 1) / kPfKC, S = S0 + SE;  // steps: of K, of the adapters, all
   const int grp = w / WPG, mat = (w % WPG) / (WPG / 2), half = w % (WPG / 2);
+  (void)R4;
   // base-path flags of the rows this lane finishes (see the epilogue), four to a word
   const int lm0 = 64 * grp + (mat ? 0 : 32);
   uint32_t base4[MT / 2];
@@ -215,35 +225,52 @@ __global__ __launch_bounds__(kPfThreads, 2) void pf_gateup_kernel(PfArgs a) {
   for (int i = 0; i < MT / 2; ++i)
     base4[i] = CAL ? 0u : *reinterpret_cast<const uint32_t *>(a.gbase + m0 + lm0 + 16 * i + 4 * g);
   const int rows16 = (a.n + 15) / 16;
-  const __amdgpu_buffer_rsrc_t rsa = dense_rsrc(a.A, (uint32_t)((size_t)rows16 * S * 1024));
+  const __amdgpu_buffer_rsrc_t rsa = dense_rsrc(a.A, (uint32_t)((size_t)rows16 * S0 * 1024));
   const uint32_t wbytes = (uint32_t)((size_t)N * K * 2);
   // h: load i = w + 8 q of a stage is row block m0 / 16 + i at the stage's k (past the last row: zeros)
-  uint32_t aoff[IA];
+  uint32_t aoff[IA], aext[IA];
 #pragma unroll
   for (int q = 0; q < IA; ++q) {
     const int rb = m0 / 16 + w + 8 * q;
-    aoff[q] = rb < rows16 ? (uint32_t)rb * (uint32_t)S * 1024u + 16u * lane : kDenseOffNone;
+    aoff[q] = rb < rows16 ? (uint32_t)rb * (uint32_t)S0 * 1024u + 16u * lane : kDenseOffNone;
+    aext[q] = rb < rows16 ? (uint32_t)rb * (uint32_t)SE * 1024u + 16u * lane : kDenseOffNone;
   }
   // weights: load i = w + 8 q of a stage is rows 8 i .. 8 i + 7 of [W_gate | W_up], 128 bytes each
   const int lr = lane >> 3, lq = (lane & 7) ^ lr;
-  uint32_t woff[IW];
+  uint32_t woff[IW], wext[IW];
 #pragma unroll
   for (int q = 0; q < IW; ++q) {
     const int row = 8 * (w + 8 * q) + lr, c = n0 + (row < NT ? row : row - NT);
     woff[q] = row < 2 * NT && c < N ? (uint32_t)(((size_t)c * K + 8 * lq) * 2) : kDenseOffNone;
+    wext[q] = LORA && c < N ? (uint32_t)c * (uint32_t)a.rank * 2u : kDenseOffNone;
   }
   auto issue_a = [&](uint8_t *buf, int s) {
+    const bool e = LORA && s >= S0;  // (scalar selects, no branch: see the ring buffers)
 #pragma unroll
     for (int q = 0; q < IA; ++q)
-      pf_dma(rsa, buf + (w + 8 * q) * 1024, s < S ? aoff[q] : kDenseOffNone, (uint32_t)s * 1024u);
+      if constexpr (LORA)
+        pf_dma(dense_rsrc(e ? a.ext : a.A, (uint32_t)(rows16 * (e ? SE : S0)) * 1024u), buf + (w + 8 * q) * 1024,
+               s < S ? (e ? aext[q] : aoff[q]) : kDenseOffNone, (uint32_t)(e ? s - S0 : s) * 1024u);
+      else
+        pf_dma(rsa, buf + (w + 8 * q) * 1024, s < S ? aoff[q] : kDenseOffNone, (uint32_t)s * 1024u);
   };
   auto issue_w = [&](uint8_t *buf, int j) {
     const bool v = 64 * j + 8 * lq < K;
+    const bool e = LORA && 2 * j >= S0;
+    const int ke = 64 * (j - S0 / 2) + 8 * lq;  // the lane's k among the further ones
 #pragma unroll
     for (int q = 0; q < IW; ++q) {
       const int i = w + 8 * q;
-      pf_dma(dense_rsrc(i < NT / 8 ? a.Wg : a.Wu, wbytes), buf + i * 1024,
-             v ? woff[q] : kDenseOffNone, (uint32_t)j * 128u);
+      const bool up = i >= NT / 8;
+      if constexpr (LORA) {
+        const bool on = ke < R4 && (ke >= R4 / 2) == up && wext[q] != kDenseOffNone;
+        pf_dma(dense_rsrc(e ? (up ? a.BuT : a.BgT) : (up ? a.Wu : a.Wg), e ? (uint32_t)N * (uint32_t)a.rank * 2u : wbytes),
+               buf + i * 1024, e ? (on ? wext[q] + 2u * (uint32_t)(ke & (a.rank - 1)) : kDenseOffNone)
+                                 : (v ? woff[q] : kDenseOffNone),
+               e ? 0u : (uint32_t)j * 128u);
+      } else {
+        pf_dma(dense_rsrc(up ? a.Wu : a.Wg, wbytes), buf + i * 1024, v ? woff[q] : kDenseOffNone, (uint32_t)j * 128u);
+      }
     }
   };
   bf16x8 oa0[MT], oa1[MT], ob[CT];  // operands: h of even and of odd steps, weights

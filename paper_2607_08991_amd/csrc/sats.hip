@@ -236,6 +236,7 @@ size_t layout(char *base, const Plan &p, int64_t pass, int64_t d, int64_t d_ff, 
 // the per-block counters follow.  Every counter is zero whenever no kernel is
 // running.
 constexpr size_t kCtl = 512;
+constexpr size_t kPfCounters = kCtl + 2 * (2048 / 16);  // tiled products: LoRA arrivals per row tile and adapter
 constexpr size_t kErr = 320;
 constexpr size_t kLoraV = 448;  // [8] batched LoRA: arrivals of the s (h A) chunks
 constexpr size_t kDecDone = 324;  // single-token layer launch: workgroups finished (small layers)
@@ -311,7 +312,7 @@ bool pf_split(int64_t d, int64_t d_ff) { return d % sats::kDenseDownNT != 0 || d
 // The tiles with the least modelled time: rounds of workgroups over the
 // compute units times the cycles of one; for the down-projection also the
 // partials' write and read (about 2000 bytes per cycle).
-PfPlan pf_plan(int64_t np, int64_t d, int64_t d_ff, int esz) {
+PfPlan pf_plan(int64_t np, int64_t d, int64_t d_ff, int esz, bool lora = false) {
   const int64_t cus = std::max(1, device_cus());
   auto cdiv = [](int64_t a, int64_t b) { return (a + b - 1) / b; };
   PfPlan p{};
@@ -328,7 +329,7 @@ PfPlan pf_plan(int64_t np, int64_t d, int64_t d_ff, int esz) {
   }
   double best = 1e300;
   for (const auto &[bm, nt] : {std::pair<int, int>{256, 128}, {256, 96}, {256, 64}, {128, 64}}) {
-    if (split && nt != 64) continue;
+    if ((split || lora) && nt != 64) continue;  // (registers)
     const double c = (double)cdiv(cdiv(np, bm) * cdiv(d_ff, nt), cus) *
                      (double)(cdiv(d, sats::kPfKC) + 16) * pf_step_cycles(bm, 2 * nt, 4, bm == 256 ? nt / 16 : nt / 32);
     if (c < best) best = c, p.bm = bm, p.nt = nt;
@@ -352,10 +353,13 @@ struct PfBuffers {
   float *part;           // [ks][np][d]
   uint8_t *gbase;        // [np], whole tiles of 256
   uint8_t *keep;         // [np][d_ff] keep flags (inspection)
+  uint16_t *ext, *bgt;   // LoRA: further k of h in row blocks, B_gate^T
+  float *vpart, *zpart;  // LoRA: chunk partials of h A, partials [kPfZChunks][np][rank] of p A_down
 };
+constexpr int kPfZChunks = 16;
 // bytes of n rows of length k in row blocks
 int64_t pf_block_bytes(int64_t n, int64_t k, int esz) { return (n + 15) / 16 * ((k * esz + 63) / 64) * 1024; }
-size_t pf_layout(char *base, int64_t np, int ks, int64_t d, int64_t d_ff, int esz, PfBuffers *b) {
+size_t pf_layout(char *base, int64_t np, int ks, int64_t d, int64_t d_ff, int esz, PfBuffers *b, int64_t rank = 0) {
   Carve c{base};
   PfBuffers t{};
   t.h = c.take<uint8_t>(pf_block_bytes(np, d, esz));
@@ -363,21 +367,28 @@ size_t pf_layout(char *base, int64_t np, int ks, int64_t d, int64_t d_ff, int es
   t.gbase = c.take<uint8_t>((np + 255) / 256 * 256);
   t.part = c.take<float>((int64_t)ks * np * d);
   t.keep = c.take<uint8_t>(np * d_ff);
+  if (rank > 0) {
+    t.ext = c.take<uint16_t>(pf_block_bytes(np, 4 * rank, 2) / 2);
+    t.bgt = c.take<uint16_t>(d_ff * rank);
+    t.vpart = c.take<float>(2 * ((np + 15) / 16) * sats::kLoraVChunks * 16 * rank);
+    t.zpart = c.take<float>(kPfZChunks * np * rank);
+  }
   if (b) *b = t;
   return c.off;
 }
 // Workspace of a call of n tokens (every pass), and of any call of up to n.
-size_t pf_bytes(int64_t n, int64_t d, int64_t d_ff, int esz) {
+size_t pf_bytes(int64_t n, int64_t d, int64_t d_ff, int esz, int64_t rank = 0) {
   const int64_t pass = pf_pass(n, esz), last = n - (n - 1) / pass * pass;
   size_t b = 0;
   for (const int64_t np : {std::min(pass, n), last})
-    b = std::max(b, pf_layout(nullptr, np, pf_plan(np, d, d_ff, esz).ks, d, d_ff, esz, nullptr));
+    b = std::max(b, pf_layout(nullptr, np, pf_plan(np, d, d_ff, esz, rank > 0).ks, d, d_ff, esz, nullptr, rank));
   return b;
 }
 size_t pf_bytes_upto(int64_t n, int64_t d, int64_t d_ff, int esz) {
   size_t b = 0;
   for (int64_t m = 1; m <= std::min<int64_t>(n, esz == 4 ? kMaxPass : kPfMaxPass); ++m)
-    b = std::max(b, pf_layout(nullptr, m, pf_plan(m, d, d_ff, esz).ks, d, d_ff, esz, nullptr));
+    b = std::max(b, pf_layout(nullptr, m, pf_plan(m, d, d_ff, esz).ks, d, d_ff, esz, nullptr,
+                              esz == 2 && !pf_split(d, d_ff) ? sats::kLoraMaxRank : 0));
   return b;
 }
 
@@ -406,7 +417,7 @@ typedef void (*PfKernel)(sats::PfArgs);
 template <int MODE> PfKernel pf_gateup_fn(const PfPlan &p) {
   using namespace sats;
   if (p.bm == 128) return pf_gateup_kernel<128, 64, MODE>;
-  if constexpr (MODE != PF_SPLIT) {
+  if constexpr (MODE != PF_SPLIT && MODE != PF_LORA) {
     if (p.nt == 128) return pf_gateup_kernel<256, 128, MODE>;
     if (p.nt == 96) return pf_gateup_kernel<256, 96, MODE>;
   }
@@ -577,14 +588,15 @@ struct Call {
 };
 
 // One pass of np rows from token `base` on through the tiled products (see pf_ok).
-template <typename T> int run_prefill(const Call &c, char *mem, int64_t base, int np) {
+template <typename T> int run_prefill(const Call &c, char *mem, unsigned *counters, int64_t base, int np) {
   using namespace sats;
   constexpr int esz = sizeof(T);
   const int64_t d = c.d, d_ff = c.d_ff;
   const size_t wl = (size_t)d * (size_t)d_ff;
-  const PfPlan p = pf_plan(np, d, d_ff, esz);
+  const PfPlan p = pf_plan(np, d, d_ff, esz, c.Ag != nullptr);
   PfBuffers b{};
-  pf_layout(mem, np, p.ks, d, d_ff, esz, &b);
+  const bool lora = c.Ag != nullptr;  // (bf16 shapes of the 64-row kernels: see lora_tiled)
+  pf_layout(mem, np, p.ks, d, d_ff, esz, &b, lora ? c.rank : 0);
   const bool lists = c.active_count || c.active_idx, split = pf_split(d, d_ff);
   {
     PfPackArgs pa{};
@@ -617,6 +629,32 @@ template <typename T> int run_prefill(const Call &c, char *mem, int64_t base, in
     u.K = (int)d;
     u.N = (int)d_ff;
     u.units = (int)((d_ff + p.nt - 1) / p.nt);
+    const size_t al = (size_t)d * c.rank, bl = (size_t)d_ff * c.rank;  // adapter elements per layer
+    if (lora) {
+      LoraVArgs va{};
+      va.rows = np;
+      va.gbase = b.gbase;
+      va.H = u.A;
+      va.Ag = static_cast<const uint16_t *>(c.Ag) + l * al;
+      va.Au = static_cast<const uint16_t *>(c.Au) + l * al;
+      va.vpart = b.vpart;
+      va.ext = b.ext;
+      va.Bg = static_cast<const uint16_t *>(c.Bg) + l * bl;
+      va.BgT = b.bgt;
+      va.N = (int)d_ff;
+      va.cnt = counters + kCtl;
+      va.K = (int)d;
+      va.R = (int)c.rank;
+      va.s = c.lscale;
+      TimedLaunch tl(SATS_K_LORA_V, c.stream);
+      hipExtLaunchKernelGGL(lora_v_kernel, dim3(kLoraVChunks, (np + 15) / 16, 3), dim3(256), 0, c.stream, tl.start,
+                            tl.stop, 0, va);
+      HIP_TRY(hipGetLastError());
+      u.ext = b.ext;
+      u.BgT = b.bgt;
+      u.BuT = static_cast<const uint16_t *>(c.BuT) + l * bl;
+      u.rank = (int)c.rank;
+    }
     if (p.small) {
       TimedLaunch tl(SATS_K_DENSE, c.stream);
       hipExtLaunchKernelGGL(sm_gateup_fn<T>(np), dim3((unsigned)u.units), dim3(kPfThreads), 0, c.stream, tl.start, tl.stop,
@@ -624,7 +662,8 @@ template <typename T> int run_prefill(const Call &c, char *mem, int64_t base, in
     } else {
       u.mtiles = (np + p.bm - 1) / p.bm;
       TimedLaunch tl(SATS_K_DENSE, c.stream);
-      hipExtLaunchKernelGGL(split ? pf_gateup_fn<PF_SPLIT>(p) : pf_gateup_fn<PF_P16>(p), dim3(pf_grid(u.mtiles, u.units)), dim3(kPfThreads), 0, c.stream, tl.start,
+      hipExtLaunchKernelGGL(lora ? pf_gateup_fn<PF_LORA>(p) : split ? pf_gateup_fn<PF_SPLIT>(p) : pf_gateup_fn<PF_P16>(p),
+                            dim3(pf_grid(u.mtiles, u.units)), dim3(kPfThreads), 0, c.stream, tl.start,
                             tl.stop, 0, u);
     }
     HIP_TRY(hipGetLastError());
@@ -650,6 +689,26 @@ template <typename T> int run_prefill(const Call &c, char *mem, int64_t base, in
     }
     HIP_TRY(hipGetLastError());
     GlueArgs ga{};
+    if (lora) {  // z = p A_down as one more product with rank columns
+      PfArgs z = w;
+      z.Wd = static_cast<const uint16_t *>(c.Ad) + l * bl;
+      z.part = b.zpart;
+      z.N = (int)c.rank;
+      z.kchunk = (int)(((d_ff + kPfZChunks - 1) / kPfZChunks + kPfKC - 1) / kPfKC * kPfKC);
+      z.ks = (int)((d_ff + z.kchunk - 1) / z.kchunk);
+      z.mtiles = (np + 127) / 128;
+      z.units = z.ks;
+      hipLaunchKernelGGL((pf_down_kernel<128, 128, false>), dim3(pf_grid(z.mtiles, z.units)), dim3(kPfThreads), 0,
+                         c.stream, z);
+      HIP_TRY(hipGetLastError());
+      ga.zpart = b.zpart;
+      ga.Bd = static_cast<const uint16_t *>(c.Bd) + l * (size_t)c.rank * d;
+      ga.gbase = b.gbase;
+      ga.rank = (int)c.rank;
+      ga.nzb = z.ks;
+      ga.zrows = np;
+      ga.lscale = c.lscale;
+    }
     ga.rows = np;
     ga.part = b.part;
     ga.ksplit = p.ks;
@@ -800,6 +859,7 @@ int run_pass(const Call &c, const Plan &p, const Buffers &b, unsigned *counters,
         ga.gbase = b.gbase;
         ga.rank = (int)c.rank;
         ga.nzb = (int)((d_ff + nt_gu - 1) / nt_gu);
+        ga.zrows = kDenseMaxTokens;
         ga.lscale = c.lscale;
       }
       hipLaunchKernelGGL(dense_glue_kernel<uint16_t>, dim3(np), dim3(kGlueThreads), 0, c.stream, ga);
@@ -1028,6 +1088,13 @@ bool lora_batched(const Call &c, int esz, bool vec_ok) {
          batch_whole() && !g_opt.lora_per_token;
 }
 
+// ... and above two passes of 64 tokens the tiled products, with the adapters
+// as further k of the gate/up product (200 tokens of a Llama-3.1-8B layer at
+// rank 16: four passes 388 us, here 147).
+bool lora_tiled(const Call &c, int esz, bool vec_ok) {
+  return c.n > 2 * kMaxPass && lora_batched(c, esz, vec_ok) && pf_ok(esz, vec_ok, c.n, c.d, c.d_ff);
+}
+
 // LoRA calls on the single-token path, token after token (each token takes
 // its own route; the inspection outputs are written at the token's offsets).
 template <typename T>
@@ -1097,9 +1164,10 @@ int run(const Call &c) {
     if (!lora_batched(c, esz, vec_ok)) return run_lora<T>(c, vec_ok);
   }
   const int64_t lrank = c.Ag ? c.rank : 0;
-  if (!c.Ag && pf_ok(esz, vec_d, c.n, c.d, c.d_ff)) {
-    const size_t need = pf_bytes(c.n, c.d, c.d_ff, esz);
+  if (c.Ag ? lora_tiled(c, esz, vec_ok) : pf_ok(esz, vec_d, c.n, c.d, c.d_ff)) {
+    const size_t need = pf_bytes(c.n, c.d, c.d_ff, esz, lrank);
     char *mem = nullptr;
+    unsigned *counters = nullptr;  // (LoRA only)
     int rc = 0;
     // the allocation-free call takes this path when its workspace fits
     if (c.noalloc) {
@@ -1109,13 +1177,14 @@ int run(const Call &c) {
       }
     } else {
       Workspace *ws = nullptr;
-      if ((rc = ensure_workspace(c.stream, need, kCtl, &ws))) return rc;
+      if ((rc = ensure_workspace(c.stream, need, kPfCounters, &ws))) return rc;
       mem = ws->mem;
+      counters = ws->counters;
     }
     if (mem) {
       const int rows = pf_pass(c.n, esz);
       for (int64_t base = 0; base < c.n; base += rows)
-        if ((rc = run_prefill<T>(c, mem, base, (int)std::min<int64_t>(rows, c.n - base)))) return rc;
+        if ((rc = run_prefill<T>(c, mem, counters, base, (int)std::min<int64_t>(rows, c.n - base)))) return rc;
       return SATS_OK;
     }
   }
@@ -1890,7 +1959,7 @@ int sats_reserve(int64_t max_tokens, int64_t d, int64_t d_ff, int64_t n_layers, 
         nc = std::max(nc, counter_count(p, pass, dp));
       }
   if (pf_ok(elem_bytes, true, max_tokens, d, d_ff))
-    bytes = std::max(bytes, pf_bytes_upto(max_tokens, d, d_ff, elem_bytes));
+    bytes = std::max(bytes, pf_bytes_upto(max_tokens, d, d_ff, elem_bytes)), nc = std::max(nc, kPfCounters);
   Workspace *ws = nullptr;
   return ensure_workspace(stream, bytes, nc, &ws);
 }

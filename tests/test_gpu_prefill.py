@@ -103,3 +103,30 @@ def test_allocation_free_call_takes_the_same_kernels(d, dff, n):
         outs.append(from_dev(o))
     torch.cuda.synchronize()
     np.testing.assert_array_equal(*outs)
+
+
+# LoRA batches above two passes of 64: adapters as further k of the gate/up product
+LORA = [
+    # seed, layers, d, d_ff, tokens, rank
+    (151, 2, 256, 1024, 129, 16),
+    (152, 1, 128, 512, 200, 8),    # the further k fill half a weight stage
+    (153, 1, 512, 1536, 300, 64),  # ... and four
+    (154, 3, 384, 448, 257, 32),
+]
+
+
+@pytest.mark.parametrize("seed,L,d,dff,n,rank", LORA)
+def test_lora_prompt_matches_oracle(seed, L, d, dff, n, rank):
+    from test_gpu_lora import check_lora, run_lora, scale_for, thresholds_for
+    print(f"lora prompt seed={seed} L={L} d={d} d_ff={dff} n={n} rank={rank}", flush=True)
+    w_std = 1.0 / np.sqrt(d)
+    c = synth.small_case(seed, L, d, dff, "bf16", n, vocab=40, n_dense_ids=12, w_std=w_std)
+    ad = synth.stack_lora_adapters(seed, L, d, dff, rank, "bf16")
+    s = scale_for(w_std, rank)
+    ts = thresholds_for(c, "bf16", seed)
+    for lut in (None, c["route_lut"]):
+        res = run_lora(c, ad, rank, s, ts, lut, "bf16")
+        worst = check_lora(c, ad, s, ts, lut, "bf16", res)
+        again = run_lora(c, ad, rank, s, ts, lut, "bf16", inspect=False)
+        np.testing.assert_array_equal(again["out"], res["out"])
+        print(f"  lut={'yes' if lut is not None else 'no'} worst rel err {worst:.3g}", flush=True)
