@@ -1,7 +1,10 @@
 // Batched calls: token routing with a stable partition, and the base-path
 // (dense) group on MFMA matrix cores.
 //
-// route_kernel   per token r = table[id] (Eq. 13); a stable partition puts
+// route_kernel   (calls that split the batch, LoRA passes and inspection; with
+//                every token on the matrix cores the gate/up kernel reads the
+//                call input and the table itself: a launch of 4.7 us less)
+//                per token r = table[id] (Eq. 13); a stable partition puts
 //                the base-path tokens first (perm), counts them (n_dense) and
 //                gathers their inputs into a packed [n_dense][d] buffer.  When
 //                n_dense reaches the MFMA threshold the dense group is done
@@ -109,10 +112,30 @@ __global__ __launch_bounds__(kThreads) void route_kernel(RouteArgs a) {
   }
 }
 
+// The base-path flag of row `lane` of a pass of at most 64 tokens, in two
+// steps so that the two dependent loads overlap others: the id, then its
+// table entry.  Without a table both loads have an empty range and return
+// zero, so no branch comes before the loads that follow.
+__device__ __forceinline__ int route_id(int mode, const int32_t *ids, int rows, int lane) {
+  const __amdgpu_buffer_rsrc_t r = __builtin_amdgcn_make_buffer_rsrc(
+      const_cast<int32_t *>(ids), (short)0, mode == ROUTE_LUT ? rows * 4 : 0, 0x00020000);
+  return __builtin_amdgcn_raw_buffer_load_b32(r, lane * 4, 0, 0);
+}
+__device__ __forceinline__ int route_flag(int mode, const uint8_t *lut, int id) {
+  const __amdgpu_buffer_rsrc_t r = __builtin_amdgcn_make_buffer_rsrc(
+      const_cast<uint8_t *>(lut), (short)0, mode == ROUTE_LUT ? 0x7fffffff : 0, 0x00020000);
+  return __builtin_amdgcn_raw_buffer_load_b8(r, id, 0, 0);
+}
+
 struct DenseArgs {
-  const int *ctl;         // [0] rows of the MFMA group, [1] MFMA path on
-  const uint8_t *gbase;   // [rows] base-path flag per group row
-  const int *perm;        // group row -> token of the pass
+  const int *ctl;         // [0] rows of the MFMA group, [1] MFMA path on; null: `rows` rows, every
+                          // token of the pass in its own order
+  int rows;
+  const uint8_t *gbase;   // [rows] base-path flag per group row; null: from ids and lut
+  const int32_t *ids;
+  const uint8_t *lut;
+  int route_mode;
+  const int *perm;        // group row -> token of the pass (ctl given)
   const float *thr;       // threshold of this layer (gate/up)
   uint8_t *keep_out;      // optional inspection: [n][N] keep flags, rows through perm
   const uint16_t *H;      // [n_dense][K] bf16 layer input (gate/up) or p (down)
@@ -311,9 +334,11 @@ __global__ __launch_bounds__(kDenseThreads) void dense_gateup_kernel(DenseArgs a
   // (every allocated row of H: rows past the group feed only results that
   // are not stored); a workgroup of an empty group then waits for its loads
   // and returns
-  const int ctl_on = a.ctl[1], ctl_n = a.ctl[0];
+  const int ctl_on = a.ctl ? a.ctl[1] : 1, ctl_n = a.ctl ? a.ctl[0] : a.rows;
   int nd = 16 * MT;
   const int lane = threadIdx.x & 63, w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int dmode = a.gbase ? ROUTE_SPARSE : a.route_mode;  // the flags looked up here
+  int rid = route_id(dmode, a.ids, a.rows, lane), rflag = 0;
   const int mat = w >> 2, g = lane >> 4, l16 = lane & 15, c = 16 * (w & 3) + l16;
   const int n0 = tile * a.nt;
   const int K = a.K, N = a.N;
@@ -374,7 +399,8 @@ __global__ __launch_bounds__(kDenseThreads) void dense_gateup_kernel(DenseArgs a
     return;                                                                                  \
   }                                                                                          \
   nd = min(ctl_n, 16 * MT);                                                                  \
-  hv = dr < nd
+  hv = dr < nd;                                                                              \
+  rflag = route_flag(dmode, a.lut, rid)
   if constexpr (MT == 1) {
     SATS_DENSE_RING8_H(S, SATS_GU_ISSUE, SATS_GU_COMPUTE, SATS_GU_GROUP)
   } else {
@@ -456,18 +482,20 @@ __global__ __launch_bounds__(kDenseThreads) void dense_gateup_kernel(DenseArgs a
   __syncthreads();
   if (mat == 1) {
     const float thr = a.thr ? *a.thr : 0.0f;
+    const int flag = dmode == ROUTE_BASE || rflag != 0;  // of row `lane`
     bool any = false;  // some row of the group keeps column c
 #pragma unroll
     for (int mt = 0; mt < MT; ++mt)
 #pragma unroll
       for (int r = 0; r < 4; ++r) {
         const int m = 16 * mt + 4 * g + r;
+        const int fm = __shfl(flag, m, 64);
         if (m < nd) {
           const float gv = xs[m * kDenseXP + c];
-          const bool keep = a.gbase[m] || fabsf(gv) >= thr;  // Eq. 4-5; every column on the base path
+          const bool keep = (a.gbase ? (int)a.gbase[m] : fm) || fabsf(gv) >= thr;  // Eq. 4-5; every column on the base path
           pt[m * 64 + c] = keep ? f32_to_bf16(gv * acc[mt][r]) : (uint16_t)0;
           any = any || keep;
-          if (a.keep_out && c < ncol) a.keep_out[(size_t)a.perm[m] * N + n0 + c] = (uint8_t)keep;
+          if (a.keep_out && c < ncol) a.keep_out[(size_t)(a.ctl ? a.perm[m] : m) * N + n0 + c] = (uint8_t)keep;
         }
       }
     // the four lanes of column c (g = 0..3) hold its rows; lane g = 0 publishes the union flag
@@ -524,7 +552,7 @@ __global__ __launch_bounds__(kDenseThreads) void dense_down_kernel(DenseArgs a) 
       rg2[kDenseStageBytes], rg3[kDenseStageBytes], rg4[kDenseStageBytes], rg5[kDenseStageBytes];
   // the group's control words are read while the first two stages load (as
   // in the gate/up kernel)
-  const int ctl_on = a.ctl[1], ctl_n = a.ctl[0];
+  const int ctl_on = a.ctl ? a.ctl[1] : 1, ctl_n = a.ctl ? a.ctl[0] : a.rows;
   int nd = 16 * MT;
   const int lane = threadIdx.x & 63, w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int g = lane >> 4, l16 = lane & 15, c = 16 * w + l16;
@@ -869,11 +897,12 @@ __device__ __forceinline__ int pf_swz(int r) { return ((r >> 1) & 2) ^ (((r >> 3
 struct GlueArgs {
   const int *ctl;         // null: `rows` rows, each its own token (perm unused)
   int rows;
+  int blocks;             // hnext in row blocks (prefill.hpp)
   const int *perm;
   const float *part;      // [KSPLIT][n_dense][d]
   int ksplit, d;
   void *out;              // last layer: [n][d] of the pass (T), rows through perm; else null
-  void *hnext;        // otherwise: next layer input of the dense group, [n_dense][d] (ctl null: row blocks)
+  void *hnext;        // otherwise: next layer input of the dense group, [n_dense][d] or row blocks
   void *layer_in;         // optional: inspection copy of the next layer input, rows through perm
   // LoRA (zpart null: none): y += s z B_down for sparse-path rows, z the sum
   // over the nzb partials of zpart [nzb][zrows][rank], in order
@@ -982,7 +1011,7 @@ template <typename T> __global__ __launch_bounds__(kGlueThreads) void dense_glue
 #pragma unroll
     for (int i = 0; i < 4; ++i) h.v[i] = Elem<T>::round(y[i] / scale);
     constexpr int KB = 64 / sizeof(T), CE = 16 / sizeof(T);  // elements of a block's row and of a chunk
-    const size_t o = a.ctl ? (size_t)m * a.d + c
+    const size_t o = !a.blocks ? (size_t)m * a.d + c
                            : ((size_t)(m >> 4) * ((a.d + KB - 1) / KB) + c / KB) * (16 * KB) + (m & 15) * KB +
                                  ((c / CE & 3) ^ pf_swz(m & 15)) * CE + c % CE;
     *reinterpret_cast<Quad *>(static_cast<T *>(a.hnext) + o) = h;

@@ -77,6 +77,10 @@ struct PfArgs {
   float *part;            // down: partials [ks][n][N]
   const float *thr;       // layer threshold, or null (base path for every row)
   const uint8_t *gbase;   // base-path flag of each row (gate/up; allocated to whole tiles of 256)
+  const uint8_t *x;       // up to 64 rows, first layer: the call input [n][K] in place of A
+  const int32_t *ids;     // up to 64 rows: the flags are looked up in the kernel
+  const uint8_t *lut;
+  int route_mode;
   uint8_t *keep_out;      // optional [n][N] keep flags
   int n, K, N;            // rows; reduction length; output columns
   int mtiles, units;      // row tiles; column tiles (times k chunks, down)
@@ -92,8 +96,8 @@ struct PfArgs {
 // flags, and the inspection copies of both.  A wavefront per block.
 struct PfPackArgs {
   const uint8_t *x;       // [n] rows of `bytes` bytes (a multiple of 16)
-  uint8_t *A;             // row blocks
-  uint8_t *gbase;         // [n]
+  uint8_t *A;             // row blocks, or null
+  uint8_t *gbase;         // [n], or null
   const int32_t *ids;
   const uint8_t *lut;
   int route_mode;
@@ -112,10 +116,10 @@ __global__ __launch_bounds__(kThreads) void pf_pack_kernel(PfPackArgs a) {
     v = *reinterpret_cast<const u32x4 *>(a.x + (size_t)m * a.bytes + k);
     if (a.layer_in) *reinterpret_cast<u32x4 *>(a.layer_in + (size_t)m * a.bytes + k) = v;
   }
-  *reinterpret_cast<u32x4 *>(a.A + (size_t)b * 1024 + 16 * lane) = v;
-  if (b % nb == 0 && (lane & 3) == 0 && m < a.n && a.gbase) {
+  if (a.A) *reinterpret_cast<u32x4 *>(a.A + (size_t)b * 1024 + 16 * lane) = v;
+  if (b % nb == 0 && (lane & 3) == 0 && m < a.n && (a.gbase || a.route_out)) {
     const uint8_t base = (uint8_t)token_is_base(a.route_mode, a.ids, a.lut, m);
-    a.gbase[m] = base;
+    if (a.gbase) a.gbase[m] = base;
     if (a.route_out) a.route_out[m] = base;
   }
 }
@@ -652,22 +656,27 @@ __global__ __launch_bounds__(kPfThreads, 2) void sm_gateup_kernel(PfArgs a, int 
   const int K = a.K, N = a.N, n0 = blockIdx.x * nt;
   constexpr int E = sizeof(T), KB = 64 / E;  // bytes of an element, k of a block
   const int nb = (K + KB - 1) / KB, S = (nb + 1) / 2;
-  uint32_t base4[MT];
-#pragma unroll
-  for (int i = 0; i < MT; ++i) base4[i] = *reinterpret_cast<const uint32_t *>(a.gbase + 16 * i + 4 * g);
+  const int rid = route_id(a.route_mode, a.ids, a.n, lane);  // of row `lane`
   const int rows16 = (a.n + 15) / 16;
-  const __amdgpu_buffer_rsrc_t rsa = dense_rsrc(a.A, (uint32_t)(rows16 * nb * 1024));
   const uint32_t wbytes = (uint32_t)((size_t)N * K * E);
   const __amdgpu_buffer_rsrc_t rsg = dense_rsrc(a.Wg, wbytes), rsu = dense_rsrc(a.Wu, wbytes);
   // wavefront w: rows 8 w .. 8 w + 7 of each projection, and block w & 1 of row tile w / 2 of h
   const int lr = lane >> 3, lq = (lane & 7) ^ lr, row = 8 * w + lr;
   const uint32_t woff = row < nt && n0 + row < N ? (uint32_t)((size_t)(n0 + row) * K * E + 16 * lq) : kDenseOffNone;
-  const uint32_t aoff = w / 2 < MT && w / 2 < rows16 ? (uint32_t)((w / 2 * nb + (w & 1)) * 1024 + 16 * lane) : kDenseOffNone;
+  // (the call input is read as it is, a row's 64 bytes by four lanes, into the same LDS layout)
+  const bool direct = a.x != nullptr;
+  const int am = w / 2 * 16 + (lane >> 2), ak = 64 * (w & 1) + 16 * ((lane & 3) ^ pf_swz(lane >> 2));
+  const uint32_t aoff = w / 2 >= MT || am >= a.n ? kDenseOffNone
+                        : direct                 ? (uint32_t)(am * K * E + ak)
+                                                 : (uint32_t)((w / 2 * nb + (w & 1)) * 1024 + 16 * lane);
+  const uint32_t astep = direct ? 128u : 2048u;
+  const __amdgpu_buffer_rsrc_t rsa = dense_rsrc(direct ? (const void *)a.x : (const void *)a.A,
+                                                direct ? (uint32_t)(a.n * K * E) : (uint32_t)(rows16 * nb * 1024));
   auto issue = [&](uint8_t *buf, int s) {
     const bool v = 128 * s + 16 * lq < K * E;
     pf_dma(rsg, buf + w * 1024, v ? woff : kDenseOffNone, (uint32_t)s * 128u);
     pf_dma(rsu, buf + 8192 + w * 1024, v ? woff : kDenseOffNone, (uint32_t)s * 128u);
-    pf_dma(rsa, buf + SW + w * 1024, 2 * s + (w & 1) < nb ? aoff : kDenseOffNone, (uint32_t)s * 2048u);
+    pf_dma(rsa, buf + SW + w * 1024, 128 * s + ak < K * E ? aoff : kDenseOffNone, (uint32_t)s * astep);
   };
   u32x4 oa0[2][MT], oa1[2][MT], ob0[2], ob1[2];  // operands of even and odd stages
   auto load = [&](const uint8_t *buf, u32x4(&xa)[2][MT], u32x4(&xb)[2]) {
@@ -682,7 +691,8 @@ __global__ __launch_bounds__(kPfThreads, 2) void sm_gateup_kernel(PfArgs a, int 
   f32x4v acc0[MT] = {}, acc1[MT] = {}, sum[MT] = {}, comp[MT] = {};  // stage sums (even, odd); total
 #pragma unroll
   for (int s = 0; s < R - 1; ++s) issue(rb(s), s);
-  pf_barrier<(R - 2) * 3>();
+  const int rflag = route_flag(a.route_mode, a.lut, rid);
+  pf_barrier<(R - 2) * 3 + 1>();
   load(rg0, oa0, ob0);
   // stage s: stage s + 1 has landed, every wavefront holds the operands of stage s
   auto step = [&](int s, int p, u32x4(&xa)[2][MT], u32x4(&xb)[2], u32x4(&ya)[2][MT], u32x4(&yb)[2],
@@ -720,6 +730,7 @@ __global__ __launch_bounds__(kPfThreads, 2) void sm_gateup_kernel(PfArgs a, int 
   __syncthreads();
   if (mat == 0 || 16 * ct >= nt) return;
   const float thr = a.thr ? *a.thr : 0.0f;
+  const int flag = a.route_mode == ROUTE_BASE || rflag != 0;
   const int c0 = n0 + 16 * ct;
 #pragma unroll
   for (int i = 0; i < MT; ++i) {
@@ -727,7 +738,7 @@ __global__ __launch_bounds__(kPfThreads, 2) void sm_gateup_kernel(PfArgs a, int 
 #pragma unroll
     for (int r = 0; r < 4; ++r) {
       const int m = 16 * i + 4 * g + r, c = c0 + l16;
-      const bool keep = ((base4[i] >> (8 * r)) & 0xffu) || fabsf(gv[r]) >= thr;
+      const bool keep = __shfl(flag, m, 64) || fabsf(gv[r]) >= thr;
       *reinterpret_cast<float *>(xt + i * 1024 + (4 * g + r) * 64 + l16 * 4) = keep ? gv[r] * sum[i][r] : 0.0f;
       if (a.keep_out && m < a.n && c < N) a.keep_out[(size_t)m * N + c] = (uint8_t)keep;
     }

@@ -598,11 +598,12 @@ template <typename T> int run_prefill(const Call &c, char *mem, unsigned *counte
   const bool lora = c.Ag != nullptr;  // (bf16 shapes of the 64-row kernels: see lora_tiled)
   pf_layout(mem, np, p.ks, d, d_ff, esz, &b, lora ? c.rank : 0);
   const bool lists = c.active_count || c.active_idx, split = pf_split(d, d_ff);
-  {
+  const uint8_t *x = static_cast<const uint8_t *>(c.x) + (size_t)base * d * esz;
+  if (!p.small || c.route_out || c.layer_in) {  // (up to 64 rows the first layer reads x itself)
     PfPackArgs pa{};
-    pa.x = static_cast<const uint8_t *>(c.x) + (size_t)base * d * esz;
-    pa.A = b.h;
-    pa.gbase = b.gbase;
+    pa.x = x;
+    pa.A = p.small ? nullptr : b.h;
+    pa.gbase = p.small ? nullptr : b.gbase;
     pa.ids = c.ids ? c.ids + base : nullptr;
     pa.lut = c.lut;
     pa.route_mode = c.route_mode;
@@ -620,6 +621,10 @@ template <typename T> int run_prefill(const Call &c, char *mem, unsigned *counte
     PfArgs u = a;
     u.A = reinterpret_cast<const uint16_t *>(b.h);
     u.gbase = b.gbase;
+    u.x = p.small && l == 0 ? x : nullptr;
+    u.ids = c.ids ? c.ids + base : nullptr;
+    u.lut = c.lut;
+    u.route_mode = c.route_mode;
     u.Wg = reinterpret_cast<const uint16_t *>(static_cast<const T *>(c.Wg) + l * wl);
     u.Wu = reinterpret_cast<const uint16_t *>(static_cast<const T *>(c.Wu) + l * wl);
     u.P = reinterpret_cast<uint16_t *>(b.p);
@@ -710,6 +715,7 @@ template <typename T> int run_prefill(const Call &c, char *mem, unsigned *counte
       ga.lscale = c.lscale;
     }
     ga.rows = np;
+    ga.blocks = 1;
     ga.part = b.part;
     ga.ksplit = p.ks;
     ga.d = (int)d;
@@ -751,7 +757,10 @@ int run_pass(const Call &c, const Plan &p, const Buffers &b, unsigned *counters,
   const bool whole = batch_whole();
   const bool all_mfma = mfma && whole;
   if (lora && !all_mfma) return fail(SATS_ERR_SHAPE, "batched LoRA pass without the MFMA path");
-  {
+  // every token on the matrix cores: the kernels take the call input and the
+  // table as they are, and the partition is only made for its inspection copies
+  const bool direct = all_mfma && !lora;
+  if (!direct || c.route_out || c.layer_in) {
     RouteArgs ra{};
     ra.ids = c.ids ? c.ids + base : nullptr;
     ra.lut = c.lut;
@@ -778,20 +787,24 @@ int run_pass(const Call &c, const Plan &p, const Buffers &b, unsigned *counters,
     if (mfma) {
       // base-path group on MFMA (kernels return at once when the group is small)
       DenseArgs da{};
-      da.ctl = b.ctl;
-      da.gbase = b.gbase;
+      da.ctl = direct ? nullptr : b.ctl;
+      da.rows = np;
+      da.gbase = direct ? nullptr : b.gbase;
+      da.ids = c.ids ? c.ids + base : nullptr;
+      da.lut = c.lut;
+      da.route_mode = c.route_mode;
       da.perm = b.perm;
       da.thr = c.thr ? c.thr + l : nullptr;
       da.keep_out = inspect_lists ? b.keep : nullptr;
       da.uflag = b.uflag;
-      da.H = (l == 0) ? b.xd : b.hnext;
+      da.H = l > 0 ? b.hnext : direct ? static_cast<const uint16_t *>(c.x) + base * d : b.xd;
       da.Wg = static_cast<const uint16_t *>(c.Wg) + l * wl;
       da.Wt = static_cast<const uint16_t *>(c.Wu) + l * wl;
       da.P = b.pdense;
       da.K = (int)d;
       da.N = (int)d_ff;
       da.nt = nt_gu;
-      da.hcap = b.prows;
+      da.hcap = direct && l == 0 ? np : b.prows;
       const size_t al = (size_t)d * c.rank;   // elements of A_gate, A_up (per layer)
       const size_t bl = (size_t)d_ff * c.rank;  // elements of B_gate, B_up_T, A_down (per layer)
       if (lora) {
@@ -827,7 +840,8 @@ int run_pass(const Call &c, const Plan &p, const Buffers &b, unsigned *counters,
       }
       HIP_TRY(hipGetLastError());
       DenseArgs dd{};
-      dd.ctl = b.ctl;
+      dd.ctl = direct ? nullptr : b.ctl;
+      dd.rows = np;
       dd.H = b.pdense;
       dd.hcap = b.prows;
       dd.Wb = static_cast<const uint16_t *>(c.Wd) + l * wl;
@@ -844,7 +858,8 @@ int run_pass(const Call &c, const Plan &p, const Buffers &b, unsigned *counters,
       }
       HIP_TRY(hipGetLastError());
       GlueArgs ga{};
-      ga.ctl = b.ctl;
+      ga.ctl = direct ? nullptr : b.ctl;
+      ga.rows = np;
       ga.perm = b.perm;
       ga.part = b.ddpart;
       ga.ksplit = ks;
