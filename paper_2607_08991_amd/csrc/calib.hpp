@@ -28,6 +28,7 @@ namespace sats {
 constexpr int kCalThreads = 256;
 constexpr int kCalMaxLevels = 64;     // levels of one quantile call
 constexpr int kCalCand = 15;          // candidates of one error product (row 15 is y)
+constexpr int kCalBucket = 2 * kCalCand;  // candidates of one bucket pass (two products)
 constexpr float kCalEps = 1e-6f;      // eps of Eq. 6
 
 __device__ __forceinline__ uint32_t abs_bits(float v) { return __float_as_uint(v) & 0x7fffffffu; }
@@ -226,27 +227,30 @@ __global__ __launch_bounds__(kCalThreads) void cal_transpose_kernel(const uint16
   }
 }
 
-// c = #{r < 15 : t_r <= |g|} per value, as a byte (the error product
+// c = #{r < NC : t_r <= |g|} per value, as a byte (the error product
 // removes a neuron at candidate r when c <= r), and ge[r] = #{|g| >= t_r},
-// the values kept at t_r, over the launch (integer counts: exact in any
+// the values kept at t_r, over the launch; one pass serves two products (NC
+// 15, 20 or 30: the 19 positive candidates of the coarse grid took 2 x 38 us
+// in passes of 15, SATS_BUCKET in one of 20) (integer counts: exact in any
 // order; ge must be zero on entry).  A thread reads four values per 16-byte
 // load and has kCalLoads loads in flight; workgroup 0 takes the N % 4 tail.
-__global__ __launch_bounds__(kCalThreads) void cal_bucket_kernel(const float *G, size_t N, const float *thr15,
+template <int NC>
+__global__ __launch_bounds__(kCalThreads) void cal_bucket_kernel(const float *G, size_t N, const float *thr,
                                                                  uint8_t *cnt, unsigned long long *ge) {
-  __shared__ unsigned int h[kCalCand];
-  if (threadIdx.x < kCalCand) h[threadIdx.x] = 0u;
-  float t[kCalCand];
-  uint32_t n_ge[kCalCand];
+  __shared__ unsigned int h[NC];
+  if (threadIdx.x < NC) h[threadIdx.x] = 0u;
+  float t[NC];
+  uint32_t n_ge[NC];
 #pragma unroll
-  for (int r = 0; r < kCalCand; ++r) {
-    t[r] = thr15[r];
+  for (int r = 0; r < NC; ++r) {
+    t[r] = thr[r];
     n_ge[r] = 0u;
   }
   auto bucket = [&](float g) -> uint32_t {
     const float v = fabsf(g);
     uint32_t c = 0u;
 #pragma unroll
-    for (int r = 0; r < kCalCand; ++r) {
+    for (int r = 0; r < NC; ++r) {
       const uint32_t f = t[r] <= v ? 1u : 0u;
       c += f;
       n_ge[r] += f;
@@ -267,15 +271,15 @@ __global__ __launch_bounds__(kCalThreads) void cal_bucket_kernel(const float *G,
   }
   if (blockIdx.x == 0 && threadIdx.x < N - 4 * N4) cnt[4 * N4 + threadIdx.x] = (uint8_t)bucket(G[4 * N4 + threadIdx.x]);
 #pragma unroll
-  for (int r = 0; r < kCalCand; ++r)
+  for (int r = 0; r < NC; ++r)
     for (int o = 32; o > 0; o >>= 1) n_ge[r] += __shfl_xor(n_ge[r], o);
   __syncthreads();
   if ((threadIdx.x & 63) == 0)
 #pragma unroll
-    for (int r = 0; r < kCalCand; ++r)
+    for (int r = 0; r < NC; ++r)
       if (n_ge[r]) atomicAdd(&h[r], n_ge[r]);
   __syncthreads();
-  if (threadIdx.x < kCalCand && h[threadIdx.x]) atomicAdd(&ge[threadIdx.x], (unsigned long long)h[threadIdx.x]);
+  if (threadIdx.x < NC && h[threadIdx.x]) atomicAdd(&ge[threadIdx.x], (unsigned long long)h[threadIdx.x]);
 }
 
 // Eq. 6 from part[tile][m][16] (sums of squares over column tile `tile`;

@@ -693,34 +693,43 @@ __global__ __launch_bounds__(kDenseThreads) void dense_down_kernel(DenseArgs a) 
 
 struct CalErrArgs {
   const uint16_t *ph, *pl;  // [n][d_ff] bf16 hi and lo terms of p
-  const uint8_t *cnt;       // [n][d_ff] candidates at or below |g|
+  const uint8_t *cnt;       // [n][d_ff] candidates at or below |g| (of the bucket pass)
+  int off;                  // the product's first candidate among those
   const uint16_t *WdT;      // W_down^T of the layer, [d][d_ff]
   float *part;              // [d / 128][n][16] column-tile sums of squares ([d / 64] with PACK 4)
   int n, d, d_ff;
 };
 
-constexpr int kCalRows = 16;  // calibration rows per workgroup (2 per wavefront)
+// calibration rows per workgroup: 16 (2 per wavefront), with four to an A tile
+// 32 (8 per wavefront: at 16 the W_down^T stream, one stage per half the
+// products, bound it: 1012 us, 0.44 of the matrix cores' time, for the last 4
+// of 19 candidates of 1024 rows of a Llama-3.1-8B layer; at 32 SATS_ERR4)
+constexpr int cal_rows(int pack) { return pack == 4 ? 32 : 16; }
 
 __device__ __forceinline__ int ct_pos(int r, int q) { return q ^ (r & 7); }
 
 // PACK = calibration rows per A tile: 1 (15 candidates and y), 2 (up to 7
 // candidates and y), or 4 (up to 4 candidates, no y row: ||y||^2 comes from
 // an earlier product).  With PACK 4 wavefront w takes calibration rows
-// 4 (w & 3) .. 4 (w & 3) + 3 over the 64 columns of half w >> 2 of the tile,
+// 8 (w & 3) .. 8 (w & 3) + 7 over the 64 columns of half w >> 2 of the tile,
 // and its sums of squares go to part tile 2 blockIdx.x + (w >> 2).
 template <int PACK>
 __global__ __launch_bounds__(kDenseThreads) void cal_err_kernel(CalErrArgs a) {
   static_assert(PACK == 1 || PACK == 2 || PACK == 4, "one, two or four calibration rows per A tile");
-  __shared__ __attribute__((aligned(1024))) uint8_t rg0[kDenseStageBytes], rg1[kDenseStageBytes],
-      rg2[kDenseStageBytes], rg3[kDenseStageBytes], rg4[kDenseStageBytes], rg5[kDenseStageBytes];
+  constexpr int ROWS = cal_rows(PACK);
+  constexpr int LO = 16384 + ROWS * 128, CN = LO + ROWS * 128;  // offsets of lo and c in a stage
+  constexpr int SB = PACK == 4 ? CN + ROWS * 64 : kDenseStageBytes, NL = PACK == 4 ? 4 : 3;  // its bytes; loads per wavefront
+  __shared__ __attribute__((aligned(1024))) uint8_t rg0[SB], rg1[SB], rg2[SB], rg3[SB], rg4[SB], rg5[SB],
+      spare[PACK == 4 ? 1024 : 16];
+  (void)spare;
   constexpr int CT = kDenseDownNT / 16 / (PACK == 4 ? 2 : 1);  // column tiles of 16 per wavefront
-  constexpr int NA = PACK == 4 ? 1 : 2 / PACK;                 // A tiles per wavefront
+  constexpr int NA = PACK == 4 ? 2 : 2 / PACK;                 // A tiles per wavefront
   constexpr int RPT = 16 / PACK;                               // A rows per calibration row
   constexpr bool Y = PACK != 4;                                // the last of them is y
   const int lane = threadIdx.x & 63, w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int ch = PACK == 4 ? w >> 2 : 0;  // column half (PACK 4)
   const int g = lane >> 4, l16 = lane & 15;
-  const int n0 = blockIdx.x * kDenseDownNT, m0 = blockIdx.y * kCalRows;
+  const int n0 = blockIdx.x * kDenseDownNT, m0 = blockIdx.y * ROWS;
   const int K = a.d_ff;
   const int S = K / kDenseKC;
   const __amdgpu_buffer_rsrc_t rsw = dense_rsrc(a.WdT, (uint32_t)((size_t)K * a.d * 2));
@@ -734,28 +743,30 @@ __global__ __launch_bounds__(kDenseThreads) void cal_err_kernel(CalErrArgs a) {
   const int r0 = s0 >> 3, r1 = s1 >> 3;
   const uint32_t ow0 = (uint32_t)(((size_t)(n0 + r0) * K + 8 * ct_pos(r0, s0 & 7)) * 2);
   const uint32_t ow1 = (uint32_t)(((size_t)(n0 + r1) * K + 8 * ct_pos(r1, s1 & 7)) * 2);
-  // hi and lo: wavefronts 0-1 and 2-3, 16 rows x 128 bytes each (lane: row, 16-byte chunk);
-  // c: wavefront 4, 16 rows x 64 bytes
-  const int ar = 8 * (w & 1) + (lane >> 3), aq = lane & 7;
+  // hi and lo: 8 rows x 128 bytes per load, c: 16 rows x 64 bytes.  16 rows:
+  // wavefronts 0-1 hi, 2-3 lo, 4 c (5-7 read zeros past the range into the
+  // stage's last 3 KB); 32 rows: 0-3 hi, 4-7 lo, then 0-1 c (the others zeros
+  // into a spare buffer).  Chosen without branches: a branch around the loads
+  // would cost the compiler its record of which LDS buffer each pending load
+  // writes, and with it waits on loads of later stages
+  constexpr int HW = ROWS / 8;  // wavefronts that load hi, and lo
+  const int ar = 8 * (w % HW) + (lane >> 3), aq = lane & 7;
   const bool arv = m0 + ar < a.n;
   const uint32_t oa = (uint32_t)(((size_t)(m0 + ar) * K + 8 * aq) * 2);
-  const int cr = lane >> 2, cq = lane & 3;
-  const bool crv = m0 + cr < a.n;
+  const int cr = (PACK == 4 ? 16 * (w & 1) : 0) + (lane >> 2), cq = lane & 3;
   const uint32_t oc = (uint32_t)((size_t)(m0 + cr) * K + 16 * cq);
   const uint32_t sk = kDenseKC * 2;
-  // the third load of every wavefront, chosen without branches (wavefronts
-  // 5-7 read zeros past the range into the stage's last 3 KB): a branch
-  // around the loads would cost the compiler its record of which LDS buffer
-  // each pending load writes, and with it waits on loads of later stages
-  const __amdgpu_buffer_rsrc_t r3 = w < 2 ? rsh : (w < 4 ? rsl : rsc);
-  const int d3 = w < 4 ? 16384 + w * 1024 : 20480 + (w - 4) * 1024;
-  const bool v3 = w < 4 ? arv : (w == 4 && crv);
-  const uint32_t o3 = w < 4 ? oa : oc, st3 = w < 4 ? sk : (uint32_t)kDenseKC;
-  // A row of this lane: calibration row 2 w + t (tile t; PACK 4: 4 (w & 3) +
-  // l16 / 4), candidate lim; with a y row the last row of a calibration row
-  // is y (lim 15: every neuron)
+  const bool c4 = PACK != 4 && w >= 4;  // the third load is of c
+  const bool crv = m0 + cr < a.n && (PACK == 4 ? w < 2 : w == 4);
+  const __amdgpu_buffer_rsrc_t r3 = c4 ? rsc : (w < HW ? rsh : rsl);
+  const int d3 = PACK == 4 ? 16384 + w * 1024 : w < 4 ? 16384 + w * 1024 : CN + (w - 4) * 1024;
+  const bool v3 = c4 ? crv : arv;
+  const uint32_t o3 = c4 ? oc : oa, st3 = c4 ? (uint32_t)kDenseKC : sk;
+  // A row of this lane: calibration row 2 w + t (tile t; PACK 4: 8 (w & 3) +
+  // 4 t + l16 / 4), removed up to candidate lim; with a y row the last row of a
+  // calibration row is y (every neuron).  lim: the bytes 0x80 + candidate
   const int rr = l16 % RPT;
-  const uint32_t lim = (Y && rr == RPT - 1) ? 15u : (uint32_t)rr;
+  const uint32_t lim = 0x80808080u + 0x01010101u * ((Y && rr == RPT - 1) ? 127u : (uint32_t)(a.off + rr));
   f32x4v acc[NA][CT];
 #pragma unroll
   for (int t = 0; t < NA; ++t)
@@ -769,18 +780,22 @@ __global__ __launch_bounds__(kDenseThreads) void cal_err_kernel(CalErrArgs a) {
     const int k = 32 * j + 8 * g;
 #pragma unroll
     for (int t = 0; t < NA; ++t) {
-      const int row = PACK == 4 ? 4 * (w & 3) + l16 / RPT : 2 * w + (PACK == 1 ? t : l16 / RPT);
+      const int row = PACK == 4 ? 8 * (w & 3) + 4 * t + l16 / RPT : 2 * w + (PACK == 1 ? t : l16 / RPT);
       const u32x4 hv = *reinterpret_cast<const u32x4 *>(buf + 16384 + row * 128 + 2 * k);
-      const u32x4 lv = *reinterpret_cast<const u32x4 *>(buf + 18432 + row * 128 + 2 * k);
-      const uint2 cv = *reinterpret_cast<const uint2 *>(buf + 20480 + row * 64 + k);
+      const u32x4 lv = *reinterpret_cast<const u32x4 *>(buf + LO + row * 128 + 2 * k);
+      const uint2 cv = *reinterpret_cast<const uint2 *>(buf + CN + row * 64 + k);
+      // four counts at a time: bit 7 of byte i of d is c_i <= lim (no borrow
+      // crosses a byte: c and lim are below 128), and a byte permute spreads
+      // the signs of a pair of bytes over the pair's 16-bit halves
       u32x4 mh, ml;
 #pragma unroll
-      for (int q = 0; q < 4; ++q) {
-        const uint32_t cw = q < 2 ? cv.x : cv.y;
-        const uint32_t c0 = (cw >> (16 * (q & 1))) & 0xffu, c1 = (cw >> (16 * (q & 1) + 8)) & 0xffu;
-        const uint32_t keep = (c0 <= lim ? 0x0000ffffu : 0u) | (c1 <= lim ? 0xffff0000u : 0u);
-        mh[q] = hv[q] & keep;
-        ml[q] = lv[q] & keep;
+      for (int q = 0; q < 2; ++q) {
+        const uint32_t d = lim - (q ? cv.y : cv.x), e = d << 8;
+        const uint32_t k0 = __builtin_amdgcn_perm(d, e, 0x0a0a0808u), k1 = __builtin_amdgcn_perm(d, e, 0x0b0b0909u);
+        mh[2 * q] = hv[2 * q] & k0;
+        mh[2 * q + 1] = hv[2 * q + 1] & k1;
+        ml[2 * q] = lv[2 * q] & k0;
+        ml[2 * q + 1] = lv[2 * q + 1] & k1;
       }
       ah[t] = __builtin_bit_cast(bf16x8, mh);
       al[t] = __builtin_bit_cast(bf16x8, ml);
@@ -819,9 +834,11 @@ __global__ __launch_bounds__(kDenseThreads) void cal_err_kernel(CalErrArgs a) {
     dma16<0>(rsw, (BUF) + w * 2048, dense_off(v_, ow0 + ss_ * sk, 0));                       \
     dma16<0>(rsw, (BUF) + w * 2048 + 1024, dense_off(v_, ow1 + ss_ * sk, 1));                \
     dma16<0>(r3, (BUF) + d3, dense_off(v_ && v3, o3 + ss_ * st3, 2));                        \
+    if constexpr (PACK == 4)                                                                 \
+      dma16<0>(rsc, w < 2 ? (BUF) + CN + w * 1024 : spare, dense_off(v_ && crv, oc + ss_ * (uint32_t)kDenseKC, 3)); \
   }
-  // step s: wait until stage s + 1 has landed (the loads of s + 2 .. s + 4,
-  // nine, may be outstanding) and every wavefront is done with stage s - 1,
+  // step s: wait until stage s + 1 has landed (the loads of s + 2 .. s + 4
+  // may be outstanding) and every wavefront is done with stage s - 1,
   // whose buffer takes stage s + 5; then stage s, whose first-half operands
   // are already in registers, with its second-half operands built under the
   // first half's products and the first-half operands of stage s + 1 under
@@ -829,7 +846,7 @@ __global__ __launch_bounds__(kDenseThreads) void cal_err_kernel(CalErrArgs a) {
 #define SATS_CE_STEP(CUR, NXT, FREE, P)                                                      \
   {                                                                                          \
     const int s_ = s0_ + (P);                                                                \
-    dense_stage_barrier<9>();                                                                \
+    dense_stage_barrier<3 * NL>();                                                                \
     SATS_CE_ISSUE(FREE, s_ + 5);                                                             \
     if (s_ < S) {                                                                            \
       load_ops((CUR), 1, ah1, al1, bq1);                                                     \
@@ -845,7 +862,7 @@ __global__ __launch_bounds__(kDenseThreads) void cal_err_kernel(CalErrArgs a) {
   SATS_CE_ISSUE(rg2, 2);
   SATS_CE_ISSUE(rg3, 3);
   SATS_CE_ISSUE(rg4, 4);
-  dense_stage_barrier<12>();  // stage 0 has landed
+  dense_stage_barrier<4 * NL>();  // stage 0 has landed
   load_ops(rg0, 0, ah0, al0, bq0);
   for (int s0_ = 0; s0_ < S; s0_ += 6) {
     SATS_CE_STEP(rg0, rg1, rg5, 0)
@@ -871,7 +888,7 @@ __global__ __launch_bounds__(kDenseThreads) void cal_err_kernel(CalErrArgs a) {
 #pragma unroll
       for (int o = 8; o >= 1; o >>= 1) v += __shfl_xor(v, o, 16);
       const int arow = 4 * g + r;
-      const int m = m0 + (PACK == 4 ? 4 * (w & 3) + arow / RPT : 2 * w + (PACK == 1 ? t : arow / RPT));
+      const int m = m0 + (PACK == 4 ? 8 * (w & 3) + 4 * t + arow / RPT : 2 * w + (PACK == 1 ? t : arow / RPT));
       const int cand = arow % RPT;
       const int slot = (Y && cand == RPT - 1) ? 15 : cand;
       const int tile = PACK == 4 ? 2 * blockIdx.x + ch : blockIdx.x;

@@ -1272,9 +1272,9 @@ struct CalBuffers {
   uint16_t *WdT = nullptr;         // [d][d_ff] W_down^T of the layer
   float *part = nullptr;           // [d / 64][n][16] (products with a y row use the first d / 128 tiles)
   uint32_t *hpart = nullptr, *hist = nullptr, *prefix = nullptr, *rank = nullptr;
-  float *tk = nullptr, *thr15 = nullptr;
-  unsigned long long *ge15 = nullptr;  // #{|g| >= t_r} of a product's candidates
-  double *errsum = nullptr;
+  float *tk = nullptr, *thr = nullptr;  // Eq. 3 statistics; the positive candidates, padded
+  unsigned long long *ge = nullptr;     // #{|g| >= t_r} of each
+  double *errsum = nullptr;             // sum over the rows of the Eq. 6 terms of each
   double *rsum = nullptr;          // [ceil(n / 64)][16] workgroup sums of the Eq. 6 terms
   float *ny2 = nullptr;            // [n] ||y||^2 of each row (from the first product)
   uint8_t *hp = nullptr;           // the rows of a gate/up pass in row blocks
@@ -1317,14 +1317,15 @@ int cal_release_all() {
     HIP_TRY(hipDeviceSynchronize());
     const CalBuffers &b = kv.second.b;
     for (void *q : {(void *)b.G, (void *)b.ph, (void *)b.pl, (void *)b.cnt, (void *)b.WdT, (void *)b.part,
-                    (void *)b.hpart, (void *)b.hist, (void *)b.prefix, (void *)b.rank, (void *)b.tk, (void *)b.thr15,
-                    (void *)b.ge15, (void *)b.errsum, (void *)b.hp, (void *)b.rsum, (void *)b.ny2})
+                    (void *)b.hpart, (void *)b.hist, (void *)b.prefix, (void *)b.rank, (void *)b.tk, (void *)b.thr,
+                    (void *)b.ge, (void *)b.errsum, (void *)b.hp, (void *)b.rsum, (void *)b.ny2})
       if (q) HIP_TRY(hipFree(q));
   }
   g_cal.clear();
   return SATS_OK;
 }
 
+constexpr int kCalBatch = 1024 / sats::kCalBucket * sats::kCalBucket;  // candidates between two synchronisations
 constexpr int kCalHistParts = 256;  // workgroups of a radix pass (each writes its own histogram)
 
 // Rank m = ceil(q N) of the Eq. 3 order statistic at level q (q taken to 1e-6).
@@ -1435,57 +1436,61 @@ int cal_curves(CalBuffers &cb, const uint16_t *Wd, int64_t n, int64_t d, int64_t
                        dim3(kCalThreads), 0, s, err_rows, (size_t)n, K, z);
     HIP_TRY(hipGetLastError());
   }
+  // the launches of up to kCalBatch candidates, then one copy back of their sums
   bool have_y = false;  // ||y||^2 of every row is in cb.ny2
-  for (int k0 = z; k0 < K; k0 += kCalCand) {
-    const int kc = std::min(kCalCand, K - k0);
-    const bool pack4 = have_y && kc <= 4;
-    float thr[kCalCand];
-    for (int r = 0; r < kCalCand; ++r) thr[r] = r < kc ? t[k0 + r] : INFINITY;
-    HIP_TRY(hipMemcpyAsync(cb.thr15, thr, sizeof thr, hipMemcpyHostToDevice, s));
-    HIP_TRY(hipMemsetAsync(cb.ge15, 0, kCalCand * sizeof(unsigned long long), s));
-    hipLaunchKernelGGL(cal_bucket_kernel, dim3(grid), dim3(kCalThreads), 0, s, cb.G, (size_t)N, cb.thr15, cb.cnt,
-                       cb.ge15);
-    if (err) {
-      CalErrArgs ce{};
-      ce.ph = cb.ph;
-      ce.pl = cb.pl;
-      ce.cnt = cb.cnt;
-      ce.WdT = cb.WdT;
-      ce.part = cb.part;
-      ce.n = (int)n;
-      ce.d = (int)d;
-      ce.d_ff = (int)d_ff;
-      {
-        TimedLaunch tl(SATS_K_CAL_ERR, s);
+  for (int c0 = z; c0 < K; c0 += kCalBatch) {
+    const int nc = std::min(kCalBatch, K - c0);
+    std::vector<float> thr(kCalBatch, INFINITY);  // (padding: nothing is kept there)
+    std::copy(t + c0, t + c0 + nc, thr.begin());
+    HIP_TRY(hipMemcpyAsync(cb.thr, thr.data(), (nc + kCalBucket - 1) / kCalBucket * kCalBucket * sizeof(float),
+                           hipMemcpyHostToDevice, s));
+    HIP_TRY(hipMemsetAsync(cb.ge, 0, kCalBatch * sizeof(unsigned long long), s));
+    for (int b0 = 0; b0 < nc; b0 += kCalBucket) {
+      const int bc = std::min(kCalBucket, nc - b0);
+      hipLaunchKernelGGL(bc <= kCalCand ? cal_bucket_kernel<kCalCand> : bc <= 20 ? cal_bucket_kernel<20>
+                                                                                 : cal_bucket_kernel<kCalBucket>,
+                         dim3(grid), dim3(kCalThreads), 0, s, cb.G, (size_t)N, cb.thr + b0, cb.cnt, cb.ge + b0);
+      HIP_TRY(hipGetLastError());
+      for (int off = 0; err && off < bc; off += kCalCand) {
+        const int kc = std::min(kCalCand, bc - off), k0 = c0 + b0 + off;
+        const bool pack4 = have_y && kc <= 4;
+        CalErrArgs ce{};
+        ce.ph = cb.ph;
+        ce.pl = cb.pl;
+        ce.cnt = cb.cnt;
+        ce.off = off;
+        ce.WdT = cb.WdT;
+        ce.part = cb.part;
+        ce.n = (int)n;
+        ce.d = (int)d;
+        ce.d_ff = (int)d_ff;
         // at most 4 candidates and ||y||^2 known: four calibration rows per
         // MFMA tile, no y row; at most 7: two per tile
-        if (pack4)
-          hipExtLaunchKernelGGL(cal_err_kernel<4>, dim3(d / kDenseDownNT, (n + kCalRows - 1) / kCalRows),
-                                dim3(kDenseThreads), 0, s, tl.start, tl.stop, 0, ce);
-        else if (kc <= 7)
-          hipExtLaunchKernelGGL(cal_err_kernel<2>, dim3(d / kDenseDownNT, (n + kCalRows - 1) / kCalRows),
-                                dim3(kDenseThreads), 0, s, tl.start, tl.stop, 0, ce);
-        else
-          hipExtLaunchKernelGGL(cal_err_kernel<1>, dim3(d / kDenseDownNT, (n + kCalRows - 1) / kCalRows),
-                                dim3(kDenseThreads), 0, s, tl.start, tl.stop, 0, ce);
+        const int pack = pack4 ? 4 : kc <= 7 ? 2 : 1;
+        {
+          TimedLaunch tl(SATS_K_CAL_ERR, s);
+          hipExtLaunchKernelGGL(pack == 4 ? cal_err_kernel<4> : pack == 2 ? cal_err_kernel<2> : cal_err_kernel<1>,
+                                dim3(d / kDenseDownNT, (n + cal_rows(pack) - 1) / cal_rows(pack)), dim3(kDenseThreads), 0, s,
+                                tl.start, tl.stop, 0, ce);
+        }
+        const int rblocks = (int)((n + 63) / 64);
+        hipLaunchKernelGGL(cal_reduce_kernel, dim3(rblocks), dim3(64 * kCalRedWaves), 0, s, cb.part,
+                           (int)(d / kDenseDownNT) * (pack4 ? 2 : 1), (int)n, kc,
+                           err_rows ? err_rows + k0 : (float *)nullptr, K, cb.rsum,
+                           pack4 ? (const float *)cb.ny2 : (const float *)nullptr, have_y ? (float *)nullptr : cb.ny2);
+        have_y = true;
+        hipLaunchKernelGGL(cal_reduce_sum_kernel, dim3(1), dim3(64), 0, s, cb.rsum, rblocks, kc, cb.errsum + b0 + off);
+        HIP_TRY(hipGetLastError());
       }
-      const int rblocks = (int)((n + 63) / 64);
-      hipLaunchKernelGGL(cal_reduce_kernel, dim3(rblocks), dim3(64 * kCalRedWaves), 0, s, cb.part,
-                         (int)(d / kDenseDownNT) * (pack4 ? 2 : 1), (int)n, kc,
-                         err_rows ? err_rows + k0 : (float *)nullptr, K, cb.rsum,
-                         pack4 ? (const float *)cb.ny2 : (const float *)nullptr, have_y ? (float *)nullptr : cb.ny2);
-      have_y = true;
-      hipLaunchKernelGGL(cal_reduce_sum_kernel, dim3(1), dim3(64), 0, s, cb.rsum, rblocks, kc, cb.errsum);
     }
-    HIP_TRY(hipGetLastError());
-    double es[kCalCand];
-    unsigned long long ge[kCalCand];
-    if (err) HIP_TRY(hipMemcpyAsync(es, cb.errsum, kc * sizeof(double), hipMemcpyDeviceToHost, s));
-    HIP_TRY(hipMemcpyAsync(ge, cb.ge15, kc * sizeof(unsigned long long), hipMemcpyDeviceToHost, s));
+    std::vector<double> es(nc);
+    std::vector<unsigned long long> ge(nc);
+    if (err) HIP_TRY(hipMemcpyAsync(es.data(), cb.errsum, nc * sizeof(double), hipMemcpyDeviceToHost, s));
+    HIP_TRY(hipMemcpyAsync(ge.data(), cb.ge, nc * sizeof(unsigned long long), hipMemcpyDeviceToHost, s));
     HIP_TRY(hipStreamSynchronize(s));
-    for (int r = 0; r < kc; ++r) {
-      if (err) err[k0 + r] = es[r] / (double)n;
-      sp[k0 + r] = (double)(N - ge[r]) / (double)N;  // #{|g| < t_r} / N
+    for (int r = 0; r < nc; ++r) {
+      if (err) err[c0 + r] = es[r] / (double)n;
+      sp[c0 + r] = (double)(N - ge[r]) / (double)N;  // #{|g| < t_r} / N
     }
   }
   return SATS_OK;
@@ -1507,8 +1512,8 @@ int cal_buffers(CalBuffers &cb, int64_t n, int64_t d, int64_t d_ff) {
       (rc = cal_alloc(&b.hpart, &k[6], (size_t)kCalHistParts * sats::kCalHistLds)) ||
       (rc = cal_alloc(&b.hist, &k[7], sats::kCalHistLds)) || (rc = cal_alloc(&b.prefix, &k[8], sats::kCalMaxLevels)) ||
       (rc = cal_alloc(&b.rank, &k[9], sats::kCalMaxLevels)) || (rc = cal_alloc(&b.tk, &k[10], sats::kCalMaxLevels)) ||
-      (rc = cal_alloc(&b.thr15, &k[11], sats::kCalCand)) || (rc = cal_alloc(&b.ge15, &k[12], sats::kCalCand)) ||
-      (rc = cal_alloc(&b.errsum, &k[13], sats::kCalCand)) ||
+      (rc = cal_alloc(&b.thr, &k[11], kCalBatch)) || (rc = cal_alloc(&b.ge, &k[12], kCalBatch)) ||
+      (rc = cal_alloc(&b.errsum, &k[13], kCalBatch)) ||
       (rc = cal_alloc(&b.hp, &k[14], (size_t)pf_block_bytes(std::min<int64_t>(n, kPfMaxPass), d, 2))) ||
       (rc = cal_alloc(&b.rsum, &k[15], (size_t)((n + 63) / 64) * 16)) || (rc = cal_alloc(&b.ny2, &k[16], (size_t)n)))
     return rc;
