@@ -231,7 +231,7 @@ __global__ __launch_bounds__(kCalThreads) void cal_transpose_kernel(const uint16
 // removes a neuron at candidate r when c <= r), and ge[r] = #{|g| >= t_r},
 // the values kept at t_r, over the launch; one pass serves two products (NC
 // 15, 20 or 30: the 19 positive candidates of the coarse grid took 2 x 38 us
-// in passes of 15, SATS_BUCKET in one of 20) (integer counts: exact in any
+// in passes of 15, 51 in one of 20) (integer counts: exact in any
 // order; ge must be zero on entry).  A thread reads four values per 16-byte
 // load and has kCalLoads loads in flight; workgroup 0 takes the N % 4 tail.
 template <int NC>

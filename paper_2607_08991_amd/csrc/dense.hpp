@@ -700,34 +700,35 @@ struct CalErrArgs {
   int n, d, d_ff;
 };
 
-// calibration rows per workgroup: 16 (2 per wavefront), with four to an A tile
-// 32 (8 per wavefront: at 16 the W_down^T stream, one stage per half the
-// products, bound it: 1012 us, 0.44 of the matrix cores' time, for the last 4
-// of 19 candidates of 1024 rows of a Llama-3.1-8B layer; at 32 SATS_ERR4)
-constexpr int cal_rows(int pack) { return pack == 4 ? 32 : 16; }
-
 __device__ __forceinline__ int ct_pos(int r, int q) { return q ^ (r & 7); }
 
 // PACK = calibration rows per A tile: 1 (15 candidates and y), 2 (up to 7
 // candidates and y), or 4 (up to 4 candidates, no y row: ||y||^2 comes from
-// an earlier product).  With PACK 4 wavefront w takes calibration rows
-// 8 (w & 3) .. 8 (w & 3) + 7 over the 64 columns of half w >> 2 of the tile,
-// and its sums of squares go to part tile 2 blockIdx.x + (w >> 2).
-template <int PACK>
+// an earlier product).  ROWS = calibration rows per workgroup: 16, or with
+// PACK 4, whose tiles hold a quarter of the products per operand, 64
+// (wavefront w rows 8 w .. + 7 over all 128 columns) or 32 (rows 8 (w & 3) ..
+// + 7 over the 64 columns of half w >> 2, sums of squares to part tile
+// 2 blockIdx.x + (w >> 2)).  At 32 the operand reads bound it (LDS: 1360
+// cycles per 1024 of products a stage); 64 needs the rows to fill the chip.
+// The last 4 of 19 candidates of 1024 rows of a Llama-3.1-8B layer: 832 us at
+// 32, 676 at 64.
+template <int PACK, int ROWS>
 __global__ __launch_bounds__(kDenseThreads) void cal_err_kernel(CalErrArgs a) {
-  static_assert(PACK == 1 || PACK == 2 || PACK == 4, "one, two or four calibration rows per A tile");
-  constexpr int ROWS = cal_rows(PACK);
+  static_assert((PACK != 4 && ROWS == 16) || (PACK == 4 && (ROWS == 32 || ROWS == 64)), "rows per A tile and workgroup");
+  constexpr bool HALVES = PACK == 4 && ROWS == 32;  // a wavefront takes half of the columns
   constexpr int LO = 16384 + ROWS * 128, CN = LO + ROWS * 128;  // offsets of lo and c in a stage
-  constexpr int SB = PACK == 4 ? CN + ROWS * 64 : kDenseStageBytes, NL = PACK == 4 ? 4 : 3;  // its bytes; loads per wavefront
-  __shared__ __attribute__((aligned(1024))) uint8_t rg0[SB], rg1[SB], rg2[SB], rg3[SB], rg4[SB], rg5[SB],
-      spare[PACK == 4 ? 1024 : 16];
+  constexpr int SB = PACK == 4 ? CN + ROWS * 64 : kDenseStageBytes;  // its bytes
+  constexpr int NL = PACK != 4 ? 3 : ROWS == 32 ? 4 : 5, R = ROWS == 64 ? 4 : 6;     // loads per wavefront; ring stages
+  __shared__ __attribute__((aligned(1024))) uint8_t rg0[SB], rg1[SB], rg2[SB], rg3[SB],
+      rg4[R > 4 ? SB : 16], rg5[R > 4 ? SB : 16], spare[PACK == 4 ? 1024 : 16];
   (void)spare;
-  constexpr int CT = kDenseDownNT / 16 / (PACK == 4 ? 2 : 1);  // column tiles of 16 per wavefront
+  constexpr int CT = kDenseDownNT / 16 / (HALVES ? 2 : 1);  // column tiles of 16 per wavefront
   constexpr int NA = PACK == 4 ? 2 : 2 / PACK;                 // A tiles per wavefront
   constexpr int RPT = 16 / PACK;                               // A rows per calibration row
   constexpr bool Y = PACK != 4;                                // the last of them is y
   const int lane = threadIdx.x & 63, w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-  const int ch = PACK == 4 ? w >> 2 : 0;  // column half (PACK 4)
+  const int ch = HALVES ? w >> 2 : 0;  // column half
+  const int wrow = PACK == 4 ? 8 * (HALVES ? w & 3 : w) : 2 * w;  // the wavefront's first row
   const int g = lane >> 4, l16 = lane & 15;
   const int n0 = blockIdx.x * kDenseDownNT, m0 = blockIdx.y * ROWS;
   const int K = a.d_ff;
@@ -745,25 +746,26 @@ __global__ __launch_bounds__(kDenseThreads) void cal_err_kernel(CalErrArgs a) {
   const uint32_t ow1 = (uint32_t)(((size_t)(n0 + r1) * K + 8 * ct_pos(r1, s1 & 7)) * 2);
   // hi and lo: 8 rows x 128 bytes per load, c: 16 rows x 64 bytes.  16 rows:
   // wavefronts 0-1 hi, 2-3 lo, 4 c (5-7 read zeros past the range into the
-  // stage's last 3 KB); 32 rows: 0-3 hi, 4-7 lo, then 0-1 c (the others zeros
-  // into a spare buffer).  Chosen without branches: a branch around the loads
-  // would cost the compiler its record of which LDS buffer each pending load
-  // writes, and with it waits on loads of later stages
-  constexpr int HW = ROWS / 8;  // wavefronts that load hi, and lo
+  // stage's last 3 KB); 32 rows: 0-3 hi, 4-7 lo, then 0-1 c; 64 rows: all hi,
+  // all lo, then 0-3 c (the others zeros into a spare buffer).  Chosen without
+  // branches: a branch around the loads would cost the compiler its record of
+  // which LDS buffer each pending load writes, and with it waits on loads of
+  // later stages
+  constexpr int HW = ROWS / 8, CW = ROWS / 16;  // loads of hi, and of lo; of c
   const int ar = 8 * (w % HW) + (lane >> 3), aq = lane & 7;
   const bool arv = m0 + ar < a.n;
   const uint32_t oa = (uint32_t)(((size_t)(m0 + ar) * K + 8 * aq) * 2);
-  const int cr = (PACK == 4 ? 16 * (w & 1) : 0) + (lane >> 2), cq = lane & 3;
+  const int cr = (PACK == 4 ? 16 * (w % CW) : 0) + (lane >> 2), cq = lane & 3;
   const uint32_t oc = (uint32_t)((size_t)(m0 + cr) * K + 16 * cq);
   const uint32_t sk = kDenseKC * 2;
   const bool c4 = PACK != 4 && w >= 4;  // the third load is of c
-  const bool crv = m0 + cr < a.n && (PACK == 4 ? w < 2 : w == 4);
+  const bool crv = m0 + cr < a.n && (PACK == 4 ? w < CW : w == 4);
   const __amdgpu_buffer_rsrc_t r3 = c4 ? rsc : (w < HW ? rsh : rsl);
-  const int d3 = PACK == 4 ? 16384 + w * 1024 : w < 4 ? 16384 + w * 1024 : CN + (w - 4) * 1024;
+  const int d3 = PACK == 4 || w < 4 ? 16384 + w * 1024 : CN + (w - 4) * 1024;
   const bool v3 = c4 ? crv : arv;
   const uint32_t o3 = c4 ? oc : oa, st3 = c4 ? (uint32_t)kDenseKC : sk;
-  // A row of this lane: calibration row 2 w + t (tile t; PACK 4: 8 (w & 3) +
-  // 4 t + l16 / 4), removed up to candidate lim; with a y row the last row of a
+  // A row of this lane: calibration row wrow + t (tile t; PACK 4: + 4 t +
+  // l16 / 4), removed up to candidate lim; with a y row the last row of a
   // calibration row is y (every neuron).  lim: the bytes 0x80 + candidate
   const int rr = l16 % RPT;
   const uint32_t lim = 0x80808080u + 0x01010101u * ((Y && rr == RPT - 1) ? 127u : (uint32_t)(a.off + rr));
@@ -780,7 +782,7 @@ __global__ __launch_bounds__(kDenseThreads) void cal_err_kernel(CalErrArgs a) {
     const int k = 32 * j + 8 * g;
 #pragma unroll
     for (int t = 0; t < NA; ++t) {
-      const int row = PACK == 4 ? 8 * (w & 3) + 4 * t + l16 / RPT : 2 * w + (PACK == 1 ? t : l16 / RPT);
+      const int row = wrow + (PACK == 4 ? 4 * t + l16 / RPT : PACK == 1 ? t : l16 / RPT);
       const u32x4 hv = *reinterpret_cast<const u32x4 *>(buf + 16384 + row * 128 + 2 * k);
       const u32x4 lv = *reinterpret_cast<const u32x4 *>(buf + LO + row * 128 + 2 * k);
       const uint2 cv = *reinterpret_cast<const uint2 *>(buf + CN + row * 64 + k);
@@ -834,20 +836,22 @@ __global__ __launch_bounds__(kDenseThreads) void cal_err_kernel(CalErrArgs a) {
     dma16<0>(rsw, (BUF) + w * 2048, dense_off(v_, ow0 + ss_ * sk, 0));                       \
     dma16<0>(rsw, (BUF) + w * 2048 + 1024, dense_off(v_, ow1 + ss_ * sk, 1));                \
     dma16<0>(r3, (BUF) + d3, dense_off(v_ && v3, o3 + ss_ * st3, 2));                        \
+    if constexpr (ROWS == 64)                                                                \
+      dma16<0>(rsl, (BUF) + LO + w * 1024, dense_off(v_ && arv, oa + ss_ * sk, 4));          \
     if constexpr (PACK == 4)                                                                 \
-      dma16<0>(rsc, w < 2 ? (BUF) + CN + w * 1024 : spare, dense_off(v_ && crv, oc + ss_ * (uint32_t)kDenseKC, 3)); \
+      dma16<0>(rsc, w < CW ? (BUF) + CN + w * 1024 : spare, dense_off(v_ && crv, oc + ss_ * (uint32_t)kDenseKC, 3)); \
   }
-  // step s: wait until stage s + 1 has landed (the loads of s + 2 .. s + 4
+  // step s: wait until stage s + 1 has landed (the loads of s + 2 .. s + R - 2
   // may be outstanding) and every wavefront is done with stage s - 1,
-  // whose buffer takes stage s + 5; then stage s, whose first-half operands
+  // whose buffer takes stage s + R - 1; then stage s, whose first-half operands
   // are already in registers, with its second-half operands built under the
   // first half's products and the first-half operands of stage s + 1 under
   // the second half's (read but not used after the last stage)
 #define SATS_CE_STEP(CUR, NXT, FREE, P)                                                      \
   {                                                                                          \
     const int s_ = s0_ + (P);                                                                \
-    dense_stage_barrier<3 * NL>();                                                                \
-    SATS_CE_ISSUE(FREE, s_ + 5);                                                             \
+    dense_stage_barrier<(R - 3) * NL>();                                                                \
+    SATS_CE_ISSUE(FREE, s_ + R - 1);                                                             \
     if (s_ < S) {                                                                            \
       load_ops((CUR), 1, ah1, al1, bq1);                                                     \
       mma(ah0, al0, bq0);                                                                    \
@@ -860,17 +864,26 @@ __global__ __launch_bounds__(kDenseThreads) void cal_err_kernel(CalErrArgs a) {
   SATS_CE_ISSUE(rg0, 0);
   SATS_CE_ISSUE(rg1, 1);
   SATS_CE_ISSUE(rg2, 2);
-  SATS_CE_ISSUE(rg3, 3);
-  SATS_CE_ISSUE(rg4, 4);
-  dense_stage_barrier<4 * NL>();  // stage 0 has landed
+  if constexpr (R > 4) {
+    SATS_CE_ISSUE(rg3, 3);
+    SATS_CE_ISSUE(rg4, 4);
+  }
+  dense_stage_barrier<(R - 2) * NL>();  // stage 0 has landed
   load_ops(rg0, 0, ah0, al0, bq0);
-  for (int s0_ = 0; s0_ < S; s0_ += 6) {
-    SATS_CE_STEP(rg0, rg1, rg5, 0)
-    SATS_CE_STEP(rg1, rg2, rg0, 1)
-    SATS_CE_STEP(rg2, rg3, rg1, 2)
-    SATS_CE_STEP(rg3, rg4, rg2, 3)
-    SATS_CE_STEP(rg4, rg5, rg3, 4)
-    SATS_CE_STEP(rg5, rg0, rg4, 5)
+  for (int s0_ = 0; s0_ < S; s0_ += R) {
+    if constexpr (R == 4) {
+      SATS_CE_STEP(rg0, rg1, rg3, 0)
+      SATS_CE_STEP(rg1, rg2, rg0, 1)
+      SATS_CE_STEP(rg2, rg3, rg1, 2)
+      SATS_CE_STEP(rg3, rg0, rg2, 3)
+    } else {
+      SATS_CE_STEP(rg0, rg1, rg5, 0)
+      SATS_CE_STEP(rg1, rg2, rg0, 1)
+      SATS_CE_STEP(rg2, rg3, rg1, 2)
+      SATS_CE_STEP(rg3, rg4, rg2, 3)
+      SATS_CE_STEP(rg4, rg5, rg3, 4)
+      SATS_CE_STEP(rg5, rg0, rg4, 5)
+    }
   }
   __builtin_amdgcn_s_waitcnt(0);  // the zero-filling loads past the range land too
 #undef SATS_CE_STEP
@@ -888,10 +901,10 @@ __global__ __launch_bounds__(kDenseThreads) void cal_err_kernel(CalErrArgs a) {
 #pragma unroll
       for (int o = 8; o >= 1; o >>= 1) v += __shfl_xor(v, o, 16);
       const int arow = 4 * g + r;
-      const int m = m0 + (PACK == 4 ? 8 * (w & 3) + 4 * t + arow / RPT : 2 * w + (PACK == 1 ? t : arow / RPT));
+      const int m = m0 + wrow + (PACK == 4 ? 4 * t + arow / RPT : PACK == 1 ? t : arow / RPT);
       const int cand = arow % RPT;
       const int slot = (Y && cand == RPT - 1) ? 15 : cand;
-      const int tile = PACK == 4 ? 2 * blockIdx.x + ch : blockIdx.x;
+      const int tile = HALVES ? 2 * blockIdx.x + ch : blockIdx.x;
       if (l16 == 0 && m < a.n) a.part[((size_t)tile * a.n + m) * 16 + slot] = v;
     }
 }

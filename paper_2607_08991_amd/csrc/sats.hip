@@ -1465,17 +1465,22 @@ int cal_curves(CalBuffers &cb, const uint16_t *Wd, int64_t n, int64_t d, int64_t
         ce.d = (int)d;
         ce.d_ff = (int)d_ff;
         // at most 4 candidates and ||y||^2 known: four calibration rows per
-        // MFMA tile, no y row; at most 7: two per tile
-        const int pack = pack4 ? 4 : kc <= 7 ? 2 : 1;
+        // MFMA tile, no y row, in workgroups of 64 rows where those fill the
+        // chip, else of 32; at most 7: two per tile
+        const int64_t ctiles = d / kDenseDownNT;
+        const bool r64 = pack4 && (n + 63) / 64 * ctiles >= std::max(1, device_cus());
+        const int rows = !pack4 ? 16 : r64 ? 64 : 32;
         {
           TimedLaunch tl(SATS_K_CAL_ERR, s);
-          hipExtLaunchKernelGGL(pack == 4 ? cal_err_kernel<4> : pack == 2 ? cal_err_kernel<2> : cal_err_kernel<1>,
-                                dim3(d / kDenseDownNT, (n + cal_rows(pack) - 1) / cal_rows(pack)), dim3(kDenseThreads), 0, s,
-                                tl.start, tl.stop, 0, ce);
+          hipExtLaunchKernelGGL(r64       ? cal_err_kernel<4, 64>
+                                : pack4   ? cal_err_kernel<4, 32>
+                                : kc <= 7 ? cal_err_kernel<2, 16>
+                                          : cal_err_kernel<1, 16>,
+                                dim3(ctiles, (n + rows - 1) / rows), dim3(kDenseThreads), 0, s, tl.start, tl.stop, 0, ce);
         }
         const int rblocks = (int)((n + 63) / 64);
         hipLaunchKernelGGL(cal_reduce_kernel, dim3(rblocks), dim3(64 * kCalRedWaves), 0, s, cb.part,
-                           (int)(d / kDenseDownNT) * (pack4 ? 2 : 1), (int)n, kc,
+                           (int)ctiles * (pack4 && !r64 ? 2 : 1), (int)n, kc,
                            err_rows ? err_rows + k0 : (float *)nullptr, K, cb.rsum,
                            pack4 ? (const float *)cb.ny2 : (const float *)nullptr, have_y ? (float *)nullptr : cb.ny2);
         have_y = true;

@@ -216,3 +216,28 @@ def test_many_levels_select_against_its_own_counts():
             pre = np.unique(bits[c0:c0 + 64] >> hs)
             shared += len(pre) - len(np.unique(pre & 0xFFF))
     assert shared > 0
+
+
+@pytest.mark.parametrize("n", [512, 560])
+def test_four_candidate_product_of_64_row_workgroups(n):
+    """The last four of nineteen positive candidates (four rows per MFMA tile,
+    workgroups of 64 rows once those fill the chip, ||y||^2 kept from the first
+    product) against the same candidates on their own (two rows per tile, y in
+    the product): the products and their order of k are the same, so only the
+    column tiles' sums of squares are added in another order (float32, 128 and
+    64 columns: relative 1e-6 of a norm)."""
+    import torch
+    import paper_2607_08991_amd as sats
+    d, dff = 4096, 128
+    g = torch.Generator(device="cuda").manual_seed(5)
+    x = torch.randn((n, d), generator=g, device="cuda").to(torch.bfloat16)
+    w = [(torch.randn((dff, d), generator=g, device="cuda") * 0.02).to(torch.bfloat16) for _ in range(3)]
+    levels = [round(i / 20, 10) for i in range(20)]
+    rows = torch.empty((n, 20), dtype=torch.float32, device="cuda")
+    t, err, sp = sats.sats_calibration_curves(x, *w, n, d, dff, levels, err_rows=rows)
+    tail = torch.empty((n, 4), dtype=torch.float32, device="cuda")
+    t4, err4, sp4 = sats.sats_calibration_curves(x, *w, n, d, dff, levels[16:], err_rows=tail)
+    np.testing.assert_array_equal(t[16:], t4)
+    np.testing.assert_array_equal(sp[16:], sp4)
+    np.testing.assert_allclose(rows[:, 16:].cpu().numpy(), tail.cpu().numpy(), rtol=4e-6)
+    np.testing.assert_allclose(err[16:], err4, rtol=1e-6)
