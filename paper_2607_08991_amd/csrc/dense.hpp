@@ -943,8 +943,8 @@ struct GlueArgs {
   float lscale;
 };
 
-// one workgroup per dense token (blockIdx.x); thread t owns columns
-// 4 t .. 4 t + 3 and issues its loads of every partial at once
+// one workgroup per dense token (blockIdx.x), of as many wavefronts as the row
+// needs (with adapters all 16); thread t owns columns 4 t .. 4 t + 3 and issues its loads of every partial at once
 constexpr int kGlueThreads = 1024;
 template <typename T> __global__ __launch_bounds__(kGlueThreads) void dense_glue_kernel(GlueArgs a) {
   if (a.ctl && !a.ctl[1]) return;
@@ -1032,7 +1032,7 @@ template <typename T> __global__ __launch_bounds__(kGlueThreads) void dense_glue
   if (lane == 0) ssw[wv] = sq;
   __syncthreads();
   float tot = 0.0f;
-  for (int i = 0; i < kGlueThreads / 64; ++i) tot += ssw[i];
+  for (int i = 0; i < (int)blockDim.x / 64; ++i) tot += ssw[i];
   const float scale = sqrtf(tot / (float)a.d + kGlueEps);
   if (on) {
     struct alignas(4 * sizeof(T)) Quad {

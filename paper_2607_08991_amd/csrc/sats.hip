@@ -110,6 +110,12 @@ int round_pow2_down(int v) {
   return p;
 }
 
+// Threads of a row's second stage: four columns each, or the most where
+// adapters are added (16 groups of rank threads sum z).
+int glue_threads(int64_t d, bool lora) {
+  return lora ? sats::kGlueThreads : (int)std::min<int64_t>(sats::kGlueThreads, (d / 4 + 63) / 64 * 64);
+}
+
 // Execution options of the calling thread (sats_set_options).
 thread_local sats_options g_opt{};
 
@@ -328,8 +334,8 @@ PfPlan pf_plan(int64_t np, int64_t d, int64_t d_ff, int esz, bool lora = false) 
     return p;
   }
   double best = 1e300;
-  for (const auto &[bm, nt] : {std::pair<int, int>{256, 128}, {256, 96}, {256, 64}, {128, 64}}) {
-    if ((split || lora) && nt != 64) continue;  // (registers)
+  for (const auto &[bm, nt] : {std::pair<int, int>{256, 128}, {256, 96}, {256, 64}, {128, 64}, {128, 32}}) {
+    if ((split || lora) && nt > 64) continue;  // (registers)
     const double c = (double)cdiv(cdiv(np, bm) * cdiv(d_ff, nt), cus) *
                      (double)(cdiv(d, sats::kPfKC) + 16) * pf_step_cycles(bm, 2 * nt, 4, bm == 256 ? nt / 16 : nt / 32);
     if (c < best) best = c, p.bm = bm, p.nt = nt;
@@ -416,7 +422,7 @@ bool pf_ok(int esz, bool aligned, int64_t n, int64_t d, int64_t d_ff) {
 typedef void (*PfKernel)(sats::PfArgs);
 template <int MODE> PfKernel pf_gateup_fn(const PfPlan &p) {
   using namespace sats;
-  if (p.bm == 128) return pf_gateup_kernel<128, 64, MODE>;
+  if (p.bm == 128) return p.nt == 64 ? pf_gateup_kernel<128, 64, MODE> : pf_gateup_kernel<128, 32, MODE>;
   if constexpr (MODE != PF_SPLIT && MODE != PF_LORA) {
     if (p.nt == 128) return pf_gateup_kernel<256, 128, MODE>;
     if (p.nt == 96) return pf_gateup_kernel<256, 96, MODE>;
@@ -722,7 +728,7 @@ template <typename T> int run_prefill(const Call &c, char *mem, unsigned *counte
     ga.out = l == c.L - 1 ? static_cast<T *>(c.out) + base * d : nullptr;
     ga.hnext = b.h;
     ga.layer_in = c.layer_in && l + 1 < c.L ? static_cast<T *>(c.layer_in) + ((l + 1) * c.n + base) * d : nullptr;
-    hipLaunchKernelGGL(dense_glue_kernel<T>, dim3(np), dim3(kGlueThreads), 0, c.stream, ga);
+    hipLaunchKernelGGL(dense_glue_kernel<T>, dim3(np), dim3(glue_threads(d, lora)), 0, c.stream, ga);
     HIP_TRY(hipGetLastError());
     if (lists) {
       CompactArgs ca{};
@@ -877,7 +883,7 @@ int run_pass(const Call &c, const Plan &p, const Buffers &b, unsigned *counters,
         ga.zrows = kDenseMaxTokens;
         ga.lscale = c.lscale;
       }
-      hipLaunchKernelGGL(dense_glue_kernel<uint16_t>, dim3(np), dim3(kGlueThreads), 0, c.stream, ga);
+      hipLaunchKernelGGL(dense_glue_kernel<uint16_t>, dim3(np), dim3(glue_threads(d, lora)), 0, c.stream, ga);
       HIP_TRY(hipGetLastError());
     }
     auto compact = [&]() -> int {
