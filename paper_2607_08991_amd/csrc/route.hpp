@@ -3,7 +3,7 @@
 //
 // Per-id sums of a corpus split, in two launches without global atomics:
 //   route_part_kernel<DAMAGE>
-//       a chunk of kRouteChunk occurrences per workgroup: the excess damage
+//       up to 8 chunks of kRouteChunk occurrences per workgroup: the excess damage
 //       d = max(0, l_sparse - l_base) (Eq. 11) of each, in float32, as an
 //       integer number of 2^-32 units (rounded half to even); the chunk's
 //       occurrences are gathered per id in an LDS hash table (open
@@ -66,72 +66,80 @@ struct RouteAccumArgs {
 };
 
 constexpr int kRouteSlots = 2 * kRouteChunk;
+constexpr int kRouteFill = kRouteSlots / 4;  // slots taken up to which a table takes another chunk
 static_assert(kRouteSlots == 1 << 13, "the slot hash takes the top 13 bits");
 
-// The chunk's occurrences [base, base + kRouteChunk) gathered per id into
-// the LDS table skey / scnt / ssum (every slot initialised here); ends with
-// a barrier.
+// The chunk's occurrences [base, base + kRouteChunk): their ids and d in
+// units of 2^-32 (id kRouteNoId: past n, or reported in err).
+constexpr int kRoutePer = kRouteChunk / kRouteThreads;  // occurrences per thread
 template <bool DAMAGE>
-__device__ __forceinline__ void route_chunk_table(const int32_t *ids, const float *lb, const float *ls, int64_t n,
-                                                  int vocab, unsigned *err, int64_t base, uint32_t *skey,
-                                                  uint32_t *scnt, unsigned long long *ssum) {
-  const int tid = threadIdx.x;
-  constexpr int PER = kRouteChunk / kRouteThreads, SPER = kRouteSlots / kRouteThreads;
-  uint32_t k[PER];
-  unsigned long long q[PER];
-  // the chunk's loads first, then the table's initialisation
+__device__ __forceinline__ void route_chunk_load(const int32_t *ids, const float *lb, const float *ls, int64_t n,
+                                                 int64_t base, int32_t (&x)[kRoutePer], float (&fs)[kRoutePer],
+                                                 float (&fb)[kRoutePer]) {
 #pragma unroll
-  for (int m = 0; m < PER; ++m) {
-    const int64_t i = base + tid + m * kRouteThreads;
-    k[m] = kRouteNoId;
-    q[m] = 0ull;
-    if (i < n) {
-      const int32_t x = ids[i];
-      if (x >= 0 && x < vocab) {
-        k[m] = (uint32_t)x;
-        if constexpr (DAMAGE) {
-          const float diff = ls[i] - lb[i];  // float32, as in Eq. 11
-          if (diff < 2147483648.0f) {         // also false for NaN
-            // d 2^32 is exact in float32 and rintf rounds half to even: an
-            // integer-valued float below 2^63, converted exactly
-            q[m] = (unsigned long long)rintf(fmaxf(diff, 0.0f) * 4294967296.0f);
-          } else {
-            k[m] = kRouteNoId;
-            __hip_atomic_store(err, 2u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-          }
-        }
-      } else {
-        __hip_atomic_store(err, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-      }
+  for (int m = 0; m < kRoutePer; ++m) {
+    const int64_t i = base + threadIdx.x + m * kRouteThreads;
+    const bool on = i < n;
+    x[m] = on ? ids[i] : -1;
+    fs[m] = DAMAGE && on ? ls[i] : 0.0f;
+    fb[m] = DAMAGE && on ? lb[i] : 0.0f;
+  }
+}
+
+// Adds them to the LDS table skey / scnt / ssum; returns how many of this
+// thread's ids were new to it.  `left`: occurrences from the chunk's first on.
+template <bool DAMAGE>
+__device__ __forceinline__ int route_chunk_insert(int vocab, unsigned *err, int64_t left, const int32_t (&x)[kRoutePer],
+                                                  const float (&fs)[kRoutePer], const float (&fb)[kRoutePer],
+                                                  uint32_t *skey, uint32_t *scnt, unsigned long long *ssum) {
+  int fresh = 0;
+#pragma unroll
+  for (int m = 0; m < kRoutePer; ++m) {
+    if ((int64_t)threadIdx.x + m * kRouteThreads >= left) continue;
+    if (x[m] < 0 || x[m] >= vocab) {
+      __hip_atomic_store(err, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+      continue;
     }
-  }
-#pragma unroll
-  for (int m = 0; m < SPER; ++m) {
-    const int sl = tid + m * kRouteThreads;
-    skey[sl] = kRouteNoId;
-    scnt[sl] = 0u;
-    if constexpr (DAMAGE) ssum[sl] = 0ull;
-  }
-  __syncthreads();
-#pragma unroll
-  for (int m = 0; m < PER; ++m) {
-    if (k[m] == kRouteNoId) continue;
-    uint32_t h = (k[m] * 2654435761u) >> (32 - 13);  // multiplicative hash into 2^13 slots
-    // at most kRouteChunk ids share kRouteSlots slots, so a free slot is met
-    // within kRouteSlots probes; the bound only guards that argument
+    const uint32_t k = (uint32_t)x[m];
+    unsigned long long q = 0ull;
+    if constexpr (DAMAGE) {
+      const float diff = fs[m] - fb[m];   // float32, as in Eq. 11
+      if (!(diff < 2147483648.0f)) {      // also for NaN
+        __hip_atomic_store(err, 2u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        continue;
+      }
+      // d 2^32 is exact in float32 and rintf rounds half to even: an
+      // integer-valued float below 2^63, converted exactly
+      q = (unsigned long long)rintf(fmaxf(diff, 0.0f) * 4294967296.0f);
+    }
+    uint32_t h = (k * 2654435761u) >> (32 - 13);  // multiplicative hash into 2^13 slots
+    // fewer than kRouteSlots ids share the slots (see the callers), so the id
+    // or a free slot is met within kRouteSlots probes; the bound only guards that
     int probe = 0;
     for (; probe < kRouteSlots; ++probe) {
-      const uint32_t prev = atomicCAS(&skey[h], kRouteNoId, k[m]);
-      if (prev == kRouteNoId || prev == k[m]) {
+      const uint32_t prev = atomicCAS(&skey[h], kRouteNoId, k);
+      if (prev == kRouteNoId || prev == k) {
+        fresh += prev == kRouteNoId;
         atomicAdd(&scnt[h], 1u);
-        if constexpr (DAMAGE) atomicAdd(&ssum[h], q[m]);
+        if constexpr (DAMAGE) atomicAdd(&ssum[h], q);
         break;
       }
       h = (h + 1) & (kRouteSlots - 1);
     }
     if (probe == kRouteSlots) __hip_atomic_store(err, 3u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
   }
-  __syncthreads();
+  return fresh;
+}
+
+template <bool DAMAGE>
+__device__ __forceinline__ void route_table_clear(uint32_t *skey, uint32_t *scnt, unsigned long long *ssum) {
+#pragma unroll
+  for (int m = 0; m < kRouteSlots / kRouteThreads; ++m) {
+    const int sl = threadIdx.x + m * kRouteThreads;
+    skey[sl] = kRouteNoId;
+    scnt[sl] = 0u;
+    if constexpr (DAMAGE) ssum[sl] = 0ull;
+  }
 }
 
 template <bool DAMAGE>
@@ -141,8 +149,14 @@ __global__ __launch_bounds__(kRouteThreads) void route_accum_kernel(RouteAccumAr
   __shared__ unsigned long long ssum[DAMAGE ? kRouteSlots : 1];
   constexpr int SPER = kRouteSlots / kRouteThreads;
   const int tid = threadIdx.x;
-  route_chunk_table<DAMAGE>(a.ids, a.lb, a.ls, a.n, a.vocab, a.err, (int64_t)blockIdx.x * kRouteChunk, skey, scnt,
-                            ssum);
+  int32_t x[kRoutePer];
+  float fs[kRoutePer], fb[kRoutePer];
+  const int64_t base = (int64_t)blockIdx.x * kRouteChunk;
+  route_chunk_load<DAMAGE>(a.ids, a.lb, a.ls, a.n, base, x, fs, fb);
+  route_table_clear<DAMAGE>(skey, scnt, ssum);
+  __syncthreads();
+  route_chunk_insert<DAMAGE>(a.vocab, a.err, a.n - base, x, fs, fb, skey, scnt, ssum);
+  __syncthreads();
   const size_t cp = (size_t)(blockIdx.x % kRouteCopies) * (size_t)a.vocab;
 #pragma unroll
   for (int m = 0; m < SPER; ++m) {
@@ -154,15 +168,22 @@ __global__ __launch_bounds__(kRouteThreads) void route_accum_kernel(RouteAccumAr
   }
 }
 
+// A workgroup gathers up to `per` chunks in a row in one table and writes it
+// out once more than a quarter of its slots is taken and at its end: the table's set-up, the scan of its ranges and the entries
+// are paid once for the chunks, not for each, and the chunk after is loaded
+// while one is added.  (2^22 Zipf occurrences of a 128256-id vocabulary, 4
+// chunks a workgroup: 36 us and 23 us for the merge of its entries; a chunk a
+// workgroup 43 and 26.)
 struct RoutePartArgs {
   const int32_t *ids;
   const float *lb, *ls;  // DAMAGE: per-occurrence losses of the base and sparse paths
   int64_t n;
   int vocab;
   int rbits, nr;         // 2^rbits ids a range, nr ranges (<= kRouteRanges)
-  int nchunks;
-  u32x4 *ent;            // [nchunks][kRouteChunk] (id, count, sum lo, sum hi), grouped by range
-  uint32_t *off;         // [nr + 1][nchunks] start of range r in chunk c's entries (row nr: their number)
+  int per;               // chunks per workgroup
+  u32x4 *ent;            // [workgroups][per kRouteChunk] (id, count, sum lo, sum hi): each table written, grouped by range
+  uint32_t *off;         // [nr + 1][workgroups per] start of range r in table f of workgroup b at b per + f
+  unsigned *tabs;        // [workgroups] tables written
   unsigned *err;
 };
 
@@ -173,51 +194,93 @@ __global__ __launch_bounds__(kRouteThreads) void route_part_kernel(RoutePartArgs
   __shared__ unsigned long long ssum[DAMAGE ? kRouteSlots : 1];
   __shared__ uint32_t hist[kRouteRanges];
   __shared__ uint32_t wtot[kRouteThreads / 64];
+  __shared__ uint32_t taken;  // slots in use
   static_assert(kRouteRanges == kRouteThreads, "one range per thread in the scan");
   constexpr int SPER = kRouteSlots / kRouteThreads;
   const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6;
-  const int c = blockIdx.x;
-  hist[tid] = 0u;
-  route_chunk_table<DAMAGE>(a.ids, a.lb, a.ls, a.n, a.vocab, a.err, (int64_t)c * kRouteChunk, skey, scnt, ssum);
+  const int64_t first = (int64_t)blockIdx.x * a.per * kRouteChunk;
+  const size_t nseg = (size_t)gridDim.x * a.per;
+  u32x4 *const ce = a.ent + first;
+  int32_t x[kRoutePer];
+  float fs[kRoutePer], fb[kRoutePer];
+  route_chunk_load<DAMAGE>(a.ids, a.lb, a.ls, a.n, first, x, fs, fb);
+  route_table_clear<DAMAGE>(skey, scnt, ssum);
+  if (tid == 0) taken = 0u;
+  uint32_t written = 0u;  // entries of the tables written
+  int tab = 0;
+  for (int j = 0; j < a.per; ++j) {
+    const int64_t base = first + (int64_t)j * kRouteChunk;
+    if (base >= a.n) break;
+    const bool last = j + 1 == a.per || base + kRouteChunk >= a.n;
+    int32_t nx[kRoutePer];
+    float ns[kRoutePer], nb[kRoutePer];
+    route_chunk_load<DAMAGE>(a.ids, a.lb, a.ls, last ? 0 : a.n, base + kRouteChunk, nx, ns, nb);
+    hist[tid] = 0u;
+    __syncthreads();
+    int fresh = route_chunk_insert<DAMAGE>(a.vocab, a.err, a.n - base, x, fs, fb, skey, scnt, ssum);
 #pragma unroll
-  for (int m = 0; m < SPER; ++m) {
-    const uint32_t key = skey[tid + m * kRouteThreads];
-    if (key != kRouteNoId) atomicAdd(&hist[key >> a.rbits], 1u);
-  }
-  __syncthreads();
-  // exclusive scan of the ranges' entry counts: within the wavefront, then
-  // the wavefronts' totals
-  const uint32_t hv = hist[tid];
-  uint32_t incl = hv;
+    for (int o = 32; o >= 1; o >>= 1) fresh += __shfl_xor(fresh, o, 64);
+    if (lane == 0 && fresh) atomicAdd(&taken, (uint32_t)fresh);
+    __syncthreads();
 #pragma unroll
-  for (int o = 1; o < 64; o <<= 1) {
-    const uint32_t t = __shfl_up(incl, o, 64);
-    if (lane >= o) incl += t;
-  }
-  if (lane == 63) wtot[wv] = incl;
-  __syncthreads();
-  uint32_t excl = incl - hv;
-  for (int q = 0; q < wv; ++q) excl += wtot[q];
-  if (tid < a.nr) a.off[(size_t)tid * a.nchunks + c] = excl;
-  if (tid == kRouteThreads - 1) a.off[(size_t)a.nr * a.nchunks + c] = excl + hv;  // ranges past nr are empty
-  hist[tid] = excl;  // the range's next free entry (every thread read its count above)
-  __syncthreads();
-  u32x4 *ce = a.ent + (size_t)c * kRouteChunk;
+    for (int m = 0; m < kRoutePer; ++m) x[m] = nx[m], fs[m] = ns[m], fb[m] = nb[m];
+    // another chunk goes into the table while at most a quarter of the slots is
+    // taken: they are then at most three quarters full, and probes stay short
+    // (with half, 2^22 occurrences without repeats took 1.8 ms, here 45 us)
+    if (!last && taken <= (uint32_t)kRouteFill) continue;
 #pragma unroll
-  for (int m = 0; m < SPER; ++m) {
-    const int sl = tid + m * kRouteThreads;
-    const uint32_t key = skey[sl];
-    if (key == kRouteNoId) continue;
-    const uint32_t pos = atomicAdd(&hist[key >> a.rbits], 1u);
-    const unsigned long long sm = DAMAGE ? ssum[sl] : 0ull;
-    ce[pos] = u32x4{key, scnt[sl], (uint32_t)sm, (uint32_t)(sm >> 32)};
+    for (int m = 0; m < SPER; ++m) {
+      const uint32_t key = skey[tid + m * kRouteThreads];
+      if (key != kRouteNoId) atomicAdd(&hist[key >> a.rbits], 1u);
+    }
+    __syncthreads();
+    // exclusive scan of the ranges' entry counts: within the wavefront, then
+    // the wavefronts' totals
+    const uint32_t hv = hist[tid];
+    uint32_t incl = hv;
+#pragma unroll
+    for (int o = 1; o < 64; o <<= 1) {
+      const uint32_t t = __shfl_up(incl, o, 64);
+      if (lane >= o) incl += t;
+    }
+    if (lane == 63) wtot[wv] = incl;
+    __syncthreads();
+    uint32_t excl = incl - hv, total = 0u;
+    for (int q = 0; q < kRouteThreads / 64; ++q) {
+      if (q < wv) excl += wtot[q];
+      total += wtot[q];
+    }
+    excl += written;
+    const size_t seg = (size_t)blockIdx.x * a.per + tab;
+    if (tid < a.nr) a.off[(size_t)tid * nseg + seg] = excl;
+    if (tid == kRouteThreads - 1) a.off[(size_t)a.nr * nseg + seg] = excl + hv;  // ranges past nr are empty
+    hist[tid] = excl;  // the range's next free entry (every thread read its count above)
+    __syncthreads();
+#pragma unroll
+    for (int m = 0; m < SPER; ++m) {
+      const int sl = tid + m * kRouteThreads;
+      const uint32_t key = skey[sl];
+      if (key == kRouteNoId) continue;
+      const uint32_t pos = atomicAdd(&hist[key >> a.rbits], 1u);
+      const unsigned long long sm = DAMAGE ? ssum[sl] : 0ull;
+      ce[pos] = u32x4{key, scnt[sl], (uint32_t)sm, (uint32_t)(sm >> 32)};
+    }
+    written += total;
+    ++tab;
+    if (last) break;
+    __syncthreads();  // every thread is done with hist
+    route_table_clear<DAMAGE>(skey, scnt, ssum);  // (a thread's own slots, which it has read)
+    if (tid == 0) taken = 0u;
   }
+  if (tid == 0) a.tabs[blockIdx.x] = (unsigned)tab;
 }
 
 struct RouteMergeArgs {
   const u32x4 *ent;
   const uint32_t *off;
-  int nchunks, rbits, nr, vocab, parts;
+  const unsigned *tabs;
+  int blocks, per;           // workgroups of the part launch, chunks of each
+  int rbits, nr, vocab, parts;
   unsigned *count;           // [parts][vocab]
   unsigned long long *sum;   // [parts][vocab] (DAMAGE)
 };
@@ -234,10 +297,16 @@ __global__ __launch_bounds__(kRouteThreads) void route_merge_kernel(RouteMergeAr
     if constexpr (DAMAGE) lsum[i] = 0ull;
   }
   __syncthreads();
-  const int c0 = (int)((int64_t)p * a.nchunks / a.parts), c1 = (int)((int64_t)(p + 1) * a.nchunks / a.parts);
-  for (int c = c0 + wv; c < c1; c += kRouteThreads / 64) {
-    const uint32_t b = a.off[(size_t)r * a.nchunks + c], e = a.off[(size_t)(r + 1) * a.nchunks + c];
-    const u32x4 *ce = a.ent + (size_t)c * kRouteChunk;
+  const int b0 = (int)((int64_t)p * a.blocks / a.parts), b1 = (int)((int64_t)(p + 1) * a.blocks / a.parts);
+  const size_t nseg = (size_t)a.blocks * a.per;
+  // a wavefront per table of the group's workgroups, first tables first
+  const int nb = b1 - b0;
+  for (int t = wv; t < nb * a.per; t += kRouteThreads / 64) {
+    const int wg = b0 + t % nb, f = t / nb;
+    if ((unsigned)f >= a.tabs[wg]) continue;
+    const size_t c = (size_t)wg * a.per + f;
+    const uint32_t b = a.off[(size_t)r * nseg + c], e = a.off[(size_t)(r + 1) * nseg + c];
+    const u32x4 *ce = a.ent + (size_t)wg * a.per * kRouteChunk;
     for (uint32_t j = b + lane; j < e; j += 64 * U) {
       u32x4 v[U];
 #pragma unroll

@@ -1779,12 +1779,16 @@ int route_build(const float *lb, const float *ls, const int32_t *ids, int64_t n,
   const int64_t nc = (n + kRouteChunk - 1) / kRouteChunk, nhc = (nh + kRouteChunk - 1) / kRouteChunk;
   if (nc > INT32_MAX || nhc > INT32_MAX) return fail(SATS_ERR_SHAPE, "too many occurrences");
   const int P = part ? kRouteParts : kRouteCopies;
-  const int64_t mc = std::max<int64_t>(nc, nhc);
+  // chunks per workgroup of the part launch: one workgroup per compute unit, at most 8
+  const int64_t cus = std::max(1, device_cus());
+  const int per[2] = {(int)std::clamp<int64_t>(nc / cus, 1, 8), (int)std::clamp<int64_t>(nhc / cus, 1, 8)};
+  const int64_t blocks[2] = {(nc + per[0] - 1) / per[0], (nhc + per[1] - 1) / per[1]};
+  const int64_t mc = std::max<int64_t>(blocks[0] * per[0], blocks[1] * per[1]);
   int rc = 0;
   size_t cap_sum = b.parts, cap_h = b.parts, cap_v = b.vocab, cap_v2 = b.vocab, cap_sel = kSelWords, cap_o = 2,
          cap_e = 1;
   if ((part && ((rc = route_grow(&b.pent, &b.ent, (size_t)mc * kRouteChunk)) ||
-                (rc = route_grow(&b.poff, &b.off, (size_t)(nr + 1) * mc)))) ||
+                (rc = route_grow(&b.poff, &b.off, (size_t)(nr + 2) * mc)))) ||
       (rc = route_grow(&b.cnt, &b.parts, (size_t)P * V)) || (rc = route_grow(&b.sum, &cap_sum, (size_t)P * V)) ||
       (rc = route_grow(&b.hcnt, &cap_h, (size_t)P * V)) || (rc = route_grow(&b.htot, &b.vocab, V)) ||
       (rc = route_grow(&b.score, &cap_v, V)))
@@ -1802,15 +1806,18 @@ int route_build(const float *lb, const float *ls, const int32_t *ids, int64_t n,
     // merge also runs for an empty split: zero totals)
     for (int split = 0; split < 2; ++split) {
       const bool dmg = split == 0;
-      const int64_t nn = dmg ? n : nh, ch = dmg ? nc : nhc;
+      const int64_t nn = dmg ? n : nh;
+      // the tables written by each workgroup, after the offsets
+      unsigned *tabs = b.poff + (size_t)(nr + 1) * blocks[split] * per[split];
       if (nn > 0) {
-        RoutePartArgs pa{dmg ? ids : hids, lb, ls, nn, (int)vocab, rbits, nr, (int)ch, b.pent, b.poff, b.err};
+        RoutePartArgs pa{dmg ? ids : hids, lb, ls, nn, (int)vocab, rbits, nr, per[split], b.pent, b.poff, tabs, b.err};
         TimedLaunch tl(dmg ? SATS_K_ROUTE_ACCUM : -1, s);
-        hipExtLaunchKernelGGL(dmg ? route_part_kernel<true> : route_part_kernel<false>, dim3((unsigned)ch),
+        hipExtLaunchKernelGGL(dmg ? route_part_kernel<true> : route_part_kernel<false>, dim3((unsigned)blocks[split]),
                               dim3(kRouteThreads), 0, s, tl.start, tl.stop, 0, pa);
         HIP_TRY(hipGetLastError());
       }
-      RouteMergeArgs ma{b.pent, b.poff, (int)ch, rbits, nr, (int)vocab, P, dmg ? b.cnt : b.hcnt, b.sum};
+      RouteMergeArgs ma{b.pent, b.poff, tabs, (int)blocks[split], per[split], rbits, nr, (int)vocab, P,
+                        dmg ? b.cnt : b.hcnt, b.sum};
       TimedLaunch tl(dmg ? SATS_K_ROUTE_MERGE : -1, s);
       hipExtLaunchKernelGGL(dmg ? route_merge_kernel<true> : route_merge_kernel<false>, dim3(nr, P),
                             dim3(kRouteThreads), 0, s, tl.start, tl.stop, 0, ma);

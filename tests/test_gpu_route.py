@@ -123,3 +123,29 @@ def test_route_table_wide_vocabularies(vocab):
         t_ref, r_ref = route.select_tau(s_ref, held, r_tar)
         assert (tau, r) == (t_ref, r_ref), (r_tar, tau, t_ref)
         np.testing.assert_array_equal(table, route.route_table(s_ref, t_ref))
+
+
+@pytest.mark.parametrize("pattern", ["few", "unique", "mixed", "runs"])
+def test_tables_of_several_chunks(pattern):
+    """Enough chunks that a workgroup gathers several in one table: ids that
+    all fit one table, ids without repeats (a table per chunk), both in turn,
+    and one id per chunk.  Scores are exact integer sums, so they equal
+    numpy's bit for bit; the table follows the returned tau."""
+    n, vocab = 4096 * 1100 + 77, 1_200_000
+    rng = np.random.default_rng(7)
+    i = np.arange(n, dtype=np.int64)
+    ids = {"few": rng.integers(0, 1500, n), "unique": i * 7 % vocab,
+           "mixed": np.where((i // 6000) % 2 == 0, rng.integers(0, 500, n), i * 11 % vocab),
+           "runs": i // 4096}[pattern].astype(np.int32)
+    lb = rng.gamma(2.0, 1.2, n).astype(np.float32)
+    ls = (lb + rng.normal(0.1, 0.3, n)).astype(np.float32)
+    held = rng.integers(0, vocab, 4096 * 600 + 5).astype(np.int32)
+    table, tau, _, scores = run(ids, lb, ls, held, vocab, 0.5)
+    units = np.rint(np.maximum(ls - lb, np.float32(0)).astype(np.float64) * 2.0 ** 32).astype(np.int64)
+    tot = np.zeros(vocab, np.int64)
+    np.add.at(tot, ids, units)
+    cnt = np.bincount(ids, minlength=vocab)
+    want = np.full(vocab, np.inf)
+    want[cnt > 0] = tot[cnt > 0] / cnt[cnt > 0] * 2.0 ** -32
+    np.testing.assert_array_equal(scores, want)
+    np.testing.assert_array_equal(table, np.where(scores < tau, 0, 1))
