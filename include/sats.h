@@ -212,6 +212,8 @@ int sats_mlp_forward_lora_f32(const float *x, const int32_t *token_ids, const fl
  * Allocate the workspace of (current device, stream) for calls of up to
  * max_tokens tokens at this d, d_ff, n_layers and element size (2 = bf16,
  * 4 = f32), so that later calls of that size or smaller allocate nothing.
+ * A bf16 call of more than 64 tokens that is captured without a reserve of
+ * more than 64 runs in passes of 64 (the results agree within rounding).
  */
 int sats_reserve(int64_t max_tokens, int64_t d, int64_t d_ff, int64_t n_layers,
                  int elem_bytes, hipStream_t stream);

@@ -382,7 +382,7 @@ size_t pf_layout(char *base, int64_t np, int ks, int64_t d, int64_t d_ff, int es
   if (b) *b = t;
   return c.off;
 }
-// Workspace of a call of n tokens (every pass), and of any call of up to n.
+// Bytes of a call of n tokens (every pass).
 size_t pf_bytes(int64_t n, int64_t d, int64_t d_ff, int esz, int64_t rank = 0) {
   const int64_t pass = pf_pass(n, esz), last = n - (n - 1) / pass * pass;
   size_t b = 0;
@@ -390,9 +390,10 @@ size_t pf_bytes(int64_t n, int64_t d, int64_t d_ff, int esz, int64_t rank = 0) {
     b = std::max(b, pf_layout(nullptr, np, pf_plan(np, d, d_ff, esz, rank > 0).ks, d, d_ff, esz, nullptr, rank));
   return b;
 }
-size_t pf_bytes_upto(int64_t n, int64_t d, int64_t d_ff, int esz) {
+// Bytes of any call of up to 64 tokens (`large` false), or of any call.
+size_t pf_bytes_all(bool large, int64_t d, int64_t d_ff, int esz) {
   size_t b = 0;
-  for (int64_t m = 1; m <= std::min<int64_t>(n, esz == 4 ? kMaxPass : kPfMaxPass); ++m)
+  for (int64_t m = 1; m <= (large ? kPfMaxPass : kMaxPass); ++m)
     b = std::max(b, pf_layout(nullptr, m, pf_plan(m, d, d_ff, esz).ks, d, d_ff, esz, nullptr,
                               esz == 2 && !pf_split(d, d_ff) ? sats::kLoraMaxRank : 0));
   return b;
@@ -410,14 +411,18 @@ size_t pf_bytes_upto(int64_t n, int64_t d, int64_t d_ff, int esz) {
 //    2730: 186 us there, 35 here).
 // and float32 batches of 2 or more tokens (16 tokens of a Qwen3-8B layer 563 us on the
 // compacted kernels, 117 here; 2 tokens of 3712 x 14016, half the columns kept: 163 and 118).
-bool pf_ok(int esz, bool aligned, int64_t n, int64_t d, int64_t d_ff) {
+bool pf_shape(int esz, bool aligned, int64_t n, int64_t d, int64_t d_ff) {
   if (!aligned || d * esz % 16 != 0 || d > 4096 || d_ff > (1 << 19) - 32 || (uint64_t)d * d_ff * esz >= (1ull << 31) ||
       n < sats::kMfmaMinTokens)
     return false;
-  if (esz == 4) return true;
-  return (n > kMaxPass || pf_split(d, d_ff)) &&
-         (g_opt.batch_path == SATS_BATCH_AUTO || g_opt.batch_path == SATS_BATCH_MFMA);
+  return esz == 4 || n > kMaxPass || pf_split(d, d_ff);
 }
+bool pf_ok(int esz, bool aligned, int64_t n, int64_t d, int64_t d_ff) {
+  return pf_shape(esz, aligned, n, d, d_ff) &&
+         (esz == 4 || g_opt.batch_path == SATS_BATCH_AUTO || g_opt.batch_path == SATS_BATCH_MFMA);
+}
+// float32 passes never exceed 64 rows
+bool pf_large(int esz, int64_t n) { return esz == 2 && n > kMaxPass; }
 
 typedef void (*PfKernel)(sats::PfArgs);
 template <int MODE> PfKernel pf_gateup_fn(const PfPlan &p) {
@@ -455,7 +460,14 @@ struct Workspace {
   size_t bytes = 0;
   unsigned *counters = nullptr;
   size_t n_counters = 0;
+  // The tiled products' buffers, of calls of up to 64 tokens and of longer
+  // ones, each with its arrival counters in front.  They are allocations of
+  // their own, for every token count of their shape: a prompt neither moves the
+  // buffers that a captured decode step uses nor those of a shorter prompt.
+  char *tiled[2] = {};
+  size_t tiled_bytes[2] = {};
 };
+constexpr size_t kPfCounterBytes = (kPfCounters * sizeof(unsigned) + 255) / 256 * 256;
 
 std::mutex g_ws_mu;
 std::map<std::pair<int, hipStream_t>, Workspace> g_ws;
@@ -469,14 +481,14 @@ int ensure_workspace(hipStream_t stream, size_t bytes, size_t n_counters, Worksp
     HIP_TRY(hipStreamSynchronize(stream));  // the old buffers may still be in use
     if (w.mem) HIP_TRY(hipFree(w.mem));
     if (w.counters) HIP_TRY(hipFree(w.counters));
-    w = Workspace{};
+    w.mem = nullptr, w.counters = nullptr, w.bytes = w.n_counters = 0;
     const size_t nb = std::max(bytes, (size_t)256);
     const size_t nc = std::max(n_counters, (size_t)64);
     if (hipMalloc(&w.mem, nb) != hipSuccess)
       return fail(SATS_ERR_WORKSPACE, "workspace allocation of %zu bytes failed", nb);
     if (hipMalloc(&w.counters, nc * sizeof(unsigned)) != hipSuccess) {
       (void)hipFree(w.mem);
-      w = Workspace{};
+      w.mem = nullptr;
       return fail(SATS_ERR_WORKSPACE, "counter allocation failed");
     }
     HIP_TRY(hipMemsetAsync(w.counters, 0, nc * sizeof(unsigned), stream));
@@ -484,6 +496,40 @@ int ensure_workspace(hipStream_t stream, size_t bytes, size_t n_counters, Worksp
     w.n_counters = nc;
   }
   *out = &w;
+  return SATS_OK;
+}
+
+// The tiled products' buffer of a call of n tokens (counters at *counters, the
+// rest at *mem).  *mem stays null where the buffer would have to grow and cannot, under
+// stream capture or for want of memory: the call then takes the passes of 64.
+int ensure_tiled(hipStream_t stream, int64_t n, int64_t d, int64_t d_ff, int esz, size_t need, char **mem,
+                 unsigned **counters) {
+  int dev = 0;
+  HIP_TRY(hipGetDevice(&dev));
+  std::lock_guard<std::mutex> lk(g_ws_mu);
+  Workspace &w = g_ws[{dev, stream}];
+  const int large = pf_large(esz, n);
+  char *&t = w.tiled[large];
+  if (w.tiled_bytes[large] < need) {
+    hipStreamCaptureStatus st = hipStreamCaptureStatusNone;
+    if (hipStreamIsCapturing(stream, &st) != hipSuccess || st != hipStreamCaptureStatusNone) {
+      (void)hipGetLastError();
+      return SATS_OK;
+    }
+    HIP_TRY(hipStreamSynchronize(stream));  // the old buffer may still be in use
+    if (t) HIP_TRY(hipFree(t));
+    t = nullptr, w.tiled_bytes[large] = 0;
+    const size_t bytes = std::max(need, pf_bytes_all(large, d, d_ff, esz));
+    if (hipMalloc(&t, kPfCounterBytes + bytes) != hipSuccess) {
+      (void)hipGetLastError();
+      t = nullptr;
+      return SATS_OK;
+    }
+    w.tiled_bytes[large] = bytes;
+    HIP_TRY(hipMemsetAsync(t, 0, kPfCounterBytes, stream));
+  }
+  *counters = reinterpret_cast<unsigned *>(t);
+  *mem = t + kPfCounterBytes;
   return SATS_OK;
 }
 
@@ -1204,10 +1250,7 @@ int run(const Call &c) {
         mem += kScratchCounterBytes;
       }
     } else {
-      Workspace *ws = nullptr;
-      if ((rc = ensure_workspace(c.stream, need, kPfCounters, &ws))) return rc;
-      mem = ws->mem;
-      counters = ws->counters;
+      if ((rc = ensure_tiled(c.stream, c.n, c.d, c.d_ff, esz, need, &mem, &counters))) return rc;
     }
     if (mem) {
       const int rows = pf_pass(c.n, esz);
@@ -2003,10 +2046,18 @@ int sats_reserve(int64_t max_tokens, int64_t d, int64_t d_ff, int64_t n_layers, 
                                        elem_bytes == 2 ? sats::kLoraMaxRank : 0));
         nc = std::max(nc, counter_count(p, pass, dp));
       }
-  if (pf_ok(elem_bytes, true, max_tokens, d, d_ff))
-    bytes = std::max(bytes, pf_bytes_upto(max_tokens, d, d_ff, elem_bytes)), nc = std::max(nc, kPfCounters);
   Workspace *ws = nullptr;
-  return ensure_workspace(stream, bytes, nc, &ws);
+  int rc = ensure_workspace(stream, bytes, nc, &ws);
+  // the tiled products' buffers, whatever the options are now: up to 64 tokens and beyond
+  for (const int64_t n : {std::min<int64_t>(max_tokens, kMaxPass), max_tokens}) {
+    if (rc || !pf_shape(elem_bytes, true, n, d, d_ff)) continue;
+    char *mem = nullptr;
+    unsigned *counters = nullptr;
+    rc = ensure_tiled(stream, n, d, d_ff, elem_bytes, pf_bytes_all(pf_large(elem_bytes, n), d, d_ff, elem_bytes), &mem,
+                      &counters);
+    if (!rc && !mem) return fail(SATS_ERR_WORKSPACE, "the tiled products' workspace could not be allocated");
+  }
+  return rc;
 }
 
 int sats_release(void) {
@@ -2019,6 +2070,8 @@ int sats_release(void) {
     HIP_TRY(hipDeviceSynchronize());
     if (kv.second.mem) HIP_TRY(hipFree(kv.second.mem));
     if (kv.second.counters) HIP_TRY(hipFree(kv.second.counters));
+    for (char *t : kv.second.tiled)
+      if (t) HIP_TRY(hipFree(t));
   }
   g_ws.clear();
   HIP_TRY(hipSetDevice(cur));

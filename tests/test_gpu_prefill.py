@@ -130,3 +130,43 @@ def test_lora_prompt_matches_oracle(seed, L, d, dff, n, rank):
         again = run_lora(c, ad, rank, s, ts, lut, "bf16", inspect=False)
         np.testing.assert_array_equal(again["out"], res["out"])
         print(f"  lut={'yes' if lut is not None else 'no'} worst rel err {worst:.3g}", flush=True)
+
+
+def test_captured_prompts_keep_their_buffers():
+    """Under capture a prompt takes the passes of 64 where only those are
+    reserved (nothing is allocated), and the tiled products once a prompt is;
+    longer eager prompts between the replays move no buffer of either graph."""
+    import torch
+    import paper_2607_08991_amd as sats
+    d, dff, n, longer = 256, 1024, 130, 700
+    c = synth.small_case(161, 2, d, dff, "bf16", longer, vocab=40, n_dense_ids=12, w_std=1.0 / np.sqrt(d))
+    ts = case_thresholds(c, "bf16", seed=161)
+    x, w = to_dev(c["x"], "bf16"), list(weights_dev(c, "bf16"))
+    ids, lut = to_dev(np.asarray(c["token_ids"], np.int32), "bf16"), to_dev(c["route_lut"], "bf16")
+    thr = torch.tensor(np.asarray(ts, np.float32)).cuda()
+    torch.cuda.synchronize()
+    outs = [torch.zeros_like(x) for _ in range(4)]
+
+    def call(o, a, b):
+        sats.sats_mlp_forward(x[a:b], ids[a:b], *w, thr, lut, o[a:b], b - a, d, dff, 2)
+
+    stream, graphs = torch.cuda.Stream(), []
+    with torch.cuda.stream(stream):
+        for reserve, o in ((64, outs[0]), (n, outs[1])):
+            sats.sats_reserve(reserve, d, dff, 2, 2)
+            torch.cuda.synchronize()
+            graphs.append(torch.cuda.CUDAGraph())
+            with torch.cuda.graph(graphs[-1], stream=stream):
+                call(o, 0, n)
+        for a in range(0, n, 64):
+            call(outs[2], a, min(n, a + 64))  # the passes of 64, eagerly
+        call(outs[3], 0, n)
+        torch.cuda.synchronize()
+        want = [from_dev(outs[2][:n]), from_dev(outs[3][:n])]
+        for _ in range(3):
+            call(outs[3], 0, longer)
+            for g, o, y in zip(graphs, outs, want):
+                o.zero_()
+                g.replay()
+                torch.cuda.synchronize()
+                np.testing.assert_array_equal(from_dev(o[:n]), y)
