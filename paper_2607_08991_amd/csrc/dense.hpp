@@ -149,8 +149,8 @@ struct DenseArgs {
   float *part;            // down output partials, [KSPLIT][n_dense][N]
   int K, N, kchunk;       // reduction length, output columns, k per split (down)
   int nt;                 // gate/up: output columns per workgroup (a multiple of 8, at most 64)
-  // gate/up: W_down of the layer and the split of the launch that follows (or
-  // null): each workgroup reads a part of the rows that launch starts with, so
+  // gate/up, AHEAD: W_down of the layer and the split of the launch that
+  // follows: each workgroup reads a part of the rows that launch starts with, so
   // that memory is not idle while this one drains and the next one starts
   const uint16_t *Wnext;
   int nks, nchunk, nN;    // its k chunks, their length, its columns
@@ -246,9 +246,10 @@ __device__ __forceinline__ f32x4v mfma16(const bf16x8 &a, const bf16x8 &b, const
 // The stage loop shared by both products: stage s lives in ring buffer
 // s % 6; `issue(buf, s)` starts three buffer loads per lane for stage s
 // (loads past the k range read zeros) and `compute(buf)` consumes a stage.
-// SATS_DENSE_RING_H runs HOOK after the first two stages are issued.
-#define SATS_DENSE_RING(S, ISSUE, COMPUTE) SATS_DENSE_RING_H(S, ISSUE, COMPUTE, (void)0)
-#define SATS_DENSE_RING_H(S, ISSUE, COMPUTE, HOOK)                                           \
+// SATS_DENSE_RING_H runs HOOK after the first two stages are issued and TAIL
+// after all that precede the loop.
+#define SATS_DENSE_RING(S, ISSUE, COMPUTE) SATS_DENSE_RING_H(S, ISSUE, COMPUTE, (void)0, (void)0)
+#define SATS_DENSE_RING_H(S, ISSUE, COMPUTE, HOOK, TAIL)                                     \
   {                                                                                          \
     uint8_t *const rb_[6] = {rg0, rg1, rg2, rg3, rg4, rg5};                                  \
     (void)rb_;                                                                               \
@@ -258,6 +259,7 @@ __device__ __forceinline__ f32x4v mfma16(const bf16x8 &a, const bf16x8 &b, const
     ISSUE(rg2, 2);                                                                           \
     ISSUE(rg3, 3);                                                                           \
     ISSUE(rg4, 4);                                                                           \
+    TAIL;                                                                                    \
     for (int s0 = 0; s0 < (S); s0 += 6) {                                                    \
       SATS_DENSE_STEP(S, ISSUE, COMPUTE, rg0, rg5, 0)                                        \
       SATS_DENSE_STEP(S, ISSUE, COMPUTE, rg1, rg0, 1)                                        \
@@ -283,8 +285,8 @@ __device__ __forceinline__ f32x4v mfma16(const bf16x8 &a, const bf16x8 &b, const
 // W_up_T 8 KB each, H 2 KB), seven in flight.  Wavefronts 0-1 also load the
 // 16 H rows (three loads per stage, the others two), so their wait allows
 // 18 outstanding loads and the others' 12.
-#define SATS_DENSE_RING8(S, ISSUE, COMPUTE) SATS_DENSE_RING8_H(S, ISSUE, COMPUTE, (void)0)
-#define SATS_DENSE_RING8_H(S, ISSUE, COMPUTE, HOOK)                                          \
+#define SATS_DENSE_RING8(S, ISSUE, COMPUTE) SATS_DENSE_RING8_H(S, ISSUE, COMPUTE, (void)0, (void)0)
+#define SATS_DENSE_RING8_H(S, ISSUE, COMPUTE, HOOK, TAIL)                                    \
   {                                                                                          \
     ISSUE(rg0, 0);                                                                           \
     ISSUE(rg1, 1);                                                                           \
@@ -294,6 +296,7 @@ __device__ __forceinline__ f32x4v mfma16(const bf16x8 &a, const bf16x8 &b, const
     ISSUE(rg4, 4);                                                                           \
     ISSUE(rg5, 5);                                                                           \
     ISSUE(rg6, 6);                                                                           \
+    TAIL;                                                                                    \
     for (int s0 = 0; s0 < (S); s0 += 8) {                                                    \
       SATS_DENSE_STEP8(S, ISSUE, COMPUTE, rg0, rg7, 0)                                       \
       SATS_DENSE_STEP8(S, ISSUE, COMPUTE, rg1, rg0, 1)                                       \
@@ -325,7 +328,16 @@ __device__ __forceinline__ f32x4v mfma16(const bf16x8 &a, const bf16x8 &b, const
 // shapes).  Wavefronts 0-3 accumulate h W_gate, 4-7 h W_up, 16 columns each.
 // Groups of one row tile use the eight-stage ring of 18 KB stages, larger ones
 // six stages of 24 KB.
-template <int MT, bool LORA = false>
+//
+// MODE: what the rows are and what else the launch does.  The looks at the
+// route table of DIRECT cost a stack nothing only if every stage before the
+// loop is on its way when the first is waited for (36 Qwen3-8B layers at 4
+// tokens: 2.112 ms with the first look waited for after two stages, 2.079 so; 2.085
+// with a route launch in front instead).
+enum { GU_GROUP, GU_LORA, GU_DIRECT, GU_AHEAD };  // GROUP: rows, flags by ctl and gbase; LORA: so, with adapters;
+                                                  // DIRECT: `rows` rows, their flags by ids and lut; AHEAD: so, and
+                                                  // the first rows of W_down for the launch that follows
+template <int MT, int MODE>
 __global__ __launch_bounds__(kDenseThreads) void dense_gateup_kernel(DenseArgs a) {
   constexpr int NB = MT == 1 ? 8 : 6, SB = MT == 1 ? 18 * 1024 : kDenseStageBytes;  // ring stages and their bytes
   __shared__ __attribute__((aligned(1024))) uint8_t ring[NB * SB];
@@ -335,15 +347,16 @@ __global__ __launch_bounds__(kDenseThreads) void dense_gateup_kernel(DenseArgs a
   (void)rg6;
   (void)rg7;
   const int tile = blockIdx.x;
+  constexpr bool LORA = MODE == GU_LORA, DIRECT = MODE >= GU_DIRECT;
   // the group's control words are read while the first two stages load
   // (every allocated row of H: rows past the group feed only results that
   // are not stored); a workgroup of an empty group then waits for its loads
   // and returns
-  const int ctl_on = a.ctl ? a.ctl[1] : 1, ctl_n = a.ctl ? a.ctl[0] : a.rows;
-  int nd = 16 * MT;
+  const int ctl_on = DIRECT ? 1 : a.ctl[1], ctl_n = DIRECT ? a.rows : a.ctl[0];
+  int nd = DIRECT ? min(a.rows, 16 * MT) : 16 * MT;
   const int lane = threadIdx.x & 63, w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-  const int dmode = a.gbase ? ROUTE_SPARSE : a.route_mode;  // the flags looked up here
-  int rid = route_id(dmode, a.ids, a.rows, lane), rflag = 0;
+  int rid = 0, rflag = 0;  // DIRECT: the route of row `lane`
+  if constexpr (DIRECT) rid = route_id(a.route_mode, a.ids, a.rows, lane);
   const int mat = w >> 2, g = lane >> 4, l16 = lane & 15, c = 16 * (w & 3) + l16;
   const int n0 = tile * a.nt;
   const int K = a.K, N = a.N;
@@ -357,7 +370,7 @@ __global__ __launch_bounds__(kDenseThreads) void dense_gateup_kernel(DenseArgs a
   const bool wv_ = dr < ncol;  // a weight row of this workgroup (else zeros, no memory access)
   const uint32_t ou = (uint32_t)(((size_t)(n0 + min(dr, ncol - 1)) * K + 8 * row_pos(dr, dp)) * 2);
   const uint32_t oh = (uint32_t)(((size_t)dr * K + 8 * row_pos(dr, dp)) * 2);
-  bool hv = true;  // rows of the group (all rows until the group's size is known)
+  bool hv = !DIRECT || dr < nd;  // rows of the group (all rows until the group's size is known)
   const uint32_t sk = kDenseKC * 2;  // per stage
   f32x4v acc[MT];
 #pragma unroll
@@ -399,31 +412,35 @@ __global__ __launch_bounds__(kDenseThreads) void dense_gateup_kernel(DenseArgs a
     }
   }
 #define SATS_GU_GROUP                                                                        \
-  if (!ctl_on) {                                                                             \
-    __builtin_amdgcn_s_waitcnt(0);                                                           \
-    return;                                                                                  \
-  }                                                                                          \
-  nd = min(ctl_n, 16 * MT);                                                                  \
-  hv = dr < nd;                                                                              \
-  rflag = route_flag(dmode, a.lut, rid)
-  if constexpr (MT == 1) {
-    SATS_DENSE_RING8_H(S, SATS_GU_ISSUE, SATS_GU_COMPUTE, SATS_GU_GROUP)
-  } else {
-    SATS_DENSE_RING_H(S, SATS_GU_ISSUE, SATS_GU_COMPUTE, SATS_GU_GROUP)
+  if constexpr (!DIRECT) {                                                                   \
+    if (!ctl_on) {                                                                           \
+      __builtin_amdgcn_s_waitcnt(0);                                                         \
+      return;                                                                                \
+    }                                                                                        \
+    nd = min(ctl_n, 16 * MT);                                                                \
+    hv = dr < nd;                                                                            \
   }
+#define SATS_GU_FLAG                                                                         \
+  if constexpr (DIRECT) rflag = route_flag(a.route_mode, a.lut, rid)
+  if constexpr (MT == 1) {
+    SATS_DENSE_RING8_H(S, SATS_GU_ISSUE, SATS_GU_COMPUTE, SATS_GU_GROUP, SATS_GU_FLAG)
+  } else {
+    SATS_DENSE_RING_H(S, SATS_GU_ISSUE, SATS_GU_COMPUTE, SATS_GU_GROUP, SATS_GU_FLAG)
+  }
+#undef SATS_GU_FLAG
 #undef SATS_GU_GROUP
 #undef SATS_GU_ISSUE
 #undef SATS_GU_COMPUTE
-  // workgroup b of the next launch is on XCD b mod 8 and takes chunk b mod nks:
+  // AHEAD: workgroup b of the next launch is on XCD b mod 8 and takes chunk b mod nks:
   // the rows of a chunk are read by the workgroups of its XCD (where 8 divides
   // by nks or nks by 8), 96 KB each (64 tokens of a Llama-3.1-8B layer 77.2 ->
   // 74.0 us, 75.5 with 48 KB)
   constexpr int NPF = 12;
   u32x4 pf[NPF];
-  {
-    const int pk = tile % max(a.nks, 1), pi = tile / max(a.nks, 1);
+  if constexpr (MODE == GU_AHEAD) {
+    const int pk = tile % a.nks, pi = tile / a.nks;
     const size_t p0 = (size_t)pk * a.nchunk * a.nN * 2;
-    const uint32_t pbytes = a.Wnext ? (uint32_t)(min((size_t)a.nchunk, (size_t)max(0, N - pk * a.nchunk)) * a.nN * 2) : 0u;
+    const uint32_t pbytes = (uint32_t)(min((size_t)a.nchunk, (size_t)max(0, N - pk * a.nchunk)) * a.nN * 2);
     const __amdgpu_buffer_rsrc_t rp = dense_rsrc(reinterpret_cast<const uint8_t *>(a.Wnext) + p0, pbytes);
 #pragma unroll
     for (int i = 0; i < NPF; ++i)
@@ -502,20 +519,21 @@ __global__ __launch_bounds__(kDenseThreads) void dense_gateup_kernel(DenseArgs a
   __syncthreads();
   if (mat == 1) {
     const float thr = a.thr ? *a.thr : 0.0f;
-    const int flag = dmode == ROUTE_BASE || rflag != 0;  // of row `lane`
+    const int flag = a.route_mode == ROUTE_BASE || rflag != 0;  // of row `lane`
     bool any = false;  // some row of the group keeps column c
 #pragma unroll
     for (int mt = 0; mt < MT; ++mt)
 #pragma unroll
       for (int r = 0; r < 4; ++r) {
         const int m = 16 * mt + 4 * g + r;
-        const int fm = __shfl(flag, m, 64);
+        int fm = 0;
+        if constexpr (DIRECT) fm = __shfl(flag, m, 64);
         if (m < nd) {
           const float gv = xs[m * kDenseXP + c];
-          const bool keep = (a.gbase ? (int)a.gbase[m] : fm) || fabsf(gv) >= thr;  // Eq. 4-5; every column on the base path
+          const bool keep = (DIRECT ? fm : (int)a.gbase[m]) || fabsf(gv) >= thr;  // Eq. 4-5; every column on the base path
           pt[m * 64 + c] = keep ? f32_to_bf16(gv * acc[mt][r]) : (uint16_t)0;
           any = any || keep;
-          if (a.keep_out && c < ncol) a.keep_out[(size_t)(a.ctl ? a.perm[m] : m) * N + n0 + c] = (uint8_t)keep;
+          if (a.keep_out && c < ncol) a.keep_out[(size_t)(DIRECT ? m : a.perm[m]) * N + n0 + c] = (uint8_t)keep;
         }
       }
     // the four lanes of column c (g = 0..3) hold its rows; lane g = 0 publishes the union flag
@@ -547,8 +565,10 @@ __global__ __launch_bounds__(kDenseThreads) void dense_gateup_kernel(DenseArgs a
       }
     }
   }
+  if constexpr (MODE == GU_AHEAD) {
 #pragma unroll
-  for (int i = 0; i < NPF; ++i) asm volatile("" ::"v"(pf[i]));
+    for (int i = 0; i < NPF; ++i) asm volatile("" ::"v"(pf[i]));
+  }
 }
 
 // partial y over one k chunk for 128 output columns; workgroup b takes
@@ -657,7 +677,7 @@ __global__ __launch_bounds__(kDenseThreads) void dense_down_kernel(DenseArgs a) 
   nd = min(ctl_n, 16 * MT);                                                                  \
   hv = hr < nd;                                                                              \
   fl = row_flags()
-  SATS_DENSE_RING_H(S, SATS_DN_ISSUE, SATS_DN_COMPUTE, SATS_DN_GROUP)
+  SATS_DENSE_RING_H(S, SATS_DN_ISSUE, SATS_DN_COMPUTE, SATS_DN_GROUP, (void)0)
 #undef SATS_DN_GROUP
 #undef SATS_DN_ISSUE
 #undef SATS_DN_COMPUTE

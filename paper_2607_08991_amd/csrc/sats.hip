@@ -88,14 +88,23 @@ int dense_ksplit(int64_t d, int64_t d_ff) {
 
 // MFMA kernels specialised on the 16-row tiles that cover a pass of np tokens
 typedef void (*DenseKernel)(sats::DenseArgs);
-DenseKernel dense_gateup_fn(int np, bool lora = false) {
+template <int MODE> DenseKernel dense_gateup_mode(int np) {
   using namespace sats;
   const int mt = (np + 15) / 16;
-  if (lora)
-    return mt <= 1 ? dense_gateup_kernel<1, true> : mt == 2 ? dense_gateup_kernel<2, true>
-                                                  : mt == 3 ? dense_gateup_kernel<3, true> : dense_gateup_kernel<4, true>;
-  return mt <= 1 ? dense_gateup_kernel<1> : mt == 2 ? dense_gateup_kernel<2> : mt == 3 ? dense_gateup_kernel<3>
-                                                                                        : dense_gateup_kernel<4>;
+  return mt <= 1 ? dense_gateup_kernel<1, MODE> : mt == 2 ? dense_gateup_kernel<2, MODE>
+                                              : mt == 3   ? dense_gateup_kernel<3, MODE> : dense_gateup_kernel<4, MODE>;
+}
+// AHEAD above 16 tokens: 32 Llama-3.1-8B layers at 64 tokens 2.376 -> 2.358 ms.
+// Fewer tokens may all leave out a row read ahead (one layer, 70 % of the columns
+// removed: 2 tokens 60.8 us, 61.8 with it; 4 tokens 65.1 and 68.1; 36 Qwen3-8B
+// layers at 16 tokens 2.161 ms before, 2.172 with it).
+DenseKernel dense_gateup_fn(int np, bool lora, bool direct) {
+  using namespace sats;
+  if (lora) return dense_gateup_mode<GU_LORA>(np);
+  if (!direct) return dense_gateup_mode<GU_GROUP>(np);
+  return np <= 16 ? dense_gateup_kernel<1, GU_DIRECT> : np <= 32 ? dense_gateup_kernel<2, GU_AHEAD>
+                                                    : np <= 48   ? dense_gateup_kernel<3, GU_AHEAD>
+                                                                 : dense_gateup_kernel<4, GU_AHEAD>;
 }
 DenseKernel dense_down_fn(int np) {
   using namespace sats;
@@ -858,9 +867,7 @@ int run_pass(const Call &c, const Plan &p, const Buffers &b, unsigned *counters,
       da.nt = nt_gu;
       const int ks = dense_ksplit(d, d_ff);
       const int kchunk = (int)(((d_ff + ks - 1) / ks + kDenseKC - 1) / kDenseKC * kDenseKC);
-      // (fewer tokens may all leave out a row read ahead: 2 tokens, 70 % of the
-      // columns removed: 60.8 us, 61.8 with it; 4 tokens 65.1 and 68.1)
-      da.Wnext = all_mfma && np >= 8 ? static_cast<const uint16_t *>(c.Wd) + l * wl : nullptr;
+      da.Wnext = static_cast<const uint16_t *>(c.Wd) + l * wl;
       da.nks = ks;
       da.nchunk = kchunk;
       da.nN = (int)d;
@@ -895,7 +902,7 @@ int run_pass(const Call &c, const Plan &p, const Buffers &b, unsigned *counters,
       }
       {
         TimedLaunch tl(SATS_K_DENSE, c.stream);
-        hipExtLaunchKernelGGL(dense_gateup_fn(np, lora), dim3((unsigned)((d_ff + da.nt - 1) / da.nt)),
+        hipExtLaunchKernelGGL(dense_gateup_fn(np, lora, direct), dim3((unsigned)((d_ff + da.nt - 1) / da.nt)),
                               dim3(kDenseThreads), 0, c.stream, tl.start, tl.stop, 0, da);
       }
       HIP_TRY(hipGetLastError());
