@@ -469,6 +469,9 @@ struct Workspace {
   size_t bytes = 0;
   unsigned *counters = nullptr;
   size_t n_counters = 0;
+  bool captured = false;        // a call under capture has used mem and counters
+  size_t refused = SIZE_MAX;    // a size of mem that could not be allocated beside the tiled products'
+  std::vector<void *> kept;     // replaced buffers that captured graphs point at
   // The tiled products' buffers, of calls of up to 64 tokens and of longer
   // ones, each with its arrival counters in front.  They are allocations of
   // their own, for every token count of their shape: a prompt neither moves the
@@ -481,28 +484,67 @@ constexpr size_t kPfCounterBytes = (kPfCounters * sizeof(unsigned) + 255) / 256 
 std::mutex g_ws_mu;
 std::map<std::pair<int, hipStream_t>, Workspace> g_ws;
 
-int ensure_workspace(hipStream_t stream, size_t bytes, size_t n_counters, Workspace **out) {
-  int dev = 0;
+// Whether the stream records a graph (or another does and forbids calls here).
+bool stream_captures(hipStream_t stream) {
+  hipStreamCaptureStatus st = hipStreamCaptureStatusNone;
+  if (hipStreamIsCapturing(stream, &st) == hipSuccess) return st != hipStreamCaptureStatusNone;
+  (void)hipGetLastError();
+  return true;
+}
+
+// Frees a buffer that a larger one replaces, or keeps it until sats_release where a
+// captured call has used it: its graph still points there.  (The replacement of a kept
+// buffer is at least twice as large, so the kept ones together stay below it.)
+int drop_or_keep(Workspace &w, void *p, bool captured) {
+  if (p && captured) w.kept.push_back(p);
+  else if (p) HIP_TRY(hipFree(p));
+  return SATS_OK;
+}
+
+// hipMalloc of `want` bytes, or of `need` where that much is not there (*got: which; null: neither).
+char *alloc_or(size_t want, size_t need, size_t *got) {
+  void *p = nullptr;
+  for (const size_t size : {std::max(want, need), need})
+    if (hipMalloc(&p, size) == hipSuccess) {
+      *got = size;
+      return static_cast<char *>(p);
+    } else {
+      (void)hipGetLastError();
+    }
+  return nullptr;
+}
+
+// `optional`: the call that asks can do without, so what is there stays in any case.
+int ensure_workspace(hipStream_t stream, size_t bytes, size_t n_counters, Workspace **out, bool optional = false) {
+  int dev = 0, rc = 0;
   HIP_TRY(hipGetDevice(&dev));
   std::lock_guard<std::mutex> lk(g_ws_mu);
   Workspace &w = g_ws[{dev, stream}];
   if (w.bytes < bytes || w.n_counters < n_counters) {
     HIP_TRY(hipStreamSynchronize(stream));  // the old buffers may still be in use
-    if (w.mem) HIP_TRY(hipFree(w.mem));
-    if (w.counters) HIP_TRY(hipFree(w.counters));
-    w.mem = nullptr, w.counters = nullptr, w.bytes = w.n_counters = 0;
-    const size_t nb = std::max(bytes, (size_t)256);
-    const size_t nc = std::max(n_counters, (size_t)64);
-    if (hipMalloc(&w.mem, nb) != hipSuccess)
-      return fail(SATS_ERR_WORKSPACE, "workspace allocation of %zu bytes failed", nb);
-    if (hipMalloc(&w.counters, nc * sizeof(unsigned)) != hipSuccess) {
-      (void)hipFree(w.mem);
-      w.mem = nullptr;
-      return fail(SATS_ERR_WORKSPACE, "counter allocation failed");
+    const size_t nb = std::max({bytes, w.bytes, (size_t)256}), nc = std::max({n_counters, w.n_counters, (size_t)64});
+    auto drop = [&]() -> int {
+      if ((rc = drop_or_keep(w, w.mem, w.captured)) || (rc = drop_or_keep(w, w.counters, w.captured))) return rc;
+      w.mem = nullptr, w.counters = nullptr, w.bytes = w.n_counters = 0;
+      return SATS_OK;
+    };
+    size_t got = 0, gotc = 0;
+    char *mem = nullptr, *cnt = nullptr;
+    for (int attempt = 0; attempt < (optional ? 1 : 2) && !cnt; ++attempt) {
+      if (attempt && (rc = drop())) return rc;  // without the old ones
+      mem = alloc_or(w.captured ? 2 * w.bytes : 0, nb, &got);
+      if (mem && !(cnt = alloc_or(0, nc * sizeof(unsigned), &gotc))) HIP_TRY(hipFree(mem));
     }
-    HIP_TRY(hipMemsetAsync(w.counters, 0, nc * sizeof(unsigned), stream));
-    w.bytes = nb;
+    if (!cnt) return fail(SATS_ERR_WORKSPACE, "workspace allocation of %zu bytes failed", nb);
+    if ((rc = drop())) return rc;
+    w.captured = false;
+    w.mem = mem;
+    w.bytes = got;
+    w.counters = reinterpret_cast<unsigned *>(cnt);
     w.n_counters = nc;
+    HIP_TRY(hipMemsetAsync(w.counters, 0, nc * sizeof(unsigned), stream));
+  } else if (stream_captures(stream)) {
+    w.captured = true;
   }
   *out = &w;
   return SATS_OK;
@@ -520,11 +562,7 @@ int ensure_tiled(hipStream_t stream, int64_t n, int64_t d, int64_t d_ff, int esz
   const int large = pf_large(esz, n);
   char *&t = w.tiled[large];
   if (w.tiled_bytes[large] < need) {
-    hipStreamCaptureStatus st = hipStreamCaptureStatusNone;
-    if (hipStreamIsCapturing(stream, &st) != hipSuccess || st != hipStreamCaptureStatusNone) {
-      (void)hipGetLastError();
-      return SATS_OK;
-    }
+    if (stream_captures(stream)) return SATS_OK;
     HIP_TRY(hipStreamSynchronize(stream));  // the old buffer may still be in use
     if (t) HIP_TRY(hipFree(t));
     t = nullptr, w.tiled_bytes[large] = 0;
@@ -647,6 +685,38 @@ struct Call {
   // allocation-free call: the workspace is the library's static scratch array
   bool noalloc;
 };
+
+// Whether a call can have a workspace of these sizes without an error: the fixed array
+// of the allocation-free call, under capture what is there, else whatever it asks for.
+bool workspace_there(const Call &c, size_t bytes, size_t ncount) {
+  if (c.noalloc) return bytes <= kScratchBytes - kScratchCounterBytes && ncount * sizeof(unsigned) <= kScratchCounterBytes;
+  if (!stream_captures(c.stream)) return true;
+  int dev = 0;
+  if (hipGetDevice(&dev) != hipSuccess) return false;
+  std::lock_guard<std::mutex> lk(g_ws_mu);
+  const Workspace &w = g_ws[{dev, c.stream}];
+  return w.bytes >= bytes && w.n_counters >= ncount;
+}
+
+// Beside a call on the tiled products: the workspace that its shorter calls use, as
+// large as this call would have it on those kernels, so that such a call can be
+// captured next (nothing is allocated under capture).  A size that could not be had
+// is not tried again: the call itself does not need it.
+int reserve_shorter(const Call &c, size_t bytes, size_t ncount) {
+  int dev = 0;
+  HIP_TRY(hipGetDevice(&dev));
+  {
+    std::lock_guard<std::mutex> lk(g_ws_mu);
+    const Workspace &w = g_ws[{dev, c.stream}];
+    if ((w.bytes >= bytes && w.n_counters >= ncount) || bytes >= w.refused) return SATS_OK;
+  }
+  Workspace *ws = nullptr;
+  if (stream_captures(c.stream) || ensure_workspace(c.stream, bytes, ncount, &ws, true) == SATS_OK) return SATS_OK;
+  g_err.clear();
+  std::lock_guard<std::mutex> lk(g_ws_mu);
+  g_ws[{dev, c.stream}].refused = bytes;
+  return SATS_OK;
+}
 
 // One pass of np rows from token `base` on through the tiled products (see pf_ok).
 template <typename T> int run_prefill(const Call &c, char *mem, unsigned *counters, int64_t base, int np) {
@@ -1245,11 +1315,25 @@ int run(const Call &c) {
     if (!lora_batched(c, esz, vec_ok)) return run_lora<T>(c, vec_ok);
   }
   const int64_t lrank = c.Ag ? c.rank : 0;
+  // single-token path: one token, vector layout, h fits the LDS copy
+  bool decode = c.n == 1 && vec_d && g_opt.single_token != SATS_SINGLE_OFF;
+  DecodePlan dp;
+  if (decode) decode = make_decode_plan(c.d, c.d_ff, esz, &dp);
+  size_t bytes = layout(nullptr, p, pass, c.d, c.d_ff, esz, c.L, dp, nullptr, lrank);
+  const size_t ncount = counter_count(p, pass, dp);
+  if (decode && !vec_ok && !workspace_there(c, bytes, ncount)) {
+    // d_ff off the vector layout: the compacted kernels, which need less
+    decode = false;
+    dp = DecodePlan{};
+    bytes = layout(nullptr, p, pass, c.d, c.d_ff, esz, c.L, dp, nullptr, lrank);
+  }
+  Workspace *ws = nullptr;
+  Workspace fixed{};
+  int rc = 0;
   if (c.Ag ? lora_tiled(c, esz, vec_ok) : pf_ok(esz, vec_d, c.n, c.d, c.d_ff)) {
     const size_t need = pf_bytes(c.n, c.d, c.d_ff, esz, lrank);
     char *mem = nullptr;
     unsigned *counters = nullptr;  // (LoRA only)
-    int rc = 0;
     // the allocation-free call takes this path when its workspace fits
     if (c.noalloc) {
       if (need <= kScratchBytes - kScratchCounterBytes) {
@@ -1258,6 +1342,8 @@ int run(const Call &c) {
       }
     } else {
       if ((rc = ensure_tiled(c.stream, c.n, c.d, c.d_ff, esz, need, &mem, &counters))) return rc;
+      // a shorter call may follow under capture, where nothing can be allocated
+      if (mem && (rc = reserve_shorter(c, bytes, ncount))) return rc;
     }
     if (mem) {
       const int rows = pf_pass(c.n, esz);
@@ -1266,17 +1352,8 @@ int run(const Call &c) {
       return SATS_OK;
     }
   }
-  // single-token path: one token, vector layout, h fits the LDS copy
-  bool decode = c.n == 1 && vec_d && g_opt.single_token != SATS_SINGLE_OFF;
-  DecodePlan dp;
-  if (decode) decode = make_decode_plan(c.d, c.d_ff, esz, &dp);
-  const size_t bytes = layout(nullptr, p, pass, c.d, c.d_ff, esz, c.L, dp, nullptr, lrank);
-  Workspace *ws = nullptr;
-  size_t ncount = counter_count(p, pass, dp);
-  Workspace fixed{};
-  int rc = 0;
   if (c.noalloc) {
-    if (bytes > kScratchBytes - kScratchCounterBytes || ncount * sizeof(unsigned) > kScratchCounterBytes)
+    if (!workspace_there(c, bytes, ncount))
       return fail(SATS_ERR_WORKSPACE,
                   "the call needs %zu bytes of workspace and %zu counters; the allocation-free forward has %zu and %zu",
                   bytes, ncount, kScratchBytes - kScratchCounterBytes, kScratchCounterBytes / sizeof(unsigned));
@@ -2079,6 +2156,7 @@ int sats_release(void) {
     if (kv.second.counters) HIP_TRY(hipFree(kv.second.counters));
     for (char *t : kv.second.tiled)
       if (t) HIP_TRY(hipFree(t));
+    for (void *t : kv.second.kept) HIP_TRY(hipFree(t));
   }
   g_ws.clear();
   HIP_TRY(hipSetDevice(cur));
