@@ -212,8 +212,15 @@ int sats_mlp_forward_lora_f32(const float *x, const int32_t *token_ids, const fl
  * Allocate the workspace of (current device, stream) for calls of up to
  * max_tokens tokens at this d, d_ff, n_layers and element size (2 = bf16,
  * 4 = f32), so that later calls of that size or smaller allocate nothing.
- * A bf16 call of more than 64 tokens that is captured without a reserve of
- * more than 64 runs in passes of 64 (the results agree within rounding).
+ * Without it a call allocates what it needs, once; a buffer that a captured
+ * call has used is kept until sats_release, also where a later call grows it.
+ * A batch whose matrix-core workspace is not there and cannot be allocated
+ * (under stream capture, or for want of memory) runs on other kernels in
+ * passes of 64 tokens, and its results agree with the usual ones within
+ * rounding: bf16 prompts of more than 64 tokens (LoRA: 128), float32 batches,
+ * and bf16 batches with d no multiple of 128 or d_ff none of 64.  A size that
+ * could not be allocated is not tried again until the next sats_reserve or
+ * sats_release.
  */
 int sats_reserve(int64_t max_tokens, int64_t d, int64_t d_ff, int64_t n_layers,
                  int elem_bytes, hipStream_t stream);

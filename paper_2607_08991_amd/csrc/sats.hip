@@ -399,12 +399,12 @@ size_t pf_bytes(int64_t n, int64_t d, int64_t d_ff, int esz, int64_t rank = 0) {
     b = std::max(b, pf_layout(nullptr, np, pf_plan(np, d, d_ff, esz, rank > 0).ks, d, d_ff, esz, nullptr, rank));
   return b;
 }
-// Bytes of any call of up to 64 tokens (`large` false), or of any call.
-size_t pf_bytes_all(bool large, int64_t d, int64_t d_ff, int esz) {
+// Bytes of any call of up to n tokens (adapters of any rank with `lora`).
+size_t pf_bytes_upto(int64_t n, int64_t d, int64_t d_ff, int esz, bool lora) {
   size_t b = 0;
-  for (int64_t m = 1; m <= (large ? kPfMaxPass : kMaxPass); ++m)
+  for (int64_t m = 1; m <= std::min<int64_t>(n, esz == 4 ? kMaxPass : kPfMaxPass); ++m)
     b = std::max(b, pf_layout(nullptr, m, pf_plan(m, d, d_ff, esz).ks, d, d_ff, esz, nullptr,
-                              esz == 2 && !pf_split(d, d_ff) ? sats::kLoraMaxRank : 0));
+                              lora && esz == 2 && !pf_split(d, d_ff) ? sats::kLoraMaxRank : 0));
   return b;
 }
 
@@ -473,11 +473,13 @@ struct Workspace {
   size_t refused = SIZE_MAX;    // a size of mem that could not be allocated beside the tiled products'
   std::vector<void *> kept;     // replaced buffers that captured graphs point at
   // The tiled products' buffers, of calls of up to 64 tokens and of longer
-  // ones, each with its arrival counters in front.  They are allocations of
-  // their own, for every token count of their shape: a prompt neither moves the
-  // buffers that a captured decode step uses nor those of a shorter prompt.
-  char *tiled[2] = {};
-  size_t tiled_bytes[2] = {};
+  // ones, each an allocation with its arrival counters in front.
+  struct Tiled {
+    char *mem = nullptr;
+    size_t bytes = 0;           // behind the counters
+    size_t refused = SIZE_MAX;  // a size that could not be allocated: not tried again until sats_reserve
+    bool captured = false;
+  } tiled[2];
 };
 constexpr size_t kPfCounterBytes = (kPfCounters * sizeof(unsigned) + 255) / 256 * 256;
 
@@ -550,33 +552,54 @@ int ensure_workspace(hipStream_t stream, size_t bytes, size_t n_counters, Worksp
   return SATS_OK;
 }
 
-// The tiled products' buffer of a call of n tokens (counters at *counters, the
-// rest at *mem).  *mem stays null where the buffer would have to grow and cannot, under
-// stream capture or for want of memory: the call then takes the passes of 64.
-int ensure_tiled(hipStream_t stream, int64_t n, int64_t d, int64_t d_ff, int esz, size_t need, char **mem,
-                 unsigned **counters) {
-  int dev = 0;
+// The tiled products' buffer of a call of n tokens: at least `need` bytes, `want` where
+// it is allocated for the first time, twice the old one where it grows (counters at
+// *counters, the rest at *mem).  *mem stays null, and what is there stays, where it
+// would have to grow and cannot, under stream capture or for want of memory: the call
+// then takes the kernels it has without it.
+int ensure_tiled(hipStream_t stream, int64_t n, int esz, size_t need, size_t want, char **mem, unsigned **counters) {
+  int dev = 0, rc = 0;
   HIP_TRY(hipGetDevice(&dev));
   std::lock_guard<std::mutex> lk(g_ws_mu);
   Workspace &w = g_ws[{dev, stream}];
-  const int large = pf_large(esz, n);
-  char *&t = w.tiled[large];
-  if (w.tiled_bytes[large] < need) {
-    if (stream_captures(stream)) return SATS_OK;
-    HIP_TRY(hipStreamSynchronize(stream));  // the old buffer may still be in use
-    if (t) HIP_TRY(hipFree(t));
-    t = nullptr, w.tiled_bytes[large] = 0;
-    const size_t bytes = std::max(need, pf_bytes_all(large, d, d_ff, esz));
-    if (hipMalloc(&t, kPfCounterBytes + bytes) != hipSuccess) {
-      (void)hipGetLastError();
-      t = nullptr;
-      return SATS_OK;
+  Workspace::Tiled &t = w.tiled[pf_large(esz, n)];
+  const bool capturing = stream_captures(stream);
+  if (t.bytes < need && need < t.refused && !capturing) {
+    size_t got = 0;
+    char *m = alloc_or(kPfCounterBytes + std::max(want, 2 * t.bytes), kPfCounterBytes + need, &got);
+    if (m) {
+      if (t.mem) HIP_TRY(hipStreamSynchronize(stream));  // the old buffer may still be in use
+      if ((rc = drop_or_keep(w, t.mem, t.captured))) return rc;
+      t.mem = m, t.bytes = got - kPfCounterBytes, t.refused = SIZE_MAX, t.captured = false;
+      HIP_TRY(hipMemsetAsync(m, 0, kPfCounterBytes, stream));
+    } else {
+      t.refused = need;
     }
-    w.tiled_bytes[large] = bytes;
-    HIP_TRY(hipMemsetAsync(t, 0, kPfCounterBytes, stream));
   }
-  *counters = reinterpret_cast<unsigned *>(t);
-  *mem = t + kPfCounterBytes;
+  if (t.bytes < need) return SATS_OK;
+  if (capturing) t.captured = true;
+  *counters = reinterpret_cast<unsigned *>(t.mem);
+  *mem = t.mem + kPfCounterBytes;
+  return SATS_OK;
+}
+
+// For sats_reserve: the buffer of every call of up to n tokens of n's class.  Where it
+// cannot be had, later calls do not try again.
+int reserve_tiled(hipStream_t stream, int64_t n, int64_t d, int64_t d_ff, int esz) {
+  int dev = 0, rc = 0;
+  HIP_TRY(hipGetDevice(&dev));
+  size_t *refused = nullptr;
+  {
+    std::lock_guard<std::mutex> lk(g_ws_mu);
+    *(refused = &g_ws[{dev, stream}].tiled[pf_large(esz, n)].refused) = SIZE_MAX;
+  }
+  char *mem = nullptr;
+  unsigned *counters = nullptr;
+  if ((rc = ensure_tiled(stream, n, esz, pf_bytes_upto(n, d, d_ff, esz, pf_large(esz, n)), 0, &mem, &counters))) return rc;
+  if (!mem) {
+    std::lock_guard<std::mutex> lk(g_ws_mu);
+    *refused = 0;
+  }
   return SATS_OK;
 }
 
@@ -698,13 +721,17 @@ bool workspace_there(const Call &c, size_t bytes, size_t ncount) {
   return w.bytes >= bytes && w.n_counters >= ncount;
 }
 
-// Beside a call on the tiled products: the workspace that its shorter calls use, as
-// large as this call would have it on those kernels, so that such a call can be
-// captured next (nothing is allocated under capture).  A size that could not be had
-// is not tried again: the call itself does not need it.
-int reserve_shorter(const Call &c, size_t bytes, size_t ncount) {
-  int dev = 0;
+// Beside a call on the tiled products: the workspaces that its shorter calls use, so
+// that such a call can be captured next (nothing is allocated under capture): the
+// other kernels', as large as this call would have it on those, and for a prompt
+// those of up to 64 tokens (`any` bytes; 0: not on the tiled products).  A size that
+// could not be had is not tried again: the call itself does not need it.
+int reserve_shorter(const Call &c, int esz, size_t any, size_t bytes, size_t ncount) {
+  int dev = 0, rc = 0;
   HIP_TRY(hipGetDevice(&dev));
+  char *mem = nullptr;
+  unsigned *counters = nullptr;
+  if (any && pf_large(esz, c.n) && (rc = ensure_tiled(c.stream, kMaxPass, esz, any, any, &mem, &counters))) return rc;
   {
     std::lock_guard<std::mutex> lk(g_ws_mu);
     const Workspace &w = g_ws[{dev, c.stream}];
@@ -1341,9 +1368,11 @@ int run(const Call &c) {
         mem += kScratchCounterBytes;
       }
     } else {
-      if ((rc = ensure_tiled(c.stream, c.n, c.d, c.d_ff, esz, need, &mem, &counters))) return rc;
+      // (up to 64 tokens: for all of them at once)
+      const size_t any = pf_shape(esz, vec_d, kMaxPass, c.d, c.d_ff) ? pf_bytes(kMaxPass, c.d, c.d_ff, esz) : 0;
+      if ((rc = ensure_tiled(c.stream, c.n, esz, need, pf_large(esz, c.n) ? need : any, &mem, &counters))) return rc;
       // a shorter call may follow under capture, where nothing can be allocated
-      if (mem && (rc = reserve_shorter(c, bytes, ncount))) return rc;
+      if (mem && (rc = reserve_shorter(c, esz, any, bytes, ncount))) return rc;
     }
     if (mem) {
       const int rows = pf_pass(c.n, esz);
@@ -2133,14 +2162,8 @@ int sats_reserve(int64_t max_tokens, int64_t d, int64_t d_ff, int64_t n_layers, 
   Workspace *ws = nullptr;
   int rc = ensure_workspace(stream, bytes, nc, &ws);
   // the tiled products' buffers, whatever the options are now: up to 64 tokens and beyond
-  for (const int64_t n : {std::min<int64_t>(max_tokens, kMaxPass), max_tokens}) {
-    if (rc || !pf_shape(elem_bytes, true, n, d, d_ff)) continue;
-    char *mem = nullptr;
-    unsigned *counters = nullptr;
-    rc = ensure_tiled(stream, n, d, d_ff, elem_bytes, pf_bytes_all(pf_large(elem_bytes, n), d, d_ff, elem_bytes), &mem,
-                      &counters);
-    if (!rc && !mem) return fail(SATS_ERR_WORKSPACE, "the tiled products' workspace could not be allocated");
-  }
+  for (const int64_t n : {std::min<int64_t>(max_tokens, kMaxPass), max_tokens})
+    if (!rc && pf_shape(elem_bytes, true, n, d, d_ff)) rc = reserve_tiled(stream, n, d, d_ff, elem_bytes);
   return rc;
 }
 
@@ -2154,8 +2177,8 @@ int sats_release(void) {
     HIP_TRY(hipDeviceSynchronize());
     if (kv.second.mem) HIP_TRY(hipFree(kv.second.mem));
     if (kv.second.counters) HIP_TRY(hipFree(kv.second.counters));
-    for (char *t : kv.second.tiled)
-      if (t) HIP_TRY(hipFree(t));
+    for (const Workspace::Tiled &t : kv.second.tiled)
+      if (t.mem) HIP_TRY(hipFree(t.mem));
     for (void *t : kv.second.kept) HIP_TRY(hipFree(t));
   }
   g_ws.clear();
