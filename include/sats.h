@@ -317,7 +317,9 @@ int sats_route_table(const float *loss_base, const float *loss_sparse, const int
  * and measurement (results of every choice agree with the definition above
  * within the stated tolerances); nothing else changes the kernels a call
  * takes.  Errors: SATS_ERR_ARG for a value outside its range.
- *   batch_path      SATS_BATCH_AUTO, or for batches of 2 or more bf16 tokens:
+ *   batch_path      SATS_BATCH_AUTO, or for batches of 2 or more tokens (float32
+ *                   and shapes without a matrix-core kernel for the base-path
+ *                   group: SPLIT takes the compacted kernels):
  *                   SATS_BATCH_MFMA     every token on the matrix cores, each
  *                                       with its own route and keep rule;
  *                   SATS_BATCH_SPLIT    the base-path group on the matrix
@@ -351,12 +353,13 @@ int sats_set_options(const sats_options *opt);
  * under the calling thread's options, answered on the host without device
  * work: *path receives SATS_PATH_SINGLE_TOKEN, SATS_PATH_BATCH_MFMA,
  * SATS_PATH_BATCH_SPLIT or SATS_PATH_BATCH_COMPACT (for the first pass of
- * up to 64 tokens; 0 for n_tokens == 0).  SATS_PATH_BATCH_COMPACT also names
- * the float32 batch kernels (float32 matrix-core products where rows are
- * 16-byte pieces and d <= 4096, else the compacted kernels).  elem_bytes: 2 (bf16) or 4
- * (float32); aligned16: whether x, out and the weights are 16-byte aligned;
- * n_cus: compute units of the device (0: the current device's).  Errors:
- * SATS_ERR_NULL, SATS_ERR_SHAPE and SATS_ERR_ARG as for the forward calls.
+ * up to 64 tokens; 0 for n_tokens == 0).  For float32 batches it is
+ * SATS_PATH_BATCH_COMPACT on every path: it does not tell their matrix-core
+ * kernels (batch_path AUTO or MFMA, rows in 16-byte pieces, d <= 4096) from the
+ * compacted ones.  elem_bytes: 2 (bf16) or 4 (float32); aligned16: whether x,
+ * out and the weights are 16-byte aligned; n_cus: compute units of the device
+ * (0: the current device's).  Errors: SATS_ERR_NULL, SATS_ERR_SHAPE and
+ * SATS_ERR_ARG as for the forward calls.
  */
 enum { SATS_PATH_SINGLE_TOKEN = 1, SATS_PATH_BATCH_MFMA = 2, SATS_PATH_BATCH_SPLIT = 3,
        SATS_PATH_BATCH_COMPACT = 4 };

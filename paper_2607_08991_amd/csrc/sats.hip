@@ -428,7 +428,7 @@ bool pf_shape(int esz, bool aligned, int64_t n, int64_t d, int64_t d_ff) {
 }
 bool pf_ok(int esz, bool aligned, int64_t n, int64_t d, int64_t d_ff) {
   return pf_shape(esz, aligned, n, d, d_ff) &&
-         (esz == 4 || g_opt.batch_path == SATS_BATCH_AUTO || g_opt.batch_path == SATS_BATCH_MFMA);
+         (g_opt.batch_path == SATS_BATCH_AUTO || g_opt.batch_path == SATS_BATCH_MFMA);
 }
 // float32 passes never exceed 64 rows
 bool pf_large(int esz, int64_t n) { return esz == 2 && n > kMaxPass; }

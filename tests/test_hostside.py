@@ -128,3 +128,25 @@ fake.fake_capture(1); fwd(9, {d}, {dff}, "{dtype}"); b = launches(log())
 fake.fake_capture(0); fwd(9, {d}, {dff}, "{dtype}")
 print(json.dumps([launches(log()), b]))""")
     assert eager == captured and any("sm_gateup" in k for k in eager)
+
+
+@pytest.mark.parametrize("dtype,d,dff", [("f32", 256, 1024), ("f32", 256, 1001), ("bf16", 256, 1000),
+                                         ("bf16", 256, 1024)])
+def test_the_batch_path_option_holds_for_every_type(run, dtype, d, dff):
+    """SATS_BATCH_COMPACT takes the compacted kernels for float32 as for bf16 (and so
+    does SATS_BATCH_SPLIT where no matrix-core group applies); the default does not."""
+    got = run(f"""
+out = dict()
+for name, path in (("auto", AUTO), ("mfma", MFMA), ("split", SPLIT), ("compact", COMPACT)):
+    options(path)
+    for n in (2, 64, 100):
+        assert fwd(n, {d}, {dff}, "{dtype}") == 0
+        out[name + str(n)] = launches(log())
+print(json.dumps(out))""")
+    for key, names in got.items():
+        compacted = any("4sats11gate_kernel" in k for k in names)
+        tiled = any("sm_gateup" in k or "pf_gateup" in k or "dense_gateup" in k for k in names)
+        if key.startswith(("auto", "mfma")):
+            assert tiled and not compacted, (key, names)
+        elif key.startswith("compact") or dtype == "f32":
+            assert compacted and not tiled, (key, names)
