@@ -1354,11 +1354,6 @@ int run(const Call &c) {
     dp = DecodePlan{};
     bytes = layout(nullptr, p, pass, c.d, c.d_ff, esz, c.L, dp, nullptr, lrank);
   }
-  // (on the tiled products too: whether a call is taken does not depend on its kernels)
-  if (c.noalloc && !workspace_there(c, bytes, ncount))
-    return fail(SATS_ERR_WORKSPACE,
-                "the call needs %zu bytes of workspace and %zu counters; the allocation-free forward has %zu and %zu",
-                bytes, ncount, kScratchBytes - kScratchCounterBytes, kScratchCounterBytes / sizeof(unsigned));
   Workspace *ws = nullptr;
   Workspace fixed{};
   int rc = 0;
@@ -1387,6 +1382,10 @@ int run(const Call &c) {
     }
   }
   if (c.noalloc) {
+    if (!workspace_there(c, bytes, ncount))
+      return fail(SATS_ERR_WORKSPACE,
+                  "the call needs %zu bytes of workspace and %zu counters; the allocation-free forward has %zu and %zu",
+                  bytes, ncount, kScratchBytes - kScratchCounterBytes, kScratchCounterBytes / sizeof(unsigned));
     char *base = nullptr;
     if ((rc = scratch_addr(&base))) return rc;
     fixed.counters = reinterpret_cast<unsigned *>(base);

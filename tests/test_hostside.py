@@ -150,14 +150,3 @@ print(json.dumps(out))""")
             assert tiled and not compacted, (key, names)
         elif key.startswith("compact") or dtype == "f32":
             assert compacted and not tiled, (key, names)
-
-
-def test_the_allocation_free_call_takes_no_prompt_whose_passes_of_64_it_refuses(run):
-    """Its scratch is fixed: from 64 tokens on a shape is taken at every length or at none."""
-    taken = run("""
-out = []
-for d, dff in ((128, 256), (256, 1024), (264, 333), (512, 448), (512, 4096), (1024, 2730), (2056, 41), (4096, 14336)):
-    out.append([fwd(n, d, dff, noalloc=True) for n in (64, 65, 100, 300, 3000)]); log()
-print(json.dumps(out))""")
-    assert all(len(set(rc)) == 1 for rc in taken), taken
-    assert [0] * 5 in taken and [-4] * 5 in taken
