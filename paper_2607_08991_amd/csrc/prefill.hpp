@@ -165,17 +165,26 @@ template <int MT, int CT> __device__ __forceinline__ void pf_fold(f32x4v (&sum)[
     }
 }
 
-// Eight columns of p as three bf16 terms, 16 bytes of each term's row blocks.
+// Eight columns of p as three bf16 terms, 16 bytes of each term's row blocks.  A term
+// is the leading 8 bits of what is left, cut off and not rounded: three of them hold
+// the 24 bits of p, none leaves the range, and an infinite p has no remainder.
 __device__ __forceinline__ void pf_store_terms(uint16_t *o, size_t pterm, float (&v)[8]) {
 #pragma unroll
   for (int h = 0; h < 3; ++h) {
-    uint16_t b[8];
+    u32x4 b;
 #pragma unroll
     for (int k = 0; k < 8; ++k) {
-      b[k] = f32_to_bf16(v[k]);
-      v[k] -= bf16_to_f32(b[k]);
+      const uint32_t t = __float_as_uint(v[k]) & 0xffff0000u;
+      if (k & 1)
+        b[k / 2] |= t;
+      else
+        b[k / 2] = t >> 16;
+      if (h < 2) {
+        const float rest = v[k] - __uint_as_float(t);
+        v[k] = h > 0 || fabsf(v[k]) < INFINITY ? rest : 0.0f;
+      }
     }
-    *reinterpret_cast<u32x4 *>(o + h * pterm) = *reinterpret_cast<const u32x4 *>(b);
+    *reinterpret_cast<u32x4 *>(o + h * pterm) = b;
   }
 }
 
@@ -191,7 +200,7 @@ __device__ __forceinline__ void pf_store_terms(uint16_t *o, size_t pterm, float 
 // weights (64 k, used by steps 2 j and 2 j + 1).
 // MODE: how p leaves the kernel.
 enum { PF_P16 = 0,   // rounded to bf16
-       PF_SPLIT = 1,  // three bf16 terms whose sum is p: rne(p), rne of the remainder, and the rest
+       PF_SPLIT = 1,  // three bf16 terms whose sum is p
        PF_CAL = 2,    // calibration: g in float32, and p as two terms, without the keep rule
        PF_LORA = 3 }; // as PF_P16, with 4 R further k for the adapters (K a multiple of 64): rows of
                       // h continue with [hi | lo] of s (h A_gate) and of s (h A_up), W_gate rows with
@@ -608,18 +617,28 @@ __global__ __launch_bounds__(kPfThreads, 2) void pf_down_kernel(PfArgs a) {
 // of a Qwen3-8B layer: 563 us, here 117: 604 MB at 5.2 TB/s).
 
 // Every stage sums into accumulators of its own, which the next stage adds to
-// the total under its products, with a compensation term (Kahan's sum): only
-// the sums within a stage carry rounding.  Plain folds of 64 k left float32
-// results 1.4 times as far from 64 bits as the compacted kernels'; these are
-// as near or nearer (1.9e-7 to 2.1e-7 of a layer's output, there 2.0e-7 to
-// 3.4e-7).
-template <int MT> __device__ __forceinline__ void sm_fold(f32x4v (&sum)[MT], f32x4v (&comp)[MT], const f32x4v (&acc)[MT]) {
+// the total under its products; what each of those additions rounds off is summed
+// apart and added at the end (sm_total): only the sums within a stage carry rounding.
+// Plain folds of 64 k left float32 results 1.4 times as far from 64 bits as the
+// compacted kernels'; these are as near or nearer (1.9e-7 to 2.1e-7 of a layer's
+// output, there 2.0e-7 to 3.4e-7).  The total is a plain sum, so an overflow stays
+// an infinity; the part rounded off is then meaningless (inf - inf) and left out.
+// (Kahan's form, with the compensation in the next addend, takes as many operations,
+// but an infinite total turns into NaN; guarded there it cost up to 8 %.)
+template <int MT> __device__ __forceinline__ void sm_fold(f32x4v (&sum)[MT], f32x4v (&off)[MT], const f32x4v (&acc)[MT]) {
 #pragma unroll
   for (int i = 0; i < MT; ++i) {
-    const f32x4v y = acc[i] - comp[i], t = sum[i] + y;
-    comp[i] = (t - sum[i]) - y;
+    const f32x4v t = sum[i] + acc[i];
+    off[i] += acc[i] - (t - sum[i]);
     sum[i] = t;
   }
+}
+template <int MT> __device__ __forceinline__ void sm_total(f32x4v (&sum)[MT], const f32x4v (&off)[MT]) {
+#pragma unroll
+  for (int i = 0; i < MT; ++i)
+#pragma unroll
+    for (int r = 0; r < 4; ++r)
+      if (fabsf(sum[i][r]) < INFINITY) sum[i][r] += off[i][r];
 }
 
 // acc[i] = (first) or += the block product of row tile i (operand x[i]) and b
@@ -688,7 +707,7 @@ __global__ __launch_bounds__(kPfThreads, 2) void sm_gateup_kernel(PfArgs a, int 
       for (int i = 0; i < MT; ++i) xa[h][i] = sm_block_operand(buf + SW + (2 * i + h) * 1024, l16, g);
     }
   };
-  f32x4v acc0[MT] = {}, acc1[MT] = {}, sum[MT] = {}, comp[MT] = {};  // stage sums (even, odd); total
+  f32x4v acc0[MT] = {}, acc1[MT] = {}, sum[MT] = {}, off[MT] = {};  // stage sums (even, odd); total
 #pragma unroll
   for (int s = 0; s < R - 1; ++s) issue(rb(s), s);
   const int rflag = route_flag(a.route_mode, a.lut, rid);
@@ -702,7 +721,7 @@ __global__ __launch_bounds__(kPfThreads, 2) void sm_gateup_kernel(PfArgs a, int 
     load(rb(p + 1), ya, yb);
 #pragma unroll
     for (int h = 0; h < 2; ++h) sm_mfma<T, MT>(xa[h], xb[h], cur, h == 0);
-    sm_fold(sum, comp, prv);
+    sm_fold(sum, off, prv);
     __builtin_amdgcn_sched_barrier(0);  // (the next step's reads stay there: registers)
   };
   for (int s0 = 0; s0 < S; s0 += R) {
@@ -713,7 +732,8 @@ __global__ __launch_bounds__(kPfThreads, 2) void sm_gateup_kernel(PfArgs a, int 
     step(s0 + 4, 4, oa0, ob0, oa1, ob1, acc0, acc1);
     step(s0 + 5, 5, oa1, ob1, oa0, ob0, acc1, acc0);
   }
-  sm_fold(sum, comp, acc1);  // (rounds end on an odd stage)
+  sm_fold(sum, off, acc1);  // (rounds end on an odd stage)
+  sm_total(sum, off);
   __builtin_amdgcn_s_waitcnt(0);
   __syncthreads();
   // epilogue: SiLU lane to lane to the wavefront of W_up, p through LDS to 16-byte stores of its terms
@@ -818,7 +838,7 @@ __global__ __launch_bounds__(kPfThreads, 2) void sm_down_kernel(PfArgs a) {
       pf_dma(dense_rsrc(a.A + min((w + 8 * q) / (2 * MT), NP - 1) * a.pterm, pbytes), buf + SW + (w + 8 * q) * 1024,
              aq < left ? aoff[q] : kDenseOffNone, (uint32_t)s * 2048u);
   };
-  f32x4v acc0[MT] = {}, acc1[MT] = {}, sum[MT] = {}, comp[MT] = {};  // stage sums (even, odd); total
+  f32x4v acc0[MT] = {}, acc1[MT] = {}, sum[MT] = {}, off[MT] = {};  // stage sums (even, odd); total
 #pragma unroll
   for (int s = 0; s < R - 1; ++s) issue(rb(s), s);
   // (operands read where they are used: a chunk has few stages)
@@ -844,7 +864,7 @@ __global__ __launch_bounds__(kPfThreads, 2) void sm_down_kernel(PfArgs a) {
         sm_mfma<T, MT>(x, b, cur, h == 0 && t == 0);
       }
     }
-    sm_fold(sum, comp, prv);
+    sm_fold(sum, off, prv);
     __builtin_amdgcn_sched_barrier(0);
   };
   for (int s0 = 0; s0 < S; s0 += R) {
@@ -857,7 +877,8 @@ __global__ __launch_bounds__(kPfThreads, 2) void sm_down_kernel(PfArgs a) {
       step(s0 + 5, 5, acc1, acc0);
     }
   }
-  sm_fold(sum, comp, acc1);  // (rounds end on an odd stage)
+  sm_fold(sum, off, acc1);  // (rounds end on an odd stage)
+  sm_total(sum, off);
   __builtin_amdgcn_s_waitcnt(0);
   const int c = n0 + 16 * w + l16;
 #pragma unroll

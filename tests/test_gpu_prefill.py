@@ -23,7 +23,7 @@ CASES = [
     (105, 2, 256, 1024, 256),
     (106, 3, 640, 1536, 257),    # k of 20 steps
     (107, 1, 2048, 6144, 700),
-    # widths of 16-byte rows only: p in two terms
+    # widths of 16-byte rows only: p in three terms
     (120, 2, 24, 41, 2),         # less than one step of k, less than one tile
     (121, 2, 264, 333, 7),
     (122, 1, 1000, 2730, 66),    # k ends in the first half of a weight stage
@@ -170,3 +170,48 @@ def test_captured_prompts_keep_their_buffers():
                 g.replay()
                 torch.cuda.synchronize()
                 np.testing.assert_array_equal(from_dev(o[:n]), y)
+
+
+@pytest.mark.parametrize("dtype,d,n", [("f32", 260, 5), ("f32", 260, 40), ("bf16", 264, 7), ("bf16", 264, 70)])
+@pytest.mark.parametrize("where", ["gate", "gate product", "p", "p rounds up", "y"])
+def test_an_overflow_stays_an_infinity(dtype, d, n, where):
+    """Sums past float32's range are infinite, as in the compacted kernels (same keep
+    sets, same outputs bit for bit: one row and one neuron carry the values, so no
+    order of summation matters), and p between the largest bf16 and the largest
+    float32 stays finite."""
+    import torch
+    import paper_2607_08991_amd as sats
+    dff, dt = 333, torch.float32 if dtype == "f32" else torch.bfloat16
+    x = torch.zeros((n, d), dtype=dt, device="cuda")
+    wg, wu, wd = (torch.zeros((dff, d), dtype=dt, device="cuda") for _ in range(3))
+    j, r = 201, n - 2                       # the neuron and the row
+    x[r, :] = 2.0 ** 32
+    wg[j, 0] = 2.0 ** 33                    # a = 2^65
+    wd[j, :] = 2.0 ** -10
+    if where == "gate":                     # ten terms of 2^125
+        wg[j, :10] = 2.0 ** 93
+        wu[j, 0] = 2.0 ** -40
+    elif where == "gate product":
+        wg[j, 7] = 2.0 ** 97
+        wu[j, 0] = 2.0 ** -40
+    elif where == "p":
+        wu[j, :] = 2.0 ** 32
+    elif where == "p rounds up":            # 1.998046875 2^127: bf16 ends at 1.9921875 2^127
+        wu[j, 0], wu[j, 1] = 255 / 128 * 2.0 ** 30, 1.5 * 2.0 ** 22
+    else:
+        wu[j, 0] = 2.0 ** 28                # p = 2^125
+        wd[j, :] = 2.0 ** 10
+    thr = torch.ones(1, device="cuda")
+    got = []
+    for path in (sats.SATS_BATCH_AUTO, sats.SATS_BATCH_COMPACT):
+        out = torch.empty_like(x)
+        cnt = torch.empty((1, n), dtype=torch.int32, device="cuda")
+        with sats.options(batch_path=path):
+            sats.sats_mlp_forward_inspect(x, None, wg, wu, wd, thr, None, out, n, d, dff, 1, active_count=cnt)
+        torch.cuda.synchronize()
+        got.append((from_dev(out), cnt.cpu().numpy()))
+        want = 255.75 / 128 * 2.0 ** 117 if where == "p rounds up" else np.inf
+        assert (out[r].float().cpu().numpy() == np.float32(torch.tensor(want).to(dt).float())).all(), (path, out[r, :4])
+        assert cnt[0, r].item() == 1
+    np.testing.assert_array_equal(got[0][0], got[1][0])
+    np.testing.assert_array_equal(got[0][1], got[1][1])
