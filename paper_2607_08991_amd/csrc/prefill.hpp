@@ -685,9 +685,11 @@ __global__ __launch_bounds__(kPfThreads, 2) void sm_gateup_kernel(PfArgs a, int 
   // (the call input is read as it is, a row's 64 bytes by four lanes, into the same LDS layout)
   const bool direct = a.x != nullptr;
   const int am = w / 2 * 16 + (lane >> 2), ak = 64 * (w & 1) + 16 * ((lane & 3) ^ pf_swz(lane >> 2));
-  const uint32_t aoff = w / 2 >= MT || am >= a.n ? kDenseOffNone
-                        : direct                 ? (uint32_t)(am * K * E + ak)
-                                                 : (uint32_t)((w / 2 * nb + (w & 1)) * 1024 + 16 * lane);
+  // (24-bit products and selects, no branch: a 64-bit multiply-add in a branch here took the
+  // register that the id's load was still writing, and so waited for it before the first stage)
+  const uint32_t adir = __umul24((uint32_t)am, (uint32_t)(K * E)) + (uint32_t)ak;
+  const uint32_t ablk = (__umul24((uint32_t)(w / 2), (uint32_t)nb) + (uint32_t)(w & 1)) * 1024u + 16u * lane;
+  const uint32_t aoff = (w / 2 < MT) & (am < a.n) ? (direct ? adir : ablk) : kDenseOffNone;
   const uint32_t astep = direct ? 128u : 2048u;
   const __amdgpu_buffer_rsrc_t rsa = dense_rsrc(direct ? (const void *)a.x : (const void *)a.A,
                                                 direct ? (uint32_t)(a.n * K * E) : (uint32_t)(rows16 * nb * 1024));
