@@ -82,6 +82,8 @@ struct PfArgs {
   const uint8_t *lut;
   int route_mode;
   uint8_t *keep_out;      // optional [n][N] keep flags
+  uint16_t *kept;         // few float32 rows, else null: bit c mod 16 of word c / 16 is set where some row keeps
+                          // column c (written by gate/up for down, which reads up to 32 words of 32 past the last)
   int n, K, N;            // rows; reduction length; output columns
   int mtiles, units;      // row tiles; column tiles (times k chunks, down)
   int ks, kchunk;         // down: k chunks and their length (a multiple of 32)
@@ -754,6 +756,8 @@ __global__ __launch_bounds__(kPfThreads, 2) void sm_gateup_kernel(PfArgs a, int 
   const float thr = a.thr ? *a.thr : 0.0f;
   const int flag = a.route_mode == ROUTE_BASE || rflag != 0;
   const int c0 = n0 + 16 * ct;
+  constexpr bool KEPT = E == 4 && MT == 1;  // (see sm_down_kernel)
+  bool any = false;                         // some row keeps column c0 + l16
 #pragma unroll
   for (int i = 0; i < MT; ++i) {
     const f32x4v gv = reinterpret_cast<const f32x4v *>(xt)[i * 64 + lane];
@@ -761,11 +765,18 @@ __global__ __launch_bounds__(kPfThreads, 2) void sm_gateup_kernel(PfArgs a, int 
     for (int r = 0; r < 4; ++r) {
       const int m = 16 * i + 4 * g + r, c = c0 + l16;
       const bool keep = __shfl(flag, m, 64) || fabsf(gv[r]) >= thr;
+      if constexpr (KEPT) any = any || (keep && m < a.n);
       *reinterpret_cast<float *>(xt + i * 1024 + (4 * g + r) * 64 + l16 * 4) = keep ? gv[r] * sum[i][r] : 0.0f;
       if (a.keep_out && m < a.n && c < N) a.keep_out[(size_t)m * N + c] = (uint8_t)keep;
     }
   }
   if constexpr (E == 4) {  // a tile is a row block: lane's row and 4 columns
+    if constexpr (KEPT) {
+      uint64_t b = __ballot(any);
+      b |= b >> 32;
+      b |= b >> 16;
+      if (a.kept && lane == 0 && c0 < N) a.kept[c0 >> 4] = (uint16_t)b;
+    }
     const int r = lane >> 2, q = lane & 3, nbp = (N + 15) / 16;
 #pragma unroll
     for (int i = 0; i < MT; ++i)
@@ -788,11 +799,19 @@ __global__ __launch_bounds__(kPfThreads, 2) void sm_gateup_kernel(PfArgs a, int 
   }
 }
 
+typedef const __attribute__((address_space(4))) uint32_t *ConstWords;  // not written during the kernel
+
 // 128 columns of one k chunk: wavefront w columns 16 w .. 16 w + 15.  A stage
 // holds 16 KB of W_down (64 rows, float32: 32) and the blocks of p of its k:
 // three terms of two blocks per row tile (float32: one).
-template <typename T, int MT>
+//
+// FLAGS: W_down rows that no row of the batch keeps are not read (as in
+// dense_down_kernel and the compacted kernels) but for the first two stages,
+// which are on their way while the flags come.  A stage's rows are one word of
+// flags, loaded a round of R stages ahead.
+template <typename T, int MT, bool FLAGS = false>
 __global__ __launch_bounds__(kPfThreads, 2) void sm_down_kernel(PfArgs a) {
+  static_assert(!FLAGS || sizeof(T) == 4, "a word of flags per stage of 32 rows");
   constexpr int E = sizeof(T), KB = 64 / E, KS = 2 * KB, NP = E == 2 ? 3 : 1;  // k of a block and a stage; terms of p
   constexpr int IP = (2 * NP * MT + 7) / 8;                  // loads of p per wavefront and stage (2 NP MT KB)
   constexpr int SW = 16 * 1024, SB = SW + IP * 8 * 1024, R = SB <= 24 * 1024 ? 6 : 4, IS = 2 + IP;
@@ -829,12 +848,21 @@ __global__ __launch_bounds__(kPfThreads, 2) void sm_down_kernel(PfArgs a) {
     const int i = w + 8 * q, t = i / 2 % MT;
     aoff[q] = i < 2 * NP * MT && t < rows16 ? (uint32_t)((t * nbp + kb / KB + (i & 1)) * 1024 + 16 * lane) : kDenseOffNone;
   }
-  auto issue = [&](uint8_t *buf, int s) {
+  // flags of the rows of stages s .. s + R - 1 (scalar loads, which the waits for the
+  // stages' loads do not count; those past the last column are not looked at: `left`)
+  const ConstWords fw = (ConstWords)(uintptr_t)a.kept + kb / KS;
+  auto flags = [&](uint32_t(&f)[R], int s) {
+#pragma unroll
+    for (int i = 0; i < R; ++i) f[i] = FLAGS ? fw[s + i] : ~0u;
+  };
+  auto issue = [&](uint8_t *buf, int s, uint32_t f) {
     const int left = ke - kb - KS * s;
 #pragma unroll
-    for (int q = 0; q < 2; ++q)
-      pf_dma(rsw, buf + (w + 8 * q) * 1024, wr + 8 * RPL * q < left ? woff[q] : kDenseOffNone,
-             (uint32_t)s * (uint32_t)(KS * E * N));
+    for (int q = 0; q < 2; ++q) {
+      const int r = wr + 8 * RPL * q;
+      const bool on = r < left && (!FLAGS || (f >> (r & 31) & 1u));
+      pf_dma(rsw, buf + (w + 8 * q) * 1024, on ? woff[q] : kDenseOffNone, (uint32_t)s * (uint32_t)(KS * E * N));
+    }
 #pragma unroll
     for (int q = 0; q < IP; ++q)
       pf_dma(dense_rsrc(a.A + min((w + 8 * q) / (2 * MT), NP - 1) * a.pterm, pbytes), buf + SW + (w + 8 * q) * 1024,
@@ -842,11 +870,16 @@ __global__ __launch_bounds__(kPfThreads, 2) void sm_down_kernel(PfArgs a) {
   };
   f32x4v acc0[MT] = {}, acc1[MT] = {}, sum[MT] = {}, off[MT] = {};  // stage sums (even, odd); total
 #pragma unroll
-  for (int s = 0; s < R - 1; ++s) issue(rb(s), s);
+  for (int s = 0; s < 2; ++s) issue(rb(s), s, ~0u);
+  uint32_t fl[R], fn[R];  // of the stages that this round and the next one load
+  flags(fn, 0);
+#pragma unroll
+  for (int s = 2; s < R - 1; ++s) issue(rb(s), s, fn[s]);
+  flags(fl, R - 1);
   // (operands read where they are used: a chunk has few stages)
   auto step = [&](int s, int p, f32x4v(&cur)[MT], const f32x4v(&prv)[MT]) {
     pf_barrier<(R - 2) * IS>();
-    issue(rb(p + R - 1), s + R - 1);
+    issue(rb(p + R - 1), s + R - 1, fl[p]);
     uint8_t *buf = rb(p);
 #pragma unroll
     for (int h = 0; h < 2; ++h) {
@@ -870,6 +903,7 @@ __global__ __launch_bounds__(kPfThreads, 2) void sm_down_kernel(PfArgs a) {
     __builtin_amdgcn_sched_barrier(0);
   };
   for (int s0 = 0; s0 < S; s0 += R) {
+    flags(fn, s0 + 2 * R - 1);
     step(s0, 0, acc0, acc1);
     step(s0 + 1, 1, acc1, acc0);
     step(s0 + 2, 2, acc0, acc1);
@@ -878,6 +912,8 @@ __global__ __launch_bounds__(kPfThreads, 2) void sm_down_kernel(PfArgs a) {
       step(s0 + 4, 4, acc0, acc1);
       step(s0 + 5, 5, acc1, acc0);
     }
+#pragma unroll
+    for (int i = 0; i < R; ++i) fl[i] = fn[i];
   }
   sm_fold(sum, off, acc1);  // (rounds end on an odd stage)
   sm_total(sum, off);

@@ -368,6 +368,7 @@ struct PfBuffers {
   float *part;           // [ks][np][d]
   uint8_t *gbase;        // [np], whole tiles of 256
   uint8_t *keep;         // [np][d_ff] keep flags (inspection)
+  uint16_t *kept;        // float32: a bit per column (PfArgs)
   uint16_t *ext, *bgt;   // LoRA: further k of h in row blocks, B_gate^T
   float *vpart, *zpart;  // LoRA: chunk partials of h A, partials [kPfZChunks][np][rank] of p A_down
 };
@@ -382,6 +383,7 @@ size_t pf_layout(char *base, int64_t np, int ks, int64_t d, int64_t d_ff, int es
   t.gbase = c.take<uint8_t>((np + 255) / 256 * 256);
   t.part = c.take<float>((int64_t)ks * np * d);
   t.keep = c.take<uint8_t>(np * d_ff);
+  if (esz == 4) t.kept = c.take<uint16_t>((d_ff + 31) / 32 * 2 + 64);
   if (rank > 0) {
     t.ext = c.take<uint16_t>(pf_block_bytes(np, 4 * rank, 2) / 2);
     t.bgt = c.take<uint16_t>(d_ff * rank);
@@ -456,9 +458,18 @@ template <typename T> SmGateup sm_gateup_fn(int np) {
   return mt <= 1 ? sm_gateup_kernel<T, 1> : mt == 2 ? sm_gateup_kernel<T, 2>
                                         : mt == 3   ? sm_gateup_kernel<T, 3> : sm_gateup_kernel<T, 4>;
 }
-template <typename T> PfKernel sm_down_fn(int np) {
+// Whether the float32 down launch leaves out the W_down rows that no row keeps: few
+// rows, and a matrix that takes longer to read than its chunks' stages to work off.
+// (Qwen3-8B layer, 2 tokens with 90 % of the columns removed: 104 us, 115 with every row
+// read, the compacted kernels 103; 70 %: 111, 121, 124; half: 115, 122, 142.  Llama-3.1-8B
+// layer, 2 tokens: 130, 142, 118 at 90 %, 139, 151, 144 at 70 %.  2048 x 8192: 42, 44, 61.
+// 16 tokens gain nothing at 70 % and lose 1 us; 3 tokens of 512 x 8192 take 23.9, 23.1 without.)
+bool pf_flags(int np, int64_t d, int64_t d_ff) { return np <= 8 && d * d_ff >= (8 << 20); }
+template <typename T> PfKernel sm_down_fn(int np, bool flags) {
   using namespace sats;
   const int mt = (np + 15) / 16;
+  if constexpr (sizeof(T) == 4)
+    if (flags) return sm_down_kernel<T, 1, true>;
   return mt <= 1 ? sm_down_kernel<T, 1> : mt == 2 ? sm_down_kernel<T, 2>
                                       : mt == 3   ? sm_down_kernel<T, 3> : sm_down_kernel<T, 4>;
 }
@@ -775,6 +786,8 @@ template <typename T> int run_prefill(const Call &c, char *mem, unsigned *counte
   }
   PfArgs a{};
   a.n = np;
+  const bool flags = esz == 4 && pf_flags(np, d, d_ff);
+  a.kept = flags ? b.kept : nullptr;
   for (int64_t l = 0; l < c.L; ++l) {
     PfArgs u = a;
     u.A = reinterpret_cast<const uint16_t *>(b.h);
@@ -841,7 +854,7 @@ template <typename T> int run_prefill(const Call &c, char *mem, unsigned *counte
     w.kchunk = p.kchunk;
     if (p.small) {
       TimedLaunch tl(SATS_K_DENSE_DOWN, c.stream);
-      hipExtLaunchKernelGGL(sm_down_fn<T>(np), dim3((unsigned)((d + 127) / 128 * p.ks)), dim3(kPfThreads), 0, c.stream,
+      hipExtLaunchKernelGGL(sm_down_fn<T>(np, flags), dim3((unsigned)((d + 127) / 128 * p.ks)), dim3(kPfThreads), 0, c.stream,
                             tl.start, tl.stop, 0, w);
     } else {
       w.mtiles = (np + p.dbm - 1) / p.dbm;

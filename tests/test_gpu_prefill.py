@@ -215,3 +215,44 @@ def test_an_overflow_stays_an_infinity(dtype, d, n, where):
         assert cnt[0, r].item() == 1
     np.testing.assert_array_equal(got[0][0], got[1][0])
     np.testing.assert_array_equal(got[0][1], got[1][1])
+
+
+@pytest.mark.parametrize("d,dff,n,level", [(4096, 4096, 2, 0.9), (4096, 4096, 3, 0.97), (512, 16400, 5, 0.95),
+                                           (1028, 9001, 8, 0.97), (512, 17001, 6, 0.5), (4096, 2048, 2, None)])
+def test_float32_batches_read_no_row_that_nothing_keeps(d, dff, n, level):
+    """W_down rows that no token keeps are not read (NaN there changes no bit) but for
+    the first two stages (64 rows) of a workgroup's chunk, which are loaded before the
+    flags are there; every kept row counts (float64 sums over the call's keep sets)."""
+    import torch
+    import paper_2607_08991_amd as sats
+    print(f"float32 rows nothing keeps d={d} d_ff={dff} n={n} level={level}", flush=True)
+    g = torch.Generator(device="cuda")
+    g.manual_seed(d + dff + n)
+    x = torch.randn((n, d), generator=g, device="cuda")
+    wg, wu, wd = (torch.randn((dff, d), generator=g, device="cuda") / d ** 0.5 for _ in range(3))
+    a = x.double() @ wg.double().T
+    p = a * torch.sigmoid(a) * (x.double() @ wu.double().T)
+    mag = (a * torch.sigmoid(a)).abs().reshape(-1)
+    thr = torch.tensor([np.inf if level is None else float(torch.quantile(mag[:1 << 20], level))], device="cuda").float()
+
+    def call(w):
+        out, cnt = torch.empty_like(x), torch.empty((1, n), dtype=torch.int32, device="cuda")
+        idx = torch.empty((1, n, dff), dtype=torch.int32, device="cuda")
+        sats.sats_mlp_forward_inspect(x, None, wg, wu, w, thr, None, out, n, d, dff, 1, active_count=cnt, active_idx=idx)
+        torch.cuda.synchronize()
+        keep = torch.zeros((n, dff), dtype=torch.bool, device="cuda")
+        for m in range(n):
+            keep[m, idx[0, m, :int(cnt[0, m])].long()] = True
+        return out, keep
+
+    out, keep = call(wd)
+    y = (p * keep) @ wd.double()
+    assert float((out - y).abs().max()) <= 1e-5 * max(float(y.abs().max()), 1e-30)
+    # d_ff in chunks of whole stages of 32 rows, a workgroup per compute unit and 128 columns, at most 16
+    cus = torch.cuda.get_device_properties(0).multi_processor_count
+    chunk = -(-dff // min(16, max(1, cus // -(-d // 128)))) + 31 & -32
+    rows = ~keep.any(0) & (torch.arange(dff, device="cuda") % chunk >= 64)
+    assert int(rows.sum()) > dff // 100
+    poisoned = wd.clone()
+    poisoned[rows] = float("nan")
+    np.testing.assert_array_equal(from_dev(call(poisoned)[0]), from_dev(out))
