@@ -747,30 +747,33 @@ __device__ __forceinline__ int ct_pos(int r, int q) { return q ^ (r & 7); }
 // PACK = calibration rows per A tile: 1 (15 candidates and y), 2 (up to 7
 // candidates and y), or 4 (up to 4 candidates, no y row: ||y||^2 comes from
 // an earlier product).  ROWS = calibration rows per workgroup: 16, or with
-// PACK 4, whose tiles hold a quarter of the products per operand, 64
+// PACK 4, whose tiles hold a quarter of the products per operand, also 64
 // (wavefront w rows 8 w .. + 7 over all 128 columns) or 32 (rows 8 (w & 3) ..
 // + 7 over the 64 columns of half w >> 2, sums of squares to part tile
-// 2 blockIdx.x + (w >> 2)).  At 32 the operand reads bound it (LDS: 1360
-// cycles per 1024 of products a stage); 64 needs the rows to fill the chip.
-// The last 4 of 19 candidates of 1024 rows of a Llama-3.1-8B layer: 832 us at
-// 32, 676 at 64.
+// 2 blockIdx.x + (w >> 2); 16 rows likewise, 4 a wavefront).  At 32 the operand
+// reads bound it (LDS: 1360 cycles per 1024 of products a stage); 64 needs the
+// rows to fill the chip, and with few rows a workgroup's own chain of stages is
+// the time, which grows with them.  The last 4 of 19 candidates of a
+// Llama-3.1-8B layer, 1024 rows: 832 us at 32, 676 at 64; 16 to 64 rows:
+// 182 us at 32, 107 at 16; 160 rows 185 and 221.
 template <int PACK, int ROWS>
 __global__ __launch_bounds__(kDenseThreads) void cal_err_kernel(CalErrArgs a) {
-  static_assert((PACK != 4 && ROWS == 16) || (PACK == 4 && (ROWS == 32 || ROWS == 64)), "rows per A tile and workgroup");
-  constexpr bool HALVES = PACK == 4 && ROWS == 32;  // a wavefront takes half of the columns
+  static_assert(ROWS == 16 || (PACK == 4 && (ROWS == 32 || ROWS == 64)), "rows per A tile and workgroup");
+  constexpr bool WIDE = ROWS > 16;                  // the loads of its rows
+  constexpr bool HALVES = PACK == 4 && ROWS <= 32;  // a wavefront takes half of the columns
   constexpr int LO = 16384 + ROWS * 128, CN = LO + ROWS * 128;  // offsets of lo and c in a stage
-  constexpr int SB = PACK == 4 ? CN + ROWS * 64 : kDenseStageBytes;  // its bytes
-  constexpr int NL = PACK != 4 ? 3 : ROWS == 32 ? 4 : 5, R = ROWS == 64 ? 4 : 6;     // loads per wavefront; ring stages
+  constexpr int SB = WIDE ? CN + ROWS * 64 : kDenseStageBytes;  // its bytes
+  constexpr int NL = !WIDE ? 3 : ROWS == 32 ? 4 : 5, R = ROWS == 64 ? 4 : 6;     // loads per wavefront; ring stages
   __shared__ __attribute__((aligned(1024))) uint8_t rg0[SB], rg1[SB], rg2[SB], rg3[SB],
-      rg4[R > 4 ? SB : 16], rg5[R > 4 ? SB : 16], spare[PACK == 4 ? 1024 : 16];
+      rg4[R > 4 ? SB : 16], rg5[R > 4 ? SB : 16], spare[WIDE ? 1024 : 16];
   (void)spare;
   constexpr int CT = kDenseDownNT / 16 / (HALVES ? 2 : 1);  // column tiles of 16 per wavefront
-  constexpr int NA = PACK == 4 ? 2 : 2 / PACK;                 // A tiles per wavefront
+  constexpr int NA = WIDE ? 2 : PACK == 4 ? 1 : 2 / PACK;      // A tiles per wavefront
   constexpr int RPT = 16 / PACK;                               // A rows per calibration row
   constexpr bool Y = PACK != 4;                                // the last of them is y
   const int lane = threadIdx.x & 63, w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int ch = HALVES ? w >> 2 : 0;  // column half
-  const int wrow = PACK == 4 ? 8 * (HALVES ? w & 3 : w) : 2 * w;  // the wavefront's first row
+  const int wrow = PACK == 4 ? 4 * NA * (HALVES ? w & 3 : w) : 2 * w;  // the wavefront's first row
   const int g = lane >> 4, l16 = lane & 15;
   const int n0 = blockIdx.x * kDenseDownNT, m0 = blockIdx.y * ROWS;
   const int K = a.d_ff;
@@ -797,13 +800,13 @@ __global__ __launch_bounds__(kDenseThreads) void cal_err_kernel(CalErrArgs a) {
   const int ar = 8 * (w % HW) + (lane >> 3), aq = lane & 7;
   const bool arv = m0 + ar < a.n;
   const uint32_t oa = (uint32_t)(((size_t)(m0 + ar) * K + 8 * aq) * 2);
-  const int cr = (PACK == 4 ? 16 * (w % CW) : 0) + (lane >> 2), cq = lane & 3;
+  const int cr = (WIDE ? 16 * (w % CW) : 0) + (lane >> 2), cq = lane & 3;
   const uint32_t oc = (uint32_t)((size_t)(m0 + cr) * K + 16 * cq);
   const uint32_t sk = kDenseKC * 2;
-  const bool c4 = PACK != 4 && w >= 4;  // the third load is of c
-  const bool crv = m0 + cr < a.n && (PACK == 4 ? w < CW : w == 4);
+  const bool c4 = !WIDE && w >= 4;  // the third load is of c
+  const bool crv = m0 + cr < a.n && (WIDE ? w < CW : w == 4);
   const __amdgpu_buffer_rsrc_t r3 = c4 ? rsc : (w < HW ? rsh : rsl);
-  const int d3 = PACK == 4 || w < 4 ? 16384 + w * 1024 : CN + (w - 4) * 1024;
+  const int d3 = WIDE || w < 4 ? 16384 + w * 1024 : CN + (w - 4) * 1024;
   const bool v3 = c4 ? crv : arv;
   const uint32_t o3 = c4 ? oc : oa, st3 = c4 ? (uint32_t)kDenseKC : sk;
   // A row of this lane: calibration row wrow + t (tile t; PACK 4: + 4 t +
@@ -880,7 +883,7 @@ __global__ __launch_bounds__(kDenseThreads) void cal_err_kernel(CalErrArgs a) {
     dma16<0>(r3, (BUF) + d3, dense_off(v_ && v3, o3 + ss_ * st3, 2));                        \
     if constexpr (ROWS == 64)                                                                \
       dma16<0>(rsl, (BUF) + LO + w * 1024, dense_off(v_ && arv, oa + ss_ * sk, 4));          \
-    if constexpr (PACK == 4)                                                                 \
+    if constexpr (WIDE)                                                                      \
       dma16<0>(rsc, w < CW ? (BUF) + CN + w * 1024 : spare, dense_off(v_ && crv, oc + ss_ * (uint32_t)kDenseKC, 3)); \
   }
   // step s: wait until stage s + 1 has landed (the loads of s + 2 .. s + R - 2
@@ -892,7 +895,7 @@ __global__ __launch_bounds__(kDenseThreads) void cal_err_kernel(CalErrArgs a) {
 #define SATS_CE_STEP(CUR, NXT, FREE, P)                                                      \
   {                                                                                          \
     const int s_ = s0_ + (P);                                                                \
-    dense_stage_barrier<(R - 3) * NL>();                                                                \
+    dense_stage_barrier<(R - 3) * NL>();                                                      \
     SATS_CE_ISSUE(FREE, s_ + R - 1);                                                             \
     if (s_ < S) {                                                                            \
       load_ops((CUR), 1, ah1, al1, bq1);                                                     \

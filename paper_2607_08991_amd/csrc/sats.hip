@@ -1648,13 +1648,17 @@ int cal_curves(CalBuffers &cb, const uint16_t *Wd, int64_t n, int64_t d, int64_t
         ce.d_ff = (int)d_ff;
         // at most 4 candidates and ||y||^2 known: four calibration rows per
         // MFMA tile, no y row, in workgroups of 64 rows where those fill the
-        // chip, else of 32; at most 7: two per tile
+        // chip, of 16 where all of those run at once, else of 32; at most 7:
+        // two per tile
         const int64_t ctiles = d / kDenseDownNT;
-        const bool r64 = pack4 && (n + 63) / 64 * ctiles >= std::max(1, device_cus());
-        const int rows = !pack4 ? 16 : r64 ? 64 : 32;
+        const int64_t cus = std::max(1, device_cus());
+        const bool r16 = pack4 && (n + 15) / 16 * ctiles <= cus;
+        const bool r64 = pack4 && !r16 && (n + 63) / 64 * ctiles >= cus;
+        const int rows = !pack4 || r16 ? 16 : r64 ? 64 : 32;
         {
           TimedLaunch tl(SATS_K_CAL_ERR, s);
           hipExtLaunchKernelGGL(r64       ? cal_err_kernel<4, 64>
+                                : r16     ? cal_err_kernel<4, 16>
                                 : pack4   ? cal_err_kernel<4, 32>
                                 : kc <= 7 ? cal_err_kernel<2, 16>
                                           : cal_err_kernel<1, 16>,

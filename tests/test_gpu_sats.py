@@ -241,3 +241,10 @@ def test_four_candidate_product_of_64_row_workgroups(n):
     np.testing.assert_array_equal(sp[16:], sp4)
     np.testing.assert_allclose(rows[:, 16:].cpu().numpy(), tail.cpu().numpy(), rtol=4e-6)
     np.testing.assert_allclose(err[16:], err4, rtol=1e-6)
+
+
+@pytest.mark.parametrize("n", [1, 16, 17, 128, 129])
+def test_four_candidate_product_of_few_rows(n):
+    """... in workgroups of 16 rows, while all of them run at once (128 rows at this
+    width on 256 compute units), and of 32 beyond."""
+    test_four_candidate_product_of_64_row_workgroups(n)
