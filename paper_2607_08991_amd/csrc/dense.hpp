@@ -155,6 +155,14 @@ struct DenseArgs {
   const uint16_t *Wnext;
   int nks, nchunk, nN;    // its k chunks, their length, its columns
   int hcap;               // rows of H allocated (the first stages read them all, before the group's size is known)
+  // gate/up, CAL: g = SiLU(a) in float32, [rows][N], and p = g u as two bf16 terms, hi = rne(p),
+  // lo = rne(p - hi).  Passes of 64 rows in one launch: workgroup b takes column tile
+  // (b / 8 / cal_passes) * 8 + b % 8 and pass (b / 8) % cal_passes, so that the passes of a
+  // tile run at once on one XCD (workgroup b on XCD b mod 8) and read its weights through
+  // that XCD's L2; tiles past cal_tiles return
+  float *cal_g;
+  uint16_t *cal_ph, *cal_pl;
+  int cal_passes, cal_tiles;
   // LoRA adapters of the sparse path (gate/up with LORA): lv [2][kDenseMaxTokens][rank]
   // = s (h A_gate), s (h A_up) per group row; B_gate [rank][N], B_up_T [N][rank] and
   // A_down [N][rank] of the layer; zpart [tiles][kDenseMaxTokens][rank]: per column
@@ -334,9 +342,10 @@ __device__ __forceinline__ f32x4v mfma16(const bf16x8 &a, const bf16x8 &b, const
 // loop is on its way when the first is waited for (36 Qwen3-8B layers at 4
 // tokens: 2.112 ms with the first look waited for after two stages, 2.079 so; 2.085
 // with a route launch in front instead).
-enum { GU_GROUP, GU_LORA, GU_DIRECT, GU_AHEAD };  // GROUP: rows, flags by ctl and gbase; LORA: so, with adapters;
-                                                  // DIRECT: `rows` rows, their flags by ids and lut; AHEAD: so, and
-                                                  // the first rows of W_down for the launch that follows
+enum { GU_GROUP, GU_LORA,     // GROUP: rows, flags by ctl and gbase; LORA: so, with adapters;
+       GU_DIRECT, GU_AHEAD,   // DIRECT: `rows` rows, their flags by ids and lut; AHEAD: so, and
+                              // the first rows of W_down for the launch that follows
+       GU_CAL };              // `rows` calibration rows (no keep rule)
 template <int MT, int MODE>
 __global__ __launch_bounds__(kDenseThreads) void dense_gateup_kernel(DenseArgs a) {
   constexpr int NB = MT == 1 ? 8 : 6, SB = MT == 1 ? 18 * 1024 : kDenseStageBytes;  // ring stages and their bytes
@@ -346,8 +355,20 @@ __global__ __launch_bounds__(kDenseThreads) void dense_gateup_kernel(DenseArgs a
   uint8_t *const rg6 = ring + (NB > 6 ? 6 : 0) * SB, *const rg7 = ring + (NB > 7 ? 7 : 0) * SB;
   (void)rg6;
   (void)rg7;
-  const int tile = blockIdx.x;
-  constexpr bool LORA = MODE == GU_LORA, DIRECT = MODE >= GU_DIRECT;
+  int tile = blockIdx.x;
+  constexpr bool LORA = MODE == GU_LORA, CAL = MODE == GU_CAL, DIRECT = MODE >= GU_DIRECT;
+  if constexpr (CAL) {
+    const int j = blockIdx.x >> 3, pass = j % a.cal_passes;
+    tile = (j / a.cal_passes) * 8 + (blockIdx.x & 7);
+    if (tile >= a.cal_tiles) return;
+    const int first = pass * kDenseMaxTokens;
+    a.H += (size_t)first * a.K;
+    a.rows -= first;
+    a.hcap -= first;
+    a.cal_g += (size_t)first * a.N;
+    a.cal_ph += (size_t)first * a.N;
+    a.cal_pl += (size_t)first * a.N;
+  }
   // the group's control words are read while the first two stages load
   // (every allocated row of H: rows past the group feed only results that
   // are not stored); a workgroup of an empty group then waits for its loads
@@ -356,7 +377,7 @@ __global__ __launch_bounds__(kDenseThreads) void dense_gateup_kernel(DenseArgs a
   int nd = DIRECT ? min(a.rows, 16 * MT) : 16 * MT;
   const int lane = threadIdx.x & 63, w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   int rid = 0, rflag = 0;  // DIRECT: the route of row `lane`
-  if constexpr (DIRECT) rid = route_id(a.route_mode, a.ids, a.rows, lane);
+  if constexpr (DIRECT && !CAL) rid = route_id(a.route_mode, a.ids, a.rows, lane);
   const int mat = w >> 2, g = lane >> 4, l16 = lane & 15, c = 16 * (w & 3) + l16;
   const int n0 = tile * a.nt;
   const int K = a.K, N = a.N;
@@ -421,7 +442,7 @@ __global__ __launch_bounds__(kDenseThreads) void dense_gateup_kernel(DenseArgs a
     hv = dr < nd;                                                                            \
   }
 #define SATS_GU_FLAG                                                                         \
-  if constexpr (DIRECT) rflag = route_flag(a.route_mode, a.lut, rid)
+  if constexpr (DIRECT && !CAL) rflag = route_flag(a.route_mode, a.lut, rid)
   if constexpr (MT == 1) {
     SATS_DENSE_RING8_H(S, SATS_GU_ISSUE, SATS_GU_COMPUTE, SATS_GU_GROUP, SATS_GU_FLAG)
   } else {
@@ -517,6 +538,24 @@ __global__ __launch_bounds__(kDenseThreads) void dense_gateup_kernel(DenseArgs a
       for (int r = 0; r < 4; ++r) xs[(16 * mt + 4 * g + r) * kDenseXP + c] = silu(acc[mt][r]);
   }
   __syncthreads();
+  if constexpr (CAL) {
+    if (mat == 1)
+#pragma unroll
+      for (int mt = 0; mt < MT; ++mt)
+#pragma unroll
+        for (int r = 0; r < 4; ++r) {
+          const int m = 16 * mt + 4 * g + r;
+          if (m < nd && c < ncol) {
+            const float gv = xs[m * kDenseXP + c], pv = gv * acc[mt][r];
+            const uint16_t hi = f32_to_bf16(pv);
+            const size_t o = (size_t)m * N + n0 + c;
+            a.cal_g[o] = gv;
+            a.cal_ph[o] = hi;
+            a.cal_pl[o] = f32_to_bf16(pv - bf16_to_f32(hi));
+          }
+        }
+    return;
+  }
   if (mat == 1) {
     const float thr = a.thr ? *a.thr : 0.0f;
     const int flag = a.route_mode == ROUTE_BASE || rflag != 0;  // of row `lane`

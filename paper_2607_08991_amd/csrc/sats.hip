@@ -1530,10 +1530,36 @@ int cal_check_shape(int64_t n, int64_t d, int64_t d_ff) {
 }
 
 // g and p of n calibration rows into G, ph, pl: the tiled gate/up product, up
-// to kPfMaxPass rows at a time.
+// to kPfMaxPass rows at a time, or the 64-row kernel where its passes over all
+// column tiles run at once: a tile of 128 rows takes its chain of k whatever
+// the rows, 61 us at d = 4096, and this one streams the weights (64 rows of a
+// Llama-3.1-8B layer 41 us; 100 rows are two rounds of it, 68 us, there 66).
 int cal_gate_up(const uint16_t *h, const uint16_t *Wg, const uint16_t *Wu, int64_t n, int64_t d, int64_t d_ff,
                 CalBuffers &cb, hipStream_t s) {
   using namespace sats;
+  const int nt = dense_tile_cols(d_ff);
+  const int64_t tiles = (d_ff + nt - 1) / nt, passes = (n + kDenseMaxTokens - 1) / kDenseMaxTokens;
+  if (tiles * passes <= std::max(1, device_cus())) {
+    DenseArgs a{};
+    a.rows = (int)n;
+    a.hcap = (int)n;
+    a.H = h;
+    a.Wg = Wg;
+    a.Wt = Wu;
+    a.K = (int)d;
+    a.N = (int)d_ff;
+    a.nt = nt;
+    a.cal_g = cb.G;
+    a.cal_ph = cb.ph;
+    a.cal_pl = cb.pl;
+    a.cal_passes = (int)passes;
+    a.cal_tiles = (int)tiles;
+    TimedLaunch tl(SATS_K_CAL_GATEUP, s);
+    hipExtLaunchKernelGGL((dense_gateup_kernel<4, GU_CAL>), dim3((unsigned)((tiles + 7) / 8 * 8 * passes)),
+                          dim3(kDenseThreads), 0, s, tl.start, tl.stop, 0, a);
+    HIP_TRY(hipGetLastError());
+    return SATS_OK;
+  }
   const int pass = pf_pass(n, 2);
   for (int64_t base = 0; base < n; base += pass) {
     const int np = (int)std::min<int64_t>(pass, n - base);
@@ -2380,7 +2406,7 @@ const char *sats_kernel_name(int kind) {
     case SATS_K_DEC_REDUCE: return "dec_reduce_kernel";
     case SATS_K_DEC_REDUCE_LORA: return "dec_reduce_lora_kernel";
     case SATS_K_CAL_ERR: return "cal_err_kernel";
-    case SATS_K_CAL_GATEUP: return "pf_gateup_kernel (calibration)";
+    case SATS_K_CAL_GATEUP: return "pf_gateup_kernel or dense_gateup_kernel (calibration)";
     default: return "";
   }
 }

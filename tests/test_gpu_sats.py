@@ -248,3 +248,30 @@ def test_four_candidate_product_of_few_rows(n):
     """... in workgroups of 16 rows, while all of them run at once (128 rows at this
     width on 256 compute units), and of 32 beyond."""
     test_four_candidate_product_of_64_row_workgroups(n)
+
+
+@pytest.mark.parametrize("seed,d,dff,n", [(71, 128, 512, 65), (72, 128, 4096, 1), (73, 128, 4096, 128),
+                                          (74, 128, 4096, 129), (75, 384, 4160, 300)])
+def test_gate_up_passes_of_64_and_tiles(seed, d, dff, n):
+    """Gate and up of the rows in passes of 64 while all of those run at once (128
+    rows of 4096 columns on 256 compute units), on the tiled product beyond.  As
+    test_curves_match_oracle, with a neuron near a threshold also where its g lies
+    within 4e-6: products of bf16 are exact in float32, and a running sum of
+    magnitude below 12 rounds by at most 6e-8 of that in each of its few steps (the
+    small thresholds of the low levels are reached by cancellation)."""
+    x, wg, wu, wd = _layer(seed, d, dff, n)
+    t, err, sp, er = _gpu_curves(x, wg, wu, wd, LEVELS20)
+    H, W = numerics.decode(x, "bf16"), [numerics.decode(w, "bf16") for w in (wg, wu, wd)]
+    g, p, y = osats.layer_terms(H, *W)
+    a, ny = np.abs(g), np.linalg.norm(y, axis=1)
+    flat = np.sort(a.reshape(-1))
+    for k, q in enumerate(LEVELS20):
+        assert abs(t[k] - calibrate.percentile_threshold(a, q)) <= 4e-6 + 1e-5 * t[k], (k, q)
+        near = np.abs(a - t[k]) <= 4e-6 + 1e-5 * t[k]
+        sure = (a < t[k]) & ~near
+        e = [np.linalg.norm(np.where(m, p, 0.0) @ W[2], axis=1) / (ny + 1e-6) for m in (sure, sure | near)]
+        # the removed set lies between the two: its product from each by at most the near neurons'
+        slack = np.linalg.norm(np.where(near, np.abs(p), 0.0) @ np.abs(W[2]), axis=1) / (ny + 1e-6) + 1e-4 * e[1] + 1e-6
+        assert (np.abs(er[:, k] - e[0]) <= slack).all(), (k, q)
+        assert abs(err[k] - er[:, k].mean()) <= 1e-5 * err[k] + 1e-7
+        assert abs(sp[k] - np.searchsorted(flat, t[k]) / flat.size) <= (near.sum() + 0.5) / flat.size
