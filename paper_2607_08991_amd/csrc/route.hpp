@@ -187,7 +187,10 @@ struct RoutePartArgs {
   unsigned *err;
 };
 
-template <bool DAMAGE>
+// MANY: per > 1.  (One chunk needs no count of the taken slots and no word of the
+// tables written: the part and merge launches of both splits, 2^20 and 2^18
+// occurrences of a 128256-id vocabulary, 39.2 us, with those 42.6.)
+template <bool DAMAGE, bool MANY>
 __global__ __launch_bounds__(kRouteThreads) void route_part_kernel(RoutePartArgs a) {
   __shared__ uint32_t skey[kRouteSlots];
   __shared__ uint32_t scnt[kRouteSlots];
@@ -198,36 +201,40 @@ __global__ __launch_bounds__(kRouteThreads) void route_part_kernel(RoutePartArgs
   static_assert(kRouteRanges == kRouteThreads, "one range per thread in the scan");
   constexpr int SPER = kRouteSlots / kRouteThreads;
   const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6;
-  const int64_t first = (int64_t)blockIdx.x * a.per * kRouteChunk;
-  const size_t nseg = (size_t)gridDim.x * a.per;
+  const int per = MANY ? a.per : 1;
+  const int64_t first = (int64_t)blockIdx.x * per * kRouteChunk;
+  const size_t nseg = (size_t)gridDim.x * per;
   u32x4 *const ce = a.ent + first;
   int32_t x[kRoutePer];
   float fs[kRoutePer], fb[kRoutePer];
   route_chunk_load<DAMAGE>(a.ids, a.lb, a.ls, a.n, first, x, fs, fb);
   route_table_clear<DAMAGE>(skey, scnt, ssum);
-  if (tid == 0) taken = 0u;
+  if (MANY && tid == 0) taken = 0u;
   uint32_t written = 0u;  // entries of the tables written
   int tab = 0;
-  for (int j = 0; j < a.per; ++j) {
+  for (int j = 0; j < per; ++j) {
     const int64_t base = first + (int64_t)j * kRouteChunk;
     if (base >= a.n) break;
-    const bool last = j + 1 == a.per || base + kRouteChunk >= a.n;
+    const bool last = j + 1 == per || base + kRouteChunk >= a.n;
     int32_t nx[kRoutePer];
     float ns[kRoutePer], nb[kRoutePer];
-    route_chunk_load<DAMAGE>(a.ids, a.lb, a.ls, last ? 0 : a.n, base + kRouteChunk, nx, ns, nb);
+    if constexpr (MANY) route_chunk_load<DAMAGE>(a.ids, a.lb, a.ls, last ? 0 : a.n, base + kRouteChunk, nx, ns, nb);
     hist[tid] = 0u;
     __syncthreads();
     int fresh = route_chunk_insert<DAMAGE>(a.vocab, a.err, a.n - base, x, fs, fb, skey, scnt, ssum);
+    if constexpr (MANY) {
 #pragma unroll
-    for (int o = 32; o >= 1; o >>= 1) fresh += __shfl_xor(fresh, o, 64);
-    if (lane == 0 && fresh) atomicAdd(&taken, (uint32_t)fresh);
+      for (int o = 32; o >= 1; o >>= 1) fresh += __shfl_xor(fresh, o, 64);
+      if (lane == 0 && fresh) atomicAdd(&taken, (uint32_t)fresh);
+    }
     __syncthreads();
+    if constexpr (MANY)
 #pragma unroll
-    for (int m = 0; m < kRoutePer; ++m) x[m] = nx[m], fs[m] = ns[m], fb[m] = nb[m];
+      for (int m = 0; m < kRoutePer; ++m) x[m] = nx[m], fs[m] = ns[m], fb[m] = nb[m];
     // another chunk goes into the table while at most a quarter of the slots is
     // taken: they are then at most three quarters full, and probes stay short
     // (with half, 2^22 occurrences without repeats took 1.8 ms, here 45 us)
-    if (!last && taken <= (uint32_t)kRouteFill) continue;
+    if (MANY && !last && taken <= (uint32_t)kRouteFill) continue;
 #pragma unroll
     for (int m = 0; m < SPER; ++m) {
       const uint32_t key = skey[tid + m * kRouteThreads];
@@ -251,7 +258,7 @@ __global__ __launch_bounds__(kRouteThreads) void route_part_kernel(RoutePartArgs
       total += wtot[q];
     }
     excl += written;
-    const size_t seg = (size_t)blockIdx.x * a.per + tab;
+    const size_t seg = (size_t)blockIdx.x * per + tab;
     if (tid < a.nr) a.off[(size_t)tid * nseg + seg] = excl;
     if (tid == kRouteThreads - 1) a.off[(size_t)a.nr * nseg + seg] = excl + hv;  // ranges past nr are empty
     hist[tid] = excl;  // the range's next free entry (every thread read its count above)
@@ -267,25 +274,25 @@ __global__ __launch_bounds__(kRouteThreads) void route_part_kernel(RoutePartArgs
     }
     written += total;
     ++tab;
-    if (last) break;
+    if (!MANY || last) break;
     __syncthreads();  // every thread is done with hist
     route_table_clear<DAMAGE>(skey, scnt, ssum);  // (a thread's own slots, which it has read)
     if (tid == 0) taken = 0u;
   }
-  if (tid == 0) a.tabs[blockIdx.x] = (unsigned)tab;
+  if (MANY && tid == 0) a.tabs[blockIdx.x] = (unsigned)tab;
 }
 
 struct RouteMergeArgs {
   const u32x4 *ent;
   const uint32_t *off;
-  const unsigned *tabs;
+  const unsigned *tabs;      // (per > 1)
   int blocks, per;           // workgroups of the part launch, chunks of each
   int rbits, nr, vocab, parts;
   unsigned *count;           // [parts][vocab]
   unsigned long long *sum;   // [parts][vocab] (DAMAGE)
 };
 
-template <bool DAMAGE>
+template <bool DAMAGE, bool MANY>
 __global__ __launch_bounds__(kRouteThreads) void route_merge_kernel(RouteMergeArgs a) {
   constexpr int WMAX = 1 << kRouteMaxRangeBits, U = 4;
   __shared__ uint32_t lc[WMAX];
@@ -298,15 +305,16 @@ __global__ __launch_bounds__(kRouteThreads) void route_merge_kernel(RouteMergeAr
   }
   __syncthreads();
   const int b0 = (int)((int64_t)p * a.blocks / a.parts), b1 = (int)((int64_t)(p + 1) * a.blocks / a.parts);
-  const size_t nseg = (size_t)a.blocks * a.per;
+  const int per = MANY ? a.per : 1;
+  const size_t nseg = (size_t)a.blocks * per;
   // a wavefront per table of the group's workgroups, first tables first
   const int nb = b1 - b0;
-  for (int t = wv; t < nb * a.per; t += kRouteThreads / 64) {
-    const int wg = b0 + t % nb, f = t / nb;
-    if ((unsigned)f >= a.tabs[wg]) continue;
-    const size_t c = (size_t)wg * a.per + f;
+  for (int t = wv; t < nb * per; t += kRouteThreads / 64) {
+    const int wg = b0 + (MANY ? t % nb : t), f = MANY ? t / nb : 0;
+    if (MANY && (unsigned)f >= a.tabs[wg]) continue;
+    const size_t c = (size_t)wg * per + f;
     const uint32_t b = a.off[(size_t)r * nseg + c], e = a.off[(size_t)(r + 1) * nseg + c];
-    const u32x4 *ce = a.ent + (size_t)wg * a.per * kRouteChunk;
+    const u32x4 *ce = a.ent + (size_t)wg * per * kRouteChunk;
     for (uint32_t j = b + lane; j < e; j += 64 * U) {
       u32x4 v[U];
 #pragma unroll

@@ -2018,14 +2018,18 @@ int route_build(const float *lb, const float *ls, const int32_t *ids, int64_t n,
       if (nn > 0) {
         RoutePartArgs pa{dmg ? ids : hids, lb, ls, nn, (int)vocab, rbits, nr, per[split], b.pent, b.poff, tabs, b.err};
         TimedLaunch tl(dmg ? SATS_K_ROUTE_ACCUM : -1, s);
-        hipExtLaunchKernelGGL(dmg ? route_part_kernel<true> : route_part_kernel<false>, dim3((unsigned)blocks[split]),
+        hipExtLaunchKernelGGL(per[split] > 1 ? (dmg ? route_part_kernel<true, true> : route_part_kernel<false, true>)
+                                             : (dmg ? route_part_kernel<true, false> : route_part_kernel<false, false>),
+                              dim3((unsigned)blocks[split]),
                               dim3(kRouteThreads), 0, s, tl.start, tl.stop, 0, pa);
         HIP_TRY(hipGetLastError());
       }
       RouteMergeArgs ma{b.pent, b.poff, tabs, (int)blocks[split], per[split], rbits, nr, (int)vocab, P,
                         dmg ? b.cnt : b.hcnt, b.sum};
       TimedLaunch tl(dmg ? SATS_K_ROUTE_MERGE : -1, s);
-      hipExtLaunchKernelGGL(dmg ? route_merge_kernel<true> : route_merge_kernel<false>, dim3(nr, P),
+      hipExtLaunchKernelGGL(per[split] > 1 ? (dmg ? route_merge_kernel<true, true> : route_merge_kernel<false, true>)
+                                           : (dmg ? route_merge_kernel<true, false> : route_merge_kernel<false, false>),
+                            dim3(nr, P),
                             dim3(kRouteThreads), 0, s, tl.start, tl.stop, 0, ma);
       HIP_TRY(hipGetLastError());
     }
