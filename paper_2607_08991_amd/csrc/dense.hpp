@@ -1011,7 +1011,6 @@ __device__ __forceinline__ int pf_swz(int r) { return ((r >> 1) & 2) ^ (((r >> 3
 struct GlueArgs {
   const int *ctl;         // null: `rows` rows, each its own token (perm unused)
   int rows;
-  int blocks;             // hnext in row blocks (prefill.hpp)
   const int *perm;
   const float *part;      // [KSPLIT][n_dense][d]
   int ksplit, d;
@@ -1019,18 +1018,18 @@ struct GlueArgs {
   void *hnext;        // otherwise: next layer input of the dense group, [n_dense][d] or row blocks
   void *layer_in;         // optional: inspection copy of the next layer input, rows through perm
   // LoRA (zpart null: none): y += s z B_down for sparse-path rows, z the sum
-  // over the nzb partials of zpart [nzb][zrows][rank], in order
+  // over the nzb partials of zpart [nzb][kDenseMaxTokens (BLOCKS: rows)][rank], in order
   const float *zpart;
   const uint16_t *Bd;     // [rank][d] of the layer
   const uint8_t *gbase;
-  int rank, nzb, zrows;
+  int rank, nzb;
   float lscale;
 };
 
 // one workgroup per dense token (blockIdx.x), of as many wavefronts as the row
-// needs (with adapters all 16); thread t owns columns 4 t .. 4 t + 3 and issues its loads of every partial at once
+// needs (with adapters all 16); BLOCKS: hnext in row blocks (prefill.hpp); thread t owns columns 4 t .. 4 t + 3 and issues its loads of every partial at once
 constexpr int kGlueThreads = 1024;
-template <typename T> __global__ __launch_bounds__(kGlueThreads) void dense_glue_kernel(GlueArgs a) {
+template <typename T, bool BLOCKS> __global__ __launch_bounds__(kGlueThreads) void dense_glue_kernel(GlueArgs a) {
   if (a.ctl && !a.ctl[1]) return;
   const int m = blockIdx.x;
   const int nd = a.ctl ? a.ctl[0] : a.rows;
@@ -1042,6 +1041,7 @@ template <typename T> __global__ __launch_bounds__(kGlueThreads) void dense_glue
   // LoRA, sparse-path row: B_down[k][c .. c + 3] of the first 16 ranks, loaded
   // with the partials (it does not depend on z)
   const bool lora = sizeof(T) == 2 && a.zpart && !a.gbase[m];
+  const int zrows = BLOCKS ? a.rows : kDenseMaxTokens;  // rows of a partial z
   constexpr int kBdPre = 16;
   uint2 bpre[kBdPre];
 #pragma unroll
@@ -1063,7 +1063,7 @@ template <typename T> __global__ __launch_bounds__(kGlueThreads) void dense_glue
     const int R = a.rank, i = tid % R, q = tid / R;
     // thread (q, i) adds tiles q, q + Q, ...; then the Q group sums in order
     if (q < Q)
-      zf[tid] = (q < a.nzb) ? sum_coherent(a.zpart + ((size_t)q * a.zrows + m) * R + i, (size_t)Q * a.zrows * R,
+      zf[tid] = (q < a.nzb) ? sum_coherent(a.zpart + ((size_t)q * zrows + m) * R + i, (size_t)Q * zrows * R,
                                            (a.nzb - q + Q - 1) / Q)
                             : 0.0f;
     __syncthreads();
@@ -1125,7 +1125,7 @@ template <typename T> __global__ __launch_bounds__(kGlueThreads) void dense_glue
 #pragma unroll
     for (int i = 0; i < 4; ++i) h.v[i] = Elem<T>::round(y[i] / scale);
     constexpr int KB = 64 / sizeof(T), CE = 16 / sizeof(T);  // elements of a block's row and of a chunk
-    const size_t o = !a.blocks ? (size_t)m * a.d + c
+    const size_t o = !BLOCKS ? (size_t)m * a.d + c
                            : ((size_t)(m >> 4) * ((a.d + KB - 1) / KB) + c / KB) * (16 * KB) + (m & 15) * KB +
                                  ((c / CE & 3) ^ pf_swz(m & 15)) * CE + c % CE;
     *reinterpret_cast<Quad *>(static_cast<T *>(a.hnext) + o) = h;
@@ -1148,35 +1148,35 @@ constexpr int kLoraVChunks = 16;
 constexpr int kLoraVMaxChunk = 4096 / kLoraVChunks;  // k rows per chunk (d <= 4096)
 constexpr int kLoraVMaxRank = 64;    // ranks 8, 16, 32, 64
 //
-// The tiled products (ctl null) take every row of a pass at once: H comes and
+// TILED: the tiled products take every row of a pass at once: H comes and
 // s (h A) leaves in row blocks, as the operand of 4 R further k steps of the
 // gate/up product, [hi | lo] of s (h A_gate), then of s (h A_up) (hi the bf16
 // value, lo its rounded remainder); and a third layer of workgroups writes
 // B_gate transposed, the other operand of those steps.
 struct LoraVArgs {
-  const int *ctl;          // [0] rows of the group, [1] MFMA path on; null: `rows` rows, row blocks
-  int rows;
+  const int *ctl;          // [0] rows of the group, [1] MFMA path on (not TILED)
+  int rows;                // TILED: the rows, in row blocks
   const uint8_t *gbase;
   const uint16_t *H;       // [rows][K] bf16 layer input of the group
   const uint16_t *Ag, *Au; // [K][R] of the layer
   float *vpart;            // [2][row tiles][kLoraVChunks][16][R]
   float *lv;               // [2][kDenseMaxTokens][R]
-  uint16_t *ext;           // ctl null: row blocks of [rows][4 R]
-  const uint16_t *Bg;      // ctl null: B_gate [R][N] of the layer ...
+  uint16_t *ext;           // TILED: row blocks of [rows][4 R]
+  const uint16_t *Bg;      // TILED: B_gate [R][N] of the layer ...
   uint16_t *BgT;           // ... and its transpose [N][R]
   int N;
   unsigned *cnt;           // [2][row tiles] arrival counts (zero between launches)
   int K, R;
   float s;
 };
-__global__ __launch_bounds__(256) void lora_v_kernel(LoraVArgs a) {
+template <bool TILED> __global__ __launch_bounds__(256) void lora_v_kernel(LoraVArgs a) {
   __shared__ uint16_t hs[16 * kLoraVMaxChunk];
   __shared__ uint16_t as[kLoraVMaxChunk * kLoraVMaxRank];
   __shared__ int flag;
-  if (a.ctl && !a.ctl[1]) return;
-  const int nd = a.ctl ? min(a.ctl[0], kDenseMaxTokens) : a.rows;
+  if (!TILED && !a.ctl[1]) return;
+  const int nd = TILED ? a.rows : min(a.ctl[0], kDenseMaxTokens);
   const int ch = blockIdx.x, mt = blockIdx.y, ad = blockIdx.z, tid = threadIdx.x;
-  if (ad == 2) {  // B_gate^T: a thread per column and 8 ranks
+  if (TILED && ad == 2) {  // B_gate^T: a thread per column and 8 ranks
     const int per = a.R / 8, tot = a.N * per, step = gridDim.x * gridDim.y * 256;
     for (int e = (blockIdx.y * gridDim.x + ch) * 256 + tid; e < tot; e += step) {
       const int c = e % a.N, q = e / a.N;
@@ -1196,7 +1196,7 @@ __global__ __launch_bounds__(256) void lora_v_kernel(LoraVArgs a) {
     u32x4 v = {0u, 0u, 0u, 0u};
     if (m < nd) {
       const int kq = k0 / 8 + q;  // chunk of the row
-      const size_t o = a.ctl ? (size_t)m * a.K + 8 * kq
+      const size_t o = !TILED ? (size_t)m * a.K + 8 * kq
                              : ((size_t)mt * (a.K / 32) + (kq >> 2)) * 512 + r * 32 + ((kq & 3) ^ pf_swz(r)) * 8;
       v = *reinterpret_cast<const u32x4 *>(a.H + o);
     }
@@ -1257,7 +1257,7 @@ __global__ __launch_bounds__(256) void lora_v_kernel(LoraVArgs a) {
     for (int s2 = 1; s2 < NS; ++s2)
 #pragma unroll
       for (int j = 0; j < 4; ++j) acc[j] += red[(s2 * 16 + r) * R + 4 * q + j];
-  const int slot = ad * gridDim.y + mt;
+  const int slot = ad * (TILED ? (int)gridDim.y : 4) + mt;
   float *vp = a.vpart + ((size_t)slot * kLoraVChunks) * 16 * R;  // [chunk][16][R]
   if (act)
 #pragma unroll
@@ -1278,9 +1278,9 @@ __global__ __launch_bounds__(256) void lora_v_kernel(LoraVArgs a) {
 #pragma unroll
       for (int c2 = 0; c2 < kLoraVChunks; ++c2) t[j] += v[j][c2];  // chunk order
       t[j] = base ? 0.0f : a.s * t[j];
-      if (a.ctl) a.lv[((size_t)ad * kDenseMaxTokens + m) * R + 4 * q + j] = t[j];
+      if (!TILED) a.lv[((size_t)ad * kDenseMaxTokens + m) * R + 4 * q + j] = t[j];
     }
-    if (!a.ctl) {
+    if constexpr (TILED) {
 #pragma unroll
       for (int h = 0; h < 2; ++h) {
         uint16_t b[4];

@@ -823,7 +823,7 @@ template <typename T> int run_prefill(const Call &c, char *mem, unsigned *counte
       va.R = (int)c.rank;
       va.s = c.lscale;
       TimedLaunch tl(SATS_K_LORA_V, c.stream);
-      hipExtLaunchKernelGGL(lora_v_kernel, dim3(kLoraVChunks, (np + 15) / 16, 3), dim3(256), 0, c.stream, tl.start,
+      hipExtLaunchKernelGGL(lora_v_kernel<true>, dim3(kLoraVChunks, (np + 15) / 16, 3), dim3(256), 0, c.stream, tl.start,
                             tl.stop, 0, va);
       HIP_TRY(hipGetLastError());
       u.ext = b.ext;
@@ -882,18 +882,16 @@ template <typename T> int run_prefill(const Call &c, char *mem, unsigned *counte
       ga.gbase = b.gbase;
       ga.rank = (int)c.rank;
       ga.nzb = z.ks;
-      ga.zrows = np;
       ga.lscale = c.lscale;
     }
     ga.rows = np;
-    ga.blocks = 1;
     ga.part = b.part;
     ga.ksplit = p.ks;
     ga.d = (int)d;
     ga.out = l == c.L - 1 ? static_cast<T *>(c.out) + base * d : nullptr;
     ga.hnext = b.h;
     ga.layer_in = c.layer_in && l + 1 < c.L ? static_cast<T *>(c.layer_in) + ((l + 1) * c.n + base) * d : nullptr;
-    hipLaunchKernelGGL(dense_glue_kernel<T>, dim3(np), dim3(glue_threads(d, lora)), 0, c.stream, ga);
+    hipLaunchKernelGGL((dense_glue_kernel<T, true>), dim3(np), dim3(glue_threads(d, lora)), 0, c.stream, ga);
     HIP_TRY(hipGetLastError());
     if (lists) {
       CompactArgs ca{};
@@ -999,7 +997,7 @@ int run_pass(const Call &c, const Plan &p, const Buffers &b, unsigned *counters,
         va.s = c.lscale;
         {
           TimedLaunch tl(SATS_K_LORA_V, c.stream);
-          hipExtLaunchKernelGGL(lora_v_kernel, dim3(kLoraVChunks, 4, 2), dim3(256), 0, c.stream, tl.start, tl.stop,
+          hipExtLaunchKernelGGL(lora_v_kernel<false>, dim3(kLoraVChunks, 4, 2), dim3(256), 0, c.stream, tl.start, tl.stop,
                                 0, va);
         }
         HIP_TRY(hipGetLastError());
@@ -1050,10 +1048,9 @@ int run_pass(const Call &c, const Plan &p, const Buffers &b, unsigned *counters,
         ga.gbase = b.gbase;
         ga.rank = (int)c.rank;
         ga.nzb = (int)((d_ff + nt_gu - 1) / nt_gu);
-        ga.zrows = kDenseMaxTokens;
         ga.lscale = c.lscale;
       }
-      hipLaunchKernelGGL(dense_glue_kernel<uint16_t>, dim3(np), dim3(glue_threads(d, lora)), 0, c.stream, ga);
+      hipLaunchKernelGGL((dense_glue_kernel<uint16_t, false>), dim3(np), dim3(glue_threads(d, lora)), 0, c.stream, ga);
       HIP_TRY(hipGetLastError());
     }
     auto compact = [&]() -> int {
