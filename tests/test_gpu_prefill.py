@@ -256,3 +256,99 @@ def test_float32_batches_read_no_row_that_nothing_keeps(d, dff, n, level):
     poisoned = wd.clone()
     poisoned[rows] = float("nan")
     np.testing.assert_array_equal(from_dev(call(poisoned)[0]), from_dev(out))
+
+
+def _picked(c, res, rows):
+    """`rows` of a case and of an inspect run of it."""
+    sub = dict(c, x=c["x"][rows], token_ids=np.asarray(c["token_ids"])[rows])
+    return sub, dict(route=res["route"][rows], count=res["count"][:, rows], idx=res["idx"][:, rows],
+                     layer_in=res["layer_in"][:, rows], out=res["out"][rows])
+
+
+# passes of at most 2048 rows, equal shares in whole tiles of 256: 2100 tokens are 1280 and
+# 820, 16385 eight of 2048 and one of a single row
+@pytest.mark.parametrize("seed,L,d,dff,n,rank", [
+    (180, 1, 8, 8, 66, 0),           # less than one step of k
+    (181, 2, 24, 41, 70, 0),
+    (182, 2, 264, 333, 2100, 0),     # off the tiles
+    (183, 1, 128, 64, 16385, 0),     # a last pass of one row
+    (184, 1, 136, 72, 16385, 0),     # ... off the tiles: on the kernels of up to 64 rows
+    (185, 2, 128, 128, 2100, 16),    # adapters
+    (186, 1, 128, 64, 16385, 8),
+])
+def test_prompts_at_the_edges_of_their_passes(seed, L, d, dff, n, rank):
+    from test_gpu_lora import check_lora, run_lora, scale_for, thresholds_for
+    print(f"pass edges seed={seed} L={L} d={d} d_ff={dff} n={n} rank={rank}", flush=True)
+    w_std = 1.0 / np.sqrt(d)
+    c = synth.small_case(seed, L, d, dff, "bf16", n, vocab=40, n_dense_ids=12, w_std=w_std)
+    rows = sorted({t for t in (0, 17, 65, 1279, 1280, 1281, 2047, 2048, 16383, n - 2, n - 1) if t < n})
+    for lut in (None, c["route_lut"]):
+        if rank:
+            ad, s, ts = synth.stack_lora_adapters(seed, L, d, dff, rank, "bf16"), scale_for(w_std, rank), \
+                thresholds_for(c, "bf16", seed)
+            res = run_lora(c, ad, rank, s, ts, lut, "bf16")
+            sub, part = _picked(c, res, rows)
+            check_lora(sub, ad, s, ts, lut, "bf16", part)
+            fwd = run_lora(c, ad, rank, s, ts, lut, "bf16", inspect=False)
+        else:
+            ts = case_thresholds(c, "bf16", seed=seed)
+            res = run_gpu(c, ts, lut, "bf16")
+            check_against_oracle(c, ts, lut, "bf16", res, tokens=rows)
+            fwd = run_gpu(c, ts, lut, "bf16", inspect=False)
+        np.testing.assert_array_equal(fwd["out"], res["out"])
+
+
+@pytest.mark.parametrize("dtype,d,dff,n", [("bf16", 128, 192, 70), ("bf16", 264, 333, 70), ("bf16", 264, 333, 7),
+                                           ("f32", 260, 333, 7), ("f32", 4096, 2048, 3)])
+def test_an_infinite_threshold_removes_every_column(dtype, d, dff, n):
+    """Sparse-path rows are exactly zero, base-path rows those of the dense call."""
+    c = synth.small_case(190, 2, d, dff, dtype, n, vocab=40, n_dense_ids=12, w_std=1.0 / np.sqrt(d))
+    c["token_ids"] = np.asarray(c["token_ids"]).copy()
+    lut = np.asarray(c["route_lut"])
+    c["token_ids"][:2] = np.flatnonzero(lut)[0], np.flatnonzero(lut == 0)[0]  # both routes
+    base = lut[c["token_ids"]] != 0
+    got = run_gpu(c, [np.inf, np.inf], c["route_lut"], dtype)
+    dense = run_gpu(c, [np.inf, np.inf], None, dtype, dense=True)
+    assert (got["count"][:, ~base] == 0).all() and (got["count"][:, base] == dff).all()
+    assert not (got["out"][~base] if dtype == "f32" else got["out"][~base] & 0x7fff).any()
+    np.testing.assert_array_equal(got["out"][base], dense["out"][base])
+
+
+@pytest.mark.parametrize("dtype,d,dff,n", [("f32", 260, 1001, 9), ("bf16", 264, 333, 9), ("bf16", 264, 333, 100)])
+def test_a_captured_batch_without_its_matrix_core_workspace(dtype, d, dff, n):
+    """Where only the other kernels' workspace is there a captured batch takes those
+    kernels, and after a reserve the usual ones; each replay gives its eager call's bits."""
+    import torch
+    import paper_2607_08991_amd as sats
+    c = synth.small_case(191, 2, d, dff, dtype, n, vocab=40, n_dense_ids=12, w_std=1.0 / np.sqrt(d))
+    ts = case_thresholds(c, dtype, seed=191)
+    x, w = to_dev(c["x"], dtype), list(weights_dev(c, dtype))
+    ids, lut = to_dev(np.asarray(c["token_ids"], np.int32), dtype), to_dev(c["route_lut"], dtype)
+    thr = torch.tensor(np.asarray(ts, np.float32)).cuda()
+    outs = [torch.zeros_like(x) for _ in range(4)]
+    torch.cuda.synchronize()
+
+    def call(o):
+        sats.sats_mlp_forward(x, ids, *w, thr, lut, o, n, d, dff, 2)
+
+    stream, graphs = torch.cuda.Stream(), []
+    sats.sats_release()
+    with torch.cuda.stream(stream):
+        with sats.options(batch_path=sats.SATS_BATCH_COMPACT):
+            call(outs[0])
+        for o in outs[1:3]:
+            torch.cuda.synchronize()
+            graphs.append(torch.cuda.CUDAGraph())
+            with torch.cuda.graph(graphs[-1], stream=stream):
+                call(o)
+            sats.sats_reserve(n, d, dff, 2, x.element_size())
+        call(outs[3])
+        torch.cuda.synchronize()
+        want = [from_dev(outs[0]), from_dev(outs[3])]
+        for _ in range(3):
+            call(outs[3])
+            for g, o, y in zip(graphs, outs[1:3], want):
+                o.zero_()
+                g.replay()
+                torch.cuda.synchronize()
+                np.testing.assert_array_equal(from_dev(o), y)
