@@ -105,15 +105,19 @@ int sats_mlp_forward(const sats_bf16 *x, const int32_t *token_ids,
  * that runs it, held until the process ends, instead of a per-stream
  * allocation; the call allocates and frees nothing.  That covers single-token
  * calls at d <= 4096 and d_ff <= 16384 (any number of layers up to 64, bf16)
- * and small batches; a call whose workspace does not fit returns
- * SATS_ERR_WORKSPACE before any device work.  Every call on a device shares
- * that device's array and leaves its last contents there (more than 64 tokens
- * run in passes of 64 here, where sats_mlp_forward takes larger ones: the
- * outputs then agree within rounding): each call first
- * clears the array's arrival counters with a small kernel (no memset), and
- * calls that overlap on one device (other streams or threads) race and must
- * not be issued.  sats_device_status also reports a bounded wait that gave up
- * in such a call.
+ * and batches whose kernels' workspace fits: a batch that sats_mlp_forward
+ * takes on the matrix-core products of prompts (more than 64 tokens, or d no
+ * multiple of 128 or d_ff none of 64) runs on those where their workspace
+ * fits, else, as any other batch, in passes of up to 64 tokens where that
+ * one fits (the outputs then agree with sats_mlp_forward's within rounding).
+ * The two differ in size, so a call may fit where one of fewer tokens does
+ * not: 4096 x 14336 takes 65 tokens and not 64.  A call whose workspace does
+ * not fit returns SATS_ERR_WORKSPACE before any device work.  Every call on a
+ * device shares that device's array and leaves its last contents there: a
+ * call that is not on the prompt products first clears the array's arrival
+ * counters with a small kernel (no memset), and calls that overlap on one
+ * device (other streams or threads) race and must not be issued.
+ * sats_device_status also reports a bounded wait that gave up in such a call.
  */
 #define SATS_NOALLOC_SCRATCH_BYTES (16u << 20)
 int sats_mlp_forward_noalloc(const sats_bf16 *x, const int32_t *token_ids,
@@ -186,7 +190,8 @@ int sats_mlp_forward_inspect_f32(const float *x, const int32_t *token_ids,
  * passes of up to 64 tokens (above 128 tokens 2048) with every row on the matrix cores: each row
  * applies its own route and keep rule, the gate and up adapter terms are
  * added in float32 before SiLU and the keep rule, z = p A_down is summed per
- * 64-column tile and scale z B_down is added with the output.  Otherwise the
+ * column tile of at most 64 (above 128 tokens per chunk of d_ff, 16 of them)
+ * and scale z B_down is added with the output.  Otherwise the
  * shapes must fit the single-token path (d <= 4096, d and d_ff multiples of
  * 16 bytes' worth of elements) and tokens are processed one after another,
  * each on its own route.  Other arguments and the optional
