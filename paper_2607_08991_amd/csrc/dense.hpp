@@ -254,10 +254,9 @@ __device__ __forceinline__ f32x4v mfma16(const bf16x8 &a, const bf16x8 &b, const
 // The stage loop shared by both products: stage s lives in ring buffer
 // s % 6; `issue(buf, s)` starts three buffer loads per lane for stage s
 // (loads past the k range read zeros) and `compute(buf)` consumes a stage.
-// SATS_DENSE_RING_H runs HOOK after the first two stages are issued and TAIL
+// SATS_DENSE_RING runs HOOK after the first two stages are issued and TAIL
 // after all that precede the loop.
-#define SATS_DENSE_RING(S, ISSUE, COMPUTE) SATS_DENSE_RING_H(S, ISSUE, COMPUTE, (void)0, (void)0)
-#define SATS_DENSE_RING_H(S, ISSUE, COMPUTE, HOOK, TAIL)                                     \
+#define SATS_DENSE_RING(S, ISSUE, COMPUTE, HOOK, TAIL)                                       \
   {                                                                                          \
     uint8_t *const rb_[6] = {rg0, rg1, rg2, rg3, rg4, rg5};                                  \
     (void)rb_;                                                                               \
@@ -293,8 +292,7 @@ __device__ __forceinline__ f32x4v mfma16(const bf16x8 &a, const bf16x8 &b, const
 // W_up_T 8 KB each, H 2 KB), seven in flight.  Wavefronts 0-1 also load the
 // 16 H rows (three loads per stage, the others two), so their wait allows
 // 18 outstanding loads and the others' 12.
-#define SATS_DENSE_RING8(S, ISSUE, COMPUTE) SATS_DENSE_RING8_H(S, ISSUE, COMPUTE, (void)0, (void)0)
-#define SATS_DENSE_RING8_H(S, ISSUE, COMPUTE, HOOK, TAIL)                                    \
+#define SATS_DENSE_RING8(S, ISSUE, COMPUTE, HOOK, TAIL)                                      \
   {                                                                                          \
     ISSUE(rg0, 0);                                                                           \
     ISSUE(rg1, 1);                                                                           \
@@ -444,9 +442,9 @@ __global__ __launch_bounds__(kDenseThreads) void dense_gateup_kernel(DenseArgs a
 #define SATS_GU_FLAG                                                                         \
   if constexpr (DIRECT && !CAL) rflag = route_flag(a.route_mode, a.lut, rid)
   if constexpr (MT == 1) {
-    SATS_DENSE_RING8_H(S, SATS_GU_ISSUE, SATS_GU_COMPUTE, SATS_GU_GROUP, SATS_GU_FLAG)
+    SATS_DENSE_RING8(S, SATS_GU_ISSUE, SATS_GU_COMPUTE, SATS_GU_GROUP, SATS_GU_FLAG)
   } else {
-    SATS_DENSE_RING_H(S, SATS_GU_ISSUE, SATS_GU_COMPUTE, SATS_GU_GROUP, SATS_GU_FLAG)
+    SATS_DENSE_RING(S, SATS_GU_ISSUE, SATS_GU_COMPUTE, SATS_GU_GROUP, SATS_GU_FLAG)
   }
 #undef SATS_GU_FLAG
 #undef SATS_GU_GROUP
@@ -716,7 +714,7 @@ __global__ __launch_bounds__(kDenseThreads) void dense_down_kernel(DenseArgs a) 
   nd = min(ctl_n, 16 * MT);                                                                  \
   hv = hr < nd;                                                                              \
   fl = row_flags()
-  SATS_DENSE_RING_H(S, SATS_DN_ISSUE, SATS_DN_COMPUTE, SATS_DN_GROUP, (void)0)
+  SATS_DENSE_RING(S, SATS_DN_ISSUE, SATS_DN_COMPUTE, SATS_DN_GROUP, (void)0)
 #undef SATS_DN_GROUP
 #undef SATS_DN_ISSUE
 #undef SATS_DN_COMPUTE
@@ -994,8 +992,6 @@ __global__ __launch_bounds__(kDenseThreads) void cal_err_kernel(CalErrArgs a) {
 }
 
 #undef SATS_DENSE_RING
-#undef SATS_DENSE_RING_H
-#undef SATS_DENSE_RING8_H
 #undef SATS_DENSE_RING8
 #undef SATS_DENSE_STEP8
 #undef SATS_DENSE_STEP
