@@ -1026,9 +1026,10 @@ struct GlueArgs {
 // needs (with adapters all 16); BLOCKS: hnext in row blocks (prefill.hpp); thread t owns columns 4 t .. 4 t + 3 and issues its loads of every partial at once
 constexpr int kGlueThreads = 1024;
 template <typename T, bool BLOCKS> __global__ __launch_bounds__(kGlueThreads) void dense_glue_kernel(GlueArgs a) {
-  if (a.ctl && !a.ctl[1]) return;
+  const int *ctl = BLOCKS ? nullptr : a.ctl;
+  if (ctl && !ctl[1]) return;
   const int m = blockIdx.x;
-  const int nd = a.ctl ? a.ctl[0] : a.rows;
+  const int nd = ctl ? ctl[0] : a.rows;
   if (m >= nd) return;
   __shared__ float ssw[kGlueThreads / 64];
   const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6;
@@ -1095,7 +1096,7 @@ template <typename T, bool BLOCKS> __global__ __launch_bounds__(kGlueThreads) vo
       y += t;
     }
   }
-  const int row = a.ctl ? a.perm[m] : m;
+  const int row = ctl ? a.perm[m] : m;
   if (a.out) {
     if (on) {
       T *o = static_cast<T *>(a.out) + (size_t)row * a.d + c;

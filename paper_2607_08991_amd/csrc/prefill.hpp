@@ -82,7 +82,7 @@ struct PfArgs {
   const uint8_t *lut;
   int route_mode;
   uint8_t *keep_out;      // optional [n][N] keep flags
-  uint16_t *kept;         // few float32 rows, else null: bit c mod 16 of word c / 16 is set where some row keeps
+  uint16_t *kept;         // few float32 rows: bit c mod 16 of word c / 16 is set where some row keeps
                           // column c (written by gate/up for down, which reads up to 32 words of 32 past the last)
   int n, K, N;            // rows; reduction length; output columns
   int mtiles, units;      // row tiles; column tiles (times k chunks, down)
@@ -665,8 +665,10 @@ __device__ __forceinline__ u32x4 sm_block_operand(const uint8_t *blk, int r, int
 }
 
 // Columns [nt b, nt b + nt) of both projections: wavefronts 0-3 W_gate, 4-7 W_up.
-template <typename T, int MT>
+// KEPT: the launch also writes a.kept (float32, one row tile: see sm_down_kernel).
+template <typename T, int MT, bool KEPT = false>
 __global__ __launch_bounds__(kPfThreads, 2) void sm_gateup_kernel(PfArgs a, int nt) {
+  static_assert(!KEPT || (sizeof(T) == 4 && MT == 1), "16 flags per tile");
   constexpr int SW = 16 * 1024, SB = SW + 8 * 1024, R = 6;  // W_gate and W_up 8 KB each, h
   __shared__ __attribute__((aligned(1024))) uint8_t rg0[SB], rg1[SB], rg2[SB], rg3[SB], rg4[SB], rg5[SB];
   auto rb = [&](int i) -> uint8_t * {
@@ -756,8 +758,7 @@ __global__ __launch_bounds__(kPfThreads, 2) void sm_gateup_kernel(PfArgs a, int 
   const float thr = a.thr ? *a.thr : 0.0f;
   const int flag = a.route_mode == ROUTE_BASE || rflag != 0;
   const int c0 = n0 + 16 * ct;
-  constexpr bool KEPT = E == 4 && MT == 1;  // (see sm_down_kernel)
-  bool any = false;                         // some row keeps column c0 + l16
+  bool any = false;  // KEPT: some row keeps column c0 + l16
 #pragma unroll
   for (int i = 0; i < MT; ++i) {
     const f32x4v gv = reinterpret_cast<const f32x4v *>(xt)[i * 64 + lane];
@@ -775,7 +776,7 @@ __global__ __launch_bounds__(kPfThreads, 2) void sm_gateup_kernel(PfArgs a, int 
       uint64_t b = __ballot(any);
       b |= b >> 32;
       b |= b >> 16;
-      if (a.kept && lane == 0 && c0 < N) a.kept[c0 >> 4] = (uint16_t)b;
+      if (lane == 0 && c0 < N) a.kept[c0 >> 4] = (uint16_t)b;
     }
     const int r = lane >> 2, q = lane & 3, nbp = (N + 15) / 16;
 #pragma unroll
@@ -851,18 +852,18 @@ __global__ __launch_bounds__(kPfThreads, 2) void sm_down_kernel(PfArgs a) {
   // flags of the rows of stages s .. s + R - 1 (scalar loads, which the waits for the
   // stages' loads do not count; those past the last column are not looked at: `left`)
   const ConstWords fw = (ConstWords)(uintptr_t)a.kept + kb / KS;
-  auto flags = [&](uint32_t(&f)[R], int s) {
+  auto flags = [&](uint32_t(&f)[FLAGS ? R : 1], int s) {
+    if constexpr (FLAGS)
 #pragma unroll
-    for (int i = 0; i < R; ++i) f[i] = FLAGS ? fw[s + i] : ~0u;
+      for (int i = 0; i < R; ++i) f[i] = fw[s + i];
   };
   auto issue = [&](uint8_t *buf, int s, uint32_t f) {
     const int left = ke - kb - KS * s;
 #pragma unroll
-    for (int q = 0; q < 2; ++q) {
-      const int r = wr + 8 * RPL * q;
-      const bool on = r < left && (!FLAGS || (f >> (r & 31) & 1u));
-      pf_dma(rsw, buf + (w + 8 * q) * 1024, on ? woff[q] : kDenseOffNone, (uint32_t)s * (uint32_t)(KS * E * N));
-    }
+    for (int q = 0; q < 2; ++q)
+      pf_dma(rsw, buf + (w + 8 * q) * 1024,
+             wr + 8 * RPL * q < left && (!FLAGS || (f >> (wr + 8 * RPL * q & 31) & 1u)) ? woff[q] : kDenseOffNone,
+             (uint32_t)s * (uint32_t)(KS * E * N));
 #pragma unroll
     for (int q = 0; q < IP; ++q)
       pf_dma(dense_rsrc(a.A + min((w + 8 * q) / (2 * MT), NP - 1) * a.pterm, pbytes), buf + SW + (w + 8 * q) * 1024,
@@ -871,15 +872,15 @@ __global__ __launch_bounds__(kPfThreads, 2) void sm_down_kernel(PfArgs a) {
   f32x4v acc0[MT] = {}, acc1[MT] = {}, sum[MT] = {}, off[MT] = {};  // stage sums (even, odd); total
 #pragma unroll
   for (int s = 0; s < 2; ++s) issue(rb(s), s, ~0u);
-  uint32_t fl[R], fn[R];  // of the stages that this round and the next one load
+  uint32_t fl[FLAGS ? R : 1], fn[FLAGS ? R : 1];  // of the stages that this round and the next one load
   flags(fn, 0);
 #pragma unroll
-  for (int s = 2; s < R - 1; ++s) issue(rb(s), s, fn[s]);
+  for (int s = 2; s < R - 1; ++s) issue(rb(s), s, FLAGS ? fn[FLAGS ? s : 0] : ~0u);
   flags(fl, R - 1);
   // (operands read where they are used: a chunk has few stages)
   auto step = [&](int s, int p, f32x4v(&cur)[MT], const f32x4v(&prv)[MT]) {
     pf_barrier<(R - 2) * IS>();
-    issue(rb(p + R - 1), s + R - 1, fl[p]);
+    issue(rb(p + R - 1), s + R - 1, FLAGS ? fl[FLAGS ? p : 0] : ~0u);
     uint8_t *buf = rb(p);
 #pragma unroll
     for (int h = 0; h < 2; ++h) {
@@ -912,8 +913,9 @@ __global__ __launch_bounds__(kPfThreads, 2) void sm_down_kernel(PfArgs a) {
       step(s0 + 4, 4, acc0, acc1);
       step(s0 + 5, 5, acc1, acc0);
     }
+    if constexpr (FLAGS)
 #pragma unroll
-    for (int i = 0; i < R; ++i) fl[i] = fn[i];
+      for (int i = 0; i < R; ++i) fl[i] = fn[i];
   }
   sm_fold(sum, off, acc1);  // (rounds end on an odd stage)
   sm_total(sum, off);

@@ -452,9 +452,11 @@ template <bool SPLIT> PfKernel pf_down_fn(const PfPlan &p) {
   return p.dbn == 256 ? pf_down_kernel<128, 256, SPLIT> : pf_down_kernel<128, 128, SPLIT>;
 }
 typedef void (*SmGateup)(sats::PfArgs, int);
-template <typename T> SmGateup sm_gateup_fn(int np) {
+template <typename T> SmGateup sm_gateup_fn(int np, bool flags) {
   using namespace sats;
   const int mt = (np + 15) / 16;
+  if constexpr (sizeof(T) == 4)
+    if (flags) return sm_gateup_kernel<T, 1, true>;
   return mt <= 1 ? sm_gateup_kernel<T, 1> : mt == 2 ? sm_gateup_kernel<T, 2>
                                         : mt == 3   ? sm_gateup_kernel<T, 3> : sm_gateup_kernel<T, 4>;
 }
@@ -787,7 +789,7 @@ template <typename T> int run_prefill(const Call &c, char *mem, unsigned *counte
   PfArgs a{};
   a.n = np;
   const bool flags = esz == 4 && pf_flags(np, d, d_ff);
-  a.kept = flags ? b.kept : nullptr;
+  a.kept = b.kept;
   for (int64_t l = 0; l < c.L; ++l) {
     PfArgs u = a;
     u.A = reinterpret_cast<const uint16_t *>(b.h);
@@ -833,7 +835,7 @@ template <typename T> int run_prefill(const Call &c, char *mem, unsigned *counte
     }
     if (p.small) {
       TimedLaunch tl(SATS_K_DENSE, c.stream);
-      hipExtLaunchKernelGGL(sm_gateup_fn<T>(np), dim3((unsigned)u.units), dim3(kPfThreads), 0, c.stream, tl.start, tl.stop,
+      hipExtLaunchKernelGGL(sm_gateup_fn<T>(np, flags), dim3((unsigned)u.units), dim3(kPfThreads), 0, c.stream, tl.start, tl.stop,
                             0, u, p.nt);
     } else {
       u.mtiles = (np + p.bm - 1) / p.bm;
