@@ -94,16 +94,18 @@ template <int MODE> DenseKernel dense_gateup_mode(int np) {
   return mt <= 1 ? dense_gateup_kernel<1, MODE> : mt == 2 ? dense_gateup_kernel<2, MODE>
                                               : mt == 3   ? dense_gateup_kernel<3, MODE> : dense_gateup_kernel<4, MODE>;
 }
-// AHEAD above 16 tokens: 32 Llama-3.1-8B layers at 64 tokens 2.376 -> 2.358 ms.
-// Fewer tokens may all leave out a row read ahead (one layer, 70 % of the columns
-// removed: 2 tokens 60.8 us, 61.8 with it; 4 tokens 65.1 and 68.1; 36 Qwen3-8B
-// layers at 16 tokens 2.161 ms before, 2.172 with it).
+// AHEAD above 48 tokens, in stacks: 32 Llama-3.1-8B layers at 64 tokens 2.325 -> 2.301 ms,
+// 36 Qwen3-8B layers 2.445 -> 2.427.  At 48 the two are the same (2.203, 2.203; 2.234,
+// 2.234) and below it costs: 32 tokens 2.176 -> 2.187 and 2.110 -> 2.126, 17 tokens 2.103 ->
+// 2.116 and 2.066 -> 2.082, with 90 % of the columns removed, where rows read ahead are
+// left out by the next launch, 2.261 -> 2.299 and 1.967 -> 2.028.  (A single Llama layer
+// gains at 32 and 48 tokens, 68.0 -> 67.3 and 66.8 -> 66.1 us, and at 64 74.0 -> 72.1.)
 DenseKernel dense_gateup_fn(int np, bool lora, bool direct) {
   using namespace sats;
   if (lora) return dense_gateup_mode<GU_LORA>(np);
   if (!direct) return dense_gateup_mode<GU_GROUP>(np);
-  return np <= 16 ? dense_gateup_kernel<1, GU_DIRECT> : np <= 32 ? dense_gateup_kernel<2, GU_AHEAD>
-                                                    : np <= 48   ? dense_gateup_kernel<3, GU_AHEAD>
+  return np <= 16 ? dense_gateup_kernel<1, GU_DIRECT> : np <= 32 ? dense_gateup_kernel<2, GU_DIRECT>
+                                                    : np <= 48   ? dense_gateup_kernel<3, GU_DIRECT>
                                                                  : dense_gateup_kernel<4, GU_AHEAD>;
 }
 DenseKernel dense_down_fn(int np) {
