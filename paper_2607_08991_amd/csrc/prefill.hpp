@@ -18,9 +18,11 @@
 // that used its last operands.
 //
 // Bound: the matrix cores, after the weight stream.  1000 rows of a
-// Llama-3.1-8B layer (352 Gflop): 16 passes of 64 rows took 1303 us; these
-// kernels take 320 us (1.10 Pflop/s; a large library product reaches 1.18):
-// gate/up 233 us, down 90 us.  Without its loads the gate/up loop takes 169 us.
+// Llama-3.1-8B layer (352 Gflop): 16 passes of 64 rows take 1276 us, a call here
+// 336 us (1.05 Pflop/s; a large library product reaches 1.18).  Its launches,
+// each under rocprofv3, where they take longer than in a row of calls: rows into
+// blocks 6 us, gate/up 234, down 114, second stage 13.  Without its loads the
+// gate/up loop takes 169 us.
 //
 // Layouts.  The left operands (h, p) are kept in row blocks: 16 rows by 32 k,
 // 1 KB, the blocks of 16 rows in k order; chunk q (16 bytes) of row r sits at
@@ -607,8 +609,8 @@ __global__ __launch_bounds__(kPfThreads, 2) void pf_down_kernel(PfArgs a) {
 // bound: stages of 128 bytes of each weight row (64 k, float32: 32), every
 // wavefront 16 columns of all rows, and enough workgroups to spread short
 // matrices over the chip (the tiles of 128 rows above put 7 tokens of a 1024 x
-// 2730 layer on 43 workgroups: gate/up 14.8 and down 8.1 us; here 7.8 and
-// 4.0).  Grid: column tiles (times k chunks).  Slots of a stage that nothing
+// 2730 layer on 43 workgroups: gate/up 14.8 and down 8.1 us; here 8.2 and
+// 5.1, rocprofv3).  Grid: column tiles (times k chunks).  Slots of a stage that nothing
 // needs are read as zeros without a memory access.
 //
 // float32 products are v_mfma_f32_16x16x4_f32, four to a 64-byte block of 16
@@ -616,7 +618,7 @@ __global__ __launch_bounds__(kPfThreads, 2) void pf_down_kernel(PfArgs a) {
 // read), and product i takes element i of both operands, so each k meets
 // itself.  The compacted kernels they replace form every product on the
 // vector units, 4 tokens a tile, and read the weights once a tile (16 tokens
-// of a Qwen3-8B layer: 563 us, here 117: 604 MB at 5.2 TB/s).
+// of a Qwen3-8B layer: 550 us, here 117 to 120: 604 MB at 5.1 TB/s).
 
 // Every stage sums into accumulators of its own, which the next stage adds to
 // the total under its products; what each of those additions rounds off is summed

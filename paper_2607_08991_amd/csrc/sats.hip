@@ -417,13 +417,16 @@ size_t pf_bytes_upto(int64_t n, int64_t d, int64_t d_ff, int esz, bool lora) {
 // for bf16, with every row on the matrix cores,
 //  - more than 64 tokens.  At 64 and below the 64-row kernels stream the
 //    weights at the memory's rate and skip W_down rows that no token keeps
-//    (64 tokens of a Llama-3.1-8B layer 75 us; here about 110); above, each
-//    further pass streams them again (1000 tokens 1303 us; here 331), or
+//    (64 tokens of a Llama-3.1-8B layer 72 us; here about 110); above, each
+//    further pass streams them again (1000 tokens 1276 us; here 336), or
 //  - 2 or more tokens of a shape that is not on the 64-row kernels' tiles and
 //    would take the compacted kernels (7 tokens through two layers of 1024 x
-//    2730: 186 us there, 35 here).
-// and float32 batches of 2 or more tokens (16 tokens of a Qwen3-8B layer 563 us on the
-// compacted kernels, 117 here; 2 tokens of 3712 x 14016, half the columns kept: 163 and 118).
+//    2730: 185 us there, 32 here).
+// and float32 batches of 2 or more tokens (16 tokens of a Qwen3-8B layer 550 us on the
+// compacted kernels, 117 to 120 here; 2 tokens with half, 70 and 90 % of the columns
+// removed 142, 124 and 103 there, 115, 110 and 104 here; 3 tokens 154, 140, 109 and 113,
+// 105, 112; 2 and 3 tokens of a Llama-3.1-8B layer at 90 % 118, 124 and 129, 130: what is
+// left there is W_up, which one gate/up launch reads whole).
 bool pf_shape(int esz, bool aligned, int64_t n, int64_t d, int64_t d_ff) {
   if (!aligned || d * esz % 16 != 0 || d > 4096 || d_ff > (1 << 19) - 32 || (uint64_t)d * d_ff * esz >= (1ull << 31) ||
       n < sats::kMfmaMinTokens)
@@ -1282,7 +1285,10 @@ bool lora_batched(const Call &c, int esz, bool vec_ok) {
 
 // ... and above two passes of 64 tokens the tiled products, with the adapters
 // as further k of the gate/up product (200 tokens of a Llama-3.1-8B layer at
-// rank 16: four passes 388 us, here 147).
+// rank 16: four passes 359 us, here 142 to 145).  Two passes are no faster either: 65, 96
+// and 128 tokens of that layer take 157, 170 and 178 us in them, 110, 110 and 117 on
+// the tiles (rank 64: 194, 209, 217 and 124, 128, 134), of a 1024 x 4096 layer 63, 68, 73
+// and 40, 43, 44, so a line at 64 would serve them better.
 bool lora_tiled(const Call &c, int esz, bool vec_ok) {
   return c.n > 2 * kMaxPass && lora_batched(c, esz, vec_ok) && pf_ok(esz, vec_ok, c.n, c.d, c.d_ff);
 }
