@@ -56,7 +56,8 @@
  * (for batches of one size class: 1 token, 2 to 64, and above 64 the batches
  * whose passes of up to 2048 rows split d_ff into as many chunks) or on the
  * stream; every reduction has a fixed order and no floating-point atomics
- * are used.
+ * are used.  Only a batch whose workspace cannot be had runs on other kernels
+ * (see sats_reserve), with results that agree within rounding.
  *
  * Concurrency: calls on different streams use different workspaces and may
  * overlap.  Calls on one stream are ordered by the stream.
